@@ -41,7 +41,14 @@ constexpr int kStageKeys = 32;                 // keys per half-stage: the unit 
 constexpr int kStageVecs = kStageKeys * 16;    // 16-byte pieces per K (or V) half-stage: 32 rows x 256 B
 constexpr int NH = 9;                          // ring depth in half-stages (16 KiB each): 288 keys
 constexpr int PRO = 6;                         // half-stages requested before the first wait; the rest of the ring right after it
-constexpr int kMaxBtLds = 1024;                // block-table entries staged in LDS per split
+// Block-table entries of a split in LDS: a ring of kBtSegs segments (entry i of the split's slice sits at i % kBtLds).
+// The first kBtLds entries are there before the first request; a later segment is requested, by LDS-DMA, when the
+// refills come within two segments of it.  512 entries are at least 16 half-stages of requests even with one token
+// per block, and the wait at the top of a stage leaves at most five half-stages in flight, so a segment has landed
+// in every wave's share before the first address that needs it.
+constexpr int kBtSeg = 256;
+constexpr int kBtSegs = 4;
+constexpr int kBtLds = kBtSeg * kBtSegs;
 // Partial softmax state in this kernel's own format, one unit per (16-row tile, split), laid out in
 // the order the MFMA accumulators hold it: for each of the 8 dim tiles dt, lane (kg, c) of the wave
 // that owns the 16 rows has 8 bytes -- o[row c][16 dt + 4 kg + {0..3}] as bf16, unnormalised, relative
@@ -84,7 +91,7 @@ __device__ __forceinline__ uint16_t f2bf(float x) {
 
 struct KeyAddr {  // resolves cache slots of one (sequence, kv head) to byte offsets
   const KvAddr* kv;
-  const int* bt;   // LDS copy of this split's slice of the block table (paged caches)
+  const int* bt;   // LDS ring of this split's slice of the block table (paged caches)
   int bt_first;    // logical block of bt[0]
   int bs_shift;    // log2(block_size)
   int seq, head;
@@ -92,7 +99,7 @@ struct KeyAddr {  // resolves cache slots of one (sequence, kv head) to byte off
     const KvAddr& a = *kv;
     if (a.block_size > 0) {
       const int lb = slot >> bs_shift;
-      int64_t blk = bt[lb - bt_first];
+      int64_t blk = bt[(lb - bt_first) & (kBtLds - 1)];
       blk = blk < 0 ? 0 : (blk >= a.num_blocks ? a.num_blocks - 1 : blk);
       return (blk * a.seq_stride + (int64_t)(slot - (lb << bs_shift)) * a.token_stride +
               (int64_t)head * a.head_stride) * 2;
@@ -122,6 +129,11 @@ __device__ __forceinline__ void ring_barrier() {
 __device__ __forceinline__ void lds_dma_b128(const CB_GLOBAL char* src, CB_LDS uint4* dst) {
   const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base) : "memory");
+}
+
+__device__ __forceinline__ void lds_dma_b32(const CB_GLOBAL int32_t* src, CB_LDS int* dst) {  // (dst + lane * 4)
+  const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(base) : "memory");
 }
 
 // Wave `w` (of 8) brings rows 4w..4w+3 of a half-stage (keys key0..key0+31) into its ring slot: one
@@ -514,7 +526,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   // The ring: NH half-stage slots, each 8 KiB of K followed by 8 KiB of V; half-stage h of the
   // split (keys k0 + 32 h ..) lives in slot h % NH.
   __shared__ uint4 ring[NH * 2 * kStageVecs];
-  __shared__ int bt_lds[kMaxBtLds];
+  __shared__ int bt_lds[kBtLds];
   __shared__ AncScratch anc_sh;  // ancestor sets of the whole tree, built here by the splits that reach the tree
   __shared__ int last_flag;
   __shared__ int merge_flag;                 // cooperative merge: thread 64's verdict (0 = not yet)
@@ -593,10 +605,11 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   ka.bs_shift = 0;
   ka.seq = b;
   ka.head = hk;
-  if (p.kv.block_size > 0) {  // the launcher guarantees a power-of-two block size and a slice that fits
+  int bt_seg = 1;  // furthest segment of the table slice that the requests have entered (the first kBtSegs are loaded here)
+  if (p.kv.block_size > 0) {  // the launcher guarantees a power-of-two block size
     ka.bs_shift = 31 - __clz(p.kv.block_size);
     const int first = k0 >> ka.bs_shift, last = (k1 - 1) >> ka.bs_shift;
-    for (int i = tid; i <= last - first && i < kMaxBtLds; i += NT)
+    for (int i = tid; i <= last - first && i < kBtLds; i += NT)
       bt_lds[i] = gbt[(int64_t)b * p.kv.max_blocks + first + i];
     ka.bt_first = first;
     __syncthreads();  // the K/V addresses below depend on it
@@ -649,6 +662,22 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   auto issue = [&](int h, int slot) {
     uint4* const base = ring + slot * (2 * kStageVecs);
     issue_half(base, base + kStageVecs, ka, kbase, vbase, k0 + h * kStageKeys, last_key, w, l);
+  };
+  // Before half-stage h of a paged cache is requested: entering segment q of the split's table slice requests
+  // segment q + 2 (its ring place held q - 2), a dword per lane of the first waves.  (An extra request among those
+  // in flight only makes the counted waits stricter.)
+  auto bt_ahead = [&](int h) {
+    const int last_blk = (k1 - 1) >> ka.bs_shift;
+    int key = k0 + (h + 1) * kStageKeys - 1;
+    key = key > last_key ? last_key : key;
+    const int q = ((key >> ka.bs_shift) - ka.bt_first) / kBtSeg;
+    if (q <= bt_seg) return;
+    bt_seg = q;
+    const int seg = q + 2;
+    if (seg < kBtSegs || ka.bt_first + seg * kBtSeg > last_blk || w >= kBtSeg / 64) return;
+    const int i = seg * kBtSeg + 64 * w + l;
+    const int blk = ka.bt_first + i > last_blk ? last_blk : ka.bt_first + i;
+    lds_dma_b32(gbt + (int64_t)b * p.kv.max_blocks + blk, (CB_LDS int*)bt_lds + ((seg * kBtSeg + 64 * w) & (kBtLds - 1)));
   };
   // The prologue requests PRO half-stages, and the rest of the ring goes out right behind the
   // first stage's barrier -- all unconditionally (requests past the split's end repeat its last
@@ -712,6 +741,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
     } else {  // stage s-1's two slots take the next two half-stages
       const int ha = 2 * s + NH - 2;
       const int ra = sa >= 2 ? sa - 2 : sa - 2 + NH, rb = sa >= 1 ? sa - 1 : sa - 1 + NH;
+      if (p.kv.block_size > 0) bt_ahead(ha + 1);
       if (ha < nh) issue(ha, ra);
       if (ha + 1 < nh) issue(ha + 1, rb);
     }
@@ -1151,7 +1181,6 @@ bool attn_mfma_supports(const AttnParams& p) {
   if (p.D != 128) return false;
   if (p.kv.block_size > 0) {
     if (p.kv.block_size & (p.kv.block_size - 1)) return false;
-    if (p.chunk / p.kv.block_size + 2 > kMaxBtLds) return false;
   }
   if (p.nsplit > 4096) return false;  // the ticket counts arrivals in 16 bits
   // partial offsets inside one sequence are 32-bit byte offsets of a buffer descriptor
