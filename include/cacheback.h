@@ -223,14 +223,16 @@ int cb_device_status(cb_ctx *ctx, int32_t *status);
 /* Options; unknown names give CB_EINVAL.
  *   "splits"     force the number of KV-sequence splits (0 = automatic)
  *   "attn_impl"  0 = automatic, 1 = scalar kernel (at most 8 splits on a configuration the MFMA kernel
- *                takes), 2 = MFMA kernel (bf16, head_dim 128 only)
+ *                takes), 2 = MFMA kernel (bf16, head_dim 64 or 128 only)
  *   "stages"     bit mask of the steps cb_verify_tree_device enqueues (1 ancestor sets, 2 attention,
  *                4 argmax, 8 acceptance; default 15) -- for timing one step in isolation; with a
  *                step left out the results of the call are those of an earlier call or undefined
  *   "parallel_scan"  1 = run the logits scan on the context's second stream beside the attention
  *   "fuse_logits"    0 = never run the logits scan and the acceptance inside the attention launch
- *                    (default 1: small calls -- MFMA attention, sequences of at most 64/g nodes, bf16
- *                    logits, no more logits chunks than attention workgroups -- are one launch)
+ *                    (default 1: calls whose sequences have at most 64/g nodes, on the MFMA kernel, are one
+ *                    launch: some of its workgroups do the logits work, the others the attention)
+ *   "logits_wgs"     workgroups of that launch for the logits work (a multiple of 8 up to 192;
+ *                    0 = automatic)
  *   "coop_merge"     0 = never merge the splits cooperatively (default 1: a grid that fits the
  *                    machine in one round has every workgroup of a tile merge a slice of it; otherwise,
  *                    and with 0, the last workgroup of a tile to finish merges it, or a merge kernel)

@@ -111,13 +111,14 @@ def build(verbose: bool = False) -> str:
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
         objs = list(ex.map(_compile, srcs))
-    asm = device_asm(os.path.join(CSRC, "cb_attn_mfma.hip"))
-    bad = untracked_load_violations(asm)
-    if bad:
-        raise RuntimeError(f"cb_attn_mfma.hip: registers of untracked loads are touched before their wait: {bad[:4]}")
-    bad = scratch_violations(asm)
-    if bad:
-        raise RuntimeError(f"cb_attn_mfma.hip: kernels that spill or use scratch memory: {bad[:4]}")
+    for name in ("cb_attn_mfma.hip", "cb_attn_wide.hip"):
+        asm = device_asm(os.path.join(CSRC, name))
+        bad = untracked_load_violations(asm)
+        if bad:
+            raise RuntimeError(f"{name}: registers of untracked loads are touched before their wait: {bad[:4]}")
+        bad = scratch_violations(asm)
+        if bad:
+            raise RuntimeError(f"{name}: kernels that spill or use scratch memory: {bad[:4]}")
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     if verbose:
         print(LIB)

@@ -29,8 +29,8 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
-  size_t anc, parent, tokens, amax_partial, amax_out, path, len_ctx, res_len, res_tok, new_len, status,
-      tickets, coop_tickets, amax_tickets, amax_lines, dbg, partial, total;
+  size_t anc, parent, tokens, amax_best, amax_out, path, len_ctx, res_len, res_tok, new_len, status,
+      tickets, coop_tickets, amax_tickets, dbg, partial, total;
   int amax_chunks;
   int max_total_nodes;
   int max_splits;
@@ -75,7 +75,7 @@ WsLayout ws_layout(const cb_config& c) {
   L.anc = take(mt * kAncWords * 4);
   L.parent = take(mt * 4 * 2);  // staged tree of the host-array form: parents, then tokens right behind them
   L.tokens = L.parent;         // (placed per call)
-  L.amax_partial = take(mt * L.amax_chunks * sizeof(ArgmaxPartial));
+  L.amax_best = take(mt * kAmaxStride * 8);
   L.amax_out = take(mt * 4);
   L.path = take(c.max_batch * stride * 4);
   L.len_ctx = take(c.max_batch * 4);
@@ -85,17 +85,15 @@ WsLayout ws_layout(const cb_config& c) {
   L.status = take(4);
   L.tickets = take((size_t)L.ticket_count * 4);
   L.coop_tickets = take((size_t)kCoopTiles * kCoopTicketStride);
-  L.amax_tickets = take(CB_MAX_BATCH * 4);
-  // argmax partials of the one-launch verification, one 128-byte line each (it takes sequences of at most 64 nodes)
-  L.amax_lines = take((size_t)c.max_batch * std::min(c.max_nodes, 64) * L.amax_chunks * 128);
+  L.amax_tickets = take((size_t)c.max_batch * kTicketWords * 4);
   L.dbg = take(1024 * 8 * 8);
   // The scalar kernel's fp32 partials are 8 times the size of the MFMA kernel's.  A configuration
-  // the MFMA kernel takes (bf16, head_dim 128) runs the scalar one only on request (option
+  // the MFMA kernel takes (bf16) runs the scalar one only on request (option
   // "attn_impl" = 1, a test aid): it gets room for 8 splits there, not for max_splits.
-  const bool mfma_cfg = c.qkv_dtype == CB_BF16 && c.head_dim == 128;
+  const bool mfma_cfg = c.qkv_dtype == CB_BF16;
   L.scalar_splits = mfma_cfg ? std::min(L.max_splits, 8) : L.max_splits;
   const size_t scalar_bytes = mt * c.num_q_heads * (size_t)L.scalar_splits * partial_stride(c.head_dim) * 4;
-  const size_t mfma_bytes = mfma_cfg ? attn_mfma_partial_bytes(mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits) : 0;
+  const size_t mfma_bytes = mfma_cfg ? attn_mfma_partial_bytes(c.head_dim, mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits) : 0;
   L.partial = take(std::max(scalar_bytes, mfma_bytes));
   L.total = o;
   return L;
@@ -139,12 +137,13 @@ struct cb_ctx {
   int32_t last_len[CB_MAX_BATCH];
   hipStream_t last_stream;
   // options
-  int64_t opt_splits, opt_impl, opt_time, opt_stages, opt_timeline, opt_external, opt_fork, opt_fuse, opt_coop, opt_spin, opt_full_sync;
+  int64_t opt_splits, opt_impl, opt_time, opt_stages, opt_timeline, opt_external, opt_fork, opt_fuse, opt_coop, opt_spin, opt_full_sync, opt_logits_wgs;
   hipEvent_t ev0, ev1, ev_fork, ev_join;
   hipStream_t aux;  // second stream (default priority) for the logits scan beside the attention
   bool ev_valid;
   const Plan* fixed_plan = nullptr;  // (cb_tree_attention_noalloc: the plan its scratch layout was cut for)
   bool counters_dirty = false;  // a launch failed: the tickets may be left non-zero
+  bool amax_dirty = false;      // a scan ran without its acceptance (option "stages"): row maxima are left behind
   char err[256];
 
   template <typename T>
@@ -199,9 +198,24 @@ bool make_kv_addr(const cb_config& c, const cb_kv_layer& l, KvAddr* a) {
   return true;
 }
 
-// Pure host arithmetic: no device call, no context state beyond the three numbers passed in.
+// Workgroups of a one-launch verification that do the logits work: the share of the chip that the logits' bytes
+// have in the call's, in whole XCD rounds of 8, at least 8, at most what gives each of their 8 wavefronts an item.
+int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const int32_t* node_offsets) {
+  const int64_t eb = c.qkv_dtype == CB_F32 ? 4 : 2, lb = c.logits_dtype == CB_F32 ? 4 : 2;
+  const int64_t rows = node_offsets[batch];
+  int64_t slots = rows;
+  for (int b = 0; b < batch; b++) slots += kv_len[b];
+  const double kv = (double)slots * c.num_kv_heads * c.head_dim * 2 * eb, lg = (double)rows * c.vocab_size * lb;
+  const int64_t items = rows * (((int64_t)c.vocab_size + kArgmaxChunk - 1) / kArgmaxChunk);
+  const int share = (int)(256.0 * lg / (lg + kv));
+  const int most = (int)std::min<int64_t>(192, (items + 7) / 8);
+  return std::max(8, std::min(share, most) / 8 * 8);
+}
+
+// Pure host arithmetic: no device call, no context state beyond the numbers passed in.  `units`: compute units that
+// the attention's workgroups can count on.
 Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int batch,
-                    const int32_t* kv_len, const int32_t* node_offsets) {
+                    const int32_t* kv_len, const int32_t* node_offsets, int units = 256) {
   Plan p{};
   int64_t rows = 0;
   for (int b = 0; b < batch; b++) {
@@ -210,7 +224,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     p.max_len = std::max(p.max_len, kv_len[b] + n);
     rows += (int64_t)n * c.num_q_heads;
   }
-  const bool mfma_ok = c.qkv_dtype == CB_BF16 && c.head_dim == 128;
+  const bool mfma_ok = c.qkv_dtype == CB_BF16;
   p.impl = (opt_impl == 1 || !mfma_ok) ? 1 : 2;
   if (p.impl == 1) max_splits = scalar_splits;
   int nsplit;
@@ -248,8 +262,8 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
         t += tl * ((kv_len[b] + n + chunk - 1) / chunk);
         keys += tl * (kv_len[b] + n);
       }
-      const int64_t rounds = (t + 255) / 256;
-      return (double)keys / ((double)rounds * 256.0 * chunk);
+      const int64_t rounds = (t + units - 1) / units;
+      return (double)keys / ((double)rounds * units * chunk);
     };
     const int cap = (int)std::max<int64_t>(1, std::min<int64_t>(max_splits, (p.max_len + 127) / 128));
     const int tiles_max = (mrows + rows_per_wg - 1) / rows_per_wg;
@@ -282,7 +296,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
           longest = std::max(longest, (full > 0 ? job_full : job_rest) + (real > 1 ? merge : 0.0));
           shortest = std::min(shortest, full > 0 ? job_full : job_rest);
         }
-        const double cost = jobs <= 256 ? longest : std::max(longest, work / 256.0 + shortest);
+        const double cost = jobs <= units ? longest : std::max(longest, work / units + shortest);
         if (ns == 1 || cost < best_cost - 1e-9) { best_cost = cost; nsplit = ns; }
       }
     } else {
@@ -295,8 +309,8 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     }
     // A grid of one round merges cooperatively (no workgroup pulls a whole tile's partials), so
     // there more splits cost next to nothing: take the best-filling count among the one-round ones.
-    if (best >= 0.85 && workgroups(nsplit) <= 256) {
-      for (int ns = nsplit + 1; ns <= cap && ns <= 64 && workgroups(ns) <= 256; ns++) {
+    if (best >= 0.85 && workgroups(nsplit) <= units) {
+      for (int ns = nsplit + 1; ns <= cap && ns <= 64 && workgroups(ns) <= units; ns++) {
         const double eff = efficiency(ns);
         if (eff > best + 1e-9) { best = eff; nsplit = ns; }
       }
@@ -345,12 +359,25 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   if (ctx->counters_dirty) {  // (after a failed launch: the kernels rely on tickets that are zero between launches)
     const hipError_t e1 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.tickets), ctx->lay.ticket_count / 2, 1, 1);
     const hipError_t e2 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.coop_tickets), kCoopTiles, kCoopTicketStride / 8, 2);
-    const hipError_t e3 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.amax_tickets), CB_MAX_BATCH / 2, 1, 1);
+    const hipError_t e3 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.amax_tickets), c.max_batch * kTicketWords / 2, 1, 1);
     if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) return set_err(ctx, CB_EHIP, "clearing the tickets after a failed launch failed");
     ctx->counters_dirty = false;
+    ctx->amax_dirty = ctx->amax_dirty || (stage_mask & 4) != 0;  // (the row maxima too)
   }
+  if (ctx->amax_dirty && (ctx->opt_stages & stage_mask & 12) == 12) {
+    CB_HIP(ctx, launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.amax_best), ctx->lay.max_total_nodes, kAmaxStride, 1));
+    ctx->amax_dirty = false;
+  }
+  // A verification whose tiles are small enough is one launch: its first workgroups do the logits work, and the
+  // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
+  // option does not change the splits and with them the rounding).
+  int max_nodes = 0;
+  for (int b = 0; b < batch; b++) max_nodes = std::max(max_nodes, node_offsets[b + 1] - node_offsets[b]);
+  const bool small_tiles = attn_mfma_tile_rows(max_nodes * (c.num_q_heads / c.num_kv_heads)) == 64;
+  int n_logits = (stage_mask & 8) && small_tiles ? fused_logits_wgs(c, batch, kv_len, node_offsets) : 0;
+  if (n_logits && ctx->opt_logits_wgs > 0) n_logits = (int)ctx->opt_logits_wgs;
   const Plan plan = ctx->fixed_plan ? *ctx->fixed_plan
-                                    : plan_attention(c, ctx->lay.max_splits, ctx->lay.scalar_splits, ctx->opt_impl, ctx->opt_splits, batch, kv_len, node_offsets);
+                                    : plan_attention(c, ctx->lay.max_splits, ctx->lay.scalar_splits, ctx->opt_impl, ctx->opt_splits, batch, kv_len, node_offsets, 256 - n_logits);
 
   AttnParams ap{};
   ap.q = q;
@@ -386,13 +413,21 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   // on the 7B shape the cross-stream edges cost more than the 5 us scan they hide, so it is off by
   // default.  The scalar attention reads the sets from the workspace: there the scan goes first and
   // carries the blocks that build them.
-  AcceptArgs acc{};
+  LogitsWork lw{};
+  lw.logits = logits;
+  lw.V = c.vocab_size;
+  lw.rows = total;
+  lw.batch = batch;
+  lw.chunks = ctx->lay.amax_chunks;
+  lw.n_wgs = n_logits;
+  lw.is_f32 = c.logits_dtype == CB_F32;
+  lw.accept_after = (stages & 8) != 0;
+  lw.tickets = ctx->dev<uint32_t>(ctx->lay.amax_tickets);
+  AcceptArgs& acc = lw.accept;
   acc.parent = d_parent;
   acc.tokens = d_tokens;
   acc.status = ctx->dev<int32_t>(ctx->lay.status);
-  acc.partial = ctx->dev<ArgmaxPartial>(ctx->lay.amax_partial);
-  acc.slot_stride = 1;
-  acc.nchunks = ctx->lay.amax_chunks;
+  acc.best = ctx->dev<unsigned long long>(ctx->lay.amax_best);
   acc.max_depth = c.max_depth;
   acc.argmax_out = ctx->dev<int32_t>(ctx->lay.amax_out);
   acc.path = ctx->dev<int32_t>(ctx->lay.path);
@@ -402,11 +437,9 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   acc.done_flag = ctx->want_done;
   acc.done_value = ctx->call_seq;
   ctx->want_done = nullptr;
-  // Small calls with the MFMA attention are one launch: the attention workgroups also scan the
-  // logits and run the acceptance (option "fuse_logits", on by default; see attn_mfma_can_fuse).
-  // Otherwise the scan, the attention and the acceptance are launches of their own.
-  const bool fused = use_mfma && ctx->opt_fuse != 0 && (stages & 2) && (stages & 4) && (stages & 8) &&
-                     attn_mfma_can_fuse(ap, plan.max_nodes, (int64_t)total * ctx->lay.amax_chunks, c.logits_dtype);
+  // Otherwise, and with option "fuse_logits" = 0, the logits work is a launch of its own in front.
+  const bool fused = use_mfma && small_tiles && ctx->opt_fuse != 0 && (stages & 2) && (stages & 4) && (stages & 8) &&
+                     attn_mfma_can_fuse(ap, plan.max_nodes);
   const bool fork = !fused && ctx->opt_fork != 0 && use_mfma && (stages & 2) && (stages & 4);
   hipStream_t scan_stream = st;
   int merge_kind = plan.nsplit > 1 ? 3 : 0, kernels = 0;  // (the scalar attention always merges with a kernel of its own)
@@ -418,10 +451,9 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   if (fused) {
   } else if (stages & 4) {
     const bool carry = !use_mfma && (stages & 1);
-    CB_LAUNCH(ctx, launch_argmax(scan_stream, logits, c.logits_dtype, total, c.vocab_size,
-                              ctx->dev<ArgmaxPartial>(ctx->lay.amax_partial), ctx->lay.amax_chunks, batch, meta,
-                              carry ? d_parent : nullptr, c.max_depth, carry ? ctx->dev<uint32_t>(ctx->lay.anc) : nullptr,
-                              carry ? ctx->dev<int32_t>(ctx->lay.status) : nullptr));
+    CB_LAUNCH(ctx, launch_logits(scan_stream, lw, meta, carry ? d_parent : nullptr, c.max_depth,
+                                 carry ? ctx->dev<uint32_t>(ctx->lay.anc) : nullptr, carry ? ctx->dev<int32_t>(ctx->lay.status) : nullptr));
+    if (!lw.accept_after) ctx->amax_dirty = true;
     kernels++;
   } else if (!use_mfma && (stages & 1)) {
     CB_LAUNCH(ctx, launch_tree_prepare(st, batch, meta, d_parent, c.max_depth, ctx->dev<uint32_t>(ctx->lay.anc),
@@ -433,16 +465,6 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   if (timing) CB_HIP(ctx, hipEventRecord(ctx->ev0, st));
   if (!(stages & 2)) {
   } else if (use_mfma) {
-    LogitsWork lw{};
-    lw.logits = static_cast<const uint16_t*>(logits);
-    lw.V = c.vocab_size;
-    lw.rows = total;
-    lw.batch = batch;
-    lw.tickets = ctx->dev<uint32_t>(ctx->lay.amax_tickets);
-    lw.accept = acc;
-    lw.accept.partial = ctx->dev<ArgmaxPartial>(ctx->lay.amax_lines);
-    lw.accept.slot_stride = 16;
-    lw.partial_out = ctx->dev<ArgmaxPartial>(ctx->lay.amax_lines);
     CB_LAUNCH(ctx, launch_attn_mfma(st, ap, meta, plan.max_nodes, total, fused ? &lw : nullptr, &merge_kind));  // merges its own splits
     kernels += merge_kind == 3 ? 2 : 1;
   } else {
@@ -455,7 +477,7 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     ctx->ev_valid = true;
   }
   if (fork) CB_HIP(ctx, hipStreamWaitEvent(st, ctx->ev_join, 0));
-  if ((stages & 8) && !fused) {
+  if ((stages & 8) && !(stages & 4)) {
     CB_LAUNCH(ctx, launch_accept(st, batch, meta, acc));
     kernels++;
   }
@@ -628,7 +650,8 @@ int cb_init(const cb_config* cfg, void* workspace, size_t workspace_bytes, cb_ct
   if (e == hipSuccess) e = hipMemset(ctx->ws + lay.status, 0, 4);
   if (e == hipSuccess) e = hipMemset(ctx->ws + lay.tickets, 0, (size_t)lay.ticket_count * 4);
   if (e == hipSuccess) e = hipMemset(ctx->ws + lay.coop_tickets, 0, (size_t)kCoopTiles * kCoopTicketStride);
-  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.amax_tickets, 0, CB_MAX_BATCH * 4);
+  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.amax_tickets, 0, (size_t)cfg->max_batch * kTicketWords * 4);
+  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.amax_best, 0, (size_t)lay.max_total_nodes * kAmaxStride * 8);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     (void)hipHostFree(ctx->h_block);
@@ -709,7 +732,7 @@ int cb_tree_attention_noalloc(const cb_config* cfg, void* hip_stream, int32_t ba
   L.anc = take((size_t)total * kAncWords * 4);
   L.dbg = L.anc;                    // (never written: the timing aid is off)
   L.partial = take(plan.nsplit <= 1 ? 0
-                   : plan.impl == 2 ? attn_mfma_partial_bytes(total, cfg->num_q_heads, cfg->num_kv_heads, batch, plan.nsplit)
+                   : plan.impl == 2 ? attn_mfma_partial_bytes(cfg->head_dim, total, cfg->num_q_heads, cfg->num_kv_heads, batch, plan.nsplit)
                                     : (size_t)total * cfg->num_q_heads * plan.nsplit * partial_stride(cfg->head_dim) * 4);
   L.total = o;
   if (L.total > kStaticScratchBytes)
@@ -895,6 +918,7 @@ int cb_set_option(cb_ctx* ctx, const char* name, int64_t value) {
   else if (!strcmp(name, "parallel_scan")) ctx->opt_fork = value;
   else if (!strcmp(name, "fuse_logits")) ctx->opt_fuse = value;
   else if (!strcmp(name, "coop_merge")) ctx->opt_coop = value;
+  else if (!strcmp(name, "logits_wgs")) ctx->opt_logits_wgs = value < 0 ? 0 : (value > 192 ? 192 : value / 8 * 8);
   else if (!strcmp(name, "merge_spin_limit")) ctx->opt_spin = value < 0 ? 0 : (value > 4096 ? 4096 : value);
   else return set_err(ctx, CB_EINVAL, "unknown option '%s'", name);
   return CB_OK;

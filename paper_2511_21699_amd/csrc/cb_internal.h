@@ -7,7 +7,8 @@
 namespace cb {
 
 constexpr int kAncWords = CB_MAX_NODES / 32;  // 256-bit ancestor set per node
-constexpr int kArgmaxChunk = 8192;            // logits elements scanned by one workgroup
+constexpr int kArgmaxChunk = 8192;            // logits elements scanned by one wavefront at a time
+constexpr int kAmaxStride = 16;               // words between the rows' argmax words: a 128-byte line each (they take atomics)
 constexpr int kRowTile = 64;                  // query rows per workgroup in the MFMA attention
 constexpr int kCoopTiles = 512;               // tiles a cooperative split merge can serve (it needs the grid resident at once)
 constexpr int kCoopTicketStride = 4096;       // bytes between their ticket words
@@ -177,22 +178,17 @@ struct AttnParams {
   unsigned long long* dbg_ts;  // timeline build: 8 timestamps (100 MHz) per workgroup, 1024 rows
 };
 
-struct ArgmaxPartial {
-  float value;
-  int32_t index;
-};
-
 // ---- launchers (defined in the .hip files); all enqueue on `st` and return the launch status
 hipError_t launch_tree_prepare(hipStream_t st, int batch, const SeqMeta& meta, const int32_t* parent,
                                int max_depth, uint32_t* anc, int32_t* status);
 // zeroes `run` 64-bit words at each of `count` places `stride` words apart
 hipError_t launch_zero_words(hipStream_t st, unsigned long long* base, int count, int stride, int run);
-// scans the logits; with prep_parent != nullptr the same launch also builds the ancestor sets
-hipError_t launch_argmax(hipStream_t st, const void* logits, int dtype, int rows, int64_t V,
-                         ArgmaxPartial* partial, int nchunks, int batch, const SeqMeta& meta,
-                         const int32_t* prep_parent, int max_depth, uint32_t* prep_anc, int32_t* status);
 struct AcceptArgs;  // cb_logits.h
 struct LogitsWork;
+// scans the logits and, with lw.accept_after, runs the acceptance (lw.n_wgs is chosen here); with prep_parent !=
+// nullptr the same launch also builds the ancestor sets
+hipError_t launch_logits(hipStream_t st, const LogitsWork& lw, const SeqMeta& meta, const int32_t* prep_parent,
+                         int max_depth, uint32_t* prep_anc, int32_t* status);
 hipError_t launch_accept(hipStream_t st, int batch, const SeqMeta& meta, const AcceptArgs& args);
 hipError_t launch_compact(hipStream_t st, int batch, const SeqMeta& meta, const KvAddr* layers,
                           int num_layers, int Hkv, int D, int elem_bytes, int max_depth,
@@ -202,11 +198,12 @@ hipError_t launch_attn_simt(hipStream_t st, const AttnParams& p, const SeqMeta& 
 hipError_t launch_merge(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int dtype, int total_nodes);
 int attn_mfma_tile_rows(int mrows);            // rows per workgroup tile chosen for a given g*N
 // bytes the MFMA path's partial states can take (its own layout, padded to 16-row tiles per kv head)
-size_t attn_mfma_partial_bytes(size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
+size_t attn_mfma_partial_bytes(int D, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
 bool attn_mfma_supports(const AttnParams& p);  // shape/geometry the MFMA kernel takes (bf16 is the caller's check)
-bool attn_mfma_can_fuse(const AttnParams& p, int max_nodes_in_call, int64_t logits_items, int logits_dtype);
+bool attn_mfma_can_fuse(const AttnParams& p, int max_nodes_in_call);
 // with logits_work != nullptr (only if attn_mfma_can_fuse) the same launch also scans the logits and runs the acceptance
 // merge_kind (may be null): 0 one split, 1 cooperative merge, 2 merge by the last workgroup to arrive, 3 merge kernel
+hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles);  // (by launch_attn_mfma)
 hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call,
                             int total_nodes, const LogitsWork* logits_work, int* merge_kind);
 

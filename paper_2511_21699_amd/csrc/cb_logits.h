@@ -1,7 +1,7 @@
 // Device code of the greedy acceptance check (Section 3.2 of the paper, last paragraphs): the
 // vocabulary argmax of every tree node's logits row, and the longest accepted root-to-leaf path.
-// Shared by the stand-alone argmax / acceptance kernels and by the attention kernel, whose
-// workgroups can run this work once their own attention duty is over.  gfx950 only.
+// Shared by the stand-alone logits kernel and by the attention kernels, whose first workgroups can
+// do this work in the same launch.  gfx950 only.
 #pragma once
 #include "cb_internal.h"
 
@@ -9,32 +9,11 @@ namespace cb {
 
 // Every pointer these functions are handed is device (global) memory, but it reaches them as a
 // generic pointer inside an argument struct.  Accesses through a generic pointer are flat
-// instructions, which the compiler orders behind every outstanding LDS-DMA load (they might touch
-// LDS) -- a vmcnt(0) wait in the middle of the attention kernel's ring.  So each access site casts
-// to the global address space.
+// instructions, which also count as LDS traffic; so each access site casts to the global address space.
 #define CBL_GLOBAL __attribute__((address_space(1)))
 template <typename T>
 __device__ __forceinline__ CBL_GLOBAL T* as_global(T* p) {
   return (CBL_GLOBAL T*)p;
-}
-
-__device__ __forceinline__ float elem_to_float(float x) { return x; }
-__device__ __forceinline__ float elem_to_float(uint16_t x) { return __uint_as_float(((uint32_t)x) << 16); }
-
-// (value, index) pairs are ordered "larger value, then smaller index" at every level, so equal
-// maxima (common with bf16 logits) resolve to the lowest index exactly as a serial scan does.
-// Both forms are written with selects: as branches they cost several times more than the loads
-// they follow.
-__device__ __forceinline__ void amax_take(float& bv, int& bi, float v, int i) {
-  const bool take = (v > bv) | ((v == bv) & (i < bi));
-  bv = take ? v : bv;
-  bi = take ? i : bi;
-}
-// the same when the candidate's index is known to be larger than the incumbent's
-__device__ __forceinline__ void amax_take_later(float& bv, int& bi, float v, int i) {
-  const bool take = v > bv;
-  bv = take ? v : bv;
-  bi = take ? i : bi;
 }
 
 // Wave-wide reductions that leave the result in every lane, without LDS traffic: four rotations
@@ -63,158 +42,31 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   return wave_allreduce_u32(x, [](uint32_t p, uint32_t q) { return p > q ? p : q; });
 }
-// first maximum over the wave's (value, index) pairs: the largest value, and the smallest index
-// among the lanes that hold it (+0 and -0 compare equal, as in a serial scan with '>')
-__device__ __forceinline__ void wave_first_max(float& bv, int& bi) {
-  const float m = wave_max_f32(bv);
-  bi = (int)wave_min_u32(bv == m ? (uint32_t)bi : 0x7fffffffu);
-  bv = m;
+
+// v_max3_f32 as such: fmaxf() costs a canonicalising instruction per operand first (the compiler cannot know that
+// loaded values are not signalling NaNs; the inputs are finite by precondition).
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
 
-// ArgmaxPartial travels as one 64-bit word so that it can be written and read with single
-// agent-scope accesses.
-__device__ __forceinline__ unsigned long long amax_pack(float v, int i) {
-  return (unsigned long long)__float_as_uint(v) | ((unsigned long long)(uint32_t)i << 32);
+// A row's first maximum as one 64-bit word that grows with the value and, among equal values, with
+// falling index, so that workgroups combine their candidates with an atomic maximum: the value's bits
+// made monotonic (-0 first made +0: the two compare equal) above the complement of the index.  Zero is
+// below every candidate.
+__device__ __forceinline__ unsigned long long amax_word(float v, int i) {
+  const uint32_t u = __float_as_uint(v + 0.0f);
+  const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+  return ((unsigned long long)key << 32) | (uint32_t)~(uint32_t)i;
 }
-template <bool COHERENT>
-__device__ __forceinline__ void amax_store(ArgmaxPartial* dst, float v, int i) {
-  CBL_GLOBAL unsigned long long* p = (CBL_GLOBAL unsigned long long*)dst;
-  if (COHERENT) __hip_atomic_store(p, amax_pack(v, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else *p = amax_pack(v, i);
-}
-template <bool COHERENT>
-__device__ __forceinline__ void amax_load(const ArgmaxPartial* src, float& v, int& i) {
-  const CBL_GLOBAL unsigned long long* p = (const CBL_GLOBAL unsigned long long*)src;
-  const unsigned long long x = COHERENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
-  v = __uint_as_float((uint32_t)x);
-  i = (int)(uint32_t)(x >> 32);
-}
-
-struct ScanLds {
-  float v[8];
-  int i[8];
-};
-
-// First maximum of elements [c*kArgmaxChunk, min(V, (c+1)*kArgmaxChunk)) of one logits row by a
-// workgroup of NT threads, in two halves so that other work can go between the loads and their use:
-// issue() requests all of the thread's 16-byte loads at once, consume() reduces them (plus the
-// elements a misaligned or ragged row leaves over) to one candidate per wavefront, which lane 0
-// of each wave leaves in `sh`.  After a workgroup barrier combine() gives the result (any thread).
-template <typename T, int NT>
-struct ChunkScan {
-  static constexpr int VEC = 16 / sizeof(T);
-  static constexpr int kVecPerThread = kArgmaxChunk / VEC / NT;
-  static_assert(kVecPerThread >= 1, "chunk smaller than one load per thread");
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 u[kVecPerThread];
-  int64_t start, end, vec_end, nvec;
-
-  // (no __restrict__ on the row: the loads must stay where they are written, in front of the
-  // caller's later waits, and not drift down to their first use)
-  // UNTRACKED: the loads are issued as instructions the compiler does not know to be loads (it
-  // would wait for every LDS-DMA request in flight at their first use); the caller must have
-  // waited for them (vmcnt) before pin_here() and consume().
-  template <bool UNTRACKED = false>
-  __device__ __forceinline__ void issue(const T* base, int64_t V, int c, int tid) {
-    start = (int64_t)c * kArgmaxChunk;
-    end = (start + kArgmaxChunk < V) ? start + kArgmaxChunk : V;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(base + start)) & 15) == 0;
-    nvec = aligned ? (end - start) / VEC : 0;
-    vec_end = start + nvec * VEC;
-    const CBL_GLOBAL u32x4* vp = (const CBL_GLOBAL u32x4*)(base + start);
-    if (nvec > 0) {  // (uniform; lanes past the end re-read the last vector and ignore it later, so
-                     //  the loads are unconditional and nothing has to wait for them here)
-#pragma unroll
-      for (int k = 0; k < kVecPerThread; k++) {
-        const int64_t i = tid + k * NT;
-        if constexpr (UNTRACKED) {
-          asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(u[k]) : "v"(vp + (i < nvec ? i : nvec - 1)) : "memory");
-        } else {
-          u[k] = vp[i < nvec ? i : nvec - 1];
-        }
-      }
-    }
-  }
-
-  // Keeps the reduction of the loaded vectors at (or behind) this point of the program: without it
-  // the compiler moves that loop-invariant arithmetic, and the wait for the loads with it, to the
-  // front of the caller's loop.
-  __device__ __forceinline__ void pin_here() {
-#pragma unroll
-    for (int k = 0; k < kVecPerThread; k++)
-      asm volatile("" : "+v"(u[k]));
-  }
-
-  __device__ __forceinline__ void consume(const T* base, int tid, ScanLds& sh) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-#pragma unroll
-    for (int k = 0; k < kVecPerThread; k++) {
-      const int64_t i = tid + k * NT;
-      if (i >= nvec) continue;
-      const int e0 = (int)(start + i * VEC);
-      if constexpr (sizeof(T) == 2) {
-        const uint32_t w[4] = {u[k].x, u[k].y, u[k].z, u[k].w};
-#pragma unroll
-        for (int j = 0; j < 4; j++) {  // (a thread meets its elements in increasing index order)
-          amax_take_later(bv, bi, __uint_as_float(w[j] << 16), e0 + 2 * j);
-          amax_take_later(bv, bi, __uint_as_float(w[j] & 0xffff0000u), e0 + 2 * j + 1);
-        }
-      } else {
-        amax_take_later(bv, bi, __uint_as_float(u[k].x), e0);
-        amax_take_later(bv, bi, __uint_as_float(u[k].y), e0 + 1);
-        amax_take_later(bv, bi, __uint_as_float(u[k].z), e0 + 2);
-        amax_take_later(bv, bi, __uint_as_float(u[k].w), e0 + 3);
-      }
-    }
-    for (int64_t i = vec_end + tid; i < end; i += NT) amax_take_later(bv, bi, elem_to_float(as_global(base)[i]), (int)i);
-    wave_first_max(bv, bi);
-    if ((tid & 63) == 0) { sh.v[tid >> 6] = bv; sh.i[tid >> 6] = bi; }
-  }
-
-  static __device__ __forceinline__ void combine(const ScanLds& sh, float& bv, int& bi) {
-    bv = sh.v[0];
-    bi = sh.i[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; w++) amax_take(bv, bi, sh.v[w], sh.i[w]);
-  }
-};
-
-// The whole scan in one go; the result is valid in every thread.  The caller separates two calls
-// that share `sh` by a barrier.
-template <typename T, int NT>
-__device__ __forceinline__ void scan_chunk(const T* __restrict__ base, int64_t V, int c, int tid, ScanLds& sh,
-                                           float& bv, int& bi) {
-  ChunkScan<T, NT> cs;
-  cs.issue(base, V, c, tid);
-  cs.consume(base, tid, sh);
-  __syncthreads();
-  ChunkScan<T, NT>::combine(sh, bv, bi);
-}
-
-// Greedy acceptance of one sequence's tree by a workgroup of at least 256 threads (thread t owns
-// node t).  A node is accepted when every non-root node on its chain carries the token generated at
-// that node's parent; with match = {x : tok[x] == a[parent(x)]} (root included) that is anc[c]
-// being a subset of match.  The accepted node of greatest depth wins (lowest index among equals);
-// its ancestor set *is* the path, each member sitting at position depth(member) = |anc(member)| - 1.
-// COHERENT: the argmax partials were written by other workgroups of the same launch (agent-scope
-// stores) and are read with agent-scope loads.  Ends with a barrier, so `sh` may be reused at once.
-struct AcceptLds {
-  int a[CB_MAX_NODES];
-  AncScratch anc;
-  uint32_t match[kAncWords];
-  uint32_t best[kAncWords];
-  uint32_t key[4];
-};
+__device__ __forceinline__ int amax_word_index(unsigned long long w) { return (int)~(uint32_t)w; }
 
 struct AcceptArgs {
   const int32_t* parent;   // [sumN] local parent indices
   const int32_t* tokens;   // [sumN] draft tokens
   int32_t* status;
-  const ArgmaxPartial* partial;  // [sumN][nchunks] entries, `slot_stride` entries apart
-  int32_t slot_stride;     // 1: packed.  16: one entry per 128-byte line, for entries that many workgroups
-                           // write through to memory at the same time (neighbours would share a line)
-  int32_t nchunks;
+  unsigned long long* best;  // [sumN] row maxima (amax_word), kAmaxStride words apart; zero between launches
   int32_t max_depth;
   int32_t* argmax_out;     // [sumN]
   int32_t* path;           // [B][max_depth + 1]
@@ -225,7 +77,7 @@ struct AcceptArgs {
   int32_t done_value;      // user results are visible to the host (the host form polls them)
 };
 
-// Tells a polling host that sequence b's results have arrived.  Called by every thread that wrote
+// Tells a polling host that sequence b's results have arrived.  Called by the wave that wrote the
 // results, after its stores: the system-scope release fence makes the wave's earlier stores visible
 // to the host before the flag store that follows can be.
 __device__ __forceinline__ void publish_done(const AcceptArgs& g, int b, bool writer) {
@@ -234,147 +86,41 @@ __device__ __forceinline__ void publish_done(const AcceptArgs& g, int b, bool wr
   if (writer) __hip_atomic_store(as_global(g.done_flag) + b, g.done_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-template <bool COHERENT>
-__device__ __forceinline__ void accept_sequence(AcceptLds& sh, const AcceptArgs& g, int b, int off, int N) {
-  const int t = threadIdx.x;
-  N = N > CB_MAX_NODES ? CB_MAX_NODES : N;
-  // everything the thread needs from memory is requested before the first use: the node's tree
-  // entries, then its row's partial maxima, four at a time
-  int par_raw = -1, tok = 0;
-  if (t < N) {
-    par_raw = as_global(g.parent)[off + t];
-    tok = as_global(g.tokens)[off + t];
-  }
-  int a = -1;
-  if (t < N) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    const ArgmaxPartial* row = g.partial + (int64_t)(off + t) * g.nchunks * g.slot_stride;
-    for (int c0 = 0; c0 < g.nchunks; c0 += 4) {
-      float v[4];
-      int i[4];
-#pragma unroll
-      for (int u = 0; u < 4; u++)  // (a repeated entry changes nothing)
-        amax_load<COHERENT>(row + (int64_t)(c0 + u < g.nchunks ? c0 + u : g.nchunks - 1) * g.slot_stride, v[u], i[u]);
-#pragma unroll
-      for (int u = 0; u < 4; u++) amax_take(bv, bi, v[u], i[u]);
-    }
-    a = bi;
-    as_global(g.argmax_out)[off + t] = a;
-  }
-  if (t < CB_MAX_NODES) sh.a[t] = a;
-  __syncthreads();
-  bool match = false;
-  int par = -1;
-  if (t < N) {
-    // (the same repair as sanitized_parent(): entries outside [0, t) become "child of the root")
-    if (t == 0) {
-      if (par_raw != -1) __hip_atomic_fetch_or(as_global(g.status), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      par = par_raw;
-      if (par < 0 || par >= t) {
-        __hip_atomic_fetch_or(as_global(g.status), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        par = 0;
-      }
-    }
-    match = (t == 0) || (tok == sh.a[par]);
-  }
-  const int unresolved = build_ancestor_sets(sh.anc, N, par, jump_rounds(g.max_depth));
-  const unsigned long long bal = __ballot(match);
-  if ((t & 63) == 0 && t < CB_MAX_NODES) {
-    sh.match[(t >> 6) * 2] = (uint32_t)bal;
-    sh.match[(t >> 6) * 2 + 1] = (uint32_t)(bal >> 32);
-  }
-  __syncthreads();
-  uint32_t my[kAncWords];
-  int depth = -1;
-  bool acc = t < N;
-#pragma unroll
-  for (int w = 0; w < kAncWords; w++) {
-    my[w] = (t < N) ? sh.anc.anc[t][w] : 0u;
-    depth += __popc(my[w]);
-    acc = acc && ((my[w] & ~sh.match[w]) == 0u);
-  }
-  if (depth > g.max_depth || unresolved >= 0) {  // (an unresolved node is deeper than the rounds reach, hence too deep)
-    acc = false;
-    if (t < N) __hip_atomic_fetch_or(as_global(g.status), 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  uint32_t key = acc ? ((uint32_t)(depth + 1) << 16) | (uint32_t)(0xffff - t) : 0u;
-  key = wave_max_u32(key);
-  if ((t & 63) == 0 && t < CB_MAX_NODES) sh.key[t >> 6] = key;
-  __syncthreads();
-  key = sh.key[0];
-  for (int w = 1; w < 4; w++) key = sh.key[w] > key ? sh.key[w] : key;
-  const int best = 0xffff - (int)(key & 0xffff);  // the root is always accepted, so key != 0
-  const int L = (int)(key >> 16) - 1;
-  if (t == best) {
-#pragma unroll
-    for (int w = 0; w < kAncWords; w++) sh.best[w] = my[w];
-  }
-  __syncthreads();
-  const int stride = g.max_depth + 1;
-  if (t < N && ((sh.best[t >> 5] >> (t & 31)) & 1u)) {
-    as_global(g.path)[b * stride + depth] = t;
-    as_global(g.tok_user)[b * stride + depth] = a;
-  }
-  if (t > L && t < stride) {
-    as_global(g.path)[b * stride + t] = -1;
-    as_global(g.tok_user)[b * stride + t] = -1;
-  }
-  if (t == 0) {
-    as_global(g.len_ctx)[b] = L;
-    as_global(g.len_user)[b] = L;
-  }
-  if (g.done_flag) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // every wave's result stores, before the barrier
-  __syncthreads();
-  publish_done(g, b, t == 0);
+// Parent of node t as loaded -> as used (-1 at the root; an entry outside [0, t) becomes "child of the
+// root" and is reported in the status word).
+__device__ __forceinline__ int checked_parent(int raw, int t, int32_t* status) {
+  const bool bad = t == 0 ? raw != -1 : (raw < 0 || raw >= t);
+  if (bad) __hip_atomic_fetch_or(as_global(status), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return t == 0 ? -1 : (bad ? 0 : raw);
+}
+// The row's first maximum; the word is made zero again for the next launch.
+__device__ __forceinline__ int take_argmax(const AcceptArgs& g, int row) {
+  CBL_GLOBAL unsigned long long* const p = as_global(g.best) + (int64_t)row * kAmaxStride;
+  const int a = amax_word_index(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  as_global(g.argmax_out)[row] = a;
+  return a;
 }
 
-// The same acceptance for a tree of at most 64 nodes by ONE wavefront (lane t owns node t; the
-// other waves of the workgroup are not involved and may do something else meanwhile): no LDS
-// allocation and no barrier, the ancestor sets are 64-bit lane values combined with lane permutes.
+// Greedy acceptance of one sequence's tree by ONE wavefront.  A node is accepted when every non-root
+// node on its chain carries the token generated at that node's parent; the accepted node of greatest
+// depth wins (lowest index among equals) and its chain is the path.  The other waves of the workgroup
+// are not involved.  This form: at most 64 nodes, lane t owns node t, no LDS; the ancestor sets are
+// 64-bit lane values combined with lane permutes, and "accepted" is "the set is a subset of the matching
+// nodes".
 __device__ __forceinline__ unsigned long long shfl_u64(unsigned long long x, int lane) {
   const uint32_t lo = __shfl((uint32_t)x, lane, 64), hi = __shfl((uint32_t)(x >> 32), lane, 64);
   return (unsigned long long)lo | ((unsigned long long)hi << 32);
 }
-template <bool COHERENT>
-__device__ __forceinline__ void accept_wave(const AcceptArgs& g, int b, int off, int N) {
+__device__ __forceinline__ void accept_small(const AcceptArgs& g, int b, int off, int N) {
   const int t = threadIdx.x & 63;
-  N = N > 64 ? 64 : N;
   const bool live = t < N;
-  int par_raw = -1, tok = 0;
+  int par = -1, tok = 0, a = -1;
   if (live) {
-    par_raw = as_global(g.parent)[off + t];
+    const int raw = as_global(g.parent)[off + t];
     tok = as_global(g.tokens)[off + t];
-  }
-  int a = -1;
-  if (live) {
-    float bv = -INFINITY;
-    int bi = 0x7fffffff;
-    const ArgmaxPartial* row = g.partial + (int64_t)(off + t) * g.nchunks * g.slot_stride;
-    for (int c0 = 0; c0 < g.nchunks; c0 += 4) {
-      float v[4];
-      int i[4];
-#pragma unroll
-      for (int u = 0; u < 4; u++)
-        amax_load<COHERENT>(row + (int64_t)(c0 + u < g.nchunks ? c0 + u : g.nchunks - 1) * g.slot_stride, v[u], i[u]);
-#pragma unroll
-      for (int u = 0; u < 4; u++) amax_take(bv, bi, v[u], i[u]);
-    }
-    a = bi;
-    as_global(g.argmax_out)[off + t] = a;
-  }
-  int par = -1;
-  if (live) {
-    if (t == 0) {
-      if (par_raw != -1) __hip_atomic_fetch_or(as_global(g.status), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      par = par_raw;
-      if (par < 0 || par >= t) {
-        __hip_atomic_fetch_or(as_global(g.status), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        par = 0;
-      }
-    }
+    a = take_argmax(g, off + t);
+    par = checked_parent(raw, t, g.status);
   }
   const int a_par = __shfl(a, par < 0 ? 0 : par, 64);
   const bool match = live && (t == 0 || tok == a_par);
@@ -420,160 +166,296 @@ __device__ __forceinline__ void accept_wave(const AcceptArgs& g, int b, int off,
   publish_done(g, b, t == 0);
 }
 
-// The logits work of one verification call as a list of items (row, chunk), item = row * nchunks +
-// chunk, shared out among the workgroups of a launch that has at least as many workgroups as there
-// are items: workgroup w takes item w.  bf16 logits and sequences of at most 64 nodes only (the
-// launcher checks all three).
+// The same for up to CB_MAX_NODES nodes, lane t owning nodes t, t + 64, t + 128, t + 192, with a few KiB
+// of LDS of the wave's own.  Pointer jumping on one word per node -- ancestor pointer, depth collected,
+// "all matched so far" --, every round's pointers kept so that the path can be marked afterwards: from
+// the winner, the 2^r-th ancestors of all marked nodes for r from the last round down mark exactly its
+// chain.  (The wave's LDS accesses execute in program order; the waits keep the compiler from moving
+// them across.)
+struct AcceptWaveLds {
+  int32_t a[CB_MAX_NODES];
+  uint32_t state[CB_MAX_NODES];      // bits 0-8 ancestor + 1 (0: none left), bit 9 matched, bits 16.. depth
+  int16_t jump[8][CB_MAX_NODES];     // each round's ancestor pointers, -1 none
+  uint32_t mark[CB_MAX_NODES];
+};
+__device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+__device__ __forceinline__ void accept_large(AcceptWaveLds& sh, const AcceptArgs& g, int b, int off, int N) {
+  constexpr int KN = CB_MAX_NODES / 64;
+  const int lane = threadIdx.x & 63;
+  int par[KN], tok[KN], a[KN];
+#pragma unroll
+  for (int k = 0; k < KN; k++) {
+    const int t = lane + 64 * k;
+    par[k] = t < N ? as_global(g.parent)[off + t] : -1;
+    tok[k] = t < N ? as_global(g.tokens)[off + t] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < KN; k++) {
+    const int t = lane + 64 * k;
+    a[k] = -1;
+    if (t < N) {
+      a[k] = take_argmax(g, off + t);
+      par[k] = checked_parent(par[k], t, g.status);
+    }
+    sh.a[t] = a[k];
+    sh.mark[t] = 0;
+  }
+  wave_lds_sync();
+  uint32_t st[KN];
+#pragma unroll
+  for (int k = 0; k < KN; k++) {
+    const int t = lane + 64 * k;
+    const bool match = t == 0 || (t < N && tok[k] == sh.a[par[k] < 0 ? 0 : par[k]]);
+    st[k] = (uint32_t)(par[k] + 1) | (match ? 0x200u : 0u) | (par[k] >= 0 ? 0x10000u : 0u);
+    sh.state[t] = st[k];
+  }
+  const int rounds = jump_rounds(g.max_depth);
+  for (int r = 0; r < rounds; r++) {
+    wave_lds_sync();
+    uint32_t other[KN];
+#pragma unroll
+    for (int k = 0; k < KN; k++) {
+      const int j = (int)(st[k] & 0x1ffu) - 1;
+      sh.jump[r][lane + 64 * k] = (int16_t)j;
+      other[k] = sh.state[j < 0 ? 0 : j];
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < KN; k++) {
+      if ((st[k] & 0x1ffu) != 0) {
+        st[k] = (other[k] & 0x1ffu) | (st[k] & other[k] & 0x200u) | ((st[k] & 0xffff0000u) + (other[k] & 0xffff0000u));
+        sh.state[lane + 64 * k] = st[k];
+      }
+    }
+  }
+  uint32_t key = 0;
+#pragma unroll
+  for (int k = 0; k < KN; k++) {
+    const int t = lane + 64 * k;
+    if (t >= N) continue;
+    const int depth = (int)(st[k] >> 16);
+    if (depth > g.max_depth || (st[k] & 0x1ffu) != 0) {  // (an unresolved node is deeper than the rounds reach, hence too deep)
+      __hip_atomic_fetch_or(as_global(g.status), 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (st[k] & 0x200u) {
+      const uint32_t kk = ((uint32_t)(depth + 1) << 16) | (uint32_t)(0xffff - t);
+      key = kk > key ? kk : key;
+    }
+  }
+  key = wave_max_u32(key);
+  const int best = 0xffff - (int)(key & 0xffff);  // the root is always accepted, so key != 0
+  const int L = (int)(key >> 16) - 1;
+  if (lane == 0) sh.mark[best] = 1;
+  for (int r = rounds - 1; r >= 0; r--) {
+    wave_lds_sync();
+#pragma unroll
+    for (int k = 0; k < KN; k++) {
+      const int t = lane + 64 * k;
+      const int j = sh.jump[r][t];
+      if (sh.mark[t] && j >= 0) sh.mark[j] = 1;
+    }
+  }
+  wave_lds_sync();
+  const int stride = g.max_depth + 1;
+#pragma unroll
+  for (int k = 0; k < KN; k++) {
+    const int t = lane + 64 * k;
+    if (t < N && sh.mark[t]) {
+      const int depth = (int)(st[k] >> 16);
+      as_global(g.path)[b * stride + depth] = t;
+      as_global(g.tok_user)[b * stride + depth] = a[k];
+    }
+  }
+  for (int d = lane; d < stride; d += 64) {
+    if (d > L) {
+      as_global(g.path)[b * stride + d] = -1;
+      as_global(g.tok_user)[b * stride + d] = -1;
+    }
+  }
+  if (lane == 0) {
+    as_global(g.len_ctx)[b] = L;
+    as_global(g.len_user)[b] = L;
+  }
+  publish_done(g, b, lane == 0);
+  wave_lds_sync();
+}
+
+__device__ __forceinline__ void accept_wave(AcceptWaveLds& sh, const AcceptArgs& g, int b, int off, int N) {
+  if (N <= 64) accept_small(g, b, off, N);
+  else accept_large(sh, g, b, off, N > CB_MAX_NODES ? CB_MAX_NODES : N);
+}
+
+// The logits work of one verification call: items (row, chunk of kArgmaxChunk elements), item = row *
+// chunks + chunk, shared out evenly, in order, among all wavefronts of the workgroups that do it.
 struct LogitsWork {
-  const uint16_t* logits;  // [rows][V] bf16
+  const void* logits;   // [rows][V]
   int64_t V;
   int32_t rows;         // total tree nodes of the call
   int32_t batch;
-  ArgmaxPartial* partial_out;  // same memory and spacing as accept.partial
-  uint32_t* tickets;    // [B] items finished per sequence, zero between launches
+  int32_t chunks;       // per row
+  int32_t n_wgs;        // workgroups that share the work (the first ones of the launch)
+  int32_t is_f32;       // element type of the logits: bf16 or fp32
+  int32_t accept_after;  // 1: the wave that completes a sequence's rows runs its acceptance
+  uint32_t* tickets;    // [B][kTicketWords] items finished per sequence, zero between launches
   AcceptArgs accept;
 };
 
-struct TailLds {
-  ScanLds scan;
-  int flag0;
-};
+// First maximum of elements [e0, e1) of one row by one wavefront; the result (a word of amax_word) is
+// valid in every lane.  Bound by the loads: a wave requests 16 KiB at a time (kVecs loads of 16 bytes per
+// lane, all in flight before the first is looked at) and spends about 12 vector instructions per load on the
+// maximum alone; where in the block it is first attained is looked up only in blocks that raise it.  A row may
+// start at any element: the elements in front of the first and behind the last whole 16-byte piece are taken
+// one by one.
+template <typename T>
+struct WaveScan {
+  static constexpr int VEC = 16 / sizeof(T);
+  static constexpr int kVecs = 16;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// A workgroup's item in steps that the attention code calls where they cost least: the loads in
-// front of its first K/V requests (prefetch_first), the reduction once they have landed
-// (mid_consume), the combination of the waves' candidates and the partial's store behind the next
-// barrier (mid_combine), the ticket once a full wait has covered that store (early_ticket); what has
-// not happened by the end of the key sweep is caught up on there (scan_first and the ticket halves,
-// beside the attention's own stores and ticket).  The ticket counts the finished items of the
-// item's sequence; the workgroup whose ticket completes the count (every partial is then in memory:
-// each workgroup waited for its own agent-scope store first) has its first wave run the acceptance
-// for that sequence (accept_first).  Nobody waits for anybody, so the order in which workgroups run
-// is irrelevant.  finish() does whatever has not been done by then (a workgroup may leave the
-// attention early).  Every method except the ticket halves must be called by all NT threads.
-template <int NT>
-struct LogitsHook {
-  const LogitsWork& lw;
-  const SeqMetaLanes& ml;  // the sequences' shapes, one per lane (no memory access when they are looked up)
-  TailLds& sh;
-  int wg;
-  int state;  // 0 untouched, 1 partial stored but not counted, 2 no item, 3 counted, 4 loads in flight,
-              // 5 the waves' candidates are in LDS (not yet combined), 6 counted and, where it fell to
-              // this workgroup, accepted, 7 partial stored and its ticket already drawn (early_old)
-  uint32_t early_old = 0;  // thread 0: what the early ticket returned
-  int b0;     // the item's sequence
-  ChunkScan<uint16_t, NT> pre;
-  __attribute__((address_space(3))) unsigned long long* dbg = nullptr;  // timing aid: 8 timestamps (thread 0) in LDS, or null
-
-  __device__ __forceinline__ LogitsHook(const LogitsWork& lw_, const SeqMetaLanes& ml_, TailLds& sh_, int wg_)
-      : lw(lw_), ml(ml_), sh(sh_), wg(wg_), state(0), b0(0) {}
-  __device__ __forceinline__ int node_off(int b) const { return __builtin_amdgcn_readlane(ml.o0, b); }
-  __device__ __forceinline__ int node_count(int b) const { return __builtin_amdgcn_readlane(ml.o1, b) - node_off(b); }
-  __device__ __forceinline__ const uint16_t* row_base() const { return lw.logits + (int64_t)(wg / lw.accept.nchunks) * lw.V; }
-
-  __device__ __forceinline__ void stamp(int i) const {  // (timing aid)
-    if (dbg != nullptr && threadIdx.x == 0) dbg[i] = wall_clock64();
+  static __device__ __forceinline__ float to_f32(T x) {
+    if constexpr (sizeof(T) == 2) return __uint_as_float((uint32_t)x << 16);
+    else return x;
   }
-
-  // after prefetch_first(): whether every thread has ChunkScan::kVecPerThread loads in flight
-  __device__ __forceinline__ bool loads_in_flight() const { return state == 4 && pre.nvec > 0; }
-  __device__ __forceinline__ void prefetch_first() {
-    if (state != 0) return;
-    const int nchunks = lw.accept.nchunks;
-    if (wg >= lw.rows * nchunks) {
-      state = 2;
-      return;
+  static __device__ __forceinline__ float elem(const u32x4& u, int j) {  // (j: a constant)
+    if constexpr (sizeof(T) == 2) return __uint_as_float((j & 1) ? (u[j >> 1] & 0xffff0000u) : (u[j >> 1] << 16));
+    else return __uint_as_float(u[j]);
+  }
+  static __device__ __forceinline__ float vec_max(const u32x4& u) {
+    if constexpr (sizeof(T) == 2) {
+      const float m = max3(elem(u, 0), elem(u, 1), elem(u, 2));
+      return max3(max3(m, elem(u, 3), elem(u, 4)), max3(elem(u, 5), elem(u, 6), elem(u, 7)), m);
+    } else {
+      const float m = max3(elem(u, 0), elem(u, 1), elem(u, 2));
+      return max3(m, elem(u, 3), m);
     }
-    const int row = wg / nchunks;
-    // sequence of the row: the number of sequences that end at or before it
-    b0 = __popcll(__ballot((int)(threadIdx.x & 63) < lw.batch - 1 && ml.o1 <= row));
-    pre.template issue<true>(row_base(), lw.V, wg - row * nchunks, threadIdx.x);
-    state = 4;
-  }
-  // The scan in pieces, for a caller that has barriers of its own to offer (all threads call each):
-  // mid_consume() once the prefetched loads have landed (a vmcnt wait of the caller's that covers
-  // them: the compiler does not track them) -- only if the item has no ragged rest,
-  // whose loads would have to be waited for on the spot --, a workgroup barrier, mid_combine(), and,
-  // once a vmcnt(0) wait of the first wave has followed, early_ticket().  Whatever has not happened
-  // by then, scan_first() and the ticket calls below catch up on.
-  __device__ __forceinline__ void mid_consume() {
-    if (state != 4 || pre.vec_end != pre.end) return;
-    pre.pin_here();
-    pre.consume(row_base(), threadIdx.x, sh.scan);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the candidate is in LDS before the caller's barrier
-    state = 5;
-  }
-  __device__ __forceinline__ void combine_and_store() {
-    if (threadIdx.x == 0) {
-      float bv;
-      int bi;
-      ChunkScan<uint16_t, NT>::combine(sh.scan, bv, bi);
-      amax_store<true>(lw.partial_out + (int64_t)wg * lw.accept.slot_stride, bv, bi);
-    }
-    state = 1;
-  }
-  __device__ __forceinline__ void mid_combine() {
-    if (state == 5) combine_and_store();
-  }
-  __device__ __forceinline__ void early_ticket() {
-    if (state != 1) return;
-    if (threadIdx.x == 0)
-      early_old = __hip_atomic_fetch_add(as_global(lw.tickets) + b0, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    state = 7;
-  }
-  __device__ __forceinline__ void scan_first() {
-    prefetch_first();
-    if (state == 4) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the item's loads (not tracked by the compiler)
-      pre.pin_here();
-      pre.consume(row_base(), threadIdx.x, sh.scan);
-      state = 5;
-    }
-    if (state != 5) return;
-    __syncthreads();  // the waves' candidates are in LDS
-    combine_and_store();
-  }
-  // One thread only -- the one that stored the partial -- after a vmcnt(0) wait that followed
-  // scan_first() and before a workgroup barrier.  In two halves so that the caller can put an atomic
-  // of its own between them and have both in flight together.
-  __device__ __forceinline__ uint32_t ticket_first_issue() const {
-    if (state == 7) return early_old;
-    return state == 1 ? __hip_atomic_fetch_add(as_global(lw.tickets) + b0, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-  }
-  __device__ __forceinline__ void ticket_first_resolve(uint32_t old) {
-    if (state != 1 && state != 7) return;
-    const uint32_t expect = (uint32_t)node_count(b0) * (uint32_t)lw.accept.nchunks;
-    const bool last = old + 1u == expect;
-    if (last) __hip_atomic_store(as_global(lw.tickets) + b0, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
-    sh.flag0 = last ? 1 : 0;
-  }
-  // all threads, after the barrier that followed the ticket
-  __device__ __forceinline__ void first_counted() {
-    if (state == 1 || state == 7) state = 3;
-  }
-  // all threads, after first_counted(): the acceptance, if this workgroup's ticket completed the
-  // sequence -- by the first wave alone, the other waves go on at once
-  __device__ __forceinline__ void accept_first() {
-    if (state != 3) return;
-    if (sh.flag0 && threadIdx.x < 64) accept_wave<true>(lw.accept, b0, node_off(b0), node_count(b0));
-    state = 6;
   }
 
-  __device__ __forceinline__ void finish() {
-    const bool stamp = dbg != nullptr && threadIdx.x == 0;
-    if (stamp) dbg[0] = wall_clock64();
-    scan_first();
-    if (state == 1 || state == 7) {
-      if (threadIdx.x == 0) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        ticket_first_resolve(ticket_first_issue());
+  static __device__ __forceinline__ unsigned long long run(const T* row_base, int e0, int e1) {
+    const int lane = threadIdx.x & 63;
+    const CBL_GLOBAL T* const base = (const CBL_GLOBAL T*)row_base;
+    // whole 16-byte pieces [v0, v1) of elements, and up to VEC - 1 single elements on either side
+    const int skew = (int)(((uintptr_t)row_base / sizeof(T)) & (VEC - 1));
+    int v0 = e0 + ((VEC - ((e0 + skew) & (VEC - 1))) & (VEC - 1));
+    v0 = v0 < e1 ? v0 : e1;
+    const int nv = (e1 - v0) / VEC;
+    const int v1 = v0 + nv * VEC;
+    const CBL_GLOBAL u32x4* const vp = (const CBL_GLOBAL u32x4*)(base + v0);
+    float best = -INFINITY;  // (uniform)
+    int bidx = 0x7fffffff;
+    for (int i0 = 0; i0 < nv; i0 += 64 * kVecs) {
+      u32x4 u[kVecs];
+#pragma unroll
+      for (int k = 0; k < kVecs; k++) {  // (pieces past the end repeat the last one, which changes nothing)
+        const int i = i0 + 64 * k + lane;
+        u[k] = vp[i < nv ? i : nv - 1];
       }
-      __syncthreads();
-      state = 3;
+      __builtin_amdgcn_sched_barrier(0);  // (all requested before the first is waited for)
+      float vm[kVecs];
+#pragma unroll
+      for (int k = 0; k < kVecs; k++) vm[k] = vec_max(u[k]);
+      float lm = vm[0];
+#pragma unroll
+      for (int k = 1; k + 1 < kVecs; k += 2) lm = max3(lm, vm[k], vm[k + 1]);
+      lm = max3(lm, vm[kVecs - 1], lm);
+      const float m = wave_max_f32(lm);
+      if (__builtin_amdgcn_ballot_w64(m > best) == 0ull) continue;  // (uniform; later blocks hold higher indices)
+      best = m;
+      // lowest index in the block: the lowest k that any lane attains the maximum with, its lowest lane, there
+      // the lowest element
+      uint32_t idx = 0x7fffffffu;
+#pragma unroll
+      for (int k = kVecs - 1; k >= 0; k--) {
+        if (vm[k] == m) {
+          const int i = i0 + 64 * k + lane;
+          int j = VEC - 1;
+#pragma unroll
+          for (int q = VEC - 2; q >= 0; q--) j = elem(u[k], q) == m ? q : j;
+          idx = (uint32_t)(v0 + (i < nv ? i : nv - 1) * VEC + j);
+        }
+      }
+      bidx = (int)wave_min_u32(idx);
     }
-    if (stamp) dbg[1] = wall_clock64();
-    accept_first();
-    if (stamp) dbg[7] = wall_clock64();
+    if (v0 != e0 || v1 != e1) {  // (uniform)
+      const int head = v0 - e0, tail = e1 - v1;
+      const int e = lane < head ? e0 + lane : v1 + (lane - head);
+      const bool has = lane < head + tail;
+      const float x = has ? to_f32(base[has ? e : e0]) : -INFINITY;
+      const float m = wave_max_f32(x);
+      const int mi = (int)wave_min_u32(has && x == m ? (uint32_t)e : 0x7fffffffu);
+      if (m > best || (m == best && mi < bidx)) {
+        best = m;
+        bidx = mi;
+      }
+    }
+    return amax_word(best, bidx);
   }
 };
+
+// One workgroup's share of the logits work: items [items * wg / n, items * (wg + 1) / n), its NW wavefronts
+// taking them in turn.  Their candidates go into the rows' words with atomic maxima; once those are
+// acknowledged (every wave waits for its own, then a barrier) the first wave counts the workgroup's items on
+// their sequences' tickets, and the workgroup whose count completes a sequence -- all candidates are then in
+// memory -- runs the acceptance with that wave.  Nobody waits for anybody, so the order in which workgroups
+// run is irrelevant.
+// Atomics on one word are served about 15 ns apart, so a sequence that many workgroups arrive at has its items
+// counted in 16 groups first, each on a line of its own, and the groups that are full on a last word (one word for
+// all of 512 wavefronts' arrivals: 13 us for a scan of 8 MB).
+constexpr int kTicketGroups = 16;
+constexpr int kTicketStride = 32;                                    // 32-bit words between them (128 bytes)
+constexpr int kTicketWords = (kTicketGroups + 1) * kTicketStride;    // per sequence
+constexpr int kTicketDirect = 48;  // arrivals up to which one word serves a sequence
+
+template <int NW>
+__device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMetaLanes& ml, int wg, AcceptWaveLds& sh) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t items = (int64_t)lw.rows * lw.chunks;
+  const int i0 = (int)(items * wg / lw.n_wgs), i1 = (int)(items * (wg + 1) / lw.n_wgs);
+  for (int i = i0 + w; i < i1; i += NW) {
+    const int row = i / lw.chunks, c = i - row * lw.chunks;
+    const int64_t e0 = (int64_t)c * kArgmaxChunk;
+    const int64_t e1 = e0 + kArgmaxChunk < lw.V ? e0 + kArgmaxChunk : lw.V;
+    const unsigned long long word =
+        lw.is_f32 ? WaveScan<float>::run((const float*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1)
+                  : WaveScan<uint16_t>::run((const uint16_t*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1);
+    if (lane == 0)
+      __hip_atomic_fetch_max(as_global(lw.accept.best) + (int64_t)row * kAmaxStride, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (!lw.accept_after) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (w != 0) return;
+  auto count = [&](CBL_GLOBAL uint32_t* word, uint32_t n, uint32_t full) {  // true: this arrival completed it
+    uint32_t old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(word, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool done = __builtin_amdgcn_readfirstlane(old) + n == full;
+    if (done && lane == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
+    return done;
+  };
+  for (int i = i0; i < i1;) {
+    const int row = i / lw.chunks;
+    // sequence of the row: the number of sequences that end at or before it
+    const int b = __popcll(__ballot(lane < lw.batch - 1 && ml.o1 <= row));
+    const int off = __builtin_amdgcn_readlane(ml.o0, b), N = __builtin_amdgcn_readlane(ml.o1, b) - off;
+    const int first = off * lw.chunks, end = (off + N) * lw.chunks, nb = N * lw.chunks;
+    const int seq_end = end < i1 ? end : i1;
+    CBL_GLOBAL uint32_t* const words = as_global(lw.tickets) + b * kTicketWords;
+    bool done;
+    if ((int64_t)nb * lw.n_wgs <= items * kTicketDirect) {
+      done = count(words, (uint32_t)(seq_end - i), (uint32_t)nb);
+    } else {
+      const int gs = (nb + kTicketGroups - 1) / kTicketGroups, ng = (nb + gs - 1) / gs;
+      done = false;
+      for (int j = i; j < seq_end;) {
+        const int gr = (j - first) / gs;
+        const int g0 = first + gr * gs, g1 = g0 + gs < end ? g0 + gs : end;
+        const int n = (g1 < seq_end ? g1 : seq_end) - j;
+        if (count(words + (1 + gr) * kTicketStride, (uint32_t)n, (uint32_t)(g1 - g0))) done = count(words, 1u, (uint32_t)ng);
+        j += n;
+      }
+    }
+    if (done) accept_wave(sh, lw.accept, b, off, N);
+    i = seq_end;
+  }
+}
 
 }  // namespace cb

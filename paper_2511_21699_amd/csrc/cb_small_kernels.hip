@@ -1,4 +1,4 @@
-// Tree preparation (ancestor sets), vocabulary argmax, greedy acceptance and KV compaction kernels.
+// Tree preparation (ancestor sets), logits scan with greedy acceptance, and KV compaction kernels.
 // gfx950 only; 64-wide wavefronts are assumed throughout.
 #include "cb_logits.h"
 
@@ -77,71 +77,55 @@ hipError_t launch_tree_prepare(hipStream_t st, int batch, const SeqMeta& meta, c
 }
 
 // ------------------------------------------------------------------------------------------------
-// Argmax over the vocabulary: the token the model generates at a node is the first maximum of the
-// node's logits row.  One workgroup scans kArgmaxChunk elements (scan_chunk() of cb_logits.h).
+// Logits scan and greedy acceptance as a launch of their own (logits_share() of cb_logits.h); the
+// workgroups behind the first lw.n_wgs build the ancestor sets of one sequence each, for the scalar
+// attention, which saves a launch of their own.
 // ------------------------------------------------------------------------------------------------
-// Rows [0, rows) of the grid's y dimension scan logits; when `prep` is set, rows [rows, rows + batch)
-// build the ancestor sets of one sequence each (x = 0 only), which saves a launch of their own.
 struct PrepareArgs {
   const int32_t* parent;
   uint32_t* anc;
   int32_t* status;
   int32_t max_depth;
-  int32_t enabled;
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_argmax(const T* __restrict__ logits, int64_t V, int rows,
-                                                ArgmaxPartial* __restrict__ out, int nchunks, SeqMeta meta,
-                                                PrepareArgs prep) {
-  __shared__ PrepareLds prep_lds;
-  if ((int)blockIdx.y >= rows) {
-    if (blockIdx.x == 0 && prep.enabled)
-      tree_prepare_block(prep_lds, meta, blockIdx.y - rows, prep.parent, prep.max_depth, prep.anc, prep.status);
+constexpr int kLogitsWaves = 4;
+
+__global__ __launch_bounds__(64 * kLogitsWaves) void k_logits(LogitsWork lw, SeqMeta meta, PrepareArgs prep) {
+  __shared__ union {
+    AcceptWaveLds accept;
+    PrepareLds prepare;
+  } sh;
+  if ((int)blockIdx.x >= lw.n_wgs) {
+    tree_prepare_block(sh.prepare, meta, blockIdx.x - lw.n_wgs, prep.parent, prep.max_depth, prep.anc, prep.status);
     return;
   }
-  __shared__ ScanLds scan_lds;
-  const int row = blockIdx.y, c = blockIdx.x;
-  float bv;
-  int bi;
-  scan_chunk<T, 256>(logits + (int64_t)row * V, V, c, threadIdx.x, scan_lds, bv, bi);
-  if (threadIdx.x == 0) amax_store<false>(out + (int64_t)row * nchunks + c, bv, bi);
+  const SeqMetaLanes ml = seq_meta_prefetch(meta);
+  logits_share<kLogitsWaves>(lw, ml, blockIdx.x, sh.accept);
 }
 
-hipError_t launch_argmax(hipStream_t st, const void* logits, int dtype, int rows, int64_t V,
-                         ArgmaxPartial* partial, int nchunks, int batch, const SeqMeta& meta,
-                         const int32_t* prep_parent, int max_depth, uint32_t* prep_anc, int32_t* status) {
-  PrepareArgs prep;
-  prep.parent = prep_parent;
-  prep.anc = prep_anc;
-  prep.status = status;
-  prep.max_depth = max_depth;
-  prep.enabled = prep_parent != nullptr;
-  dim3 grid(nchunks, rows + (prep.enabled ? batch : 0));
-  if (dtype == CB_BF16)
-    hipLaunchKernelGGL(k_argmax<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)logits, V, rows, partial, nchunks, meta, prep);
-  else
-    hipLaunchKernelGGL(k_argmax<float>, grid, dim3(256), 0, st, (const float*)logits, V, rows, partial, nchunks, meta, prep);
+// One wavefront per 16 KiB of bf16 logits up to the wavefronts that are resident at once (four or five of these
+// workgroups fit a compute unit), then several chunks for each.
+hipError_t launch_logits(hipStream_t st, const LogitsWork& work, const SeqMeta& meta, const int32_t* prep_parent,
+                         int max_depth, uint32_t* prep_anc, int32_t* status) {
+  LogitsWork lw = work;
+  const int64_t items = (int64_t)lw.rows * lw.chunks;
+  lw.n_wgs = (int32_t)((items + kLogitsWaves - 1) / kLogitsWaves < 1024 ? (items + kLogitsWaves - 1) / kLogitsWaves : 1024);
+  const PrepareArgs prep{prep_parent, prep_anc, status, max_depth};
+  const dim3 grid(lw.n_wgs + (prep_parent ? lw.batch : 0));
+  hipLaunchKernelGGL(k_logits, grid, dim3(64 * kLogitsWaves), 0, st, lw, meta, prep);
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------------------------
-// Greedy acceptance (Section 3.2, last paragraphs), one workgroup per sequence; the arithmetic is
-// accept_sequence() of cb_logits.h.
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_accept(SeqMeta meta, AcceptArgs args) {
-  __shared__ AcceptLds sh;
+// The acceptance alone, one wavefront per sequence (measurements of single steps).
+__global__ __launch_bounds__(64) void k_accept(SeqMeta meta, AcceptArgs args) {
+  __shared__ AcceptWaveLds sh;
   const int b = blockIdx.x;
   const int off = meta.node_off[b], N = meta.node_off[b + 1] - off;
-  if (N <= 64) {
-    if (threadIdx.x < 64) accept_wave<false>(args, b, off, N);
-  } else {
-    accept_sequence<false>(sh, args, b, off, N);
-  }
+  accept_wave(sh, args, b, off, N);
 }
 
 hipError_t launch_accept(hipStream_t st, int batch, const SeqMeta& meta, const AcceptArgs& args) {
-  hipLaunchKernelGGL(k_accept, dim3(batch), dim3(256), 0, st, meta, args);
+  hipLaunchKernelGGL(k_accept, dim3(batch), dim3(64), 0, st, meta, args);
   return hipGetLastError();
 }
 

@@ -1,0 +1,39 @@
+"""The logits scan and the acceptance at the sizes where they can go wrong: rows that start anywhere inside a
+16-byte piece, chunks of a few elements, maxima in the pieces' rests and in several chunks, more nodes than a
+wavefront has lanes, chains as long as the tree; in the attention's launch and as a launch of its own."""
+import numpy as np
+import pytest
+
+from paper_2511_21699_amd import workloads as W
+from tests.gpu_harness import run_case, sample_rows
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("fuse", [1, 0])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [1, 5, 8, 9, 1023, 8192, 8193, 8199, 16391, 33333])
+def test_first_maximum_of_rows_at_any_alignment(V, dtype, fuse):
+    rng = np.random.default_rng(V)
+    par = W.random_tree(rng, 37, 4, 6, False)[0]
+    case = W.custom_case(300 + V, dtype, 1, 2, 2, 128, V, [20], [par], p_match=0.8)
+    x = np.round(rng.standard_normal(case.logits.shape, dtype=np.float32) * 2) / 2      # many equal maxima
+    for i in range(37):                                                                 # a unique one anywhere, edges first
+        if i % 3:
+            x[i, [0, V - 1, min(V - 1, 8191), min(V - 1, 8192), int(rng.integers(V))][i % 5]] = 9.0
+    x[3] = -3.0e38
+    x[4, :] = -0.0
+    x[4, V // 2] = 0.0
+    case.logits = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    run_case(case, options={"fuse_logits": fuse}, what=f"V={V} {dtype}")
+
+
+@pytest.mark.parametrize("N", [64, 65, 128, 129, 255, 256])
+@pytest.mark.parametrize("shape", ["chain", "star", "random"])
+def test_acceptance_of_trees_beyond_a_wavefront(N, shape):
+    rng = np.random.default_rng(N)
+    pars = [W.chain_tree(N) if shape == "chain" else W.star_tree(N) if shape == "star" else W.random_tree(rng, N, 3, 9, False)[0],
+            W.chain_tree(3)]
+    for p in (0.6, 0.99, 1.0):
+        case = W.custom_case(400 + N, "bf16", 2, 2, 2, 128, 700, [33, 5], pars, p_match=p)
+        run_case(case, rows=sample_rows(case, 16), what=f"{shape} {N} p={p}")

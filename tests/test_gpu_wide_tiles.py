@@ -1,0 +1,20 @@
+"""Row tiles of the MFMA attention around their edges: up to 64 rows in one small tile, up to 128 and up to 256 in the
+two forms of the wide one, more in several; head_dim 64 and 128."""
+import numpy as np
+import pytest
+
+from paper_2511_21699_amd import workloads as W
+from tests.gpu_harness import run_case, sample_rows
+
+pytestmark = pytest.mark.gpu
+
+
+# nodes x query heads per kv head = rows of a tile; prefixes of a few keys, around a unit of 32, and enough for the
+# unmasked part of the sweep
+@pytest.mark.parametrize("n,g", [(1, 1), (17, 1), (64, 1), (65, 1), (32, 4), (129, 1), (64, 4), (86, 3), (150, 4)])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,splits", [(3, 1), (31, 1), (700, 1), (1333, 3)])
+def test_row_tile_edges(n, g, D, S, splits):
+    par = W.random_tree(np.random.default_rng(n + S), n, 4, 7, False)[0]
+    case = W.custom_case(5200 + n + S, "bf16", 1, 2 * g, 2, D, 500, [S], [par], paged=False, q_scale=2.0)
+    run_case(case, rows=sample_rows(case, 50), options={"splits": splits, "attn_impl": 2}, what=f"rows {n * g} D={D} S={S}")
