@@ -313,7 +313,7 @@ def main():
         roof_kernel = "cb::k_verify_mfma (tree attention incl. split merge + logits argmax + acceptance, one launch)"
         roof_bytes, roof_us = attn_bytes + case.logits_bytes(), verify_us
     else:
-        roof_kernel = "cb::k_attn_mfma (tree attention incl. split merge)" if info["impl"] == 2 else "cb::k_attn_simt + cb::k_merge"
+        roof_kernel = "cb::k_attn_mfma (tree attention incl. split merge)" if info["impl"] == 2 else "cb::k_attn_f32 (tree attention incl. split merge)"
         roof_bytes, roof_us = attn_bytes, attn_us
     roof_gbps = roof_bytes / roof_us / 1e3
 

@@ -103,11 +103,11 @@ int cb_workspace_bytes(const cb_config *cfg, size_t *bytes);
 int cb_init(const cb_config *cfg, void *workspace, size_t workspace_bytes, cb_ctx **out);
 
 /* Host-only: how the attention stage (Section 3.2, tree attention over prefix + ancestors) would be
- * cut up for these lengths, without touching a device.  plan[0] = kernel family (1 scalar, 2 MFMA),
+ * cut up for these lengths, without touching a device.  plan[0] = kernel family (1 fp32, 2 bf16 MFMA),
  * plan[1] = partial slots per output row (splits of the longest sequence), plan[2] = keys per split
  * (a multiple of 32; splits x keys covers the longest sequence, shorter sequences use fewer splits),
- * plan[3] = output rows per workgroup tile (1 for the scalar family), plan[4] = workgroups launched
- * that have keys to sweep.  forced_splits > 0 overrides the planner's split count (capped at the
+ * plan[3] = output rows per tile and plan[4] = (tile, split) pairs that have keys to sweep: the workgroups
+ * launched in family 2; family 1 is counted in single rows, of which a workgroup takes up to 16.  forced_splits > 0 overrides the planner's split count (capped at the
  * configuration's max_splits), like the "splits" option.  All arrays are host memory.  CB_EINVAL on
  * a bad configuration or shape. */
 int cb_plan_attention(const cb_config *cfg, int32_t batch, const int32_t *kv_len,
@@ -222,15 +222,15 @@ int cb_device_status(cb_ctx *ctx, int32_t *status);
 
 /* Options; unknown names give CB_EINVAL.
  *   "splits"     force the number of KV-sequence splits (0 = automatic)
- *   "attn_impl"  0 = automatic, 1 = scalar kernel (at most 8 splits on a configuration the MFMA kernel
- *                takes), 2 = MFMA kernel (bf16, head_dim 64 or 128 only)
+ *   "attn_impl"  0 or 2 = the matrix-core kernel of the configuration's type, 1 = scalar kernel (at most 8
+ *                splits in bf16; for comparisons)
  *   "stages"     bit mask of the steps cb_verify_tree_device enqueues (1 ancestor sets, 2 attention,
  *                4 argmax, 8 acceptance; default 15) -- for timing one step in isolation; with a
  *                step left out the results of the call are those of an earlier call or undefined
  *   "parallel_scan"  1 = run the logits scan on the context's second stream beside the attention
  *   "fuse_logits"    0 = never run the logits scan and the acceptance inside the attention launch
- *                    (default 1: calls whose sequences have at most 64/g nodes, on the MFMA kernel, are one
- *                    launch: some of its workgroups do the logits work, the others the attention)
+ *                    (default 1: calls in fp32, and in bf16 those whose sequences have at most 64/g nodes, are
+ *                    one launch: some of its workgroups do the logits work, the others the attention)
  *   "logits_wgs"     workgroups of that launch for the logits work (a multiple of 8 up to 192;
  *                    0 = automatic)
  *   "coop_merge"     0 = never merge the splits cooperatively (default 1: a grid that fits the
@@ -252,7 +252,7 @@ int cb_set_option(cb_ctx *ctx, const char *name, int64_t value);
 int cb_last_attention_ms(cb_ctx *ctx, float *ms);
 
 /* How the last verify call was launched (host memory, no device access): info[0] = attention kernel
- * family (1 scalar, 2 MFMA), info[1] = partial slots per output row, info[2] = keys per split,
+ * family (1 fp32 or scalar, 2 bf16 MFMA), info[1] = partial slots per output row, info[2] = keys per split,
  * info[3] = 1 if the logits scan and the acceptance ran inside the attention launch, else 0,
  * info[4] = how the splits were merged (0 one split, 1 cooperatively by the tile's workgroups, 2 by the
  * last workgroup of a tile to finish, 3 by a separate merge kernel), info[5] = kernels the call

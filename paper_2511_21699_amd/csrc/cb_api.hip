@@ -100,7 +100,7 @@ WsLayout ws_layout(const cb_config& c) {
 }
 
 struct Plan {
-  int impl;    // 1 scalar, 2 MFMA
+  int impl;    // 1 fp32 (or the scalar kernel on request), 2 bf16 MFMA
   int nsplit;  // partial slots per row
   int chunk;   // keys per split
   int max_nodes, max_len;
@@ -230,6 +230,8 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
   int nsplit;
   if (opt_splits > 0) {
     nsplit = (int)std::min<int64_t>(opt_splits, max_splits);
+  } else if (p.impl == 1 && c.qkv_dtype == CB_F32 && opt_impl != 1) {
+    nsplit = attn_f32_splits(c.num_q_heads, c.num_kv_heads, c.head_dim, max_splits, batch, kv_len, node_offsets, p.max_len, units);
   } else if (p.impl == 1) {
     // one workgroup per (row, split): aim for a few workgroups per compute unit, but never split
     // below 1024 keys -- a second (merge) launch costs more than a short row does
@@ -368,13 +370,14 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     CB_HIP(ctx, launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.amax_best), ctx->lay.max_total_nodes, kAmaxStride, 1));
     ctx->amax_dirty = false;
   }
-  // A verification whose tiles are small enough is one launch: its first workgroups do the logits work, and the
+  // A verification in fp32, or whose tiles are small enough, is one launch: its first workgroups do the logits work, and the
   // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
   // option does not change the splits and with them the rounding).
   int max_nodes = 0;
   for (int b = 0; b < batch; b++) max_nodes = std::max(max_nodes, node_offsets[b + 1] - node_offsets[b]);
   const bool small_tiles = attn_mfma_tile_rows(max_nodes * (c.num_q_heads / c.num_kv_heads)) == 64;
-  int n_logits = (stage_mask & 8) && small_tiles ? fused_logits_wgs(c, batch, kv_len, node_offsets) : 0;
+  const bool f32_tiles = c.qkv_dtype == CB_F32 && ctx->opt_impl != 1;
+  int n_logits = (stage_mask & 8) && (small_tiles || f32_tiles) ? fused_logits_wgs(c, batch, kv_len, node_offsets) : 0;
   if (n_logits && ctx->opt_logits_wgs > 0) n_logits = (int)ctx->opt_logits_wgs;
   const Plan plan = ctx->fixed_plan ? *ctx->fixed_plan
                                     : plan_attention(c, ctx->lay.max_splits, ctx->lay.scalar_splits, ctx->opt_impl, ctx->opt_splits, batch, kv_len, node_offsets, 256 - n_logits);
@@ -438,9 +441,9 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   acc.done_value = ctx->call_seq;
   ctx->want_done = nullptr;
   // Otherwise, and with option "fuse_logits" = 0, the logits work is a launch of its own in front.
-  const bool fused = use_mfma && small_tiles && ctx->opt_fuse != 0 && (stages & 2) && (stages & 4) && (stages & 8) &&
-                     attn_mfma_can_fuse(ap, plan.max_nodes);
-  const bool fork = !fused && ctx->opt_fork != 0 && use_mfma && (stages & 2) && (stages & 4);
+  const bool fused = ctx->opt_fuse != 0 && (stages & 2) && (stages & 4) && (stages & 8) &&
+                     (f32_tiles || (use_mfma && small_tiles && attn_mfma_can_fuse(ap, plan.max_nodes)));
+  const bool fork = !fused && ctx->opt_fork != 0 && (use_mfma || f32_tiles) && (stages & 2) && (stages & 4);
   hipStream_t scan_stream = st;
   int merge_kind = plan.nsplit > 1 ? 3 : 0, kernels = 0;  // (the scalar attention always merges with a kernel of its own)
   if (fork) {
@@ -450,12 +453,12 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   }
   if (fused) {
   } else if (stages & 4) {
-    const bool carry = !use_mfma && (stages & 1);
+    const bool carry = !use_mfma && !f32_tiles && (stages & 1);
     CB_LAUNCH(ctx, launch_logits(scan_stream, lw, meta, carry ? d_parent : nullptr, c.max_depth,
                                  carry ? ctx->dev<uint32_t>(ctx->lay.anc) : nullptr, carry ? ctx->dev<int32_t>(ctx->lay.status) : nullptr));
     if (!lw.accept_after) ctx->amax_dirty = true;
     kernels++;
-  } else if (!use_mfma && (stages & 1)) {
+  } else if (!use_mfma && !f32_tiles && (stages & 1)) {
     CB_LAUNCH(ctx, launch_tree_prepare(st, batch, meta, d_parent, c.max_depth, ctx->dev<uint32_t>(ctx->lay.anc),
                                     ctx->dev<int32_t>(ctx->lay.status)));
     kernels++;
@@ -467,6 +470,12 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   } else if (use_mfma) {
     CB_LAUNCH(ctx, launch_attn_mfma(st, ap, meta, plan.max_nodes, total, fused ? &lw : nullptr, &merge_kind));  // merges its own splits
     kernels += merge_kind == 3 ? 2 : 1;
+  } else if (f32_tiles) {
+    const bool external = plan.nsplit > 1 && ap.force_external_merge;
+    CB_LAUNCH(ctx, launch_attn_f32(st, ap, meta, plan.max_nodes, fused ? &lw : nullptr));
+    if (external) CB_LAUNCH(ctx, launch_merge(st, ap, meta, c.qkv_dtype, total));
+    merge_kind = plan.nsplit > 1 ? (external ? 3 : 2) : 0;
+    kernels += external ? 2 : 1;
   } else {
     CB_LAUNCH(ctx, launch_attn_simt(st, ap, meta, c.qkv_dtype, plan.max_nodes));
     if (plan.nsplit > 1) CB_LAUNCH(ctx, launch_merge(st, ap, meta, c.qkv_dtype, total));

@@ -1,5 +1,6 @@
-// Scalar (non-MFMA) tree attention and the split merge.  This is the fp32 path (all arithmetic in
-// fp32, accurate expf) and the fallback for shapes the MFMA kernel does not take.  gfx950 only.
+// Scalar (non-MFMA) tree attention and the split merge: all arithmetic in fp32, accurate expf.  What the matrix-core
+// kernels are compared with (option "attn_impl" = 1), and the fallback for block sizes the bf16 one does not take.
+// gfx950 only.
 //
 // Tree attention, Section 3.2 of the paper: node i of a tree attends to the KV-cached prefix
 // (slots 0..S-1) and to the tree nodes on its own ancestor chain (slots S+a, a in anc(i)).

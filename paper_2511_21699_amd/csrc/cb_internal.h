@@ -153,11 +153,12 @@ struct AttnParams {
   const void* q;     // [sumN][Hq][D]
   void* out;         // [sumN][Hq][D]
   KvAddr kv;
-  const uint32_t* anc;  // [sumN][kAncWords] (scalar kernel; the MFMA kernel builds the sets itself)
+  const uint32_t* anc;  // [sumN][kAncWords] (scalar kernel; the MFMA kernels build the sets themselves)
   const int32_t* parent;  // [sumN] device tree, local parent indices
-  float* partial;       // split partials; scalar kernel: [sumN*Hq][nsplit][partial_stride(D)]: o[D] (unnormalised), m, l, pad;
-                        // the MFMA kernel has its own bf16 layout (cb_attn_mfma.hip)
+  float* partial;       // split partials; scalar and fp32 MFMA kernels: [sumN*Hq][nsplit][partial_stride(D)]: o[D] (unnormalised), m, l, pad;
+                        // the bf16 MFMA kernels have their own layout (cb_attn_tile.h)
   uint32_t* tickets;    // two 64-bit words per (sequence, kv head, row tile): ticket, splits that gave up waiting
+                        // (fp32 MFMA kernel: one 32-bit word per 16-row tile)
   uint32_t* coop_tickets;  // cooperative merge: kCoopTiles stretches of kCoopTicketStride bytes, two 64-bit words used in each
   int32_t Hq, Hkv, D;
   int32_t chunk;        // keys per split
@@ -195,6 +196,11 @@ hipError_t launch_compact(hipStream_t st, int batch, const SeqMeta& meta, const 
                           const int32_t* path, const int32_t* acc_len, int32_t* new_len);
 hipError_t launch_attn_simt(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int dtype,
                             int max_nodes_in_call);
+// fp32 attention on the matrix cores, 16-row tiles; with lw != nullptr the same launch also scans the logits and runs the
+// acceptance.  Partials in the scalar kernel's layout (force_external_merge: launch_merge has to follow), tickets: a 32-bit
+// word per (sequence, kv head, 16-row tile), zero between launches.
+int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int32_t* kv_len, const int32_t* node_offsets, int max_len, int units);
+hipError_t launch_attn_f32(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw);
 hipError_t launch_merge(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int dtype, int total_nodes);
 int attn_mfma_tile_rows(int mrows);            // rows per workgroup tile chosen for a given g*N
 // bytes the MFMA path's partial states can take (its own layout, padded to 16-row tiles per kv head)
