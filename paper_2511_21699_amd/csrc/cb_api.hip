@@ -324,6 +324,17 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
   chunk = (chunk + 31) / 32 * 32;
   p.chunk = std::max(chunk, 32);
   p.nsplit = (p.max_len + p.chunk - 1) / p.chunk;
+  if (p.impl == 2) {
+    // A geometry that the MFMA kernel does not take (blocks that are no power of two, say) goes to the scalar kernel,
+    // whose fp32 partials have room for fewer splits: it is planned as such.
+    AttnParams ap{};
+    ap.Hq = c.num_q_heads;
+    ap.Hkv = c.num_kv_heads;
+    ap.D = c.head_dim;
+    ap.nsplit = p.nsplit;
+    ap.kv.block_size = c.block_size;
+    if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units);
+  }
   return p;
 }
 
@@ -409,7 +420,7 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   // bit 0 ancestor sets, 1 attention, 2 argmax, 3 acceptance; the option is a measurement aid, the
   // mask is what the entry point asks for (cb_tree_attention_device: the first two)
   const int64_t stages = ctx->opt_stages & stage_mask;
-  const bool use_mfma = plan.impl == 2 && attn_mfma_supports(ap);
+  const bool use_mfma = plan.impl == 2;
   // The logits scan does not depend on the attention, and the MFMA attention builds the ancestor sets
   // it needs itself, so with option "parallel_scan" the scan runs beside it on the context's second
   // stream (fork/join with events; stream capture turns them into parallel graph branches).  Measured

@@ -136,6 +136,21 @@ def test_attention_plan_invariants_on_the_paper_shapes_and_random_batches():
         assert p["nsplit"] <= forced
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("block", [1, 16, 24, 65535])
+def test_attention_plan_of_geometries_for_the_scalar_kernel(D, block):
+    """bf16 caches whose blocks are no power of two run on the scalar kernel, whose fp32 partial states have room
+    for 8 splits in a bf16 configuration, whatever the split count that is asked for."""
+    for Hkv, S, forced in ((1, 60000, 0), (1, 60000, 64), (2, 900, 40), (8, 5000, 0)):
+        cfg = B.make_config(4 * Hkv, Hkv, D, "bf16", "bf16", 1, 16, 8, 1000, block)
+        plan = B.plan_attention(cfg, [S], [0, 16], forced)
+        _plan_invariants(cfg, [S], [0, 16], plan, 4)
+        scalar = block & (block - 1) != 0
+        assert plan["impl"] == (1 if scalar else 2)
+        if scalar:
+            assert plan["nsplit"] <= 8
+
+
 def test_attention_plan_rejects_bad_shapes():
     cfg = B.make_config(8, 8, 128, "bf16", "bf16", 2, 8, 3, 100)
     for kv, offs in (([5], [1, 4]), ([5], [0, 0]), ([5], [0, 9]), ([-1], [0, 3]), ([1, 2, 3], [0, 1, 2, 3])):

@@ -20,3 +20,14 @@ def test_table_slices_beyond_the_lds_ring(block, S, splits, n, monkeypatch):
     case.block_size = block
     ver_rows = sample_rows(case, 60)
     run_case(case, rows=ver_rows, options={"splits": splits, "attn_impl": 2}, what=f"block {block} S={S}")
+
+
+# blocks that are no power of two: the scalar kernel, with the split count cut to what its partial states have room for
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,splits", [(40, 0), (3000, 40), (6000, 0)])
+def test_blocks_that_are_no_power_of_two(D, S, splits, monkeypatch):
+    monkeypatch.setattr(W, "BLOCK_TOKENS", 24)
+    par = W.random_tree(np.random.default_rng(S), 16, 4, 7, False)[0]
+    case = W.custom_case(4300 + S, "bf16", 1, 4, 1, D, 500, [S], [par], paged=True, q_scale=2.0)
+    case.block_size = 24
+    run_case(case, rows=sample_rows(case, 60), options={"splits": splits}, what=f"block 24 D={D} S={S}")
