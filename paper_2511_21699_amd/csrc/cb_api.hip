@@ -75,21 +75,23 @@ WsLayout ws_layout(const cb_config& c) {
   L.anc = take(mt * kAncWords * 4);
   L.parent = take(mt * 4 * 2);  // staged tree of the host-array form: parents, then tokens right behind them
   L.tokens = L.parent;         // (placed per call)
-  L.amax_best = take(mt * kAmaxStride * 8);
   L.amax_out = take(mt * 4);
   L.path = take(c.max_batch * stride * 4);
   L.len_ctx = take(c.max_batch * 4);
   L.res_len = take(c.max_batch * (1 + stride) * 4);  // results of the host-array form: lengths, then tokens right behind them
   L.res_tok = L.res_len;                              // (placed per call)
   L.new_len = take(c.max_batch * 4);
+  // from here to the timing table: the words that start at zero, cleared together by cb_init
   L.status = take(4);
   L.tickets = take((size_t)L.ticket_count * 4);
   L.coop_tickets = take((size_t)kCoopTiles * kCoopTicketStride);
   L.amax_tickets = take((size_t)c.max_batch * kTicketWords * 4);
+  L.amax_best = take(mt * kAmaxStride * 8);
   L.dbg = take(1024 * 8 * 8);
   // The scalar kernel's fp32 partials are 8 times the size of the MFMA kernel's.  A configuration
   // the MFMA kernel takes (bf16) runs the scalar one only on request (option
-  // "attn_impl" = 1, a test aid): it gets room for 8 splits there, not for max_splits.
+  // "attn_impl" = 1, a test aid) or when its geometry is not the MFMA kernel's (see plan_attention): it gets
+  // room for 8 splits there, not for max_splits.
   const bool mfma_cfg = c.qkv_dtype == CB_BF16;
   L.scalar_splits = mfma_cfg ? std::min(L.max_splits, 8) : L.max_splits;
   const size_t scalar_bytes = mt * c.num_q_heads * (size_t)L.scalar_splits * partial_stride(c.head_dim) * 4;
@@ -667,11 +669,7 @@ int cb_init(const cb_config* cfg, void* workspace, size_t workspace_bytes, cb_ct
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.status, 0, 4);
-  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.tickets, 0, (size_t)lay.ticket_count * 4);
-  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.coop_tickets, 0, (size_t)kCoopTiles * kCoopTicketStride);
-  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.amax_tickets, 0, (size_t)cfg->max_batch * kTicketWords * 4);
-  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.amax_best, 0, (size_t)lay.max_total_nodes * kAmaxStride * 8);
+  if (e == hipSuccess) e = hipMemset(ctx->ws + lay.status, 0, lay.dbg - lay.status);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     (void)hipHostFree(ctx->h_block);
