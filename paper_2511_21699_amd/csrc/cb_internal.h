@@ -8,6 +8,7 @@ namespace cb {
 
 constexpr int kAncWords = CB_MAX_NODES / 32;  // 256-bit ancestor set per node
 constexpr int kArgmaxChunk = 8192;            // logits elements scanned by one wavefront at a time
+constexpr int kArgmaxShortChunk = 2048;       // the same in scans that would leave most of the chip idle (launch_logits)
 constexpr int kAmaxStride = 16;               // words between the rows' argmax words: a 128-byte line each (they take atomics)
 constexpr int kRowTile = 64;                  // query rows per workgroup in the MFMA attention
 constexpr int kCoopTiles = 512;               // tiles a cooperative split merge can serve (it needs the grid resident at once)

@@ -285,7 +285,7 @@ __device__ __forceinline__ void accept_wave(AcceptWaveLds& sh, const AcceptArgs&
   else accept_large(sh, g, b, off, N > CB_MAX_NODES ? CB_MAX_NODES : N);
 }
 
-// The logits work of one verification call: items (row, chunk of kArgmaxChunk elements), item = row *
+// The logits work of one verification call: items (row, chunk of kArgmaxChunk or kArgmaxShortChunk elements), item = row *
 // chunks + chunk, shared out evenly, in order, among all wavefronts of the workgroups that do it.
 struct LogitsWork {
   const void* logits;   // [rows][V]
@@ -301,15 +301,15 @@ struct LogitsWork {
 };
 
 // First maximum of elements [e0, e1) of one row by one wavefront; the result (a word of amax_word) is
-// valid in every lane.  Bound by the loads: a wave requests 16 KiB at a time (kVecs loads of 16 bytes per
+// valid in every lane.  Bound by the loads: a wave requests up to 16 KiB at a time (kVecs loads of 16 bytes per
 // lane, all in flight before the first is looked at) and spends about 12 vector instructions per load on the
 // maximum alone; where in the block it is first attained is looked up only in blocks that raise it.  A row may
 // start at any element: the elements in front of the first and behind the last whole 16-byte piece are taken
 // one by one.
-template <typename T>
+template <typename T, int KV>
 struct WaveScan {
   static constexpr int VEC = 16 / sizeof(T);
-  static constexpr int kVecs = 16;
+  static constexpr int kVecs = KV;  // (even)
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
   static __device__ __forceinline__ float to_f32(T x) {
@@ -405,18 +405,20 @@ constexpr int kTicketStride = 32;                                    // 32-bit w
 constexpr int kTicketWords = (kTicketGroups + 1) * kTicketStride;    // per sequence
 constexpr int kTicketDirect = 48;  // arrivals up to which one word serves a sequence
 
-template <int NW>
+template <int NW, bool SHORT = false>
 __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMetaLanes& ml, int wg, AcceptWaveLds& sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t items = (int64_t)lw.rows * lw.chunks;
   const int i0 = (int)(items * wg / lw.n_wgs), i1 = (int)(items * (wg + 1) / lw.n_wgs);
   for (int i = i0 + w; i < i1; i += NW) {
     const int row = i / lw.chunks, c = i - row * lw.chunks;
-    const int64_t e0 = (int64_t)c * kArgmaxChunk;
-    const int64_t e1 = e0 + kArgmaxChunk < lw.V ? e0 + kArgmaxChunk : lw.V;
+    constexpr int CH = SHORT ? kArgmaxShortChunk : kArgmaxChunk;
+    constexpr int KB = SHORT ? kArgmaxShortChunk / 512 : 16, KF = SHORT ? kArgmaxShortChunk / 256 : 16;  // loads per lane
+    const int64_t e0 = (int64_t)c * CH;
+    const int64_t e1 = e0 + CH < lw.V ? e0 + CH : lw.V;
     const unsigned long long word =
-        lw.is_f32 ? WaveScan<float>::run((const float*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1)
-                  : WaveScan<uint16_t>::run((const uint16_t*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1);
+        lw.is_f32 ? WaveScan<float, KF>::run((const float*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1)
+                  : WaveScan<uint16_t, KB>::run((const uint16_t*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1);
     if (lane == 0)
       __hip_atomic_fetch_max(as_global(lw.accept.best) + (int64_t)row * kAmaxStride, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }

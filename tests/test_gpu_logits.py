@@ -37,3 +37,18 @@ def test_acceptance_of_trees_beyond_a_wavefront(N, shape):
     for p in (0.6, 0.99, 1.0):
         case = W.custom_case(400 + N, "bf16", 2, 2, 2, 128, 700, [33, 5], pars, p_match=p)
         run_case(case, rows=sample_rows(case, 16), what=f"{shape} {N} p={p}")
+
+
+# the stand-alone scan with short chunks (at most 1024 whole ones) around a short chunk's edges, and on either side of that line
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,V", [(3, 2047), (3, 2048), (3, 2049), (5, 6151), (128, 65536), (129, 65535), (129, 65537)])
+def test_scan_with_short_chunks(N, V, dtype):
+    rng = np.random.default_rng(N + V)
+    par = W.random_tree(rng, N, 4, 7, False)[0]
+    case = W.custom_case(500 + N + V, dtype, 1, 2, 2, 128, V, [20], [par], p_match=0.8)
+    x = np.zeros(case.logits.shape, dtype=np.float32)
+    for i in range(N):  # pairs of equal maxima on either side of an edge, or far apart
+        a = [0, 2047, 2048, V - 1, int(rng.integers(V))][i % 5]
+        x[i, [min(a, V - 1), min(a + 1, V - 1), int(rng.integers(V))]] = 5.0
+    case.logits = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    run_case(case, rows=sample_rows(case, 8), options={"fuse_logits": 0}, what=f"N={N} V={V} {dtype}")
