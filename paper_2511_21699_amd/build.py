@@ -81,6 +81,29 @@ def untracked_load_violations(asm: str) -> list:
     return bad
 
 
+def scalar_base_violations(asm: str) -> list:
+    """Loads inside inline assembly whose address has a scalar base (global_load... vN, s[a:b]).  The chip
+    wants five wait states between a vector instruction that writes a scalar register (v_readfirstlane_b32)
+    and a load that reads it; the compiler keeps that rule for its own instructions but does not look inside
+    inline assembly.  The statement may follow such a write directly, so it has to hold the five itself:
+    every instruction in front of the load counts one, s_nop n counts n + 1.  Returns a list of (line number,
+    text) pairs of the loads that come too early."""
+    bad = []
+    in_asm, states = False, 0
+    for i, line in enumerate(asm.split("\n")):
+        if "ASMSTART" in line or "ASMEND" in line:
+            in_asm, states = "ASMSTART" in line, 0
+            continue
+        code = line.split(";")[0].strip()
+        if not in_asm or not code:
+            continue
+        if re.match(r"(?:global|scratch|flat)_(?:load|store)\w* .*\bs\[\d+:\d+\]", code) and states < 5:
+            bad.append((i + 1, code))
+        nop = re.match(r"s_nop (\d+)", code)
+        states += int(nop.group(1)) + 1 if nop else 1
+    return bad
+
+
 def kernel_resources(asm: str) -> dict:
     """{kernel symbol: (vgpr_count, vgpr_spill_count, private_segment_fixed_size)} from the listing's metadata."""
     out, name, cur = {}, None, {}
@@ -116,6 +139,9 @@ def build(verbose: bool = False) -> str:
         bad = untracked_load_violations(asm)
         if bad:
             raise RuntimeError(f"{name}: registers of untracked loads are touched before their wait: {bad[:4]}")
+        bad = scalar_base_violations(asm)
+        if bad:
+            raise RuntimeError(f"{name}: loads too close behind a possible write of their scalar base: {bad[:4]}")
         bad = scratch_violations(asm)
         if bad:
             raise RuntimeError(f"{name}: kernels that spill or use scratch memory: {bad[:4]}")

@@ -112,7 +112,9 @@ __device__ __forceinline__ void lds_dma_b128(const CB_GLOBAL char* base, uint32_
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uintptr_t)base >> 32));
   const uint64_t b64 = (uint64_t)lo | ((uint64_t)hi << 32);
   const int mask = __builtin_amdgcn_readfirstlane(lanes ? -1 : 0);
-  asm volatile("s_mov_b32 m0, %2\n\ts_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+  // (a load may read a scalar register that a vector instruction wrote -- the base, where it comes from a readfirstlane --
+  // five wait states later at the earliest, and inside an asm statement nobody else counts them: three moves and s_nop 1)
+  asm volatile("s_mov_b32 m0, %2\n\ts_mov_b32 exec_lo, %3\n\ts_mov_b32 exec_hi, %3\n\ts_nop 1\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
                ::"v"(off), "s"(b64), "s"(lds), "s"(mask) : "memory");
 }
 

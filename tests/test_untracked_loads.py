@@ -62,3 +62,31 @@ def test_scratch_checker_reports_spills():
 """
     assert build.kernel_resources(meta) == {"k_good": (200, 0, 0), "k_spills": (256, 216, 864)}
     assert [k for k, _ in build.scratch_violations(meta)] == ["k_spills"]
+
+
+BASE_LISTING = """
+\tv_readfirstlane_b32 s6, v18
+\t;;#ASMSTART
+\ts_mov_b32 m0, s41
+\ts_mov_b32 exec_lo, s12
+\ts_mov_b32 exec_hi, s12
+%s\tglobal_load_lds_dwordx4 v184, s[6:7]
+\ts_mov_b64 exec, -1
+\t;;#ASMEND
+"""
+
+
+@pytest.mark.parametrize("between,ok", [("", False), ("\ts_nop 0\n", False), ("\ts_nop 1\n", True), ("\ts_nop 0\n\ts_nop 0\n", True)])
+def test_checker_counts_wait_states_before_a_scalar_base(between, ok):
+    bad = build.scalar_base_violations(BASE_LISTING % between)
+    assert (bad == []) == ok
+    if not ok:
+        assert "s[6:7]" in bad[0][1]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+@pytest.mark.parametrize("name", ["cb_attn_mfma.hip", "cb_attn_wide.hip"])
+def test_compiled_requests_keep_their_distance_from_the_base(name):
+    asm = build.device_asm(os.path.join(build.CSRC, name))
+    assert asm.count(", s[") > 0 and "global_load_lds_dwordx4" in asm
+    assert build.scalar_base_violations(asm) == []
