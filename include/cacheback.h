@@ -136,11 +136,12 @@ int cb_check_verify_args(const cb_config *cfg, int32_t batch, const cb_kv_layer 
  *                   pass always yields); the remaining entries are set to -1
  * Siblings may carry the same token; among accepted nodes of equal depth the lowest index wins.
  * Returns when accepted_len and accepted_tokens have arrived in host memory.  That can be before the
- * launch on `hip_stream` (a hipStream_t, NULL = the null stream) has ended: the acceptance flags its
- * results to the waiting host while the attention is still merging its splits.  attn_out is
- * therefore complete in stream order, not on return: work enqueued on `hip_stream` afterwards sees
- * it, a host read needs a synchronisation of the stream first.  A later call of this library on
- * another stream waits for this one's launch by itself.  Option "full_sync" = 1 (cb_set_option)
+ * launches on `hip_stream` (a hipStream_t, NULL = the null stream) have ended: the acceptance flags its
+ * results to the waiting host while the attention sweeps the cache, or before it begins.  attn_out is
+ * therefore complete in stream order, not on return, and the cache, the queries and the tree nodes' slots are
+ * read until then: work enqueued on `hip_stream` afterwards sees the one and may change the others,
+ * a host read needs a synchronisation of the stream first.  A later verification, attention or
+ * compaction call with the same context on another stream waits for this one's launches by itself.  Option "full_sync" = 1 (cb_set_option)
  * makes every call synchronise the stream before it returns.
  */
 int cb_verify_tree(cb_ctx *ctx, void *hip_stream, int32_t batch, const void *q,

@@ -351,6 +351,16 @@ int check_common(cb_ctx* ctx, int32_t batch, const void* q, const cb_kv_layer* k
   return CB_OK;
 }
 
+// A host-form call returns when its results arrive; what is left of its launches still reads the cache and uses the
+// workspace, and only work on that same stream is ordered behind it.  Work on another stream waits here.
+int order_behind_host_form(cb_ctx* ctx, hipStream_t st) {
+  if (ctx->have_unsynced && ctx->unsynced != st) {
+    CB_HIP(ctx, hipStreamSynchronize(ctx->unsynced));
+    ctx->have_unsynced = false;
+  }
+  return CB_OK;
+}
+
 // Enqueues the whole verification on `st`; the tree is already on the device.
 int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb_kv_layer* kv,
                  const int32_t* kv_len, const int32_t* node_offsets, const int32_t* d_parent,
@@ -365,12 +375,8 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     return (int64_t)kv_len[x] + node_offsets[x + 1] - node_offsets[x] > (int64_t)kv_len[y] + node_offsets[y + 1] - node_offsets[y];
   });
   const int total = node_offsets[batch];
-  if (ctx->have_unsynced && ctx->unsynced != st) {
-    // the last host-form call returned when its results arrived; what is left of its launch still uses
-    // the workspace, and only work on that same stream is ordered behind it
-    CB_HIP(ctx, hipStreamSynchronize(ctx->unsynced));
-    ctx->have_unsynced = false;
-  }
+  const int ordered = order_behind_host_form(ctx, st);
+  if (ordered) return ordered;
   if (ctx->counters_dirty) {  // (after a failed launch: the kernels rely on tickets that are zero between launches)
     const hipError_t e1 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.tickets), ctx->lay.ticket_count / 2, 1, 1);
     const hipError_t e2 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.coop_tickets), kCoopTiles, kCoopTicketStride / 8, 2);
@@ -802,7 +808,7 @@ int cb_verify_tree(cb_ctx* ctx, void* hip_stream, int32_t batch, const void* q, 
   // than the kernels' reads across the bus).  Parents and tokens back to back, lengths and tokens
   // back to back.  Calls alternate between two tree areas: this call may return before its launch
   // has ended (below), and the launch of the call before it has ended by the time this one's
-  // results arrive, because both run on one stream (run_pipeline synchronises when the stream changes).
+  // results arrive, because both run on one stream (order_behind_host_form synchronises when the stream changes).
   const bool early = ctx->opt_full_sync == 0 && (ctx->opt_stages & 8) != 0;
   ctx->call_seq = ctx->call_seq == INT32_MAX ? 1 : ctx->call_seq + 1;
   int32_t* h_tree = ctx->h_parent + (size_t)(ctx->call_seq & 1) * 2 * ctx->lay.max_total_nodes;
@@ -820,7 +826,7 @@ int cb_verify_tree(cb_ctx* ctx, void* hip_stream, int32_t batch, const void* q, 
   if (early) {
     // The acceptance stores a sequence's results, makes them visible at system scope and then stores
     // the call's number into the sequence's flag word; the host returns as soon as every flag shows
-    // it, without waiting for the rest of the launch (the attention's split merge) and for the
+    // it, without waiting for the attention (which may not have begun) and for the
     // stream's completion signal.  The stream's state is looked at now and then, so that a failed
     // launch ends the wait.
     const int32_t want = ctx->call_seq;
@@ -877,6 +883,9 @@ int cb_compact_kv(cb_ctx* ctx, void* hip_stream, int32_t num_layers, const cb_kv
     if (ctx->meta.kv_len[b] + n > room) return set_err(ctx, CB_ECAP, "sequence %d does not fit these caches", b);
   }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  // (the attention of a host-form call that has returned may not even have begun to read the slots that move here)
+  const int ordered = order_behind_host_form(ctx, st);
+  if (ordered) return ordered;
   const int eb = c.qkv_dtype == CB_F32 ? 4 : 2;
   CB_HIP(ctx, launch_compact(st, ctx->batch, ctx->meta, addrs, num_layers, c.num_kv_heads, c.head_dim, eb, c.max_depth,
                              ctx->dev<int32_t>(ctx->lay.path), ctx->dev<int32_t>(ctx->lay.len_ctx),

@@ -9,7 +9,7 @@ import pytest
 from oracle import cb_oracle as O
 from paper_2511_21699_amd import binding as B
 from paper_2511_21699_amd import workloads as W
-from tests.gpu_harness import check_attention
+from tests.gpu_harness import check_attention, sample_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -86,5 +86,46 @@ def test_alternating_streams_are_ordered_by_the_library():
         for j, case in enumerate(cases):
             got = W.to_f64(B.to_host(outs[j], case.dtype), case.dtype)
             check_attention(case, got, O.attention(case, threads=16), f"case {j}")
+    finally:
+        ver.close()
+
+
+# the acceptance's results arrive early in the launch, or in a launch in front of the attention: the compaction that
+# follows on another stream must not move slots that the attention has yet to read
+@pytest.mark.parametrize("options", [{}, {"fuse_logits": 0}, {"attn_impl": 1}])
+@pytest.mark.parametrize("n,dtype", [(60, "bf16"), (150, "bf16"), (40, "f32")])
+def test_compaction_on_another_stream_waits_for_the_attention(n, dtype, options):
+    import torch
+    S = 4000 if options.get("attn_impl") else 24000
+    par = W.random_tree(np.random.default_rng(n), n, 4, 7, False)[0]
+    case = W.custom_case(6100 + n, dtype, 1, 4, 4, 128, 4096, [S], [par], q_scale=2.0, p_match=1.0)
+    L, path, toks = _expected(case)[0]
+    assert L >= 3 and (np.asarray(path) != np.arange(len(path))).any()      # the compaction moves slots
+    rows = sample_rows(case, 60)
+    ref = O.attention_rows(case, rows, threads=16)
+    k_ref, v_ref = case.k.copy(), case.v.copy()
+    O.compact(case, k_ref, v_ref, 0, path)
+    dc = B.DeviceCase(case)
+    ver = B.Verifier(B.config_for_case(case))
+    for k, v in options.items():
+        ver.set_option(k, v)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]       # default priority
+    k0, v0 = dc.k.clone(), dc.v.clone()
+    out = torch.zeros_like(dc.q)
+    try:
+        for it in range(6):
+            print(f"[host form] compaction across streams: n={n} {dtype} {options} round {it}", flush=True)
+            dc.k.copy_(k0)
+            dc.v.copy_(v0)
+            out.zero_()
+            torch.cuda.synchronize()
+            _, acc_len, _ = ver.verify_tree(dc.q, dc.kv, case.kv_len, case.node_offsets, case.parent, case.tokens, dc.logits,
+                                            attn_out=out, stream=streams[it % 2])
+            ver.compact_kv([dc.kv], 1, stream=streams[1 - it % 2])
+            torch.cuda.synchronize()
+            assert acc_len[0] == L
+            got = W.to_f64(B.to_host(out, dtype), dtype)
+            check_attention(case, np.stack([got[i, h] for _, h, i in rows]), ref, f"round {it}")
+            assert np.array_equal(B.to_host(dc.k, dtype), k_ref) and np.array_equal(B.to_host(dc.v, dtype), v_ref)
     finally:
         ver.close()
