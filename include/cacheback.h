@@ -188,7 +188,9 @@ int cb_tree_attention_device(cb_ctx *ctx, void *hip_stream, int32_t batch, const
  * ragged one is beyond it.  All calls on one GPU share the array, which keeps the last call's
  * contents (the counters that must start at zero are cleared by the call itself): calls that overlap
  * on one GPU -- from different streams or threads -- race and give undefined results.  Results are
- * those of cb_tree_attention_device for the same arguments.
+ * those of cb_tree_attention_device for the same arguments, bit for bit unless that form's split count
+ * has to be lowered for the array (fp32, head_dim 64, or trees of more than 64 rows per kv head, close
+ * to the limit); the tolerance is the same.
  */
 int cb_tree_attention_noalloc(const cb_config *cfg, void *hip_stream, int32_t batch, const void *q,
                               const cb_kv_layer *kv, const int32_t *kv_len,

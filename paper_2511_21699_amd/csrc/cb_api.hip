@@ -88,14 +88,15 @@ WsLayout ws_layout(const cb_config& c) {
   L.amax_tickets = take((size_t)c.max_batch * kTicketWords * 4);
   L.amax_best = take(mt * kAmaxStride * 8);
   L.dbg = take(1024 * 8 * 8);
-  // The scalar kernel's fp32 partials are 8 times the size of the MFMA kernel's.  A configuration
+  // The scalar kernel's fp32 partials are twice the size of the MFMA kernel's.  A configuration
   // the MFMA kernel takes (bf16) runs the scalar one only on request (option
   // "attn_impl" = 1, a test aid) or when its geometry is not the MFMA kernel's (see plan_attention): it gets
   // room for 8 splits there, not for max_splits.
   const bool mfma_cfg = c.qkv_dtype == CB_BF16;
   L.scalar_splits = mfma_cfg ? std::min(L.max_splits, 8) : L.max_splits;
   const size_t scalar_bytes = mt * c.num_q_heads * (size_t)L.scalar_splits * partial_stride(c.head_dim) * 4;
-  const size_t mfma_bytes = mfma_cfg ? attn_mfma_partial_bytes(c.head_dim, mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits) : 0;
+  auto mfma_partials = [&](int mrows) { return attn_mfma_partial_bytes(c.head_dim, mrows, mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits); };
+  const size_t mfma_bytes = mfma_cfg ? std::max(mfma_partials(1), mfma_partials(c.max_nodes * g)) : 0;  // (calls with small tiles, and with the largest)
   L.partial = take(std::max(scalar_bytes, mfma_bytes));
   L.total = o;
   return L;
@@ -338,6 +339,51 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units);
   }
   return p;
+}
+
+// The scratch layout of a cb_tree_attention_noalloc call, and the plan it is cut for.  Whether a call fits the fixed array
+// is a property of its shape that callers rely on, so it is decided by one measure per kind of call, whatever the
+// kernels would like to have: bf16 states in 16-row tiles at the planned splits for bf16 with head_dim 128, fp32 rows at the
+// splits of one workgroup per row for the others.  A call within it gets its plan, with fewer splits if the kernels' own
+// layout at the planned ones is larger than the array (one split needs no partial states, so an end is always found).
+WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, const int32_t* kv_len, const int32_t* node_offsets, Plan* plan) {
+  const size_t total = node_offsets[batch];
+  const int g = c.num_q_heads / c.num_kv_heads;
+  auto fp32_rows = [&](int ns) { return ns <= 1 ? 0 : total * c.num_q_heads * ns * partial_stride(c.head_dim) * 4; };
+  auto bf16_tiles = [&](int mrows, int ns) {
+    return ns <= 1 ? 0 : attn_mfma_partial_bytes(c.head_dim, mrows, total, c.num_q_heads, c.num_kv_heads, batch, ns);
+  };
+  auto planned = [&](int most) {
+    return plan_attention(c, most, std::min(most, full.scalar_splits), 0, 0, batch, kv_len, node_offsets);
+  };
+  auto cut = [&](size_t partial_bytes) {
+    WsLayout L{};
+    L.max_total_nodes = (int)total;
+    L.max_splits = L.scalar_splits = plan->nsplit;
+    L.amax_chunks = full.amax_chunks;
+    L.ticket_count = 4 * batch * c.num_kv_heads * ((plan->max_nodes * g + kRowTile - 1) / kRowTile);
+    size_t o = 0;
+    auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
+    L.status = take(4);
+    L.tickets = take((size_t)L.ticket_count * 4);
+    L.coop_tickets = take((size_t)kCoopTiles * kCoopTicketStride);
+    L.anc = take(total * kAncWords * 4);
+    L.dbg = L.anc;  // (never written: the timing aid is off)
+    L.partial = take(partial_bytes);
+    L.total = o;
+    return L;
+  };
+  *plan = planned(full.max_splits);
+  const bool by_rows = c.qkv_dtype == CB_F32 || c.head_dim == 64;
+  const size_t measure = by_rows ? fp32_rows(plan_attention(c, full.max_splits, full.max_splits, 1, 0, batch, kv_len, node_offsets).nsplit)
+                         : plan->impl == 2 ? bf16_tiles(1, plan->nsplit) : fp32_rows(plan->nsplit);
+  WsLayout L = cut(measure);
+  if (L.total > kStaticScratchBytes) return L;
+  for (;;) {
+    L = cut(plan->impl == 2 ? bf16_tiles(plan->max_nodes * g, plan->nsplit) : fp32_rows(plan->nsplit));
+    if (L.total <= kStaticScratchBytes || plan->nsplit <= 1) return L;
+    *plan = planned(plan->nsplit - 1);
+  }
 }
 
 int check_common(cb_ctx* ctx, int32_t batch, const void* q, const cb_kv_layer* kv, const int32_t* kv_len,
@@ -737,28 +783,9 @@ int cb_tree_attention_noalloc(const cb_config* cfg, void* hip_stream, int32_t ba
     memcpy(g_init_err, tmp.err, sizeof g_init_err);
     return rc;
   }
-  const int total = node_offsets[batch];
   const WsLayout full = ws_layout(*cfg);
-  const Plan plan = plan_attention(*cfg, full.max_splits, full.scalar_splits, 0, 0, batch, kv_len, node_offsets);
-  const int g = cfg->num_q_heads / cfg->num_kv_heads;
-  const int tile_count = batch * cfg->num_kv_heads * ((plan.max_nodes * g + kRowTile - 1) / kRowTile);
-  WsLayout L{};
-  L.max_total_nodes = total;
-  L.max_splits = plan.nsplit;
-  L.scalar_splits = plan.nsplit;
-  L.amax_chunks = full.amax_chunks;
-  L.ticket_count = 4 * tile_count;
-  size_t o = 0;
-  auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
-  L.status = take(4);
-  L.tickets = take((size_t)L.ticket_count * 4);
-  L.coop_tickets = take((size_t)kCoopTiles * kCoopTicketStride);
-  L.anc = take((size_t)total * kAncWords * 4);
-  L.dbg = L.anc;                    // (never written: the timing aid is off)
-  L.partial = take(plan.nsplit <= 1 ? 0
-                   : plan.impl == 2 ? attn_mfma_partial_bytes(cfg->head_dim, total, cfg->num_q_heads, cfg->num_kv_heads, batch, plan.nsplit)
-                                    : (size_t)total * cfg->num_q_heads * plan.nsplit * partial_stride(cfg->head_dim) * 4);
-  L.total = o;
+  Plan plan;
+  const WsLayout L = noalloc_layout(*cfg, full, batch, kv_len, node_offsets, &plan);
   if (L.total > kStaticScratchBytes)
     return set_err(nullptr, CB_ECAP, "this call needs %zu bytes of scratch memory, the library's fixed buffer has %zu", L.total, kStaticScratchBytes);
   int dev = -1;
@@ -783,7 +810,7 @@ int cb_tree_attention_noalloc(const cb_config* cfg, void* hip_stream, int32_t ba
   // must start at zero are cleared here, by a kernel (a caller may be capturing the stream).
   e = launch_zero_words(st, tmp.dev<unsigned long long>(L.status), 1, 1, 1);
   if (e == hipSuccess) e = launch_zero_words(st, tmp.dev<unsigned long long>(L.tickets), L.ticket_count / 2, 1, 1);
-  if (e == hipSuccess) e = launch_zero_words(st, tmp.dev<unsigned long long>(L.coop_tickets), std::min(tile_count, kCoopTiles), kCoopTicketStride / 8, 2);
+  if (e == hipSuccess) e = launch_zero_words(st, tmp.dev<unsigned long long>(L.coop_tickets), std::min(L.ticket_count / 4, kCoopTiles), kCoopTicketStride / 8, 2);
   if (e != hipSuccess) return set_err(nullptr, CB_EHIP, "clearing the scratch counters: %s", hipGetErrorString(e));
   rc = run_pipeline(&tmp, st, batch, q, kv, kv_len, node_offsets, d_tree_parent, nullptr, nullptr, attn_out, nullptr, nullptr, 3);
   if (rc) memcpy(g_init_err, tmp.err, sizeof g_init_err);

@@ -292,14 +292,11 @@ static int block_bytes(int D, int tr) {
   return D == 128 ? PartialLayout<128, 32>::kBytes : PartialLayout<64, 32>::kBytes;
 }
 
-size_t attn_mfma_partial_bytes(int D, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits) {
+size_t attn_mfma_partial_bytes(int D, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits) {
   // the last sequence's blocks end at or before tile max_total_nodes * Hq / TR + (Hkv + 1) * max_batch
-  size_t most = 0;
-  for (int tr : {16, 32}) {
-    const size_t tiles = max_total_nodes * Hq / tr + (size_t)(Hkv + 1) * max_batch + 1;
-    most = std::max(most, tiles * (size_t)max_splits * block_bytes(D, tr));
-  }
-  return most;
+  const int tr = attn_mfma_tile_rows(mrows) == kSmallRows ? 16 : 32;
+  const size_t tiles = max_total_nodes * Hq / tr + (size_t)(Hkv + 1) * max_batch + 1;
+  return tiles * (size_t)max_splits * block_bytes(D, tr);
 }
 
 bool attn_mfma_supports(const AttnParams& p) {

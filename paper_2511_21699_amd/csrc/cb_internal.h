@@ -204,8 +204,9 @@ int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int
 hipError_t launch_attn_f32(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw);
 hipError_t launch_merge(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int dtype, int total_nodes);
 int attn_mfma_tile_rows(int mrows);            // rows per workgroup tile chosen for a given g*N
-// bytes the MFMA path's partial states can take (its own layout, padded to 16-row tiles per kv head)
-size_t attn_mfma_partial_bytes(int D, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
+// bytes the MFMA path's partial states can take in calls whose largest sequence has `mrows` rows per kv head (its own layout,
+// padded to 16-row tiles per kv head where one small tile holds them, else to 32-row ones)
+size_t attn_mfma_partial_bytes(int D, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
 bool attn_mfma_supports(const AttnParams& p);  // shape/geometry the MFMA kernel takes (bf16 is the caller's check)
 bool attn_mfma_can_fuse(const AttnParams& p, int max_nodes_in_call);
 // with logits_work != nullptr (only if attn_mfma_can_fuse) the same launch also scans the logits and runs the acceptance

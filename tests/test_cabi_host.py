@@ -197,3 +197,23 @@ def test_no_alloc_entry_point_checks_its_arguments_on_the_host():
     assert call(ragged, kv, [17590] * 16, offs)[0] == B.CB_ECAP      # prefix + nodes beyond the block table
     bad = B.make_config(32, 5, 128, "bf16", "bf16", 1, 64, 6, 100)
     assert call(bad, kv, [10], [0, 4])[0] == B.CB_EINVAL
+
+
+@pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="the accepted calls end at the missing device")
+@pytest.mark.parametrize("hq,hkv,d,dtype,nodes,lens", [
+    (40, 40, 128, "f32", [256, 256], [16000, 3714]),        # four splits planned, 44.5 MB of fp32 rows
+    (32, 8, 128, "f32", [32] * 4, [60000, 900, 800, 700]),
+    (320, 40, 64, "bf16", [256], [56477]),
+    (64, 32, 128, "bf16", [128, 109, 107, 63], [1322, 542, 200, 290]),     # 32-row tiles of the wide kernel
+])
+def test_no_alloc_entry_point_splits_less_near_the_scratch_limit(hq, hkv, d, dtype, nodes, lens):
+    """Calls whose planned splits are too many for the fixed array run with fewer.  Without a device an accepted
+    call ends at the device query."""
+    L = B.load()
+    cfg = B.make_config(hq, hkv, d, dtype, "bf16", len(lens), max(nodes), 8, 32000)
+    kv = B.CbKvLayer(0x1000, 0x2000, 70000, None, 0, 0)
+    a = np.asarray(lens, dtype=np.int32)
+    b = np.concatenate([[0], np.cumsum(nodes)]).astype(np.int32)
+    ip = lambda x: x.ctypes.data_as(C.POINTER(C.c_int32))
+    rc = L.cb_tree_attention_noalloc(C.byref(cfg), None, len(lens), 0x10000, C.byref(kv), ip(a), ip(b), 0x30000, 0x20000)
+    assert rc == B.CB_EHIP, (rc, L.cb_last_error(None).decode())
