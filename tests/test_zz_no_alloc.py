@@ -48,3 +48,20 @@ def test_no_alloc_entry_point_two_calls_in_a_row():
     tiny = W.make_config(1)                                 # fp32: scalar kernels, ancestor sets from the scratch array
     print("[case] no-alloc: tiny fp32 (scalar kernels)", flush=True)
     _both(tiny)
+
+
+def test_no_alloc_entry_point_with_fewer_splits_than_planned():
+    """A call whose planned splits need more than the fixed array: fewer splits, the same tolerance."""
+    import torch
+    from oracle import cb_oracle as O
+    rng = np.random.default_rng(78)
+    nodes, lens = [128, 109, 107, 63], [1322, 542, 200, 290]
+    case = W.custom_case(772, "bf16", 4, 64, 32, 128, 100, lens, [W.random_tree(rng, n, 4, 8, False)[0] for n in nodes], q_scale=2.0)
+    print("[case] no-alloc: wide tiles beyond the scratch array at the planned splits", flush=True)
+    dc = B.DeviceCase(case)
+    out = torch.zeros_like(dc.q)
+    B.tree_attention_noalloc(B.config_for_case(case), dc.q, dc.kv, case.kv_len, case.node_offsets, torch.from_numpy(case.parent).cuda(), out)
+    torch.cuda.synchronize()
+    got = W.to_f64(B.to_host(out, case.dtype), case.dtype)
+    rows = sample_rows(case, 96, seed=6)
+    check_attention(case, np.stack([got[case.node_offsets[b] + i, h] for b, h, i in rows]), O.attention_rows(case, rows), case.name)
