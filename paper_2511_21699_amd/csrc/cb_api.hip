@@ -95,14 +95,22 @@ WsLayout ws_layout(const cb_config& c) {
   const bool mfma_cfg = c.qkv_dtype == CB_BF16;
   L.scalar_splits = mfma_cfg ? std::min(L.max_splits, 8) : L.max_splits;
   const size_t scalar_bytes = mt * c.num_q_heads * (size_t)L.scalar_splits * partial_stride(c.head_dim) * 4;
-  auto mfma_partials = [&](int mrows) { return attn_mfma_partial_bytes(c.head_dim, mrows, mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits); };
+  auto mfma_partials = [&](int mrows) { return attn_mfma_partial_bytes(c.head_dim, c.head_dim == 64, mrows, mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits); };
   const size_t mfma_bytes = mfma_cfg ? std::max(mfma_partials(1), mfma_partials(c.max_nodes * g)) : 0;  // (calls with small tiles, and with the largest)
   L.partial = take(std::max(scalar_bytes, mfma_bytes));
   L.total = o;
   return L;
 }
 
+// Whether a bf16 call holds probabilities and partial sums in 32 bits: with head_dim 64, and with head_dim 128 where a split's
+// slice of the block table has more than 1022 entries, as the scalar kernel did that served these two before the MFMA
+// kernels took them; their callers keep that precision.
+bool precise_sums(const cb_config& c, int chunk) {
+  return c.qkv_dtype == CB_BF16 && (c.head_dim == 64 || (c.block_size > 0 && chunk / c.block_size + 2 > 1024));
+}
+
 struct Plan {
+  bool precise;  // (impl 2)
   int impl;    // 1 fp32 (or the scalar kernel on request), 2 bf16 MFMA
   int nsplit;  // partial slots per row
   int chunk;   // keys per split
@@ -326,6 +334,12 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
   int chunk = (p.max_len + nsplit - 1) / nsplit;
   chunk = (chunk + 31) / 32 * 32;
   p.chunk = std::max(chunk, 32);
+  p.precise = p.impl == 2 && precise_sums(c, p.chunk);
+  if (p.precise && c.head_dim == 128 && nsplit > 1 && nsplit > max_splits / 2) {
+    // fp32 partial states are twice the size, and the workspace is cut for bf16 ones (longer splits stay precise)
+    nsplit = std::max(1, max_splits / 2);
+    p.chunk = ((p.max_len + nsplit - 1) / nsplit + 31) / 32 * 32;
+  }
   p.nsplit = (p.max_len + p.chunk - 1) / p.chunk;
   if (p.impl == 2) {
     // A geometry that the MFMA kernel does not take (blocks that are no power of two, say) goes to the scalar kernel,
@@ -335,6 +349,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     ap.Hkv = c.num_kv_heads;
     ap.D = c.head_dim;
     ap.nsplit = p.nsplit;
+    ap.precise = p.precise;
     ap.kv.block_size = c.block_size;
     if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units);
   }
@@ -350,8 +365,8 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
   const size_t total = node_offsets[batch];
   const int g = c.num_q_heads / c.num_kv_heads;
   auto fp32_rows = [&](int ns) { return ns <= 1 ? 0 : total * c.num_q_heads * ns * partial_stride(c.head_dim) * 4; };
-  auto bf16_tiles = [&](int mrows, int ns) {
-    return ns <= 1 ? 0 : attn_mfma_partial_bytes(c.head_dim, mrows, total, c.num_q_heads, c.num_kv_heads, batch, ns);
+  auto tiles = [&](bool precise, int mrows, int ns) {
+    return ns <= 1 ? 0 : attn_mfma_partial_bytes(c.head_dim, precise, mrows, total, c.num_q_heads, c.num_kv_heads, batch, ns);
   };
   auto planned = [&](int most) {
     return plan_attention(c, most, std::min(most, full.scalar_splits), 0, 0, batch, kv_len, node_offsets);
@@ -376,11 +391,11 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
   *plan = planned(full.max_splits);
   const bool by_rows = c.qkv_dtype == CB_F32 || c.head_dim == 64;
   const size_t measure = by_rows ? fp32_rows(plan_attention(c, full.max_splits, full.max_splits, 1, 0, batch, kv_len, node_offsets).nsplit)
-                         : plan->impl == 2 ? bf16_tiles(1, plan->nsplit) : fp32_rows(plan->nsplit);
+                         : plan->impl == 2 ? tiles(false, 1, plan->nsplit) : fp32_rows(plan->nsplit);
   WsLayout L = cut(measure);
   if (L.total > kStaticScratchBytes) return L;
   for (;;) {
-    L = cut(plan->impl == 2 ? bf16_tiles(plan->max_nodes * g, plan->nsplit) : fp32_rows(plan->nsplit));
+    L = cut(plan->impl == 2 ? tiles(plan->precise, plan->max_nodes * g, plan->nsplit) : fp32_rows(plan->nsplit));
     if (L.total <= kStaticScratchBytes || plan->nsplit <= 1) return L;
     *plan = planned(plan->nsplit - 1);
   }
@@ -461,6 +476,7 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   ap.D = c.head_dim;
   ap.chunk = plan.chunk;
   ap.nsplit = plan.nsplit;
+  ap.precise = plan.precise;
   ap.batch = batch;
   ap.scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
   ap.status = ctx->dev<int32_t>(ctx->lay.status);

@@ -69,7 +69,7 @@ __device__ __forceinline__ uint32_t visible_keys(int key0, int S, int kend, cons
 //   probabilities stay below 2^8 and the accumulators are rarely touched by the vector ALU
 //   O^T += V^T P^T, l += 1^T P^T
 // All K and V operands are requested before the first MFMA, so that LDS latency hides behind the matrix and vector work.
-template <int D>
+template <int D, bool PX>
 __device__ __forceinline__ void compute_unit(const uint4* __restrict__ ks, const uint4* __restrict__ vs, RowState<D>& st, float c2,
                                              int key0, int S, int kend, const uint32_t* arow, int l) {
   constexpr int VPR = D / 8;
@@ -120,22 +120,30 @@ __device__ __forceinline__ void compute_unit(const uint4* __restrict__ ks, const
     st.lacc *= alpha;
   }
   const float nm = (st.mref == -INFINITY) ? 0.f : -st.mref * c2;
-  union { bf16x8 v; __bf16 h[8]; } pk;
+  union { bf16x8 v; __bf16 h[8]; } pk, rest;
 #pragma unroll
-  for (int e = 0; e < 8; e++) pk.h[e] = (__bf16)__builtin_amdgcn_exp2f(fmaf(x[e], c2, nm));
+  for (int e = 0; e < 8; e++) {
+    const float pe = __builtin_amdgcn_exp2f(fmaf(x[e], c2, nm));
+    pk.h[e] = (__bf16)pe;
+    if (PX) rest.h[e] = (__bf16)(pe - (float)pk.h[e]);
+  }
   const bf16x8 ones = __builtin_bit_cast(bf16x8, uint4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
   st.lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pk.v, st.lacc, 0, 0, 0);
+  if (PX) st.lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, rest.v, st.lacc, 0, 0, 0);
 #pragma unroll
-  for (int dt = 0; dt < D / 16; dt++)
-    st.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_shufflevector(va[dt][0], va[dt][1], 0, 1, 2, 3, 4, 5, 6, 7), pk.v, st.o[dt], 0, 0, 0);
+  for (int dt = 0; dt < D / 16; dt++) {
+    const bf16x8 v = __builtin_shufflevector(va[dt][0], va[dt][1], 0, 1, 2, 3, 4, 5, 6, 7);
+    st.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, pk.v, st.o[dt], 0, 0, 0);
+    if (PX) st.o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, rest.v, st.o[dt], 0, 0, 0);
+  }
 }
 
 // One attention workgroup; `wg` is its number among those that do attention.
-template <int D, bool TS>
+template <int D, bool PX, bool TS>
 __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, unsigned long long ts0,
                                           TileLds& sh, uint4* ring, unsigned long long* ts_sh) {
   using F = Feed<D, 8, 16>;
-  constexpr int NS = F::kSlots, PRO = F::kPrologue, P = PartialLayout<D, 16>::P;
+  constexpr int NS = F::kSlots, PRO = F::kPrologue, P = PartialLayout<D, 16, PX>::P;
   AttnParams p = p_arg;
   pin_args(p);
   CB_LDS unsigned long long* ts = (CB_LDS unsigned long long*)ts_sh;
@@ -200,7 +208,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
     if (s > 0) feed.wait_units(2 * s + 2);  // every wave's share of stage s has landed, and nobody reads stage s-1 any more
     feed.request_up_to(nu < 2 * s + NS ? nu : 2 * s + NS);
     const int key0 = k0 + (2 * s + gi) * kUnitKeys;
-    if (key0 < k1 && has_rows) compute_unit<D>(feed.k_at(slot), feed.v_at(slot), st, c2, key0, S, k1, &sh.anc.anc[node][0], l);
+    if (key0 < k1 && has_rows) compute_unit<D, PX>(feed.k_at(slot), feed.v_at(slot), st, c2, key0, S, k1, &sh.anc.anc[node][0], l);
     slot = slot + 2 >= NS ? slot + 2 - NS : slot + 2;
   }
   CB_TS(4);
@@ -227,26 +235,26 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   for (int i = 0; i < P / 2; i++) f[i] = f[i] * w0 + theirs[i * 64] * w1;
   const float lsum = st.lacc[0] * w0 + ml2.y * w1;
 #undef CB_TS
-  write_rows<D, 16, P / 2>(p, jb, wi, grow, f, gi * (P / 2), m, lsum, c2, gi == 0, l);
+  write_rows<D, 16, PX, P / 2>(p, jb, wi, grow, f, gi * (P / 2), m, lsum, c2, gi == 0, l);
   if (jb.nsplit == 1 || p.external_merge) return;  // (a following kernel merges: the kernel boundary orders the stores)
-  split_merge<D, 16, 8, kSmallRows, TS>(p, jb, sh, ts);
+  split_merge<D, 16, PX, 8, kSmallRows, TS>(p, jb, sh, ts);
 }
 
-template <int D, bool TS>
+template <int D, bool PX, bool TS>
 __global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
-  attn_tile<D, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
+  attn_tile<D, PX, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
 // The whole verification in one launch: the first lw.n_wgs workgroups do the logits work (they are dispatched
 // first, so the acceptance is through long before the attention is, and a waiting host has its results then),
 // the others the attention.  Neither waits for the other.
-template <int D, bool TS>
+template <int D, bool PX, bool TS>
 __global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
@@ -259,16 +267,16 @@ __global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta,
     logits_share<8>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
     return;
   }
-  attn_tile<D, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
+  attn_tile<D, PX, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
   flush_timestamps<TS>(p, wg, ts_sh);
 }
 
-// Stand-alone merge of the bf16 partials, used when a tile's partials are too many for one
+// Stand-alone merge of the partials, used when a tile's partials are too many for one
 // workgroup to pull through its compute unit: one workgroup per TR-row tile, its four waves take a quarter of the
 // pieces each.  grid: x = TR-row tile, y = kv head, z = sequence; block = 256 threads.
-template <int D, int TR>
-__global__ __launch_bounds__(256) void k_merge_partials_bf16(AttnParams p, SeqMeta meta) {
-  constexpr int NP = PartialLayout<D, TR>::P / 4;
+template <int D, int TR, bool PX>
+__global__ __launch_bounds__(256) void k_merge_partials(AttnParams p, SeqMeta meta) {
+  constexpr int NP = PartialLayout<D, TR, PX>::P / 4;
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   TileJob jb{};
   jb.b = blockIdx.z;
@@ -284,29 +292,28 @@ __global__ __launch_bounds__(256) void k_merge_partials_bf16(AttnParams p, SeqMe
   const int row = ti * TR + l % TR;
   const int node = row / jb.g, hg = row - node * jb.g;
   const int64_t gr = row < jb.M ? (int64_t)(jb.off + node) * p.Hq + jb.hk * jb.g + hg : -1;
-  merge_pieces<D, TR, NP, 0, 8>(partial_rsrc<D, TR>(p, jb), gr, partial_byte<D, TR>(p, jb, ti), (CB_GLOBAL uint16_t*)p.out, ns, w * NP, l);
+  merge_pieces<D, TR, PX, NP, 0, 8>(partial_rsrc<D, TR, PX>(p, jb), gr, partial_byte<D, TR, PX>(p, jb, ti), (CB_GLOBAL uint16_t*)p.out, ns, w * NP, l);
 }
 
-static int block_bytes(int D, int tr) {
-  if (tr == 16) return D == 128 ? PartialLayout<128, 16>::kBytes : PartialLayout<64, 16>::kBytes;
-  return D == 128 ? PartialLayout<128, 32>::kBytes : PartialLayout<64, 32>::kBytes;
-}
+static int block_bytes(int D, int tr, bool precise) { return tr * D * (precise ? 4 : 2) + tr * 8; }
+static_assert(PartialLayout<128, 16, false>::kBytes == 16 * 128 * 2 + 16 * 8 && PartialLayout<64, 32, true>::kBytes == 32 * 64 * 4 + 32 * 8, "");
 
-size_t attn_mfma_partial_bytes(int D, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits) {
+size_t attn_mfma_partial_bytes(int D, bool precise, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits) {
   // the last sequence's blocks end at or before tile max_total_nodes * Hq / TR + (Hkv + 1) * max_batch
   const int tr = attn_mfma_tile_rows(mrows) == kSmallRows ? 16 : 32;
   const size_t tiles = max_total_nodes * Hq / tr + (size_t)(Hkv + 1) * max_batch + 1;
-  return tiles * (size_t)max_splits * block_bytes(D, tr);
+  return tiles * (size_t)max_splits * block_bytes(D, tr, precise);
 }
 
 bool attn_mfma_supports(const AttnParams& p) {
   if (p.D != 128 && p.D != 64) return false;
+  if (p.D == 64 && !p.precise) return false;  // (not built)
   if (p.kv.block_size > 0) {
     if (p.kv.block_size & (p.kv.block_size - 1)) return false;
   }
   if (p.nsplit > 4095) return false;  // the ticket counts arrivals in 12 bits
   // partial offsets inside one sequence are 32-bit byte offsets of a buffer descriptor
-  if ((int64_t)p.Hkv * ((CB_MAX_NODES * (p.Hq / p.Hkv) + 31) / 32) * p.nsplit * block_bytes(128, 32) >= (1ll << 31)) return false;
+  if ((int64_t)p.Hkv * ((CB_MAX_NODES * (p.Hq / p.Hkv) + 31) / 32) * p.nsplit * block_bytes(128, 32, p.D == 128 && p.precise) >= (1ll << 31)) return false;
   return true;
 }
 
@@ -343,7 +350,7 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   // KiB per tile a separate, fully parallel merge kernel is cheaper than the in-kernel merge
   const int tr = rt_rows == kSmallRows ? 16 : 32;
   const int in_tile = ((M < rt_rows ? M : rt_rows) + tr - 1) / tr;
-  q.external_merge = (p.nsplit > 1 && (int64_t)p.nsplit * in_tile * block_bytes(p.D, tr) > 320 * 1024) ? 1 : 0;
+  q.external_merge = (p.nsplit > 1 && (int64_t)p.nsplit * in_tile * block_bytes(p.D, tr, p.precise) > 320 * 1024) ? 1 : 0;
   // A grid that is resident in one round (one workgroup per compute unit) merges cooperatively:
   // every workgroup of a tile takes a slice, so the volume per compute unit does not grow with
   // the split count and no second launch is needed.
@@ -360,32 +367,42 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   if (merge_kind) *merge_kind = p.nsplit <= 1 ? 0 : (q.coop_merge ? 1 : (q.external_merge ? 3 : 2));
   const bool ts = p.timeline != 0;  // (the timeline build of the same kernels: a measurement aid)
   hipError_t e;
-#define CB_LAUNCH(K, D, ...)                                                                 \
+#define CB_LAUNCH_TS(K, D, PX, ...)                                                          \
   do {                                                                                       \
-    if (ts) hipLaunchKernelGGL((K<D, true>), grid, dim3(512), 0, st, __VA_ARGS__);           \
-    else hipLaunchKernelGGL((K<D, false>), grid, dim3(512), 0, st, __VA_ARGS__);             \
+    if (ts) hipLaunchKernelGGL((K<D, PX, true>), grid, dim3(512), 0, st, __VA_ARGS__);       \
+    else hipLaunchKernelGGL((K<D, PX, false>), grid, dim3(512), 0, st, __VA_ARGS__);         \
+  } while (0)
+#define CB_LAUNCH(K, ...)                                       \
+  do {                                                          \
+    if (p.D == 64) CB_LAUNCH_TS(K, 64, true, __VA_ARGS__);      \
+    else if (p.precise) CB_LAUNCH_TS(K, 128, true, __VA_ARGS__); \
+    else CB_LAUNCH_TS(K, 128, false, __VA_ARGS__);              \
   } while (0)
   if (logits_work) {
     const LogitsWork& lw = *logits_work;
     if (!attn_mfma_can_fuse(p, max_nodes_in_call)) return hipErrorInvalidValue;
-    if (p.D == 128) CB_LAUNCH(k_verify_mfma, 128, q, meta, lw);
-    else CB_LAUNCH(k_verify_mfma, 64, q, meta, lw);
+    CB_LAUNCH(k_verify_mfma, q, meta, lw);
     e = hipGetLastError();
   } else if (rt_rows == kSmallRows) {
-    if (p.D == 128) CB_LAUNCH(k_attn_mfma, 128, q, meta);
-    else CB_LAUNCH(k_attn_mfma, 64, q, meta);
+    CB_LAUNCH(k_attn_mfma, q, meta);
     e = hipGetLastError();
   } else {
     e = launch_attn_wide(st, q, meta, (int)T);
   }
 #undef CB_LAUNCH
+#undef CB_LAUNCH_TS
   if (e != hipSuccess) return e;
   if (q.external_merge) {
     const dim3 mgrid((M + tr - 1) / tr, p.Hkv, p.batch);
-    if (p.D == 128 && tr == 16) hipLaunchKernelGGL((k_merge_partials_bf16<128, 16>), mgrid, dim3(256), 0, st, q, meta);
-    else if (p.D == 128) hipLaunchKernelGGL((k_merge_partials_bf16<128, 32>), mgrid, dim3(256), 0, st, q, meta);
-    else if (tr == 16) hipLaunchKernelGGL((k_merge_partials_bf16<64, 16>), mgrid, dim3(256), 0, st, q, meta);
-    else hipLaunchKernelGGL((k_merge_partials_bf16<64, 32>), mgrid, dim3(256), 0, st, q, meta);
+#define CB_MERGE(D, PX)                                                                                            \
+  do {                                                                                                              \
+    if (tr == 16) hipLaunchKernelGGL((k_merge_partials<D, 16, PX>), mgrid, dim3(256), 0, st, q, meta);              \
+    else hipLaunchKernelGGL((k_merge_partials<D, 32, PX>), mgrid, dim3(256), 0, st, q, meta);                       \
+  } while (0)
+    if (p.D == 64) CB_MERGE(64, true);
+    else if (p.precise) CB_MERGE(128, true);
+    else CB_MERGE(128, false);
+#undef CB_MERGE
     e = hipGetLastError();
   }
   return e;

@@ -141,17 +141,23 @@ __device__ __forceinline__ void pin_args(AttnParams& p) {
 constexpr int kUnitKeys = 32;  // keys per unit: what one wave works on at a time, and the granularity of the LDS ring
 
 // Partial softmax state, one block per (TR-row tile, split), laid out in the order the MFMA accumulators hold it (TR = 32
-// or 16, the query columns of an accumulator tile).  Piece pc of the tile is 512 bytes and holds DP = 256 / TR dims
-// from DP pc: lane (h, r), r = lane % TR, has 8 bytes -- o[row r][DP pc + 4 h + {0..3}] as bf16, unnormalised, relative
-// to the reference weight -- at pc * 512 + lane * 8, so that a wave's store or load of a piece is 512 contiguous bytes;
-// then (m, l) as fp32 for each of the rows.
+// or 16, the query columns of an accumulator tile).  Piece pc of the tile holds DP = 256 / TR dims from DP pc: lane (h, r),
+// r = lane % TR, has o[row r][DP pc + 4 h + {0..3}], unnormalised, relative to the reference weight, as bf16 (8 bytes) or,
+// PX, as fp32 (16 bytes), the lanes' pieces next to each other, so that a wave's store or load of a piece is 512 or 1024
+// contiguous bytes; then (m, l) as fp32 for each of the rows.
 // The blocks of sequence b start at tile block_tile0(b); kv head hk's row tile ti is block
 // (hk * ceil(M_b / TR) + ti) * nsplit + split behind it.
-template <int D, int TR>
+//
+// PX: the kernels' builds for calls that hold probabilities and partial sums in 32 bits (precise_sums() of the host side).
+// A probability goes to the matrix cores as two bf16 terms, the rounded value and the rounded rest (together within 2^-17
+// of the fp32 value), the denominator is the sum of both, and the partial states are fp32.
+template <int D, int TR, bool PX>
 struct PartialLayout {
   static constexpr int DP = 256 / TR;
   static constexpr int P = D / DP;  // pieces per tile
-  static constexpr int kMl = P * 512;
+  static constexpr int kLane = PX ? 16 : 8;  // bytes of a lane's piece
+  static constexpr int kPiece = 64 * kLane;
+  static constexpr int kMl = P * kPiece;
   static constexpr int kBytes = kMl + TR * 8;
 };
 // first tile of a sequence whose nodes start at `off`: room for ceil(M_b / TR) tiles per kv
@@ -248,14 +254,14 @@ __device__ __forceinline__ void first_stamps(CB_LDS unsigned long long* ts, unsi
 
 // Buffer descriptor over a sequence's partials (byte offsets fit 32 bits, checked by the launcher), and the byte
 // offset of split 0's block of the tile's i-th TR-row tile.
-template <int D, int TR>
+template <int D, int TR, bool PX>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t partial_rsrc(const AttnParams& p, const TileJob& jb) {
   return __builtin_amdgcn_make_buffer_rsrc(
-      reinterpret_cast<char*>(p.partial) + block_tile0<TR>(jb.off, p.Hq, p.Hkv, jb.b) * p.nsplit * PartialLayout<D, TR>::kBytes, 0, 0x7fffffff, 0x00020000);
+      reinterpret_cast<char*>(p.partial) + block_tile0<TR>(jb.off, p.Hq, p.Hkv, jb.b) * p.nsplit * PartialLayout<D, TR, PX>::kBytes, 0, 0x7fffffff, 0x00020000);
 }
-template <int D, int TR>
+template <int D, int TR, bool PX>
 __device__ __forceinline__ uint32_t partial_byte(const AttnParams& p, const TileJob& jb, int i) {
-  return (uint32_t)(jb.hk * ((jb.M + TR - 1) / TR) + jb.row0 / TR + i) * (uint32_t)p.nsplit * (uint32_t)PartialLayout<D, TR>::kBytes;
+  return (uint32_t)(jb.hk * ((jb.M + TR - 1) / TR) + jb.row0 / TR + i) * (uint32_t)p.nsplit * (uint32_t)PartialLayout<D, TR, PX>::kBytes;
 }
 
 // LDS of a workgroup beside the ring
@@ -404,15 +410,15 @@ struct Feed {
 };
 
 // Merge of NP pieces (from pc0) of one TR-row tile's partials by one wave: every lane merges the elements that the
-// layout gives it, so each load of the wave is 512 contiguous bytes (`byte`: offset of slot 0's block).  Slots are
+// layout gives it, so each load of the wave is contiguous (`byte`: offset of slot 0's block).  Slots are
 // combined online, BS per batch with all of a batch's loads in flight together: m = max m_t, w_t = 2^(m_t - m),
 // o = sum w_t o_t / sum w_t l_t (m_t is stored in log2 units).  POL is the buffer cache policy of
 // the loads.  A slot that saw no visible key carries m_t = -inf, l_t = 0 and gets weight 0; the
 // reference is kept finite so that (-inf) - (-inf) never occurs.  grow: the lane's output row, or -1.
-template <int D, int TR, int NP, int POL, int BS>
+template <int D, int TR, bool PX, int NP, int POL, int BS>
 __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64_t grow, uint32_t byte, CB_GLOBAL uint16_t* gout,
                                              int nslots, int pc0, int l) {
-  using Part = PartialLayout<D, TR>;
+  using Part = PartialLayout<D, TR, PX>;
   const int h = l / TR, r = l % TR;
   floatx4 acc[NP];
 #pragma unroll
@@ -420,9 +426,9 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
   float lsum = 0.f, m_run = -3.0e38f;
   // (the slot's offset is the same in all lanes: it travels as the load's scalar offset, so a
   // load costs no vector arithmetic)
-  const uint32_t vo_ml = byte + Part::kMl + r * 8, vo_v = byte + pc0 * 512 + l * 8;
+  const uint32_t vo_ml = byte + Part::kMl + r * 8, vo_v = byte + pc0 * Part::kPiece + l * Part::kLane;
   for (int t0 = 0; t0 < nslots; t0 += BS) {
-    uintx2 v[BS][NP];
+    std::conditional_t<PX, uintx4, uintx2> v[BS][NP];
     uintx2 ml[BS];
 #pragma unroll
     for (int u = 0; u < BS; u++) {
@@ -430,7 +436,8 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
       ml[u] = __builtin_amdgcn_raw_buffer_load_b64(prsrc, vo_ml, t * Part::kBytes, POL);
 #pragma unroll
       for (int i = 0; i < NP; i++)
-        v[u][i] = __builtin_amdgcn_raw_buffer_load_b64(prsrc, vo_v + i * 512, t * Part::kBytes, POL);
+        if constexpr (PX) v[u][i] = __builtin_amdgcn_raw_buffer_load_b128(prsrc, vo_v + i * Part::kPiece, t * Part::kBytes, POL);
+        else v[u][i] = __builtin_amdgcn_raw_buffer_load_b64(prsrc, vo_v + i * Part::kPiece, t * Part::kBytes, POL);
     }
     // (all of the batch's loads are requested before anything looks at a result: left alone, the
     // scheduler moves the first maxima up between the loads, and each then waits a round trip)
@@ -452,15 +459,20 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
       lsum = fmaf(__uint_as_float(ml[u][1]), wgt, lsum);
 #pragma unroll
       for (int i = 0; i < NP; i++) {
-        acc[i][0] = fmaf(__uint_as_float(v[u][i][0] << 16), wgt, acc[i][0]);
-        acc[i][1] = fmaf(__uint_as_float(v[u][i][0] & 0xffff0000u), wgt, acc[i][1]);
-        acc[i][2] = fmaf(__uint_as_float(v[u][i][1] << 16), wgt, acc[i][2]);
-        acc[i][3] = fmaf(__uint_as_float(v[u][i][1] & 0xffff0000u), wgt, acc[i][3]);
+        if constexpr (PX) {
+#pragma unroll
+          for (int x = 0; x < 4; x++) acc[i][x] = fmaf(__uint_as_float(v[u][i][x]), wgt, acc[i][x]);
+        } else {
+          acc[i][0] = fmaf(__uint_as_float(v[u][i][0] << 16), wgt, acc[i][0]);
+          acc[i][1] = fmaf(__uint_as_float(v[u][i][0] & 0xffff0000u), wgt, acc[i][1]);
+          acc[i][2] = fmaf(__uint_as_float(v[u][i][1] << 16), wgt, acc[i][2]);
+          acc[i][3] = fmaf(__uint_as_float(v[u][i][1] & 0xffff0000u), wgt, acc[i][3]);
+        }
       }
     }
   }
   if (grow < 0) return;
-  const float inv = __builtin_amdgcn_rcpf(lsum);
+  const float inv = PX ? 1.0f / lsum : __builtin_amdgcn_rcpf(lsum);
   CB_GLOBAL uint16_t* orow = gout + grow * D;
 #pragma unroll
   for (int i = 0; i < NP; i++) {
@@ -480,14 +492,14 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
 // of the arrivals' XCC_ID (hardware register 20, bits 3:0): all ids equal mine  <=>
 // sum = n*id and sumsq = n*id*id.  A second word per tile holds one bit per split whose
 // workgroup gave up waiting (cooperative merge only).
-template <int D, int TR, int NW, int MAXROWS, bool TS>
+template <int D, int TR, bool PX, int NW, int MAXROWS, bool TS>
 __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& jb, TileLds& sh, CB_LDS unsigned long long* ts) {
-  constexpr int P = PartialLayout<D, TR>::P;
+  constexpr int P = PartialLayout<D, TR, PX>::P;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const bool do_ts = TS && tid == 0, do_ts64 = TS && tid == 64;
 #define CB_TS(i) do { if (do_ts) ts[i] = wall_clock64(); } while (0)
   CB_GLOBAL uint16_t* gout = (CB_GLOBAL uint16_t*)p.out;
-  const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc<D, TR>(p, jb);
+  const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc<D, TR, PX>(p, jb);
   if (tid == 64) { sh.flag = 0; sh.flag2 = 0; }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -534,14 +546,14 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     if (!flag) return;
     // Same XCD: the write-through stores left the lines in this L2, plain (cached) loads are coherent
     // with them.  Otherwise read past the L2 with agent-coherent loads.
-    constexpr int NP = 4;
+    constexpr int NP = 4, BS = PX ? 4 : 8;
     for (int u = w; u < MAXROWS / TR * (P / NP); u += NW) {
       const int i = u / (P / NP);
       int64_t gr;
       if (!tile_row(i, &gr)) break;  // (nothing behind it either)
-      const uint32_t byte = partial_byte<D, TR>(p, jb, i);
-      if (flag == 1) merge_pieces<D, TR, NP, 0, 8>(prsrc, gr, byte, gout, nsplit, (u % (P / NP)) * NP, l);
-      else merge_pieces<D, TR, NP, kAgentCoherent, 8>(prsrc, gr, byte, gout, nsplit, (u % (P / NP)) * NP, l);
+      const uint32_t byte = partial_byte<D, TR, PX>(p, jb, i);
+      if (flag == 1) merge_pieces<D, TR, PX, NP, 0, BS>(prsrc, gr, byte, gout, nsplit, (u % (P / NP)) * NP, l);
+      else merge_pieces<D, TR, PX, NP, kAgentCoherent, BS>(prsrc, gr, byte, gout, nsplit, (u % (P / NP)) * NP, l);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     CB_TS(7);
@@ -605,17 +617,17 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
   auto merge_one = [&](int u, int64_t gr, uint32_t byte, int flag) {
     const int pc = u % P;
     if (nsplit <= 8) {  // (one batch in the common cases)
-      if (flag == 1) merge_pieces<D, TR, 1, 0, 8>(prsrc, gr, byte, gout, nsplit, pc, l);
-      else merge_pieces<D, TR, 1, kAgentCoherent, 8>(prsrc, gr, byte, gout, nsplit, pc, l);
+      if (flag == 1) merge_pieces<D, TR, PX, 1, 0, 8>(prsrc, gr, byte, gout, nsplit, pc, l);
+      else merge_pieces<D, TR, PX, 1, kAgentCoherent, 8>(prsrc, gr, byte, gout, nsplit, pc, l);
     } else {
-      if (flag == 1) merge_pieces<D, TR, 1, 0, 16>(prsrc, gr, byte, gout, nsplit, pc, l);
-      else merge_pieces<D, TR, 1, kAgentCoherent, 16>(prsrc, gr, byte, gout, nsplit, pc, l);
+      if (flag == 1) merge_pieces<D, TR, PX, 1, 0, 16>(prsrc, gr, byte, gout, nsplit, pc, l);
+      else merge_pieces<D, TR, PX, 1, kAgentCoherent, 16>(prsrc, gr, byte, gout, nsplit, pc, l);
     }
   };
   const int u_first = split + ((w + NW - 1) % NW) * nsplit;  // this wave's first unit of the own slice
   int64_t gr_first = -1;
   const bool have_first = u_first < NU && tile_row(u_first / P, &gr_first);
-  const uint32_t byte_first = partial_byte<D, TR>(p, jb, u_first / P);
+  const uint32_t byte_first = partial_byte<D, TR, PX>(p, jb, u_first / P);
   // the waves wait for thread 64's verdicts in LDS
   int flag;
   while ((flag = __hip_atomic_load(&sh.flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0) __builtin_amdgcn_s_sleep(1);
@@ -627,7 +639,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
       for (int u = s2; u < NU; u += nsplit, k++) {
         if ((k + 1) % NW != w || (first_done && u == u_first)) continue;
         int64_t gr;
-        if (tile_row(u / P, &gr)) merge_one(u, gr, partial_byte<D, TR>(p, jb, u / P), flag);
+        if (tile_row(u / P, &gr)) merge_one(u, gr, partial_byte<D, TR, PX>(p, jb, u / P), flag);
       }
     }
   };
@@ -652,10 +664,10 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
 // What a lane holds at the end of a sweep: its row's NP pieces from pc0, unnormalised, with the row's denominator and the
 // reference maximum they are relative to.  Written out as the output row (a single split) or as the split's partial
 // state (i: TR-row tile of the tile).
-template <int D, int TR, int NP>
+template <int D, int TR, bool PX, int NP>
 __device__ __forceinline__ void write_rows(const AttnParams& p, const TileJob& jb, int i, int64_t grow, const floatx4 (&f)[NP], int pc0,
                                            float mref, float lsum, float c2, bool first, int l) {
-  using Part = PartialLayout<D, TR>;
+  using Part = PartialLayout<D, TR, PX>;
   if (grow < 0) return;
   const int h = l / TR, r = l % TR;
   if (jb.nsplit == 1) {
@@ -672,13 +684,20 @@ __device__ __forceinline__ void write_rows(const AttnParams& p, const TileJob& j
   }
   // written through to memory (agent scope) so that the merging workgroup, possibly on another XCD with its own L2,
   // can read it without cache flushes
-  const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc<D, TR>(p, jb);
-  const uint32_t pbyte = partial_byte<D, TR>(p, jb, i) + (uint32_t)jb.split * Part::kBytes;
+  const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc<D, TR, PX>(p, jb);
+  const uint32_t pbyte = partial_byte<D, TR, PX>(p, jb, i) + (uint32_t)jb.split * Part::kBytes;
 #pragma unroll
   for (int n = 0; n < NP; n++) {
-    const uintx2 v = {(uint32_t)f2bf(f[n][0]) | ((uint32_t)f2bf(f[n][1]) << 16), (uint32_t)f2bf(f[n][2]) | ((uint32_t)f2bf(f[n][3]) << 16)};
-    if (p.external_merge) __builtin_amdgcn_raw_buffer_store_b64(v, prsrc, pbyte + (pc0 + n) * 512 + l * 8, 0, 0);
-    else __builtin_amdgcn_raw_buffer_store_b64(v, prsrc, pbyte + (pc0 + n) * 512 + l * 8, 0, kAgentCoherent);
+    const uint32_t at = pbyte + (pc0 + n) * Part::kPiece + l * Part::kLane;
+    if constexpr (PX) {
+      const uintx4 v = __builtin_bit_cast(uintx4, f[n]);
+      if (p.external_merge) __builtin_amdgcn_raw_buffer_store_b128(v, prsrc, at, 0, 0);
+      else __builtin_amdgcn_raw_buffer_store_b128(v, prsrc, at, 0, kAgentCoherent);
+    } else {
+      const uintx2 v = {(uint32_t)f2bf(f[n][0]) | ((uint32_t)f2bf(f[n][1]) << 16), (uint32_t)f2bf(f[n][2]) | ((uint32_t)f2bf(f[n][3]) << 16)};
+      if (p.external_merge) __builtin_amdgcn_raw_buffer_store_b64(v, prsrc, at, 0, 0);
+      else __builtin_amdgcn_raw_buffer_store_b64(v, prsrc, at, 0, kAgentCoherent);
+    }
   }
   if (h == 0 && first) {
     // m = log2 of the reference weight 2^(c2*mref)

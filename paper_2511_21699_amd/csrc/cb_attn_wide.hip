@@ -53,16 +53,21 @@ __device__ __forceinline__ void scores(const uint4 (&k)[D / 16], const TileState
     for (int t = 0; t < NV; t++)
       s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k[ds]), st.q[t][ds], s[t], 0, 0, 0);
 }
-// probabilities p = 2^(c*s - c*mref), packed as B operands of PV
-template <int D, int NVM, int NV>
-__device__ __forceinline__ void probs(const floatx16& s, const TileState<D, NVM>& st, int t, float c2, bf16x8 (&p)[2]) {
+// probabilities p = 2^(c*s - c*mref), packed as B operands of PV; with PX the roundings' rests behind them
+template <int D, int NVM, int NV, bool PX>
+__device__ __forceinline__ void probs(const floatx16& s, const TileState<D, NVM>& st, int t, float c2, bf16x8 (&p)[PX ? 4 : 2]) {
   const float nm = st.nm[t];
 #pragma unroll
   for (int j = 0; j < 2; j++) {
-    union { bf16x8 v; __bf16 e[8]; } pk;
+    union { bf16x8 v; __bf16 e[8]; } pk, rest;
 #pragma unroll
-    for (int e = 0; e < 8; e++) pk.e[e] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[8 * j + e], c2, nm));
+    for (int e = 0; e < 8; e++) {
+      const float pe = __builtin_amdgcn_exp2f(fmaf(s[8 * j + e], c2, nm));
+      pk.e[e] = (__bf16)pe;
+      if (PX) rest.e[e] = (__bf16)(pe - (float)pk.e[e]);
+    }
     p[j] = pk.v;
+    if constexpr (PX) p[2 + j] = rest.v;
   }
 }
 template <int D>
@@ -153,9 +158,9 @@ __device__ __forceinline__ void raise_reference(TileState<D, NVM>& st, const flo
 // score_half ends with the reads of add_half's first operands (v).  req(i), i = 0 .. NREQ - 1: memory requests to be
 // spread over score_half.
 // PREK: `k` is filled again in add_half, for the next score_half (its unit's K at kn).
-template <int D, int NVM, int NV, int NREQ, typename Req>
+template <int D, int NVM, int NV, bool PX, int NREQ, typename Req>
 __device__ __forceinline__ void score_half(const uint4 (&k)[D / 16], const TileState<D, NVM>& st, const floatx16 (&sc)[NV], floatx16 (&sn)[NV],
-                                           uintx4 (&pb)[NV][2], const uint4* vs, bf16x8 (&v)[D / 32], float c2, int l, Req req) {
+                                           uintx4 (&pb)[NV][PX ? 4 : 2], const uint4* vs, bf16x8 (&v)[D / 32], float c2, int l, Req req) {
   constexpr int DS = D / 16, DT = D / 32;
   // The probabilities in three stages, each a slot behind the one before it, so that no instruction waits for the one
   // in front of it: argument, exponential, packing.  Slot i handles elements 2 i and 2 i + 1 (constant indices).
@@ -181,6 +186,12 @@ __device__ __forceinline__ void score_half(const uint4 (&k)[D / 16], const TileS
     uint32_t z = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){x0[i], x1[i]}, bf16x2v));
     asm volatile("" : "+v"(z));
     pb[i >> 3][(i & 7) >> 2][i & 3] = z;
+    if constexpr (PX) {
+      const float r0 = x0[i] - __uint_as_float(z << 16), r1 = x1[i] - __uint_as_float(z & 0xffff0000u);
+      uint32_t y = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){r0, r1}, bf16x2v));
+      asm volatile("" : "+v"(y));
+      pb[i >> 3][2 + ((i & 7) >> 2)][i & 3] = y;
+    }
   };
   arg(0);
   arg(1);
@@ -209,9 +220,9 @@ __device__ __forceinline__ void score_half(const uint4 (&k)[D / 16], const TileS
     }
   }
 }
-template <int D, int NVM, int NV, bool PREK>
+template <int D, int NVM, int NV, bool PX, bool PREK>
 __device__ __forceinline__ void add_half(uint4 (&k)[D / 16], const uint4* kn, const uint4* vs, bf16x8 (&v)[D / 32], TileState<D, NVM>& st,
-                                         const uintx4 (&pb)[NV][2], const floatx16 (&sn)[NV], float (&mx)[NV], const bf16x8& ones, int l) {
+                                         const uintx4 (&pb)[NV][PX ? 4 : 2], const floatx16 (&sn)[NV], float (&mx)[NV], const bf16x8& ones, int l) {
   constexpr int DS = D / 16, DT = D / 32;
   // the maxima of the new scores, then across the lanes, a few beside every MFMA from the second on
   float m[NV];
@@ -235,6 +246,8 @@ __device__ __forceinline__ void add_half(uint4 (&k)[D / 16], const uint4* kn, co
       for (int t = 0; t < NV; t++) {
         const int n = (j * DT + dt) * NV + t;
         st.o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[dt], __builtin_bit_cast(bf16x8, pb[t][j]), st.o[t][dt], 0, 0, 0);
+        if constexpr (PX)
+          st.o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[dt], __builtin_bit_cast(bf16x8, pb[t][2 + j]), st.o[t][dt], 0, 0, 0);
         if (t == NV - 1) {  // (the operand's registers take the next thing from LDS)
           if (j == 0) v[dt] = read_v<D>(vs, dt, 1, l);
           else if (PREK) {
@@ -242,7 +255,11 @@ __device__ __forceinline__ void add_half(uint4 (&k)[D / 16], const uint4* kn, co
             for (int q = 0; q < DS / DT; q++) k[dt * (DS / DT) + q] = read_k1<D>(kn, dt * (DS / DT) + q, l);
           }
         }
-        if (dt == DT - 1) st.lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, __builtin_bit_cast(bf16x8, pb[t][j]), st.lacc[t], 0, 0, 0);
+        if (dt == DT - 1) {
+#pragma unroll
+          for (int x = j; x < (PX ? 4 : 2); x += 2)
+            st.lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, __builtin_bit_cast(bf16x8, pb[t][x]), st.lacc[t], 0, 0, 0);
+        }
 #pragma unroll
         for (int q = 0; q < MPER; q++) maxima((n - 1) * MPER + q);
         __builtin_amdgcn_sched_barrier(0);
@@ -253,13 +270,14 @@ __device__ __forceinline__ void add_half(uint4 (&k)[D / 16], const uint4* kn, co
 
 // The sweep of one workgroup whose tile has RW row groups, up to its output rows (a single split) or its partial
 // state.
-template <int D, int NW, int NVM, int RW, bool TS>
+template <int D, bool PX, int NW, int NVM, int RW, bool TS>
 __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& jb, TileLds& sh, uint4* ring,
                                            CB_LDS unsigned long long* ts) {
-  using Part = PartialLayout<D, 32>;
+  using Part = PartialLayout<D, 32, PX>;
   using F = Feed<D, NW, 32>;
   constexpr int KW = NW / RW;            // key groups
   constexpr int NS = F::kSlots, PRO = F::kPrologue;
+  constexpr int NPB = PX ? 4 : 2;        // B operands of a unit's probabilities
   constexpr int LA = KW <= 2 ? 1 : 0;    // scores run one stage ahead of the softmax (needs two stages resident)
   static_assert((LA + 2) * KW <= NS && KW <= PRO, "a stage is requested in full while the one before it is worked on");
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
@@ -348,12 +366,12 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
         for (int t = 0; t < NV; t++) mask_scores(sc[t], key0, S, k1, &sh.anc.anc[row_node[t]][0], h);
       }
     };
-    auto add_unit = [&](const bf16x8(&pb)[NV][2], int slot) {
+    auto add_unit = [&](const bf16x8(&pb)[NV][NPB], int slot) {
       const uint4* vs = feed.v_at(slot);
 #pragma unroll
       for (int t = 0; t < NV; t++)
 #pragma unroll
-        for (int j = 0; j < 2; j++) st.lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[t][j], st.lacc[t], 0, 0, 0);
+        for (int j = 0; j < NPB; j++) st.lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[t][j], st.lacc[t], 0, 0, 0);
 #pragma unroll
       for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -361,12 +379,14 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
           const bf16x8 a = read_v<D>(vs, dt, j, l);
 #pragma unroll
           for (int t = 0; t < NV; t++)
-            st.o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[t][j], st.o[t][dt], 0, 0, 0);
+#pragma unroll
+            for (int x = j; x < NPB; x += 2)
+              st.o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[t][x], st.o[t][dt], 0, 0, 0);
         }
     };
     floatx16 sc[NV];
     float mx[NV];
-    bf16x8 pb[NV][2];
+    bf16x8 pb[NV][NPB];
     if constexpr (LA == 0) {
       for (int s = 0; s < nst; s++) {
         top(s);
@@ -374,7 +394,7 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
         row_max<NV>(sc, mx);
         if (must_raise<NVM, NV>(st, mx, c2)) raise_reference<D, NVM, NV>(st, mx, c2);
 #pragma unroll
-        for (int t = 0; t < NV; t++) probs<D, NVM, NV>(sc[t], st, t, c2, pb[t]);
+        for (int t = 0; t < NV; t++) probs<D, NVM, NV, PX>(sc[t], st, t, c2, pb[t]);
         add_unit(pb, slot_cur);
         slot_cur = next_slot(slot_cur);
       }
@@ -386,7 +406,7 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
       const int fast_end = fast_stages();
       floatx16 sd[NV];
       uint4 k[D / 16];
-      uintx4 pw[NV][2];
+      uintx4 pw[NV][NPB];
       bf16x8 v[D / 32];
       auto check = [&] {
         if (must_raise<NVM, NV>(st, mx, c2)) raise_reference<D, NVM, NV>(st, mx, c2);
@@ -406,12 +426,12 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
             int64_t off[F::kParts];  // (worked out here: the paged form's branch would cut the instruction stream)
 #pragma unroll
             for (int i = 0; i < F::kParts; i++) off[i] = feed.group_off(feed.requested, i);
-            score_half<D, NVM, NV, F::kParts>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [&](int i) { feed.issue_group(feed.slot_next, i, off[i], rq); });
+            score_half<D, NVM, NV, PX, F::kParts>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [&](int i) { feed.issue_group(feed.slot_next, i, off[i], rq); });
             if (rq) feed.counted();
           };
           auto add = [&](const floatx16(&scored)[NV]) {  // unit s; scored: unit s + 1
             const int nx = next_slot(slot_cur);
-            add_half<D, NVM, NV, true>(k, feed.k_at(next_slot(nx)), feed.v_at(slot_cur), v, st, pw, scored, mx, ones, l);
+            add_half<D, NVM, NV, PX, true>(k, feed.k_at(next_slot(nx)), feed.v_at(slot_cur), v, st, pw, scored, mx, ones, l);
             check();
             slot_cur = nx;
             s++;
@@ -432,8 +452,8 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
           top(s);
           const int nx = next_slot(slot_cur);
           read_k<D, NV>(feed.k_at(nx), k, l);
-          score_half<D, NVM, NV, 0>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [](int) {});
-          add_half<D, NVM, NV, false>(k, nullptr, feed.v_at(slot_cur), v, st, pw, to, mx, ones, l);
+          score_half<D, NVM, NV, PX, 0>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [](int) {});
+          add_half<D, NVM, NV, PX, false>(k, nullptr, feed.v_at(slot_cur), v, st, pw, to, mx, ones, l);
           check();
           slot_cur = nx;
           s++;
@@ -448,7 +468,7 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
         floatx16 sn[NV];
         unit_scores(s + 1, next_slot(slot_cur), sn);
 #pragma unroll
-        for (int t = 0; t < NV; t++) probs<D, NVM, NV>(sc[t], st, t, c2, pb[t]);
+        for (int t = 0; t < NV; t++) probs<D, NVM, NV, PX>(sc[t], st, t, c2, pb[t]);
         add_unit(pb, slot_cur);
         row_max<NV>(sn, mx);
         if (must_raise<NVM, NV>(st, mx, c2)) raise_reference<D, NVM, NV>(st, mx, c2);
@@ -457,7 +477,7 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
         slot_cur = next_slot(slot_cur);
       }
 #pragma unroll
-      for (int t = 0; t < NV; t++) probs<D, NVM, NV>(sc[t], st, t, c2, pb[t]);
+      for (int t = 0; t < NV; t++) probs<D, NVM, NV, PX>(sc[t], st, t, c2, pb[t]);
       add_unit(pb, slot_cur);
     }
   };
@@ -531,12 +551,12 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
     }
   }
 #pragma unroll
-  for (int t = 0; t < NVM; t++) write_rows<D, 32, PP>(p, jb, rw * NVM + t, grow[t], f[t], kw * PP, mfin[t], lsum[t], c2, kw == 0, l);
+  for (int t = 0; t < NVM; t++) write_rows<D, 32, PX, PP>(p, jb, rw * NVM + t, grow[t], f[t], kw * PP, mfin[t], lsum[t], c2, kw == 0, l);
 #undef CB_TS
 }
 
 // One attention workgroup of 8 waves whose tile has up to 256 rows; `wg` is its number among those that do attention.
-template <int D, bool TS>
+template <int D, bool PX, bool TS>
 __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, unsigned long long ts0,
                                                TileLds& sh, uint4* ring, unsigned long long* ts_sh) {
   AttnParams p = p_arg;
@@ -545,32 +565,33 @@ __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const Se
   first_stamps<TS>(ts, ts0);
   TileJob jb;
   if (!tile_job(p, ml, wg, 256, jb)) return;
-  if (jb.M - jb.row0 <= 128) sweep_tile<D, 8, 1, 4, TS>(p, jb, sh, ring, ts);
-  else sweep_tile<D, 8, 1, 8, TS>(p, jb, sh, ring, ts);
+  if (jb.M - jb.row0 <= 128) sweep_tile<D, PX, 8, 1, 4, TS>(p, jb, sh, ring, ts);
+  else sweep_tile<D, PX, 8, 1, 8, TS>(p, jb, sh, ring, ts);
   if (jb.nsplit == 1 || p.external_merge) return;  // (a following kernel merges: the kernel boundary orders the stores)
-  split_merge<D, 32, 8, 256, TS>(p, jb, sh, ts);
+  split_merge<D, 32, PX, 8, 256, TS>(p, jb, sh, ts);
 }
 
-template <int D, bool TS>
+template <int D, bool PX, bool TS>
 __global__ __launch_bounds__(512) void k_attn_wide(AttnParams p, SeqMeta meta) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   __shared__ uint4 ring[Feed<D, 8, 32>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
-  attn_wide_tile<D, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
+  attn_wide_tile<D, PX, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
 hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles) {
   const dim3 grid(n_tiles), block(512);
-#define CB_LAUNCH(D)                                                                                  \
+#define CB_LAUNCH(D, PX)                                                                              \
   do {                                                                                                \
-    if (p.timeline) hipLaunchKernelGGL((k_attn_wide<D, true>), grid, block, 0, st, p, meta);          \
-    else hipLaunchKernelGGL((k_attn_wide<D, false>), grid, block, 0, st, p, meta);                    \
+    if (p.timeline) hipLaunchKernelGGL((k_attn_wide<D, PX, true>), grid, block, 0, st, p, meta);      \
+    else hipLaunchKernelGGL((k_attn_wide<D, PX, false>), grid, block, 0, st, p, meta);                \
   } while (0)
-  if (p.D == 128) CB_LAUNCH(128);
-  else CB_LAUNCH(64);
+  if (p.D == 64) CB_LAUNCH(64, true);
+  else if (p.precise) CB_LAUNCH(128, true);
+  else CB_LAUNCH(128, false);
 #undef CB_LAUNCH
   return hipGetLastError();
 }

@@ -166,6 +166,7 @@ struct AttnParams {
   int32_t nsplit;       // partial slots per row (>= splits any sequence uses)
   int32_t batch;
   float scale;
+  int32_t precise;      // bf16 MFMA kernels: probabilities and partial sums in 32 bits (the host reads it, to choose the build)
   int32_t xcd_remap;    // 1: renumber workgroups so that all splits of a tile run on one XCD; 2: and every XCD takes
                         // its share -- a fixed set of (kv head, row tile) pairs of all sequences -- longest sequence first
   int32_t grid_x, grid_y, grid_z;  // launch grid, repeated here so the kernel reads one argument block
@@ -206,7 +207,7 @@ hipError_t launch_merge(hipStream_t st, const AttnParams& p, const SeqMeta& meta
 int attn_mfma_tile_rows(int mrows);            // rows per workgroup tile chosen for a given g*N
 // bytes the MFMA path's partial states can take in calls whose largest sequence has `mrows` rows per kv head (its own layout,
 // padded to 16-row tiles per kv head where one small tile holds them, else to 32-row ones)
-size_t attn_mfma_partial_bytes(int D, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
+size_t attn_mfma_partial_bytes(int D, bool precise, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
 bool attn_mfma_supports(const AttnParams& p);  // shape/geometry the MFMA kernel takes (bf16 is the caller's check)
 bool attn_mfma_can_fuse(const AttnParams& p, int max_nodes_in_call);
 // with logits_work != nullptr (only if attn_mfma_can_fuse) the same launch also scans the logits and runs the acceptance
