@@ -241,7 +241,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
 }
 
 template <int D, bool PX, bool TS>
-__global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) {
+__device__ __forceinline__ void attn_workgroup(const AttnParams& p, const SeqMeta& meta) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) {
 // first, so the acceptance is through long before the attention is, and a waiting host has its results then),
 // the others the attention.  Neither waits for the other.
 template <int D, bool PX, bool TS>
-__global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) {
+__device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqMeta& meta, const LogitsWork& lw) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
@@ -270,6 +270,16 @@ __global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta,
   attn_tile<D, PX, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
   flush_timestamps<TS>(p, wg, ts_sh);
 }
+
+// head_dim 64 always holds probabilities and partial sums in 32 bits, head_dim 128 in the precise builds.
+template <int D, bool TS>
+__global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) { attn_workgroup<D, D == 64, TS>(p, meta); }
+template <bool TS>
+__global__ __launch_bounds__(512) void k_attn_precise(AttnParams p, SeqMeta meta) { attn_workgroup<128, true, TS>(p, meta); }
+template <int D, bool TS>
+__global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, TS>(p, meta, lw); }
+template <bool TS>
+__global__ __launch_bounds__(512) void k_verify_precise(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<128, true, TS>(p, meta, lw); }
 
 // Stand-alone merge of the partials, used when a tile's partials are too many for one
 // workgroup to pull through its compute unit: one workgroup per TR-row tile, its four waves take a quarter of the
@@ -367,30 +377,21 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   if (merge_kind) *merge_kind = p.nsplit <= 1 ? 0 : (q.coop_merge ? 1 : (q.external_merge ? 3 : 2));
   const bool ts = p.timeline != 0;  // (the timeline build of the same kernels: a measurement aid)
   hipError_t e;
-#define CB_LAUNCH_TS(K, D, PX, ...)                                                          \
-  do {                                                                                       \
-    if (ts) hipLaunchKernelGGL((K<D, PX, true>), grid, dim3(512), 0, st, __VA_ARGS__);       \
-    else hipLaunchKernelGGL((K<D, PX, false>), grid, dim3(512), 0, st, __VA_ARGS__);         \
-  } while (0)
-#define CB_LAUNCH(K, ...)                                       \
-  do {                                                          \
-    if (p.D == 64) CB_LAUNCH_TS(K, 64, true, __VA_ARGS__);      \
-    else if (p.precise) CB_LAUNCH_TS(K, 128, true, __VA_ARGS__); \
-    else CB_LAUNCH_TS(K, 128, false, __VA_ARGS__);              \
-  } while (0)
+  auto launch = [&](auto* stamped, auto* plain, auto... args) { hipLaunchKernelGGL(ts ? stamped : plain, grid, dim3(512), 0, st, args...); };
   if (logits_work) {
-    const LogitsWork& lw = *logits_work;
     if (!attn_mfma_can_fuse(p, max_nodes_in_call)) return hipErrorInvalidValue;
-    CB_LAUNCH(k_verify_mfma, q, meta, lw);
+    if (p.D == 64) launch(k_verify_mfma<64, true>, k_verify_mfma<64, false>, q, meta, *logits_work);
+    else if (p.precise) launch(k_verify_precise<true>, k_verify_precise<false>, q, meta, *logits_work);
+    else launch(k_verify_mfma<128, true>, k_verify_mfma<128, false>, q, meta, *logits_work);
     e = hipGetLastError();
   } else if (rt_rows == kSmallRows) {
-    CB_LAUNCH(k_attn_mfma, q, meta);
+    if (p.D == 64) launch(k_attn_mfma<64, true>, k_attn_mfma<64, false>, q, meta);
+    else if (p.precise) launch(k_attn_precise<true>, k_attn_precise<false>, q, meta);
+    else launch(k_attn_mfma<128, true>, k_attn_mfma<128, false>, q, meta);
     e = hipGetLastError();
   } else {
     e = launch_attn_wide(st, q, meta, (int)T);
   }
-#undef CB_LAUNCH
-#undef CB_LAUNCH_TS
   if (e != hipSuccess) return e;
   if (q.external_merge) {
     const dim3 mgrid((M + tr - 1) / tr, p.Hkv, p.batch);
