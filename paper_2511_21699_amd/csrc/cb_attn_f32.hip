@@ -300,7 +300,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_verify_f32(AttnParams p, Seq
   } sh;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   const int wg = (int)blockIdx.x - lw.n_wgs;
-  if (wg < 0) logits_share<kF32Waves>(lw, ml, blockIdx.x, sh.accept);
+  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept);
   else attn_f32_tile<D>(p, ml, wg, sh.attn);
 }
 

@@ -405,7 +405,9 @@ constexpr int kTicketStride = 32;                                    // 32-bit w
 constexpr int kTicketWords = (kTicketGroups + 1) * kTicketStride;    // per sequence
 constexpr int kTicketDirect = 48;  // arrivals up to which one word serves a sequence
 
-template <int NW, bool SHORT = false>
+// LOADS: loads of 16 bytes that a lane has in flight, as the kernel's registers allow.  EB: bytes of a logits element
+// where the kernel is built for one type, else 0.
+template <int NW, int LOADS, bool SHORT = false, int EB = 0>
 __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMetaLanes& ml, int wg, AcceptWaveLds& sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t items = (int64_t)lw.rows * lw.chunks;
@@ -413,11 +415,11 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
   for (int i = i0 + w; i < i1; i += NW) {
     const int row = i / lw.chunks, c = i - row * lw.chunks;
     constexpr int CH = SHORT ? kArgmaxShortChunk : kArgmaxChunk;
-    constexpr int KB = SHORT ? kArgmaxShortChunk / 512 : 16, KF = SHORT ? kArgmaxShortChunk / 256 : 16;  // loads per lane
+    constexpr int KB = LOADS < CH / 512 ? LOADS : CH / 512, KF = LOADS < CH / 256 ? LOADS : CH / 256;
     const int64_t e0 = (int64_t)c * CH;
     const int64_t e1 = e0 + CH < lw.V ? e0 + CH : lw.V;
     const unsigned long long word =
-        lw.is_f32 ? WaveScan<float, KF>::run((const float*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1)
+        EB == 4 || (EB == 0 && lw.is_f32) ? WaveScan<float, KF>::run((const float*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1)
                   : WaveScan<uint16_t, KB>::run((const uint16_t*)lw.logits + (int64_t)row * lw.V, (int)e0, (int)e1);
     if (lane == 0)
       __hip_atomic_fetch_max(as_global(lw.accept.best) + (int64_t)row * kAmaxStride, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -90,7 +90,7 @@ struct PrepareArgs {
 
 constexpr int kLogitsWaves = 4;
 
-template <bool SHORT>
+template <bool SHORT, int EB>
 __global__ __launch_bounds__(64 * kLogitsWaves) void k_logits(LogitsWork lw, SeqMeta meta, PrepareArgs prep) {
   __shared__ union {
     AcceptWaveLds accept;
@@ -101,13 +101,15 @@ __global__ __launch_bounds__(64 * kLogitsWaves) void k_logits(LogitsWork lw, Seq
     return;
   }
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  logits_share<kLogitsWaves, SHORT>(lw, ml, blockIdx.x, sh.accept);
+  logits_share<kLogitsWaves, 8, SHORT, EB>(lw, ml, blockIdx.x, sh.accept);
 }
 
-// One wavefront per 16 KiB of bf16 logits up to the wavefronts that are resident at once (four or five of these
-// workgroups fit a compute unit), then several chunks for each.  A scan that would have no more than one wavefront for
+// One wavefront per 16 KiB of bf16 logits up to the wavefronts that are resident at once, then several chunks for each.
+// Four of these workgroups fit a compute unit: built for one type and with 8 loads per lane they take 98 registers in bf16
+// and 69 in fp32 (177 built for both types with 16 loads, where a grid of 1024 ran in two rounds: 1024 rows of 32000
+// bf16 19.1 -> 17.8 us, 256 rows of 128256 17.1 -> 15.9 us).  A scan that would have no more than one wavefront for
 // each of the chip's 1024 SIMDs is bound by the latency of each wavefront's loads: there 4 KiB for each (64 rows of 32000
-// bf16: 4.3 -> 3.6 us for the launch; 128 rows: 4.6 -> 4.0 us).
+// bf16: 4.3 -> 3.6 us for the launch; 128 rows: 4.6 -> 3.9 us).
 hipError_t launch_logits(hipStream_t st, const LogitsWork& work, const SeqMeta& meta, const int32_t* prep_parent,
                          int max_depth, uint32_t* prep_anc, int32_t* status) {
   LogitsWork lw = work;
@@ -117,8 +119,12 @@ hipError_t launch_logits(hipStream_t st, const LogitsWork& work, const SeqMeta& 
   lw.n_wgs = (int32_t)((items + kLogitsWaves - 1) / kLogitsWaves < 1024 ? (items + kLogitsWaves - 1) / kLogitsWaves : 1024);
   const PrepareArgs prep{prep_parent, prep_anc, status, max_depth};
   const dim3 grid(lw.n_wgs + (prep_parent ? lw.batch : 0));
-  if (few) hipLaunchKernelGGL(k_logits<true>, grid, dim3(64 * kLogitsWaves), 0, st, lw, meta, prep);
-  else hipLaunchKernelGGL(k_logits<false>, grid, dim3(64 * kLogitsWaves), 0, st, lw, meta, prep);
+#define CB_LAUNCH(SHORT, EB) hipLaunchKernelGGL((k_logits<SHORT, EB>), grid, dim3(64 * kLogitsWaves), 0, st, lw, meta, prep)
+  if (few && lw.is_f32) CB_LAUNCH(true, 4);
+  else if (few) CB_LAUNCH(true, 2);
+  else if (lw.is_f32) CB_LAUNCH(false, 4);
+  else CB_LAUNCH(false, 2);
+#undef CB_LAUNCH
   return hipGetLastError();
 }
 

@@ -90,3 +90,13 @@ def test_compiled_requests_keep_their_distance_from_the_base(name):
     asm = build.device_asm(os.path.join(build.CSRC, name))
     assert asm.count(", s[") > 0 and "global_load_lds_dwordx4" in asm
     assert build.scalar_base_violations(asm) == []
+
+
+# The logits scan launches up to 1024 workgroups of 4 waves and counts on all of them being resident: four to a compute unit, a
+# wave of each on every SIMD.  In the fp32 verification the scan must not take the attention's occupancy at head_dim 64.
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+@pytest.mark.parametrize("name,kernel", [("cb_small_kernels.hip", "k_logits"), ("cb_attn_f32.hip", "k_verify_f32ILi64")])
+def test_registers_leave_room_for_four_waves_per_simd(name, kernel):
+    res = build.kernel_resources(build.device_asm(os.path.join(build.CSRC, name)))
+    counts = [v[0] for k, v in res.items() if kernel in k]
+    assert counts and max(counts) <= 128, res
