@@ -1,6 +1,6 @@
 // Tree attention for tiles of 65 to 256 rows (bf16, head_dim 64 or 128), gfx950 only.
 //
-// A tile's rows decide how the 8 waves share it: RW row groups of 32 * NVM rows times KW = 8 / RW key groups (two key
+// A tile's rows decide how the 8 waves share it: RW row groups of 32 rows times KW = 8 / RW key groups (two key
 // groups up to 128 rows, one beyond).  A unit of work is 32 keys; a stage is KW units, one for each key
 // group, whose softmax states are combined through LDS at the end.
 //
@@ -16,13 +16,13 @@
 
 namespace cb {
 
-template <int D, int NVM>
+template <int D>
 struct TileState {
-  bf16x8 q[NVM][D / 16];     // B operands of QK^T: query r, dims 16 ds + 8h ..
-  floatx16 o[NVM][D / 32];   // O^T accumulators, dim tiles of 32
-  floatx4 lacc[NVM];         // softmax denominator of the lane's query (all four elements equal)
-  float mref[NVM];           // reference maximum of the raw scores (q.k, before the softmax scale)
-  float nm[NVM];             // -mref in log2 units (0 while mref is -inf)
+  bf16x8 q[D / 16];     // B operands of QK^T: query r, dims 16 ds + 8h ..
+  floatx16 o[D / 32];   // O^T accumulators, dim tiles of 32
+  floatx4 lacc;         // softmax denominator of the lane's query (all four elements equal)
+  float mref;           // reference maximum of the raw scores (q.k, before the softmax scale)
+  float nm;             // -mref in log2 units (0 while mref is -inf)
 };
 
 __device__ __forceinline__ float half_swap_max(float x) {  // maximum over lanes l and l ^ 32
@@ -35,28 +35,23 @@ __device__ __forceinline__ uint4 read_k1(const uint4* ks, int ds, int l) {
   const int r = l & 31, h = l >> 5;
   return ks[r * (D / 8) + ((2 * ds + h) ^ swizzle_k<D>(r))];
 }
-template <int D, int NV>
+template <int D>
 __device__ __forceinline__ void read_k(const uint4* ks, uint4 (&k)[D / 16], int l) {
 #pragma unroll
   for (int ds = 0; ds < D / 16; ds++) k[ds] = read_k1<D>(ks, ds, l);
 }
 // scores of a unit: S^T = K Q^T
-template <int D, int NVM, int NV>
-__device__ __forceinline__ void scores(const uint4 (&k)[D / 16], const TileState<D, NVM>& st, floatx16 (&s)[NV]) {
+template <int D>
+__device__ __forceinline__ void scores(const uint4 (&k)[D / 16], const TileState<D>& st, floatx16& s) {
 #pragma unroll
-  for (int t = 0; t < NV; t++)
+  for (int v = 0; v < 16; v++) s[v] = 0.f;
 #pragma unroll
-    for (int v = 0; v < 16; v++) s[t][v] = 0.f;
-#pragma unroll
-  for (int ds = 0; ds < D / 16; ds++)
-#pragma unroll
-    for (int t = 0; t < NV; t++)
-      s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k[ds]), st.q[t][ds], s[t], 0, 0, 0);
+  for (int ds = 0; ds < D / 16; ds++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k[ds]), st.q[ds], s, 0, 0, 0);
 }
 // probabilities p = 2^(c*s - c*mref), packed as B operands of PV; with PX the roundings' rests behind them
-template <int D, int NVM, int NV, bool PX>
-__device__ __forceinline__ void probs(const floatx16& s, const TileState<D, NVM>& st, int t, float c2, bf16x8 (&p)[PX ? 4 : 2]) {
-  const float nm = st.nm[t];
+template <int D, bool PX>
+__device__ __forceinline__ void probs(const floatx16& s, const TileState<D>& st, float c2, bf16x8 (&p)[PX ? 4 : 2]) {
+  const float nm = st.nm;
 #pragma unroll
   for (int j = 0; j < 2; j++) {
     union { bf16x8 v; __bf16 e[8]; } pk, rest;
@@ -115,39 +110,29 @@ __device__ __forceinline__ void mask_scores(floatx16& s, int key0, int S, int ke
   for (int v = 0; v < 16; v++) s[v] = ((vis >> (8 * (v >> 2) + (v & 3))) & 1u) ? s[v] : -INFINITY;
 }
 
-template <int NV>
-__device__ __forceinline__ void row_max(const floatx16 (&s)[NV], float (&mx)[NV]) {
+__device__ __forceinline__ float row_max(const floatx16& s) {
+  float m = maxn(maxn(s[0], s[1]), s[2]);
 #pragma unroll
-  for (int t = 0; t < NV; t++) {
-    float m = maxn(maxn(s[t][0], s[t][1]), s[t][2]);
-#pragma unroll
-    for (int v = 3; v < 15; v += 2) m = maxn(maxn(m, s[t][v]), s[t][v + 1]);
-    mx[t] = half_swap_max(maxn(m, s[t][15]));
-  }
+  for (int v = 3; v < 15; v += 2) m = maxn(maxn(m, s[v]), s[v + 1]);
+  return half_swap_max(maxn(m, s[15]));
 }
 // Lazy reference: it is only raised (and O, l rescaled) when the maximum has grown by more than kRescaleSlack, so
 // probabilities stay below 2^8 and the accumulators are rarely touched by the vector ALU.
-template <int NVM, int NV, typename State>
-__device__ __forceinline__ bool must_raise(const State& st, const float (&mx)[NV], float c2) {  // uniform
-  bool any = false;
-#pragma unroll
-  for (int t = 0; t < NV; t++) any |= (mx[t] - st.mref[t]) * c2 > kRescaleSlack;  // false when both are -inf (NaN)
-  return __builtin_amdgcn_ballot_w64(any) != 0ull;
+template <int D>
+__device__ __forceinline__ bool must_raise(const TileState<D>& st, float mx, float c2) {  // uniform
+  return __builtin_amdgcn_ballot_w64((mx - st.mref) * c2 > kRescaleSlack) != 0ull;  // (false when both are -inf: NaN)
 }
-template <int D, int NVM, int NV>
-__device__ __forceinline__ void raise_reference(TileState<D, NVM>& st, const float (&mx)[NV], float c2) {
-#pragma unroll
-  for (int t = 0; t < NV; t++) {
-    const bool raise = (mx[t] - st.mref[t]) * c2 > kRescaleSlack;
-    const float alpha = raise ? __builtin_amdgcn_exp2f((st.mref[t] - mx[t]) * c2) : 1.0f;
-    if (raise) {
-      st.mref[t] = mx[t];
-      st.nm[t] = -mx[t] * c2;
-    }
-#pragma unroll
-    for (int dt = 0; dt < D / 32; dt++) st.o[t][dt] *= alpha;
-    st.lacc[t] *= alpha;
+template <int D>
+__device__ __forceinline__ void raise_reference(TileState<D>& st, float mx, float c2) {
+  const bool raise = (mx - st.mref) * c2 > kRescaleSlack;
+  const float alpha = raise ? __builtin_amdgcn_exp2f((st.mref - mx) * c2) : 1.0f;
+  if (raise) {
+    st.mref = mx;
+    st.nm = -mx * c2;
   }
+#pragma unroll
+  for (int dt = 0; dt < D / 32; dt++) st.o[dt] *= alpha;
+  st.lacc *= alpha;
 }
 
 // One steady step of a wave, in two halves: score_half scores a unit (its K operands in `k`, scores to sn) while the
@@ -158,19 +143,18 @@ __device__ __forceinline__ void raise_reference(TileState<D, NVM>& st, const flo
 // score_half ends with the reads of add_half's first operands (v).  req(i), i = 0 .. NREQ - 1: memory requests to be
 // spread over score_half.
 // PREK: `k` is filled again in add_half, for the next score_half (its unit's K at kn).
-template <int D, int NVM, int NV, bool PX, int NREQ, typename Req>
-__device__ __forceinline__ void score_half(const uint4 (&k)[D / 16], const TileState<D, NVM>& st, const floatx16 (&sc)[NV], floatx16 (&sn)[NV],
-                                           uintx4 (&pb)[NV][PX ? 4 : 2], const uint4* vs, bf16x8 (&v)[D / 32], float c2, int l, Req req) {
+template <int D, bool PX, int NREQ, typename Req>
+__device__ __forceinline__ void score_half(const uint4 (&k)[D / 16], const TileState<D>& st, const floatx16& sc, floatx16& sn,
+                                           uintx4 (&pb)[PX ? 4 : 2], const uint4* vs, bf16x8 (&v)[D / 32], float c2, int l, Req req) {
   constexpr int DS = D / 16, DT = D / 32;
   // The probabilities in three stages, each a slot behind the one before it, so that no instruction waits for the one
   // in front of it: argument, exponential, packing.  Slot i handles elements 2 i and 2 i + 1 (constant indices).
-  constexpr int NP2 = 8 * NV;
+  constexpr int NP2 = 8;
   float x0[NP2], x1[NP2];
   auto arg = [&](int i) {
     if (i >= NP2) return;
-    const int t = i >> 3, x = 2 * (i & 7);
-    x0[i] = fmaf(sc[t][x], c2, st.nm[t]);
-    x1[i] = fmaf(sc[t][x + 1], c2, st.nm[t]);
+    x0[i] = fmaf(sc[2 * i], c2, st.nm);
+    x1[i] = fmaf(sc[2 * i + 1], c2, st.nm);
     asm volatile("" : "+v"(x0[i]), "+v"(x1[i]));
   };
   auto expo = [&](int i) {
@@ -185,12 +169,12 @@ __device__ __forceinline__ void score_half(const uint4 (&k)[D / 16], const TileS
     typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
     uint32_t z = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){x0[i], x1[i]}, bf16x2v));
     asm volatile("" : "+v"(z));
-    pb[i >> 3][(i & 7) >> 2][i & 3] = z;
+    pb[i >> 2][i & 3] = z;
     if constexpr (PX) {
       const float r0 = x0[i] - __uint_as_float(z << 16), r1 = x1[i] - __uint_as_float(z & 0xffff0000u);
       uint32_t y = __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){r0, r1}, bf16x2v));
       asm volatile("" : "+v"(y));
-      pb[i >> 3][2 + ((i & 7) >> 2)][i & 3] = y;
+      pb[2 + (i >> 2)][i & 3] = y;
     }
   };
   arg(0);
@@ -198,88 +182,77 @@ __device__ __forceinline__ void score_half(const uint4 (&k)[D / 16], const TileS
   expo(0);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int t = 0; t < NV; t++)
-#pragma unroll
-    for (int x = 0; x < 16; x++) sn[t][x] = 0.f;
+  for (int x = 0; x < 16; x++) sn[x] = 0.f;
   constexpr int PER = 8 / DS;  // slots per MFMA
 #pragma unroll
   for (int ds = 0; ds < DS; ds++) {
+    sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k[ds]), st.q[ds], sn, 0, 0, 0);
 #pragma unroll
-    for (int t = 0; t < NV; t++) {
-      sn[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k[ds]), st.q[t][ds], sn[t], 0, 0, 0);
-#pragma unroll
-      for (int q = 0; q < PER; q++) {
-        const int i = (ds * NV + t) * PER + q;
-        expo(i + 1);
-        pack(i);
-        arg(i + 2);
-      }
-      if (t == 0 && ds >= DS - DT) v[ds - (DS - DT)] = read_v<D>(vs, ds - (DS - DT), 0, l);
-      if (NREQ > 0 && t == NV - 1 && ds % (DS / (NREQ > 0 ? NREQ : 1)) == 0) req(ds / (DS / (NREQ > 0 ? NREQ : 1)));
-      __builtin_amdgcn_sched_barrier(0);
+    for (int q = 0; q < PER; q++) {
+      const int i = ds * PER + q;
+      expo(i + 1);
+      pack(i);
+      arg(i + 2);
     }
+    if (ds >= DS - DT) v[ds - (DS - DT)] = read_v<D>(vs, ds - (DS - DT), 0, l);
+    if (NREQ > 0 && ds % (DS / (NREQ > 0 ? NREQ : 1)) == 0) req(ds / (DS / (NREQ > 0 ? NREQ : 1)));
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
-template <int D, int NVM, int NV, bool PX, bool PREK>
-__device__ __forceinline__ void add_half(uint4 (&k)[D / 16], const uint4* kn, const uint4* vs, bf16x8 (&v)[D / 32], TileState<D, NVM>& st,
-                                         const uintx4 (&pb)[NV][PX ? 4 : 2], const floatx16 (&sn)[NV], float (&mx)[NV], const bf16x8& ones, int l) {
+template <int D, bool PX, bool PREK>
+__device__ __forceinline__ void add_half(uint4 (&k)[D / 16], const uint4* kn, const uint4* vs, bf16x8 (&v)[D / 32], TileState<D>& st,
+                                         const uintx4 (&pb)[PX ? 4 : 2], const floatx16& sn, float& mx, const bf16x8& ones, int l) {
   constexpr int DS = D / 16, DT = D / 32;
   // the maxima of the new scores, then across the lanes, a few beside every MFMA from the second on
-  float m[NV];
+  float m;
   auto maxima = [&](int i) {  // (constant index)
-    if (i < 0 || i >= 10 * NV) return;
-    const int mt = i / 10, mi = i % 10;
-    if (mi == 0) m[mt] = maxn(maxn(sn[mt][0], sn[mt][1]), sn[mt][2]);
-    else if (mi < 7) m[mt] = maxn(maxn(m[mt], sn[mt][2 * mi + 1]), sn[mt][2 * mi + 2]);
-    else if (mi == 7) m[mt] = maxn(m[mt], sn[mt][15]);
-    else if (mi == 8) mx[mt] = half_swap_max(m[mt]);
-    if (mi < 8) asm volatile("" : "+v"(m[mt]));
-    else asm volatile("" : "+v"(mx[mt]));
+    if (i < 0 || i >= 10) return;
+    if (i == 0) m = maxn(maxn(sn[0], sn[1]), sn[2]);
+    else if (i < 7) m = maxn(maxn(m, sn[2 * i + 1]), sn[2 * i + 2]);
+    else if (i == 7) m = maxn(m, sn[15]);
+    else if (i == 8) mx = half_swap_max(m);
+    if (i < 8) asm volatile("" : "+v"(m));
+    else asm volatile("" : "+v"(mx));
   };
-  constexpr int NPV = 2 * DT * NV;                        // PV MFMAs
-  constexpr int MPER = (10 * NV + NPV - 3) / (NPV - 2);   // maxima per MFMA
+  constexpr int NPV = 2 * DT;                        // PV MFMAs
+  constexpr int MPER = (10 + NPV - 3) / (NPV - 2);   // maxima per MFMA
 #pragma unroll
   for (int j = 0; j < 2; j++) {
 #pragma unroll
     for (int dt = 0; dt < DT; dt++) {
+      const int n = j * DT + dt;
+      st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[dt], __builtin_bit_cast(bf16x8, pb[j]), st.o[dt], 0, 0, 0);
+      if constexpr (PX) st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[dt], __builtin_bit_cast(bf16x8, pb[2 + j]), st.o[dt], 0, 0, 0);
+      // (the operand's registers take the next thing from LDS)
+      if (j == 0) v[dt] = read_v<D>(vs, dt, 1, l);
+      else if (PREK) {
 #pragma unroll
-      for (int t = 0; t < NV; t++) {
-        const int n = (j * DT + dt) * NV + t;
-        st.o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[dt], __builtin_bit_cast(bf16x8, pb[t][j]), st.o[t][dt], 0, 0, 0);
-        if constexpr (PX)
-          st.o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[dt], __builtin_bit_cast(bf16x8, pb[t][2 + j]), st.o[t][dt], 0, 0, 0);
-        if (t == NV - 1) {  // (the operand's registers take the next thing from LDS)
-          if (j == 0) v[dt] = read_v<D>(vs, dt, 1, l);
-          else if (PREK) {
-#pragma unroll
-            for (int q = 0; q < DS / DT; q++) k[dt * (DS / DT) + q] = read_k1<D>(kn, dt * (DS / DT) + q, l);
-          }
-        }
-        if (dt == DT - 1) {
-#pragma unroll
-          for (int x = j; x < (PX ? 4 : 2); x += 2)
-            st.lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, __builtin_bit_cast(bf16x8, pb[t][x]), st.lacc[t], 0, 0, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < MPER; q++) maxima((n - 1) * MPER + q);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int q = 0; q < DS / DT; q++) k[dt * (DS / DT) + q] = read_k1<D>(kn, dt * (DS / DT) + q, l);
       }
+      if (dt == DT - 1) {
+#pragma unroll
+        for (int x = j; x < (PX ? 4 : 2); x += 2)
+          st.lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, __builtin_bit_cast(bf16x8, pb[x]), st.lacc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < MPER; q++) maxima((n - 1) * MPER + q);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
 // The sweep of one workgroup whose tile has RW row groups, up to its output rows (a single split) or its partial
 // state.
-template <int D, bool PX, int NW, int NVM, int RW, bool TS>
+template <int D, bool PX, int RW, bool TS>
 __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& jb, TileLds& sh, uint4* ring,
                                            CB_LDS unsigned long long* ts) {
   using Part = PartialLayout<D, 32, PX>;
-  using F = Feed<D, NW, 32>;
-  constexpr int KW = NW / RW;            // key groups
+  using F = Feed<D, 8, 32>;
+  constexpr int KW = 8 / RW;             // key groups
   constexpr int NS = F::kSlots, PRO = F::kPrologue;
   constexpr int NPB = PX ? 4 : 2;        // B operands of a unit's probabilities
-  constexpr int LA = KW <= 2 ? 1 : 0;    // scores run one stage ahead of the softmax (needs two stages resident)
-  static_assert((LA + 2) * KW <= NS && KW <= PRO, "a stage is requested in full while the one before it is worked on");
+  // (scores run one stage ahead of the softmax: two stages are resident while a third is requested)
+  static_assert(3 * KW <= NS && KW <= PRO, "a stage is requested in full while the one before it is worked on");
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int rw = w % RW, kw = w / RW;
   const int r = l & 31, h = l >> 5;
@@ -290,32 +263,23 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
   F feed(p, jb, sh.bt, ring);
   // Everything the first stages need is requested up front, oldest first: the query rows (to registers), then K/V
   // units (to LDS).
-  TileState<D, NVM> st;
-  int row_node[NVM];    // tree node of the lane's query (indexes the ancestor sets)
-  int64_t grow[NVM];    // global output row (node * Hq + head), or -1 past the end
-  int nvt = 0;          // this wave's row tiles that hold at least one real row (they come first)
+  TileState<D> st;
+  int row = jb.row0 + rw * 32 + r;
+  const bool has_rows = row - r < jb.M, valid = row < jb.M;
+  row = valid ? row : jb.M - 1;
+  const int node = row / jb.g, hg = row - node * jb.g;  // tree node of the lane's query (indexes the ancestor sets)
+  const int64_t gr = (int64_t)(jb.off + node) * p.Hq + jb.hk * jb.g + hg;
+  const int64_t grow = valid ? gr : -1;                 // global output row (node * Hq + head), or -1 past the end
+  const CB_GLOBAL uintx4* qp = (const CB_GLOBAL uintx4*)(gq + gr * D);
 #pragma unroll
-  for (int t = 0; t < NVM; t++) {
-    const int rl = (rw * NVM + t) * 32 + r;
-    if (jb.row0 + rl - r < jb.M) nvt = t + 1;
-    int row = jb.row0 + rl;
-    const bool valid = row < jb.M;
-    row = valid ? row : jb.M - 1;
-    const int node = row / jb.g, hg = row - node * jb.g;
-    row_node[t] = node;
-    const int64_t gr = (int64_t)(jb.off + node) * p.Hq + jb.hk * jb.g + hg;
-    grow[t] = valid ? gr : -1;
-    const CB_GLOBAL uintx4* qp = (const CB_GLOBAL uintx4*)(gq + gr * D);
+  for (int ds = 0; ds < D / 16; ds++) st.q[ds] = __builtin_bit_cast(bf16x8, load_b128_untracked(qp + 2 * ds + h));
 #pragma unroll
-    for (int ds = 0; ds < D / 16; ds++) st.q[t][ds] = __builtin_bit_cast(bf16x8, load_b128_untracked(qp + 2 * ds + h));
+  for (int dt = 0; dt < D / 32; dt++)
 #pragma unroll
-    for (int dt = 0; dt < D / 32; dt++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) st.o[t][dt][v] = 0.f;
-    st.lacc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    st.mref[t] = -INFINITY;
-    st.nm[t] = 0.f;
-  }
+    for (int v = 0; v < 16; v++) st.o[dt][v] = 0.f;
+  st.lacc = floatx4{0.f, 0.f, 0.f, 0.f};
+  st.mref = -INFINITY;
+  st.nm = 0.f;
   const bool tree_split = k1 > S;  // this split reaches the tree nodes: masks needed
   // the tree itself: one parent entry per thread, requested before the K/V loads
   int my_parent = -1;
@@ -334,13 +298,11 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
   if (tree_split) build_ancestor_sets(sh.anc, jb.N, my_parent, jump_rounds(p.max_depth));  // uniform in the workgroup; hidden behind the first K/V wait
   feed.wait_units(KW);
 #pragma unroll
-  for (int t = 0; t < NVM; t++)
-#pragma unroll
-    for (int ds = 0; ds < D / 16; ds++) asm volatile("" : "+v"(st.q[t][ds]));  // (older than every unit)
+  for (int ds = 0; ds < D / 16; ds++) asm volatile("" : "+v"(st.q[ds]));  // (older than every unit)
   CB_TS(3);
 
   auto top = [&](int s) {  // top of stage s: whatever fits is requested while stage s's units are still wanted
-    const int want = (s + 1 + LA) * KW;
+    const int want = (s + 2) * KW;
     feed.wait_units(want < nu ? want : nu);
     const int room = s * KW + NS;
     feed.request_up_to(nu < room ? nu : room);
@@ -354,135 +316,109 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
   auto next_slot = [&](int x) { return x + KW >= NS ? x + KW - NS : x + KW; };
   const bf16x8 ones = half_ones(l);
 
-  auto sweep = [&](auto nvc) {
-    constexpr int NV = decltype(nvc)::value;
-    auto unit_scores = [&](int s, int slot, floatx16(&sc)[NV]) {
-      uint4 k[D / 16];
-      read_k<D, NV>(feed.k_at(slot), k, l);
-      scores<D, NVM, NV>(k, st, sc);
-      const int key0 = k0 + (s * KW + kw) * kUnitKeys;
-      if (key0 + kUnitKeys > S || key0 + kUnitKeys > k1) {
+  auto unit_scores = [&](int s, int slot, floatx16& sc) {
+    uint4 k[D / 16];
+    read_k<D>(feed.k_at(slot), k, l);
+    scores<D>(k, st, sc);
+    const int key0 = k0 + (s * KW + kw) * kUnitKeys;
+    if (key0 + kUnitKeys > S || key0 + kUnitKeys > k1) mask_scores(sc, key0, S, k1, &sh.anc.anc[node][0], h);
+  };
+  auto add_unit = [&](const bf16x8(&pb)[NPB], int slot) {
+    const uint4* vs = feed.v_at(slot);
 #pragma unroll
-        for (int t = 0; t < NV; t++) mask_scores(sc[t], key0, S, k1, &sh.anc.anc[row_node[t]][0], h);
+    for (int j = 0; j < NPB; j++) st.lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[j], st.lacc, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int dt = 0; dt < D / 32; dt++) {
+        const bf16x8 a = read_v<D>(vs, dt, j, l);
+#pragma unroll
+        for (int x = j; x < NPB; x += 2) st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[x], st.o[dt], 0, 0, 0);
       }
+  };
+  auto sweep = [&] {
+    floatx16 sc;
+    bf16x8 pb[NPB];
+    float mx;
+    auto check = [&] {
+      if (must_raise<D>(st, mx, c2)) raise_reference<D>(st, mx, c2);
     };
-    auto add_unit = [&](const bf16x8(&pb)[NV][NPB], int slot) {
-      const uint4* vs = feed.v_at(slot);
+    unit_scores(0, slot_cur, sc);
+    mx = row_max(sc);
+    check();
+    int s = 0;
+    const int fast_end = fast_stages();
+    floatx16 sd;
+    uint4 k[D / 16];
+    uintx4 pw[NPB];
+    bf16x8 v[D / 32];
+    if constexpr (KW == 1) {
+      // Two steps per barrier, K operands a step ahead in registers, the units' requests spread over the steps (all
+      // at once they hold up the wave that makes them).  At the barrier of the pair at s the units up to s + 3 have
+      // landed, and everybody is done with those below s.
+      const int whole_units = feed.even ? (k1 - k0) / kUnitKeys : 0;
+      feed.request_up_to(nu < NS - 2 ? nu : NS - 2);
+      if (s + 2 < fast_end) {
+        feed.wait_units(s + 4 < nu ? s + 4 : nu);
+        read_k<D>(feed.k_at(next_slot(slot_cur)), k, l);
+        bool rq = false;
+        auto score = [&](const floatx16& from, floatx16& to) {  // of unit s + 1; from: of unit s
+          if (p.kv.block_size > 0) feed.bt_ahead(feed.requested);
+          int64_t off[F::kParts];  // (worked out here: the paged form's branch would cut the instruction stream)
 #pragma unroll
-      for (int t = 0; t < NV; t++)
-#pragma unroll
-        for (int j = 0; j < NPB; j++) st.lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[t][j], st.lacc[t], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < 2; j++)
-#pragma unroll
-        for (int dt = 0; dt < D / 32; dt++) {
-          const bf16x8 a = read_v<D>(vs, dt, j, l);
-#pragma unroll
-          for (int t = 0; t < NV; t++)
-#pragma unroll
-            for (int x = j; x < NPB; x += 2)
-              st.o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[t][x], st.o[t][dt], 0, 0, 0);
-        }
-    };
-    floatx16 sc[NV];
-    float mx[NV];
-    bf16x8 pb[NV][NPB];
-    if constexpr (LA == 0) {
-      for (int s = 0; s < nst; s++) {
-        top(s);
-        unit_scores(s, slot_cur, sc);
-        row_max<NV>(sc, mx);
-        if (must_raise<NVM, NV>(st, mx, c2)) raise_reference<D, NVM, NV>(st, mx, c2);
-#pragma unroll
-        for (int t = 0; t < NV; t++) probs<D, NVM, NV, PX>(sc[t], st, t, c2, pb[t]);
-        add_unit(pb, slot_cur);
-        slot_cur = next_slot(slot_cur);
-      }
-    } else {
-      unit_scores(0, slot_cur, sc);
-      row_max<NV>(sc, mx);
-      if (must_raise<NVM, NV>(st, mx, c2)) raise_reference<D, NVM, NV>(st, mx, c2);
-      int s = 0;
-      const int fast_end = fast_stages();
-      floatx16 sd[NV];
-      uint4 k[D / 16];
-      uintx4 pw[NV][NPB];
-      bf16x8 v[D / 32];
-      auto check = [&] {
-        if (must_raise<NVM, NV>(st, mx, c2)) raise_reference<D, NVM, NV>(st, mx, c2);
-      };
-      if constexpr (KW == 1) {
-        // Two steps per barrier, K operands a step ahead in registers, the units' requests spread over the steps (all
-        // at once they hold up the wave that makes them).  At the barrier of the pair at s the units up to s + 3 have
-        // landed, and everybody is done with those below s.
-        const int whole_units = feed.even ? (k1 - k0) / kUnitKeys : 0;
-        feed.request_up_to(nu < NS - 2 ? nu : NS - 2);
-        if (s + 2 < fast_end) {
-          feed.wait_units(s + 4 < nu ? s + 4 : nu);
-          read_k<D, NV>(feed.k_at(next_slot(slot_cur)), k, l);
-          bool rq = false;
-          auto score = [&](const floatx16(&from)[NV], floatx16(&to)[NV]) {  // of unit s + 1; from: of unit s
-            if (p.kv.block_size > 0) feed.bt_ahead(feed.requested);
-            int64_t off[F::kParts];  // (worked out here: the paged form's branch would cut the instruction stream)
-#pragma unroll
-            for (int i = 0; i < F::kParts; i++) off[i] = feed.group_off(feed.requested, i);
-            score_half<D, NVM, NV, PX, F::kParts>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [&](int i) { feed.issue_group(feed.slot_next, i, off[i], rq); });
-            if (rq) feed.counted();
-          };
-          auto add = [&](const floatx16(&scored)[NV]) {  // unit s; scored: unit s + 1
-            const int nx = next_slot(slot_cur);
-            add_half<D, NVM, NV, PX, true>(k, feed.k_at(next_slot(nx)), feed.v_at(slot_cur), v, st, pw, scored, mx, ones, l);
-            check();
-            slot_cur = nx;
-            s++;
-          };
-          while (s + 2 < fast_end) {
-            // The pair at s requests two units: in its score halves if both are whole, else here.
-            feed.wait_units(s + 4 < nu ? s + 4 : nu);
-            rq = feed.requested + 2 <= whole_units && feed.requested + 1 < s + NS;
-            if (!rq) feed.request_up_to(nu < s + NS ? nu : s + NS);
-            score(sc, sd);
-            add(sd);
-            score(sd, sc);
-            add(sc);
-          }
-        }
-      } else {
-        auto step = [&](const floatx16(&from)[NV], floatx16(&to)[NV]) {
-          top(s);
+          for (int i = 0; i < F::kParts; i++) off[i] = feed.group_off(feed.requested, i);
+          score_half<D, PX, F::kParts>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [&](int i) { feed.issue_group(feed.slot_next, i, off[i], rq); });
+          if (rq) feed.counted();
+        };
+        auto add = [&](const floatx16& scored) {  // unit s; scored: unit s + 1
           const int nx = next_slot(slot_cur);
-          read_k<D, NV>(feed.k_at(nx), k, l);
-          score_half<D, NVM, NV, PX, 0>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [](int) {});
-          add_half<D, NVM, NV, PX, false>(k, nullptr, feed.v_at(slot_cur), v, st, pw, to, mx, ones, l);
+          add_half<D, PX, true>(k, feed.k_at(next_slot(nx)), feed.v_at(slot_cur), v, st, pw, scored, mx, ones, l);
           check();
           slot_cur = nx;
           s++;
         };
-        while (s + 2 < fast_end) {  // (two at a time: the scores alternate between two sets of registers)
-          step(sc, sd);
-          step(sd, sc);
+        while (s + 2 < fast_end) {
+          // The pair at s requests two units: in its score halves if both are whole, else here.
+          feed.wait_units(s + 4 < nu ? s + 4 : nu);
+          rq = feed.requested + 2 <= whole_units && feed.requested + 1 < s + NS;
+          if (!rq) feed.request_up_to(nu < s + NS ? nu : s + NS);
+          score(sc, sd);
+          add(sd);
+          score(sd, sc);
+          add(sc);
         }
       }
-      for (; s + 1 < nst; s++) {
+    } else {
+      auto step = [&](const floatx16& from, floatx16& to) {
         top(s);
-        floatx16 sn[NV];
-        unit_scores(s + 1, next_slot(slot_cur), sn);
-#pragma unroll
-        for (int t = 0; t < NV; t++) probs<D, NVM, NV, PX>(sc[t], st, t, c2, pb[t]);
-        add_unit(pb, slot_cur);
-        row_max<NV>(sn, mx);
-        if (must_raise<NVM, NV>(st, mx, c2)) raise_reference<D, NVM, NV>(st, mx, c2);
-#pragma unroll
-        for (int t = 0; t < NV; t++) sc[t] = sn[t];
-        slot_cur = next_slot(slot_cur);
+        const int nx = next_slot(slot_cur);
+        read_k<D>(feed.k_at(nx), k, l);
+        score_half<D, PX, 0>(k, st, from, to, pw, feed.v_at(slot_cur), v, c2, l, [](int) {});
+        add_half<D, PX, false>(k, nullptr, feed.v_at(slot_cur), v, st, pw, to, mx, ones, l);
+        check();
+        slot_cur = nx;
+        s++;
+      };
+      while (s + 2 < fast_end) {  // (two at a time: the scores alternate between two sets of registers)
+        step(sc, sd);
+        step(sd, sc);
       }
-#pragma unroll
-      for (int t = 0; t < NV; t++) probs<D, NVM, NV, PX>(sc[t], st, t, c2, pb[t]);
-      add_unit(pb, slot_cur);
     }
+    for (; s + 1 < nst; s++) {
+      top(s);
+      floatx16 sn;
+      unit_scores(s + 1, next_slot(slot_cur), sn);
+      probs<D, PX>(sc, st, c2, pb);
+      add_unit(pb, slot_cur);
+      mx = row_max(sn);
+      check();
+      sc = sn;
+      slot_cur = next_slot(slot_cur);
+    }
+    probs<D, PX>(sc, st, c2, pb);
+    add_unit(pb, slot_cur);
   };
-  if (nvt == NVM) sweep(std::integral_constant<int, NVM>{});
-  else if (NVM > 1 && nvt > 0) sweep(std::integral_constant<int, 1>{});
+  if (has_rows) sweep();
   else {  // no rows of its own: it only brings its share, passing the same barriers
     int s = 0;
     if constexpr (KW == 1) {
@@ -494,64 +430,52 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
         feed.request_up_to(nu < s + NS ? nu : s + NS);
       }
     }
-    for (; s + LA < nst; s++) top(s);
+    for (; s + 1 < nst; s++) top(s);
   }
   CB_TS(4);
 
-  // With several key groups each finishes its share of the pieces: all park their accumulators and (mref, l) in the
+  // With two key groups each finishes one half of the pieces: all park their accumulators and (mref, l) in the
   // ring, then each adds up the groups' for its own pieces.
   constexpr int P = Part::P, PP = P / KW;
-  floatx4 f[NVM][PP];
-  float lsum[NVM], mfin[NVM];
+  floatx4 f[PP];
+  float lsum, mfin;
+  auto piece = [&](int pc) {
+    return floatx4{st.o[pc >> 2][4 * (pc & 3)], st.o[pc >> 2][4 * (pc & 3) + 1], st.o[pc >> 2][4 * (pc & 3) + 2], st.o[pc >> 2][4 * (pc & 3) + 3]};
+  };
   if constexpr (KW > 1) {
     __syncthreads();  // every wave is done with the ring
     floatx4* const park = reinterpret_cast<floatx4*>(ring);
-    float2* const park_ml = reinterpret_cast<float2*>(ring + NW * NVM * P * 64);
-    static_assert(NW * NVM * P * 64 + NW * NVM * 32 <= F::kRingVecs, "");
+    float2* const park_ml = reinterpret_cast<float2*>(ring + 8 * P * 64);
+    static_assert(8 * P * 64 + 8 * 32 <= F::kRingVecs, "");
 #pragma unroll
-    for (int t = 0; t < NVM; t++) {
-      const int blk = (kw * RW + rw) * NVM + t;
-#pragma unroll
-      for (int pc = 0; pc < P; pc++)
-        park[(blk * P + pc) * 64 + l] = floatx4{st.o[t][pc >> 2][4 * (pc & 3)], st.o[t][pc >> 2][4 * (pc & 3) + 1],
-                                                st.o[t][pc >> 2][4 * (pc & 3) + 2], st.o[t][pc >> 2][4 * (pc & 3) + 3]};
-      park_ml[blk * 64 + l] = float2{st.mref[t], st.lacc[t][0]};
-    }
+    for (int pc = 0; pc < P; pc++) park[(w * P + pc) * 64 + l] = piece(pc);  // (w = kw * RW + rw)
+    park_ml[w * 64 + l] = float2{st.mref, st.lacc[0]};
     __syncthreads();
+    float2 ml[KW];
+    mfin = -INFINITY;
 #pragma unroll
-    for (int t = 0; t < NVM; t++) {
-      float2 ml[KW];
-      float m = -INFINITY;
+    for (int k = 0; k < KW; k++) {
+      ml[k] = park_ml[(k * RW + rw) * 64 + l];
+      mfin = fmaxf(mfin, ml[k].x);
+    }
+    const float mu = (mfin == -INFINITY) ? 0.f : mfin;
+    lsum = 0.f;
 #pragma unroll
-      for (int k = 0; k < KW; k++) {
-        ml[k] = park_ml[((k * RW + rw) * NVM + t) * 64 + l];
-        m = fmaxf(m, ml[k].x);
-      }
-      const float mu = (m == -INFINITY) ? 0.f : m;
-      lsum[t] = 0.f;
-      mfin[t] = m;
+    for (int i = 0; i < PP; i++) f[i] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < PP; i++) f[t][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < KW; k++) {
+      const float wt = __builtin_amdgcn_exp2f((ml[k].x - mu) * c2);
+      lsum += ml[k].y * wt;
 #pragma unroll
-      for (int k = 0; k < KW; k++) {
-        const float wt = __builtin_amdgcn_exp2f((ml[k].x - mu) * c2);
-        lsum[t] += ml[k].y * wt;
-#pragma unroll
-        for (int i = 0; i < PP; i++) f[t][i] += park[((((k * RW + rw) * NVM + t) * P) + kw * PP + i) * 64 + l] * wt;
-      }
+      for (int i = 0; i < PP; i++) f[i] += park[((k * RW + rw) * P + kw * PP + i) * 64 + l] * wt;
     }
   } else {
+    lsum = st.lacc[0];
+    mfin = st.mref;
 #pragma unroll
-    for (int t = 0; t < NVM; t++) {
-      lsum[t] = st.lacc[t][0];
-      mfin[t] = st.mref[t];
-#pragma unroll
-      for (int i = 0; i < PP; i++)
-        f[t][i] = floatx4{st.o[t][i >> 2][4 * (i & 3)], st.o[t][i >> 2][4 * (i & 3) + 1], st.o[t][i >> 2][4 * (i & 3) + 2], st.o[t][i >> 2][4 * (i & 3) + 3]};
-    }
+    for (int i = 0; i < PP; i++) f[i] = piece(i);
   }
-#pragma unroll
-  for (int t = 0; t < NVM; t++) write_rows<D, 32, PX, PP>(p, jb, rw * NVM + t, grow[t], f[t], kw * PP, mfin[t], lsum[t], c2, kw == 0, l);
+  write_rows<D, 32, PX, PP>(p, jb, rw, grow, f, kw * PP, mfin, lsum, c2, kw == 0, l);
 #undef CB_TS
 }
 
@@ -565,8 +489,8 @@ __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const Se
   first_stamps<TS>(ts, ts0);
   TileJob jb;
   if (!tile_job(p, ml, wg, 256, jb)) return;
-  if (jb.M - jb.row0 <= 128) sweep_tile<D, PX, 8, 1, 4, TS>(p, jb, sh, ring, ts);
-  else sweep_tile<D, PX, 8, 1, 8, TS>(p, jb, sh, ring, ts);
+  if (jb.M - jb.row0 <= 128) sweep_tile<D, PX, 4, TS>(p, jb, sh, ring, ts);
+  else sweep_tile<D, PX, 8, TS>(p, jb, sh, ring, ts);
   if (jb.nsplit == 1 || p.external_merge) return;  // (a following kernel merges: the kernel boundary orders the stores)
   split_merge<D, 32, PX, 8, 256, TS>(p, jb, sh, ts);
 }
