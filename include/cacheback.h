@@ -108,8 +108,10 @@ int cb_init(const cb_config *cfg, void *workspace, size_t workspace_bytes, cb_ct
  * (a multiple of 32; splits x keys covers the longest sequence, shorter sequences use fewer splits),
  * plan[3] = output rows per tile and plan[4] = (tile, split) pairs that have keys to sweep: the workgroups
  * launched in family 2; family 1 is counted in single rows, of which a workgroup takes up to 16.  forced_splits > 0 overrides the planner's split count (capped at the
- * configuration's max_splits), like the "splits" option.  All arrays are host memory.  CB_EINVAL on
- * a bad configuration or shape. */
+ * configuration's max_splits), like the "splits" option.  The plan is that of the attention on its own
+ * (cb_tree_attention_device, _noalloc): a verification whose logits work is done by workgroups of the same
+ * launch plans its attention for the compute units these leave, often with a split fewer, and
+ * cb_last_launch_info reports it.  All arrays are host memory.  CB_EINVAL on a bad configuration or shape. */
 int cb_plan_attention(const cb_config *cfg, int32_t batch, const int32_t *kv_len,
                       const int32_t *node_offsets, int32_t forced_splits, int32_t plan[5]);
 

@@ -249,14 +249,14 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     const int64_t want = 2048;
     nsplit = (int)std::max<int64_t>(1, std::min<int64_t>((want + rows - 1) / rows, p.max_len / 1024));
   } else {
-    // one workgroup per (row tile of 64, 128 or 256 rows, kv head, split)
+    // one workgroup per (row tile of 64 or 256 rows, kv head, split)
     const int g = c.num_q_heads / c.num_kv_heads;
     const int mrows = p.max_nodes * g;
     const int rows_per_wg = attn_mfma_tile_rows(mrows);
     // Every variant runs 8 waves and a 128 KiB ring: one workgroup per compute unit, so the grid
-    // should come out just under a whole number of rounds of 256 workgroups.  Take the fewest
-    // splits that fill >= 85% of the machine in whole rounds (fewer splits = fewer partials).
-    // efficiency of ns splits: keys swept / (256 units x whole rounds x keys of a full split)
+    // should come out just under a whole number of rounds of `units` workgroups.  Take the fewest
+    // splits that fill >= 85% of them in whole rounds (fewer splits = fewer partials).
+    // efficiency of ns splits: keys swept / (units x whole rounds x keys of a full split)
     auto workgroups = [&](int ns) {
       const int chunk = ((p.max_len + ns - 1) / ns + 31) / 32 * 32;
       int64_t t = 0;

@@ -352,7 +352,7 @@ struct Feed {
   // (masked later), so every address stays inside the split's own range.
   // Small tiles take the uniform form: 58 against 62 us at 32 heads x 16384 keys.  In the wide kernel the lanes' own
   // addresses are faster: 16 sequences of up to 16384 keys in blocks of 16 (32 heads) 421 -> 402 us, with 32-bit sums
-  // 710 -> 638; 32/8 heads x 8192 keys x 128 nodes 34 -> 30; 40 heads x 65536 keys x 256 nodes 401 -> 390.
+  // 710 -> 638; 40 heads x 65536 keys x 256 nodes 401 -> 394; 32/8 heads x 8192 keys x 128 nodes no different.
   __device__ __forceinline__ void issue(int u, int slot) const {
     const bool whole = jb.k0 + (u + 1) * kUnitKeys <= jb.k1;
     const int lr = l / VPR, lc = l % VPR;

@@ -22,6 +22,18 @@ def test_table_slices_beyond_the_lds_ring(block, S, splits, n, monkeypatch):
     run_case(case, rows=ver_rows, options={"splits": splits, "attn_impl": 2}, what=f"block {block} S={S}")
 
 
+# The same at head_dim 64, whose 16 units in flight are 512 one-token entries -- two whole segments, as many as a refill may run
+# ahead -- and with blocks shorter than a request's rows (8 at head_dim 64, 4 at 128), where every lane has an address of its own.
+@pytest.mark.parametrize("D,block,S,splits", [(64, 1, 960, 1), (64, 1, 3300, 1), (64, 4, 9000, 1), (64, 16, 33000, 2), (128, 2, 5000, 1)])
+@pytest.mark.parametrize("n", [33, 150])
+def test_table_slices_beyond_the_lds_ring_per_lane_addresses(D, block, S, splits, n, monkeypatch):
+    monkeypatch.setattr(W, "BLOCK_TOKENS", block)
+    par = W.random_tree(np.random.default_rng(S), n, 4, 7, False)[0]
+    case = W.custom_case(4250 + S, "bf16", 1, 2, 2, D, 500, [S], [par], paged=True, q_scale=2.0)
+    case.block_size = block
+    run_case(case, rows=sample_rows(case, 60), options={"splits": splits, "attn_impl": 2}, what=f"D={D} block {block} S={S}")
+
+
 # blocks that are no power of two: the scalar kernel, with the split count cut to what its partial states have room for
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("S,splits", [(40, 0), (3000, 40), (6000, 0)])

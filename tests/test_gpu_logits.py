@@ -52,3 +52,14 @@ def test_scan_with_short_chunks(N, V, dtype):
         x[i, [min(a, V - 1), min(a + 1, V - 1), int(rng.integers(V))]] = 5.0
     case.logits = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
     run_case(case, rows=sample_rows(case, 8), options={"fuse_logits": 0}, what=f"N={N} V={V} {dtype}")
+
+
+# workgroups of the one-launch verification that do the logits work: the fewest, more than there are items for, the most; in one
+# round of attention workgroups and in several, and beside the fp32 kernel
+@pytest.mark.parametrize("wgs", [8, 40, 192])
+@pytest.mark.parametrize("dtype,heads,lens", [("bf16", 4, [700, 90]), ("bf16", 32, [300] * 12), ("f32", 4, [200, 33])])
+def test_any_number_of_logits_workgroups(wgs, dtype, heads, lens):
+    rng = np.random.default_rng(wgs)
+    pars = [W.random_tree(rng, 20 + 3 * i, 4, 6, False)[0] for i in range(len(lens))]
+    case = W.custom_case(600 + wgs + heads, dtype, len(lens), heads, heads, 128, 9001, lens, pars, p_match=0.8)
+    run_case(case, rows=sample_rows(case, 60), options={"logits_wgs": wgs}, what=f"{wgs} workgroups {dtype} {heads} heads")

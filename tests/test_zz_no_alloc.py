@@ -45,8 +45,8 @@ def test_no_alloc_entry_point_two_calls_in_a_row():
     small = W.custom_case(771, "bf16", 2, 8, 4, 128, 100, [700, 33], [W.random_tree(rng, 40, 3, 6, False)[0], W.chain_tree(9)], paged=True)
     print("[case] no-alloc: smaller paged batch right behind it", flush=True)
     _both(small)
-    tiny = W.make_config(1)                                 # fp32: scalar kernels, ancestor sets from the scratch array
-    print("[case] no-alloc: tiny fp32 (scalar kernels)", flush=True)
+    tiny = W.make_config(1)                                 # fp32: its own matrix-core kernel
+    print("[case] no-alloc: tiny fp32", flush=True)
     _both(tiny)
 
 
