@@ -310,7 +310,8 @@ def main():
     # (k_verify_mfma): its algorithmic bytes are the attention's plus the logits'.  Otherwise it is
     # the attention kernel (with its split merge).
     if info["fused"]:
-        roof_kernel = "cb::k_verify_mfma (tree attention incl. split merge + logits argmax + acceptance, one launch)"
+        kind = "wide" if (case.node_offsets[1:] - case.node_offsets[:-1]).max() * (case.Hq // case.Hkv) > 64 else "mfma"
+        roof_kernel = f"cb::k_verify_{kind} (tree attention incl. split merge + logits argmax + acceptance, one launch)"
         roof_bytes, roof_us = attn_bytes + case.logits_bytes(), verify_us
     else:
         roof_kernel = "cb::k_attn_mfma (tree attention incl. split merge)" if info["impl"] == 2 else "cb::k_attn_f32 (tree attention incl. split merge)"

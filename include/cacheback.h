@@ -234,8 +234,9 @@ int cb_device_status(cb_ctx *ctx, int32_t *status);
  *                step left out the results of the call are those of an earlier call or undefined
  *   "parallel_scan"  1 = run the logits scan on the context's second stream beside the attention
  *   "fuse_logits"    0 = never run the logits scan and the acceptance inside the attention launch
- *                    (default 1: calls in fp32, and in bf16 those whose sequences have at most 64/g nodes, are
- *                    one launch: some of its workgroups do the logits work, the others the attention)
+ *                    (default 1: calls in fp32, and in bf16 those whose sequences have at most 64/g nodes or
+ *                    whose logits are at most half the bytes of their K/V, are one launch: some of its
+ *                    workgroups do the logits work, the others the attention)
  *   "logits_wgs"     workgroups of that launch for the logits work (a multiple of 8 up to 192;
  *                    0 = automatic)
  *   "coop_merge"     0 = never merge the splits cooperatively (default 1: a grid that fits the

@@ -223,6 +223,26 @@ int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const
   return std::max(8, std::min(share, most) / 8 * 8);
 }
 
+// The same for calls with wide tiles, whose sweep is bound by the chain of its arithmetic: the fewest workgroups (in XCD
+// rounds) that are through with the logits, at 50 GB/s each, in 0.7 of the time the attention takes (more of them, up to
+// 64, change little: 16 sequences of up to 16384 keys 629 us with 8, 620 with 32, 633 with 64).  0: a launch of their own,
+// where the logits are more than half of what the sweep reads and would not hide behind it.  A pass of 128 nodes x 8192 keys
+// of 32/8 heads with 32000-entry rows as two launches and as one 37.7 -> 31.8 us, 256 nodes x 65536 keys of 40 heads with
+// 128256-entry rows 418 -> 406 us.
+int fused_wide_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const int32_t* node_offsets) {
+  const double lb = c.logits_dtype == CB_F32 ? 4 : 2;
+  double slots = 0, flops = 0;
+  for (int b = 0; b < batch; b++) {
+    const double n = node_offsets[b + 1] - node_offsets[b], len = kv_len[b] + n;
+    slots += len;
+    flops += 4.0 * n * c.num_q_heads * len * c.head_dim;
+  }
+  const double kv = slots * c.num_kv_heads * c.head_dim * 4, lg = (double)node_offsets[batch] * c.vocab_size * lb;
+  if (2 * lg > kv) return 0;
+  const double us = std::max(kv / 5e6, flops / 0.85e9) + 8.0;
+  return std::min(64, ((int)(lg / (50e3 * 0.7 * us)) / 8 + 1) * 8);
+}
+
 // Pure host arithmetic: no device call, no context state beyond the numbers passed in.  `units`: compute units that
 // the attention's workgroups can count on.
 Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int batch,
@@ -450,14 +470,20 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     CB_HIP(ctx, launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.amax_best), ctx->lay.max_total_nodes, kAmaxStride, 1));
     ctx->amax_dirty = false;
   }
-  // A verification in fp32, or whose tiles are small enough, is one launch: its first workgroups do the logits work, and the
+  // A verification in fp32, or with small tiles, or whose logits hide behind the sweep, is one launch: its first workgroups do the logits work, and the
   // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
   // option does not change the splits and with them the rounding).
   int max_nodes = 0;
   for (int b = 0; b < batch; b++) max_nodes = std::max(max_nodes, node_offsets[b + 1] - node_offsets[b]);
   const bool small_tiles = attn_mfma_tile_rows(max_nodes * (c.num_q_heads / c.num_kv_heads)) == 64;
   const bool f32_tiles = c.qkv_dtype == CB_F32 && ctx->opt_impl != 1;
-  int n_logits = (stage_mask & 8) && (small_tiles || f32_tiles) ? fused_logits_wgs(c, batch, kv_len, node_offsets) : 0;
+  int n_logits = 0;
+  if (!(stage_mask & 8)) {
+  } else if (small_tiles || f32_tiles) {
+    n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
+  } else if (c.qkv_dtype == CB_BF16) {
+    n_logits = fused_wide_logits_wgs(c, batch, kv_len, node_offsets);
+  }
   if (n_logits && ctx->opt_logits_wgs > 0) n_logits = (int)ctx->opt_logits_wgs;
   const Plan plan = ctx->fixed_plan ? *ctx->fixed_plan
                                     : plan_attention(c, ctx->lay.max_splits, ctx->lay.scalar_splits, ctx->opt_impl, ctx->opt_splits, batch, kv_len, node_offsets, 256 - n_logits);
@@ -523,7 +549,7 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   ctx->want_done = nullptr;
   // Otherwise, and with option "fuse_logits" = 0, the logits work is a launch of its own in front.
   const bool fused = ctx->opt_fuse != 0 && (stages & 2) && (stages & 4) && (stages & 8) &&
-                     (f32_tiles || (use_mfma && small_tiles && attn_mfma_can_fuse(ap, plan.max_nodes)));
+                     (f32_tiles || use_mfma) && n_logits > 0;
   const bool fork = !fused && ctx->opt_fork != 0 && (use_mfma || f32_tiles) && (stages & 2) && (stages & 4);
   hipStream_t scan_stream = st;
   int merge_kind = plan.nsplit > 1 ? 3 : 0, kernels = 0;  // (the scalar attention always merges with a kernel of its own)

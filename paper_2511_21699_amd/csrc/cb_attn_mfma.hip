@@ -333,11 +333,6 @@ bool attn_mfma_supports(const AttnParams& p) {
 // 58).
 int attn_mfma_tile_rows(int mrows) { return mrows <= kSmallRows ? kSmallRows : 256; }
 
-// Whether the launch for this call also carries the logits work (k_verify_mfma).
-bool attn_mfma_can_fuse(const AttnParams& p, int max_nodes_in_call) {
-  return attn_mfma_supports(p) && attn_mfma_tile_rows(max_nodes_in_call * (p.Hq / p.Hkv)) == kSmallRows;
-}
-
 hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call,
                             int total_nodes, const LogitsWork* logits_work, int* merge_kind) {
   if (!attn_mfma_supports(p)) return hipErrorInvalidValue;
@@ -378,19 +373,18 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   const bool ts = p.timeline != 0;  // (the timeline build of the same kernels: a measurement aid)
   hipError_t e;
   auto launch = [&](auto* stamped, auto* plain, auto... args) { hipLaunchKernelGGL(ts ? stamped : plain, grid, dim3(512), 0, st, args...); };
-  if (logits_work) {
-    if (!attn_mfma_can_fuse(p, max_nodes_in_call)) return hipErrorInvalidValue;
+  if (rt_rows != kSmallRows) {
+    e = launch_attn_wide(st, q, meta, (int)T, logits_work);
+  } else if (logits_work) {
     if (p.D == 64) launch(k_verify_mfma<64, true>, k_verify_mfma<64, false>, q, meta, *logits_work);
     else if (p.precise) launch(k_verify_precise<true>, k_verify_precise<false>, q, meta, *logits_work);
     else launch(k_verify_mfma<128, true>, k_verify_mfma<128, false>, q, meta, *logits_work);
     e = hipGetLastError();
-  } else if (rt_rows == kSmallRows) {
+  } else {
     if (p.D == 64) launch(k_attn_mfma<64, true>, k_attn_mfma<64, false>, q, meta);
     else if (p.precise) launch(k_attn_precise<true>, k_attn_precise<false>, q, meta);
     else launch(k_attn_mfma<128, true>, k_attn_mfma<128, false>, q, meta);
     e = hipGetLastError();
-  } else {
-    e = launch_attn_wide(st, q, meta, (int)T);
   }
   if (e != hipSuccess) return e;
   if (q.external_merge) {

@@ -506,12 +506,33 @@ __global__ __launch_bounds__(512) void k_attn_wide(AttnParams p, SeqMeta meta) {
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
-hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles) {
-  const dim3 grid(n_tiles), block(512);
-#define CB_LAUNCH(D, PX)                                                                              \
-  do {                                                                                                \
-    if (p.timeline) hipLaunchKernelGGL((k_attn_wide<D, PX, true>), grid, block, 0, st, p, meta);      \
-    else hipLaunchKernelGGL((k_attn_wide<D, PX, false>), grid, block, 0, st, p, meta);                \
+// The whole verification in one launch, as k_verify_mfma does it for small tiles: the first lw.n_wgs workgroups do the
+// logits work, the others the attention.
+template <int D, bool PX, bool TS>
+__global__ __launch_bounds__(512) void k_verify_wide(AttnParams p, SeqMeta meta, LogitsWork lw) {
+  const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
+  const SeqMetaLanes ml = seq_meta_prefetch(meta);
+  __shared__ uint4 ring[Feed<D, 8, 32>::kRingVecs];
+  __shared__ TileLds sh;
+  __shared__ unsigned long long ts_sh[TS ? 16 : 1];
+  static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
+  const int wg = (int)blockIdx.x - lw.n_wgs;
+  if (wg < 0) {
+    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
+    return;
+  }
+  attn_wide_tile<D, PX, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
+  flush_timestamps<TS>(p, wg, ts_sh);
+}
+
+hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles, const LogitsWork* lw) {
+  const dim3 grid(n_tiles + (lw ? lw->n_wgs : 0)), block(512);
+#define CB_LAUNCH(D, PX)                                                                                        \
+  do {                                                                                                          \
+    if (lw && p.timeline) hipLaunchKernelGGL((k_verify_wide<D, PX, true>), grid, block, 0, st, p, meta, *lw);   \
+    else if (lw) hipLaunchKernelGGL((k_verify_wide<D, PX, false>), grid, block, 0, st, p, meta, *lw);           \
+    else if (p.timeline) hipLaunchKernelGGL((k_attn_wide<D, PX, true>), grid, block, 0, st, p, meta);           \
+    else hipLaunchKernelGGL((k_attn_wide<D, PX, false>), grid, block, 0, st, p, meta);                          \
   } while (0)
   if (p.D == 64) CB_LAUNCH(64, true);
   else if (p.precise) CB_LAUNCH(128, true);

@@ -209,10 +209,9 @@ int attn_mfma_tile_rows(int mrows);            // rows per workgroup tile chosen
 // padded to 16-row tiles per kv head where one small tile holds them, else to 32-row ones)
 size_t attn_mfma_partial_bytes(int D, bool precise, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
 bool attn_mfma_supports(const AttnParams& p);  // shape/geometry the MFMA kernel takes (bf16 is the caller's check)
-bool attn_mfma_can_fuse(const AttnParams& p, int max_nodes_in_call);
-// with logits_work != nullptr (only if attn_mfma_can_fuse) the same launch also scans the logits and runs the acceptance
+// with logits_work != nullptr the same launch also scans the logits and runs the acceptance
 // merge_kind (may be null): 0 one split, 1 cooperative merge, 2 merge by the last workgroup to arrive, 3 merge kernel
-hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles);  // (by launch_attn_mfma)
+hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles, const LogitsWork* lw);  // (by launch_attn_mfma)
 hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call,
                             int total_nodes, const LogitsWork* logits_work, int* merge_kind);
 
