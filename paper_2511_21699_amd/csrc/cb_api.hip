@@ -224,7 +224,7 @@ int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const
 }
 
 // The same for calls with wide tiles, whose sweep is bound by the chain of its arithmetic: the fewest workgroups (in XCD
-// rounds) that are through with the logits, at 50 GB/s each, in 0.7 of the time the attention takes (more of them, up to
+// rounds) that are through with the logits, at 25 GB/s each, in 0.7 of the time the attention takes (more of them, up to
 // 64, change little: 16 sequences of up to 16384 keys 629 us with 8, 620 with 32, 633 with 64).  0: a launch of their own,
 // where the logits are more than half of what the sweep reads and would not hide behind it.  A pass of 128 nodes x 8192 keys
 // of 32/8 heads with 32000-entry rows as two launches and as one 37.7 -> 31.8 us, 256 nodes x 65536 keys of 40 heads with
@@ -240,7 +240,7 @@ int fused_wide_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, 
   const double kv = slots * c.num_kv_heads * c.head_dim * 4, lg = (double)node_offsets[batch] * c.vocab_size * lb;
   if (2 * lg > kv) return 0;
   const double us = std::max(kv / 5e6, flops / 0.85e9) + 8.0;
-  return std::min(64, ((int)(lg / (50e3 * 0.7 * us)) / 8 + 1) * 8);
+  return std::min(64, ((int)(lg / (25e3 * 0.7 * us)) / 8 + 1) * 8);
 }
 
 // Pure host arithmetic: no device call, no context state beyond the numbers passed in.  `units`: compute units that

@@ -55,10 +55,10 @@ __device__ __forceinline__ uintx4 load_b128_untracked(const CB_GLOBAL void* p) {
   return r;
 }
 
-__device__ __forceinline__ uint16_t f2bf(float x) {
-  uint32_t u = __float_as_uint(x);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {  // rounded to nearest even (v_cvt_pk_bf16_f32)
+  typedef float float2v __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){lo, hi}, bf16x2v));
 }
 
 struct KeyAddr {  // resolves cache slots of one (sequence, kv head) to byte offsets
@@ -91,6 +91,14 @@ __device__ __forceinline__ void ring_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// the same without a wait for the wave's own LDS reads, where those that are still under way read nothing that is about to be
+// overwritten
+__device__ __forceinline__ void bare_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // One LDS-DMA request: every lane's 16 bytes at `src` go to LDS at dst + lane * 16 (dst is the same
 // in all lanes of the wave).  Written as an instruction the compiler does not interpret: for the
 // builtin it keeps its own account of which request has landed, cannot relate the ring's counted
@@ -118,6 +126,11 @@ __device__ __forceinline__ void lds_dma_b128(const CB_GLOBAL char* base, uint32_
                ::"v"(off), "s"(b64), "s"(lds), "s"(mask) : "memory");
 }
 
+// and with the address in LDS as a number, uniform
+__device__ __forceinline__ void lds_dma_b128_at(const CB_GLOBAL char* src, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds) : "memory");
+}
+
 __device__ __forceinline__ void lds_dma_b32(const CB_GLOBAL int32_t* src, CB_LDS int* dst) {  // (dst + lane * 4)
   const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(base) : "memory");
@@ -143,8 +156,10 @@ constexpr int kUnitKeys = 32;  // keys per unit: what one wave works on at a tim
 // Partial softmax state, one block per (TR-row tile, split), laid out in the order the MFMA accumulators hold it (TR = 32
 // or 16, the query columns of an accumulator tile).  Piece pc of the tile holds DP = 256 / TR dims from DP pc: lane (h, r),
 // r = lane % TR, has o[row r][DP pc + 4 h + {0..3}], unnormalised, relative to the reference weight, as bf16 (8 bytes) or,
-// PX, as fp32 (16 bytes), the lanes' pieces next to each other, so that a wave's store or load of a piece is 512 or 1024
-// contiguous bytes; then (m, l) as fp32 for each of the rows.
+// PX, as fp32 (16 bytes).  A lane's pieces are stored in vectors of 16 bytes (one piece, or two as bf16), the lanes'
+// vectors next to each other, so that a wave's store or load is 1024 contiguous bytes; then (m, l) as fp32 for each
+// of the rows.  (With 8 bytes per lane, and rounded by integer
+// instructions, the tail of a 256-row tile's workgroup from its sweep to its merge was 8.5 us at 15 splits, and is 7.0.)
 // The blocks of sequence b start at tile block_tile0(b); kv head hk's row tile ti is block
 // (hk * ceil(M_b / TR) + ti) * nsplit + split behind it.
 //
@@ -155,9 +170,9 @@ template <int D, int TR, bool PX>
 struct PartialLayout {
   static constexpr int DP = 256 / TR;
   static constexpr int P = D / DP;  // pieces per tile
-  static constexpr int kLane = PX ? 16 : 8;  // bytes of a lane's piece
-  static constexpr int kPiece = 64 * kLane;
-  static constexpr int kMl = P * kPiece;
+  static constexpr int kPer = PX ? 1 : 2;    // pieces to a vector
+  static constexpr int kVec = 64 * 16;       // bytes of the lanes' vectors
+  static constexpr int kMl = P / kPer * kVec;
   static constexpr int kBytes = kMl + TR * 8;
 };
 // first tile of a sequence whose nodes start at `off`: room for ceil(M_b / TR) tiles per kv
@@ -281,6 +296,7 @@ struct Feed {
   static constexpr int kPrologue = D == 128 ? 6 : 10;           // units requested before the first wait
   static constexpr int kReq = 2 * kVecs / 64 / NW;              // requests per wave and unit
   static constexpr int kRingVecs = kSlots * 2 * kVecs;
+  static constexpr uint32_t kSlotBytes = 2 * kVecs * 16;
   static constexpr int VPR = D / 8;                             // 16-byte pieces per row
   static constexpr int RPR = 64 / VPR;                          // rows per request
   static constexpr int kParts = kReq >= 2 ? kReq / 2 : 1;       // groups of RPR rows per wave and unit
@@ -350,15 +366,13 @@ struct Feed {
   // blocks hold whole groups; then a request can be a uniform base and a lane offset that never changes.  Otherwise, and in
   // the unit that runs past the split's end, every lane works out its own row; keys past the end repeat the last one
   // (masked later), so every address stays inside the split's own range.
-  // Small tiles take the uniform form: 58 against 62 us at 32 heads x 16384 keys.  In the wide kernel the lanes' own
-  // addresses are faster: 16 sequences of up to 16384 keys in blocks of 16 (32 heads) 421 -> 402 us, with 32-bit sums
-  // 710 -> 638; 40 heads x 65536 keys x 256 nodes 401 -> 394; 32/8 heads x 8192 keys x 128 nodes no different.
+  // The uniform form is the faster one: 58 against 62 us at 32 heads x 16384 keys.  (The wide kernel has requests of its own.)
   __device__ __forceinline__ void issue(int u, int slot) const {
     const bool whole = jb.k0 + (u + 1) * kUnitKeys <= jb.k1;
     const int lr = l / VPR, lc = l % VPR;
 #pragma unroll
     for (int i = 0; i < kParts; i++) {
-      if (TR == 16 && even && whole) {
+      if (even && whole) {
         issue_group(slot, i, group_off(u, i), true);
       } else {
         const int rr = part_row(i) + lr;
@@ -412,6 +426,36 @@ struct Feed {
   }
 };
 
+// A lane's output row: NP pieces from pc0 (both even), scaled.  With 32-row tiles two lanes of a row exchange halves
+// first, so that a lane has 8 dims in a row and stores 16 bytes.
+template <int D, int TR, int NP>
+__device__ __forceinline__ void store_row(CB_GLOBAL uint16_t* gout, int64_t grow, const floatx4 (&f)[NP], int pc0, float inv, int l) {
+  constexpr int DP = 256 / TR;
+  const int h = l / TR;
+  uintx2 pk[NP];
+#pragma unroll
+  for (int n = 0; n < NP; n++) {
+    pk[n][0] = pack_bf16(f[n][0] * inv, f[n][1] * inv);
+    pk[n][1] = pack_bf16(f[n][2] * inv, f[n][3] * inv);
+  }
+  CB_GLOBAL uint16_t* orow = gout + grow * D;
+  if constexpr (TR == 32) {
+    static_assert(NP % 2 == 0, "");
+#pragma unroll
+    for (int n = 0; n < NP; n += 2) {
+      // (swaps the first operand's upper 32 lanes with the second's lower ones)
+      const auto a = __builtin_amdgcn_permlane32_swap(pk[n][0], pk[n + 1][0], false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(pk[n][1], pk[n + 1][1], false, false);
+      const uintx4 v = {a[0], b[0], a[1], b[1]};
+      if (grow >= 0) *(CB_GLOBAL uintx4*)(orow + DP * (pc0 + n) + 8 * h) = v;
+    }
+  } else {
+    if (grow < 0) return;
+#pragma unroll
+    for (int n = 0; n < NP; n++) *(CB_GLOBAL uintx2*)(orow + DP * (pc0 + n) + 4 * h) = pk[n];
+  }
+}
+
 // Merge of NP pieces (from pc0) of one TR-row tile's partials by one wave: every lane merges the elements that the
 // layout gives it, so each load of the wave is contiguous (`byte`: offset of slot 0's block).  Slots are
 // combined online, BS per batch with all of a batch's loads in flight together: m = max m_t, w_t = 2^(m_t - m),
@@ -422,25 +466,25 @@ template <int D, int TR, bool PX, int NP, int POL, int BS>
 __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64_t grow, uint32_t byte, CB_GLOBAL uint16_t* gout,
                                              int nslots, int pc0, int l) {
   using Part = PartialLayout<D, TR, PX>;
-  const int h = l / TR, r = l % TR;
+  constexpr int NV = NP / Part::kPer;  // vectors
+  static_assert(NP % Part::kPer == 0, "");
+  const int r = l % TR;
   floatx4 acc[NP];
 #pragma unroll
   for (int i = 0; i < NP; i++) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   float lsum = 0.f, m_run = -3.0e38f;
   // (the slot's offset is the same in all lanes: it travels as the load's scalar offset, so a
   // load costs no vector arithmetic)
-  const uint32_t vo_ml = byte + Part::kMl + r * 8, vo_v = byte + pc0 * Part::kPiece + l * Part::kLane;
+  const uint32_t vo_ml = byte + Part::kMl + r * 8, vo_v = byte + pc0 / Part::kPer * Part::kVec + l * 16;
   for (int t0 = 0; t0 < nslots; t0 += BS) {
-    std::conditional_t<PX, uintx4, uintx2> v[BS][NP];
+    uintx4 v[BS][NV];
     uintx2 ml[BS];
 #pragma unroll
     for (int u = 0; u < BS; u++) {
       const int t = (t0 + u < nslots) ? t0 + u : nslots - 1;  // (a repeated slot: weight 0 below)
       ml[u] = __builtin_amdgcn_raw_buffer_load_b64(prsrc, vo_ml, t * Part::kBytes, POL);
 #pragma unroll
-      for (int i = 0; i < NP; i++)
-        if constexpr (PX) v[u][i] = __builtin_amdgcn_raw_buffer_load_b128(prsrc, vo_v + i * Part::kPiece, t * Part::kBytes, POL);
-        else v[u][i] = __builtin_amdgcn_raw_buffer_load_b64(prsrc, vo_v + i * Part::kPiece, t * Part::kBytes, POL);
+      for (int i = 0; i < NV; i++) v[u][i] = __builtin_amdgcn_raw_buffer_load_b128(prsrc, vo_v + i * Part::kVec, t * Part::kBytes, POL);
     }
     // (all of the batch's loads are requested before anything looks at a result: left alone, the
     // scheduler moves the first maxima up between the loads, and each then waits a round trip)
@@ -466,24 +510,16 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
 #pragma unroll
           for (int x = 0; x < 4; x++) acc[i][x] = fmaf(__uint_as_float(v[u][i][x]), wgt, acc[i][x]);
         } else {
-          acc[i][0] = fmaf(__uint_as_float(v[u][i][0] << 16), wgt, acc[i][0]);
-          acc[i][1] = fmaf(__uint_as_float(v[u][i][0] & 0xffff0000u), wgt, acc[i][1]);
-          acc[i][2] = fmaf(__uint_as_float(v[u][i][1] << 16), wgt, acc[i][2]);
-          acc[i][3] = fmaf(__uint_as_float(v[u][i][1] & 0xffff0000u), wgt, acc[i][3]);
+          const uint32_t lo = v[u][i / 2][2 * (i & 1)], hi = v[u][i / 2][2 * (i & 1) + 1];
+          acc[i][0] = fmaf(__uint_as_float(lo << 16), wgt, acc[i][0]);
+          acc[i][1] = fmaf(__uint_as_float(lo & 0xffff0000u), wgt, acc[i][1]);
+          acc[i][2] = fmaf(__uint_as_float(hi << 16), wgt, acc[i][2]);
+          acc[i][3] = fmaf(__uint_as_float(hi & 0xffff0000u), wgt, acc[i][3]);
         }
       }
     }
   }
-  if (grow < 0) return;
-  const float inv = PX ? 1.0f / lsum : __builtin_amdgcn_rcpf(lsum);
-  CB_GLOBAL uint16_t* orow = gout + grow * D;
-#pragma unroll
-  for (int i = 0; i < NP; i++) {
-    uintx2 pk;
-    pk[0] = (uint32_t)f2bf(acc[i][0] * inv) | ((uint32_t)f2bf(acc[i][1] * inv) << 16);
-    pk[1] = (uint32_t)f2bf(acc[i][2] * inv) | ((uint32_t)f2bf(acc[i][3] * inv) << 16);
-    *(CB_GLOBAL uintx2*)(orow + Part::DP * (pc0 + i) + 4 * h) = pk;
-  }
+  store_row<D, TR, NP>(gout, grow, acc, pc0, PX ? 1.0f / lsum : __builtin_amdgcn_rcpf(lsum), l);
 }
 
 // Split merge of a tile inside the launch.  The partials of the sweeps are write-through stores; once they have
@@ -611,26 +647,37 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     sh.todo2 = todo2;
     __hip_atomic_store(&sh.flag2, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
-  // Unit u of the tile = (TR-row tile u / P, piece u % P); this workgroup's own slice holds the
+  // Unit u of the tile = pieces (u % (P / np)) * np .. of TR-row tile u / (P / np); this workgroup's own slice holds the
   // units split, split + nsplit, ...; its k-th unit goes to wave (k + 1) % NW.  What a wave needs
   // for its first unit -- the lane's output row, the partials' offsets -- is worked out before it
-  // waits, so that the loads go out as soon as the verdict is in.
+  // waits, so that the loads go out as soon as the verdict is in.  A unit is a round trip to memory for its wave, so
+  // where two pieces each make more units than the workgroups have waves a unit is four (a tile of 256 rows has 128 pieces).
   const int rows = jb.M - jb.row0 < MAXROWS ? jb.M - jb.row0 : MAXROWS;
-  const int NU = (rows + TR - 1) / TR * P;
+  const int pieces = (rows + TR - 1) / TR * P;
+  const int np = pieces <= 2 * NW * nsplit ? 2 : 4;
+  const int upt = P / np;                       // units of a TR-row tile
+  const int NU = pieces / np;
   auto merge_one = [&](int u, int64_t gr, uint32_t byte, int flag) {
-    const int pc = u % P;
+    const int pc = u % upt * np;
+    auto go = [&](auto n, auto bs) {
+      constexpr int NP = decltype(n)::value, BS = decltype(bs)::value;
+      if (flag == 1) merge_pieces<D, TR, PX, NP, 0, BS>(prsrc, gr, byte, gout, nsplit, pc, l);
+      else merge_pieces<D, TR, PX, NP, kAgentCoherent, BS>(prsrc, gr, byte, gout, nsplit, pc, l);
+    };
+    using std::integral_constant;
+    constexpr int LONG = PX || MAXROWS <= 64 ? 8 : 16;  // (as many loads as the registers hold)
     if (nsplit <= 8) {  // (one batch in the common cases)
-      if (flag == 1) merge_pieces<D, TR, PX, 1, 0, 8>(prsrc, gr, byte, gout, nsplit, pc, l);
-      else merge_pieces<D, TR, PX, 1, kAgentCoherent, 8>(prsrc, gr, byte, gout, nsplit, pc, l);
+      if (np == 2) go(integral_constant<int, 2>{}, integral_constant<int, 8>{});
+      else go(integral_constant<int, 4>{}, integral_constant<int, PX ? 4 : 8>{});
     } else {
-      if (flag == 1) merge_pieces<D, TR, PX, 1, 0, 16>(prsrc, gr, byte, gout, nsplit, pc, l);
-      else merge_pieces<D, TR, PX, 1, kAgentCoherent, 16>(prsrc, gr, byte, gout, nsplit, pc, l);
+      if (np == 2) go(integral_constant<int, 2>{}, integral_constant<int, LONG>{});
+      else go(integral_constant<int, 4>{}, integral_constant<int, PX ? 4 : LONG>{});
     }
   };
   const int u_first = split + ((w + NW - 1) % NW) * nsplit;  // this wave's first unit of the own slice
   int64_t gr_first = -1;
-  const bool have_first = u_first < NU && tile_row(u_first / P, &gr_first);
-  const uint32_t byte_first = partial_byte<D, TR, PX>(p, jb, u_first / P);
+  const bool have_first = u_first < NU && tile_row(u_first / upt, &gr_first);
+  const uint32_t byte_first = partial_byte<D, TR, PX>(p, jb, u_first / upt);
   // the waves wait for thread 64's verdicts in LDS
   int flag;
   while ((flag = __hip_atomic_load(&sh.flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0) __builtin_amdgcn_s_sleep(1);
@@ -642,7 +689,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
       for (int u = s2; u < NU; u += nsplit, k++) {
         if ((k + 1) % NW != w || (first_done && u == u_first)) continue;
         int64_t gr;
-        if (tile_row(u / P, &gr)) merge_one(u, gr, partial_byte<D, TR, PX>(p, jb, u / P), flag);
+        if (tile_row(u / upt, &gr)) merge_one(u, gr, partial_byte<D, TR, PX>(p, jb, u / upt), flag);
       }
     }
   };
@@ -671,36 +718,31 @@ template <int D, int TR, bool PX, int NP>
 __device__ __forceinline__ void write_rows(const AttnParams& p, const TileJob& jb, int i, int64_t grow, const floatx4 (&f)[NP], int pc0,
                                            float mref, float lsum, float c2, bool first, int l) {
   using Part = PartialLayout<D, TR, PX>;
-  if (grow < 0) return;
   const int h = l / TR, r = l % TR;
   if (jb.nsplit == 1) {
-    const float inv = 1.0f / lsum;
-    CB_GLOBAL uint16_t* orow = (CB_GLOBAL uint16_t*)p.out + grow * D;
-#pragma unroll
-    for (int n = 0; n < NP; n++) {
-      uintx2 pk;
-      pk[0] = (uint32_t)f2bf(f[n][0] * inv) | ((uint32_t)f2bf(f[n][1] * inv) << 16);
-      pk[1] = (uint32_t)f2bf(f[n][2] * inv) | ((uint32_t)f2bf(f[n][3] * inv) << 16);
-      *(CB_GLOBAL uintx2*)(orow + Part::DP * (pc0 + n) + 4 * h) = pk;
-    }
+    store_row<D, TR, NP>((CB_GLOBAL uint16_t*)p.out, grow, f, pc0, 1.0f / lsum, l);
     return;
   }
+  if (grow < 0) return;
   // written through to memory (agent scope) so that the merging workgroup, possibly on another XCD with its own L2,
   // can read it without cache flushes
   const __amdgpu_buffer_rsrc_t prsrc = partial_rsrc<D, TR, PX>(p, jb);
   const uint32_t pbyte = partial_byte<D, TR, PX>(p, jb, i) + (uint32_t)jb.split * Part::kBytes;
 #pragma unroll
-  for (int n = 0; n < NP; n++) {
-    const uint32_t at = pbyte + (pc0 + n) * Part::kPiece + l * Part::kLane;
+  for (int n = 0; n < NP; n += Part::kPer) {
+    const uint32_t at = pbyte + (pc0 + n) / Part::kPer * Part::kVec + l * 16;
+    uintx4 v;
     if constexpr (PX) {
-      const uintx4 v = __builtin_bit_cast(uintx4, f[n]);
-      if (p.external_merge) __builtin_amdgcn_raw_buffer_store_b128(v, prsrc, at, 0, 0);
-      else __builtin_amdgcn_raw_buffer_store_b128(v, prsrc, at, 0, kAgentCoherent);
+      v = __builtin_bit_cast(uintx4, f[n]);
     } else {
-      const uintx2 v = {(uint32_t)f2bf(f[n][0]) | ((uint32_t)f2bf(f[n][1]) << 16), (uint32_t)f2bf(f[n][2]) | ((uint32_t)f2bf(f[n][3]) << 16)};
-      if (p.external_merge) __builtin_amdgcn_raw_buffer_store_b64(v, prsrc, at, 0, 0);
-      else __builtin_amdgcn_raw_buffer_store_b64(v, prsrc, at, 0, kAgentCoherent);
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        v[2 * x] = pack_bf16(f[n + x][0], f[n + x][1]);
+        v[2 * x + 1] = pack_bf16(f[n + x][2], f[n + x][3]);
+      }
     }
+    if (p.external_merge) __builtin_amdgcn_raw_buffer_store_b128(v, prsrc, at, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b128(v, prsrc, at, 0, kAgentCoherent);
   }
   if (h == 0 && first) {
     // m = log2 of the reference weight 2^(c2*mref)
