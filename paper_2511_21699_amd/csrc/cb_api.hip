@@ -223,26 +223,6 @@ int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const
   return std::max(8, std::min(share, most) / 8 * 8);
 }
 
-// The same for calls with wide tiles, whose sweep is bound by the chain of its arithmetic: the fewest workgroups (in XCD
-// rounds) that are through with the logits, at 25 GB/s each, in 0.7 of the time the attention takes (more of them, up to
-// 64, change little: 16 sequences of up to 16384 keys 629 us with 8, 620 with 32, 633 with 64).  0: a launch of their own,
-// where the logits are more than half of what the sweep reads and would not hide behind it.  A pass of 128 nodes x 8192 keys
-// of 32/8 heads with 32000-entry rows as two launches and as one 37.7 -> 31.8 us, 256 nodes x 65536 keys of 40 heads with
-// 128256-entry rows 418 -> 406 us.
-int fused_wide_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const int32_t* node_offsets) {
-  const double lb = c.logits_dtype == CB_F32 ? 4 : 2;
-  double slots = 0, flops = 0;
-  for (int b = 0; b < batch; b++) {
-    const double n = node_offsets[b + 1] - node_offsets[b], len = kv_len[b] + n;
-    slots += len;
-    flops += 4.0 * n * c.num_q_heads * len * c.head_dim;
-  }
-  const double kv = slots * c.num_kv_heads * c.head_dim * 4, lg = (double)node_offsets[batch] * c.vocab_size * lb;
-  if (2 * lg > kv) return 0;
-  const double us = std::max(kv / 5e6, flops / 0.85e9) + 8.0;
-  return std::min(64, ((int)(lg / (25e3 * 0.7 * us)) / 8 + 1) * 8);
-}
-
 // Pure host arithmetic: no device call, no context state beyond the numbers passed in.  `units`: compute units that
 // the attention's workgroups can count on.
 Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int batch,
@@ -305,7 +285,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
       // numbering).  Such a list schedule ends no later than max(longest job, work / units + a job
       // of the shortest sequence), so: estimate that for every split count, in units of one 64-key
       // stage, with what a workgroup costs beside its stages (start-up and tail: about six stages;
-      // a workgroup of the grid that finds no keys: one), and what a tile's merge costs its last
+      // one that finds no keys, where such are launched: one), and what a tile's merge costs its last
       // workgroup, and take the cheapest count -- the fewest splits that still spread the longest
       // sequence wide enough.
       double best_cost = 0.0;
@@ -323,8 +303,8 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
           const int full = len / chunk, rest = len - full * chunk;
           const double job_full = 6.0 + (chunk + 63) / 64, job_rest = rest > 0 ? 6.0 + (rest + 63) / 64 : 0.0;
           const int real = full + (rest > 0 ? 1 : 0);
-          work += tl * (full * job_full + job_rest + (real > 1 ? merge : 0.0)) +
-                  ((int64_t)c.num_kv_heads * tiles_max * grid_x - tl * real) * 1.0;
+          work += tl * (full * job_full + job_rest + (real > 1 ? merge : 0.0));
+          if (c.num_kv_heads % 8 != 0) work += ((int64_t)c.num_kv_heads * tiles_max * grid_x - tl * real) * 1.0;
           jobs += tl * real;
           longest = std::max(longest, (full > 0 ? job_full : job_rest) + (real > 1 ? merge : 0.0));
           shortest = std::min(shortest, full > 0 ? job_full : job_rest);
@@ -374,6 +354,29 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units);
   }
   return p;
+}
+
+// Workgroups for the logits work of a verification with wide tiles, whose sweep is bound by its arithmetic: the fewest (in XCD
+// rounds, at most 96) that are through with the logits, at about 20 GB/s each, in 0.7 of the time the attention takes: 13 us
+// beside the sweep and, per 32 keys, 0.95 us with a tile of more than 128 rows and 0.55 with a smaller one.  Fewer keep the
+// launch (a pass of 8 sequences of 32/8 heads with 250 rows of 33333 entries: 32 workgroups 41.7 us, 48 33.7; 128 rows
+// of 32000 over 8192 keys: 8 44.5, 16 34.0, 24 33.5), more take compute units from the sweep (the batch with 96: 38.4).
+// 0: a launch of their own, where the logits are more than 2.5 times the K/V bytes.  One launch gains 8 us a pass on short
+// sweeps and less the more logits there are: 128 nodes of 32/8 heads x 2048 keys, 32000-entry rows (as many bytes as K/V)
+// 32.7 -> 23.4 us, 128256-entry rows 37.5 -> 29.8, and with a host waiting for the results 38.6 -> 38.8.
+int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, const int32_t* kv_len, const int32_t* node_offsets) {
+  const double lb = c.logits_dtype == CB_F32 ? 4 : 2;
+  const int g = c.num_q_heads / c.num_kv_heads, rows = std::min(attn_mfma_tile_rows(alone.max_nodes * g), alone.max_nodes * g);
+  double slots = 0, jobs = 0;
+  for (int b = 0; b < batch; b++) {
+    const int n = node_offsets[b + 1] - node_offsets[b], len = kv_len[b] + n;
+    slots += len;
+    jobs += (double)((n * g + 255) / 256) * c.num_kv_heads * len / alone.chunk;
+  }
+  const double kv = slots * c.num_kv_heads * c.head_dim * 4, lg = (double)node_offsets[batch] * c.vocab_size * lb;
+  if (lg > 2.5 * kv) return 0;
+  const double us = 13.0 + alone.chunk / 32 * (rows > 128 ? 0.95 : 0.55) * std::max(1.0, jobs / 256);
+  return std::min(96, ((int)(lg / (20e3 * 0.7 * us)) / 8 + 1) * 8);
 }
 
 // The scratch layout of a cb_tree_attention_noalloc call, and the plan it is cut for.  Whether a call fits the fixed array
@@ -482,7 +485,8 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   } else if (small_tiles || f32_tiles) {
     n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
   } else if (c.qkv_dtype == CB_BF16) {
-    n_logits = fused_wide_logits_wgs(c, batch, kv_len, node_offsets);
+    const Plan alone = plan_attention(c, ctx->lay.max_splits, ctx->lay.scalar_splits, ctx->opt_impl, ctx->opt_splits, batch, kv_len, node_offsets, 248);
+    if (alone.impl == 2) n_logits = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets);
   }
   if (n_logits && ctx->opt_logits_wgs > 0) n_logits = (int)ctx->opt_logits_wgs;
   const Plan plan = ctx->fixed_plan ? *ctx->fixed_plan
@@ -504,6 +508,19 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   ap.nsplit = plan.nsplit;
   ap.precise = plan.precise;
   ap.batch = batch;
+  if (plan.impl == 2) {
+    const int g = c.num_q_heads / c.num_kv_heads, rows = attn_mfma_tile_rows(plan.max_nodes * g);
+    int64_t live = 0;  // per kv head
+    for (int i = 0; i < CB_MAX_BATCH; i++) {
+      meta.start[i] = INT32_MAX;
+      if (i >= batch) continue;
+      const int b = meta.by_length[i];
+      const int64_t n = node_offsets[b + 1] - node_offsets[b];
+      meta.start[i] = (int32_t)(live * (c.num_kv_heads / 8));
+      live += (n * g + rows - 1) / rows * ((kv_len[b] + n + plan.chunk - 1) / plan.chunk);
+    }
+    ap.live_wgs = (int32_t)(live * c.num_kv_heads);
+  }
   ap.scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
   ap.status = ctx->dev<int32_t>(ctx->lay.status);
   ap.dbg_ts = ctx->dev<unsigned long long>(ctx->lay.dbg);

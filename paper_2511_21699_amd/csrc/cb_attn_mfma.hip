@@ -344,10 +344,15 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   q.grid_x = p.nsplit;
   q.grid_y = p.Hkv * tiles;
   q.grid_z = p.batch;
-  const int64_t T = (int64_t)p.nsplit * p.Hkv * tiles * p.batch;
+  int64_t T = (int64_t)p.nsplit * p.Hkv * tiles * p.batch;
   // renumbering needs whole groups of splits inside each XCD's share of the grid
   q.xcd_remap = (T % 8 == 0 && (T / 8) % p.nsplit == 0) ? 1 : 0;
-  if (q.grid_y % 8 == 0 && p.batch > 1) q.xcd_remap = 2;  // (several sequences: longest first within every XCD)
+  if (p.Hkv % 8 == 0 && p.batch > 1) {  // (several sequences: longest first within every XCD)
+    q.xcd_remap = 2;
+    T = p.live_wgs;
+  } else if (q.grid_y % 8 == 0 && p.batch > 1) {
+    q.xcd_remap = 3;
+  }
   // (the logits' workgroups come first; a multiple of 8 of them leaves the others' XCDs as they are)
   const int n_logits = logits_work ? logits_work->n_wgs : 0;
   const dim3 grid((uint32_t)(n_logits + T));

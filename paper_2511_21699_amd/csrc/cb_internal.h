@@ -22,6 +22,7 @@ struct SeqMeta {
   int32_t kv_len[CB_MAX_BATCH];
   int32_t node_off[CB_MAX_BATCH + 1];
   int32_t by_length[CB_MAX_BATCH];  // the sequences ordered by kv_len + nodes, longest first (filled by the host)
+  int32_t start[CB_MAX_BATCH];      // in that order: the sequence's first workgroup in every XCD's list (xcd_remap 2)
 };
 
 // Shapes of sequence `b` (uniform in the wave) without a dependent scalar load: every lane fetches
@@ -32,7 +33,7 @@ struct SeqShape {
   int S, off, N;
 };
 struct SeqMetaLanes {
-  int kv, o0, o1, ord;
+  int kv, o0, o1, ord, start;
 };
 __device__ __forceinline__ SeqMetaLanes seq_meta_prefetch(const SeqMeta& meta) {
   const int lane = threadIdx.x & 63;
@@ -41,6 +42,7 @@ __device__ __forceinline__ SeqMetaLanes seq_meta_prefetch(const SeqMeta& meta) {
   r.o0 = meta.node_off[lane];
   r.o1 = meta.node_off[lane + 1];
   r.ord = meta.by_length[lane];
+  r.start = meta.start[lane];
   return r;
 }
 __device__ __forceinline__ SeqShape seq_shape(const SeqMetaLanes& m, int b) {
@@ -165,10 +167,12 @@ struct AttnParams {
   int32_t chunk;        // keys per split
   int32_t nsplit;       // partial slots per row (>= splits any sequence uses)
   int32_t batch;
+  int32_t live_wgs;     // workgroups of the launch that have keys to sweep (the host reads it; MFMA kernels)
   float scale;
   int32_t precise;      // bf16 MFMA kernels: probabilities and partial sums in 32 bits (the host reads it, to choose the build)
   int32_t xcd_remap;    // 1: renumber workgroups so that all splits of a tile run on one XCD; 2: and every XCD takes
-                        // its share -- a fixed set of (kv head, row tile) pairs of all sequences -- longest sequence first
+                        // its share -- a fixed set of kv heads of all sequences -- longest sequence first; 3: the same with a fixed set of
+                        // (kv head, row tile) pairs, workgroups without keys among them (kv heads no multiple of 8)
   int32_t grid_x, grid_y, grid_z;  // launch grid, repeated here so the kernel reads one argument block
   int32_t external_merge;  // 1: the kernel only writes partials; launch_attn_mfma runs a merge kernel afterwards
   int32_t coop_merge;      // 1: every workgroup of a tile merges a slice of it after a bounded wait for the others
