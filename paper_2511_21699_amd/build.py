@@ -132,8 +132,9 @@ def kernel_resources(asm: str) -> dict:
 
 
 def scratch_violations(asm: str) -> list:
-    """Kernels of the listing that spill registers or use scratch memory.  In the attention kernel a spill
-    reload inside the K/V ring phase would be a compiler-generated load, and with it a wait for every load in
+    """Kernels of the listing that use scratch memory (the listing's spill count is not looked at: it also counts
+    vector registers kept in accumulation registers, which no memory access serves).  In the attention kernel a spill
+    reload from memory inside the K/V ring phase would be a compiler-generated load, and with it a wait for every load in
     flight, in a loop whose waits are counted by hand."""
     return [(k, v) for k, v in kernel_resources(asm).items() if v[2] != 0]
 
@@ -153,7 +154,7 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError(f"{name}: loads too close behind a possible write of their scalar base: {bad[:4]}")
         bad = scratch_violations(asm)
         if bad:
-            raise RuntimeError(f"{name}: kernels that spill or use scratch memory: {bad[:4]}")
+            raise RuntimeError(f"{name}: kernels that use scratch memory: {bad[:4]}")
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     if verbose:
         print(LIB)

@@ -226,7 +226,7 @@ int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const
 // Pure host arithmetic: no device call, no context state beyond the numbers passed in.  `units`: compute units that
 // the attention's workgroups can count on.
 Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int batch,
-                    const int32_t* kv_len, const int32_t* node_offsets, int units = 256) {
+                    const int32_t* kv_len, const int32_t* node_offsets, int units = 256, bool empty_wgs = false) {
   Plan p{};
   int64_t rows = 0;
   for (int b = 0; b < batch; b++) {
@@ -253,7 +253,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     const int g = c.num_q_heads / c.num_kv_heads;
     const int mrows = p.max_nodes * g;
     const int rows_per_wg = attn_mfma_tile_rows(mrows);
-    // Every variant runs 8 waves and a 128 KiB ring: one workgroup per compute unit, so the grid
+    // Every variant has a ring of more than half of the LDS: one workgroup per compute unit, so the grid
     // should come out just under a whole number of rounds of `units` workgroups.  Take the fewest
     // splits that fill >= 85% of them in whole rounds (fewer splits = fewer partials).
     // efficiency of ns splits: keys swept / (units x whole rounds x keys of a full split)
@@ -304,7 +304,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
           const double job_full = 6.0 + (chunk + 63) / 64, job_rest = rest > 0 ? 6.0 + (rest + 63) / 64 : 0.0;
           const int real = full + (rest > 0 ? 1 : 0);
           work += tl * (full * job_full + job_rest + (real > 1 ? merge : 0.0));
-          if (c.num_kv_heads % 8 != 0) work += ((int64_t)c.num_kv_heads * tiles_max * grid_x - tl * real) * 1.0;
+          if (empty_wgs || c.num_kv_heads % 8 != 0) work += ((int64_t)c.num_kv_heads * tiles_max * grid_x - tl * real) * 1.0;
           jobs += tl * real;
           longest = std::max(longest, (full > 0 ? job_full : job_rest) + (real > 1 ? merge : 0.0));
           shortest = std::min(shortest, full > 0 ? job_full : job_rest);
@@ -351,7 +351,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     ap.nsplit = p.nsplit;
     ap.precise = p.precise;
     ap.kv.block_size = c.block_size;
-    if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units);
+    if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units, empty_wgs);
   }
   return p;
 }
@@ -382,7 +382,9 @@ int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, cons
 // The scratch layout of a cb_tree_attention_noalloc call, and the plan it is cut for.  Whether a call fits the fixed array
 // is a property of its shape that callers rely on, so it is decided by one measure per kind of call, whatever the
 // kernels would like to have: bf16 states in 16-row tiles at the planned splits for bf16 with head_dim 128, fp32 rows at the
-// splits of one workgroup per row for the others.  A call within it gets its plan, with fewer splits if the kernels' own
+// splits of one workgroup per row for the others.  The measure's splits are planned as if a batch's grid held a workgroup for
+// every split of its longest sequence (empty_wgs): plans that launch fewer workgroups take more splits, and calls that
+// fit would be refused.  A call within it gets its plan, with fewer splits if the kernels' own
 // layout at the planned ones is larger than the array (one split needs no partial states, so an end is always found).
 WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, const int32_t* kv_len, const int32_t* node_offsets, Plan* plan) {
   const size_t total = node_offsets[batch];
@@ -412,9 +414,10 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
     return L;
   };
   *plan = planned(full.max_splits);
+  const int measured = plan_attention(c, full.max_splits, full.scalar_splits, 0, 0, batch, kv_len, node_offsets, 256, true).nsplit;
   const bool by_rows = c.qkv_dtype == CB_F32 || c.head_dim == 64;
   const size_t measure = by_rows ? fp32_rows(plan_attention(c, full.max_splits, full.max_splits, 1, 0, batch, kv_len, node_offsets).nsplit)
-                         : plan->impl == 2 ? tiles(false, 1, plan->nsplit) : fp32_rows(plan->nsplit);
+                         : plan->impl == 2 ? tiles(false, 1, measured) : fp32_rows(measured);
   WsLayout L = cut(measure);
   if (L.total > kStaticScratchBytes) return L;
   for (;;) {

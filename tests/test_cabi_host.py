@@ -205,6 +205,9 @@ def test_no_alloc_entry_point_checks_its_arguments_on_the_host():
     (32, 8, 128, "f32", [32] * 4, [60000, 900, 800, 700]),
     (320, 40, 64, "bf16", [256], [56477]),
     (64, 32, 128, "bf16", [128, 109, 107, 63], [1322, 542, 200, 290]),     # 32-row tiles of the wide kernel
+    # batches whose plan takes more splits than its measure does: no workgroups without keys are launched
+    (8, 8, 128, "bf16", [20] * 64, list(range(8000, 32000, 375))),
+    (32, 32, 128, "bf16", [8] * 32, list(range(12000, 36000, 750))),
 ])
 def test_no_alloc_entry_point_splits_less_near_the_scratch_limit(hq, hkv, d, dtype, nodes, lens):
     """Calls whose planned splits are too many for the fixed array run with fewer.  Without a device an accepted
