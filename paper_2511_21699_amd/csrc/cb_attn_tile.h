@@ -664,7 +664,11 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
   // where two pieces each make more units than the workgroups have waves a unit is four (a tile of 256 rows has 128 pieces).
   const int rows = jb.M - jb.row0 < MAXROWS ? jb.M - jb.row0 : MAXROWS;
   const int pieces = (rows + TR - 1) / TR * P;
-  const int np = pieces <= 2 * NW * nsplit ? 2 : 4;
+  // Tiles of up to 64 rows never do: a unit is what makes one 16-byte load, and 16 slots are in flight where there are more
+  // than 8 splits (8 in flight: 4 rows over 3911 paged keys, 31 splits, 14.4 us a pass instead of 13.4).
+  constexpr bool SMALL = MAXROWS <= 64;
+  constexpr int NP0 = SMALL ? PartialLayout<D, TR, PX>::kPer : 2;
+  const int np = SMALL || pieces <= 2 * NW * nsplit ? NP0 : 4;
   const int upt = P / np;                       // units of a TR-row tile
   const int NU = pieces / np;
   auto merge_one = [&](int u, int64_t gr, uint32_t byte, int flag) {
@@ -675,13 +679,13 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
       else merge_pieces<D, TR, PX, NP, kAgentCoherent, BS>(prsrc, gr, byte, gout, nsplit, pc, l);
     };
     using std::integral_constant;
-    constexpr int LONG = PX || MAXROWS <= 64 ? 8 : 16;  // (as many loads as the registers hold)
+    constexpr int LONG = PX && !SMALL ? 8 : 16;  // (as many loads as the registers hold)
     if (nsplit <= 8) {  // (one batch in the common cases)
-      if (np == 2) go(integral_constant<int, 2>{}, integral_constant<int, 8>{});
-      else go(integral_constant<int, 4>{}, integral_constant<int, PX ? 4 : 8>{});
+      if (np == NP0) go(integral_constant<int, NP0>{}, integral_constant<int, 8>{});
+      else if constexpr (!SMALL) go(integral_constant<int, 4>{}, integral_constant<int, PX ? 4 : 8>{});
     } else {
-      if (np == 2) go(integral_constant<int, 2>{}, integral_constant<int, LONG>{});
-      else go(integral_constant<int, 4>{}, integral_constant<int, PX ? 4 : LONG>{});
+      if (np == NP0) go(integral_constant<int, NP0>{}, integral_constant<int, LONG>{});
+      else if constexpr (!SMALL) go(integral_constant<int, 4>{}, integral_constant<int, PX ? 4 : LONG>{});
     }
   };
   const int u_first = split + ((w + NW - 1) % NW) * nsplit;  // this wave's first unit of the own slice
