@@ -364,6 +364,9 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
 // 0: a launch of their own, where the logits are more than 2.5 times the K/V bytes.  One launch gains 8 us a pass on short
 // sweeps and less the more logits there are: 128 nodes of 32/8 heads x 2048 keys, 32000-entry rows (as many bytes as K/V)
 // 32.7 -> 23.4 us, 128256-entry rows 37.5 -> 29.8, and with a host waiting for the results 38.6 -> 38.8.
+// 0 too for tiles of up to 128 rows in several rounds of workgroups, unless their sums are in 32 bits: those sweeps are bound by
+// memory (5.5 TB/s), and logits beside them only delay the longest sequences (16 paged sequences of up to 16384 keys with 32 to
+// 96 nodes, 32 heads, a step: 443 us in one launch, 433 in two; with 32-bit sums 629 and 641).
 int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, const int32_t* kv_len, const int32_t* node_offsets) {
   const double lb = c.logits_dtype == CB_F32 ? 4 : 2;
   const int g = c.num_q_heads / c.num_kv_heads, rows = std::min(attn_mfma_tile_rows(alone.max_nodes * g), alone.max_nodes * g);
@@ -375,6 +378,7 @@ int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, cons
   }
   const double kv = slots * c.num_kv_heads * c.head_dim * 4, lg = (double)node_offsets[batch] * c.vocab_size * lb;
   if (lg > 2.5 * kv) return 0;
+  if (rows <= 128 && !alone.precise && jobs > 256) return 0;
   const double us = 13.0 + alone.chunk / 32 * (rows > 128 ? 0.95 : 0.55) * std::max(1.0, jobs / 256);
   return std::min(96, ((int)(lg / (20e3 * 0.7 * us)) / 8 + 1) * 8);
 }
