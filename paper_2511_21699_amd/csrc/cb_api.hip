@@ -104,13 +104,14 @@ WsLayout ws_layout(const cb_config& c) {
 
 // Whether a bf16 call holds probabilities and partial sums in 32 bits: with head_dim 64, and with head_dim 128 where a split's
 // slice of the block table has more than 1022 entries, as the scalar kernel did that served these two before the MFMA
-// kernels took them; their callers keep that precision.
+// kernels took them; their callers keep that precision (plan_call).
 bool precise_sums(const cb_config& c, int chunk) {
   return c.qkv_dtype == CB_BF16 && (c.head_dim == 64 || (c.block_size > 0 && chunk / c.block_size + 2 > 1024));
 }
 
 struct Plan {
   bool precise;  // (impl 2)
+  int logits_wgs;  // of a verification: workgroups of the attention's launch that do the logits work (0: a launch of their own)
   int impl;    // 1 fp32 (or the scalar kernel on request), 2 bf16 MFMA
   int nsplit;  // partial slots per row
   int chunk;   // keys per split
@@ -224,9 +225,9 @@ int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const
 }
 
 // Pure host arithmetic: no device call, no context state beyond the numbers passed in.  `units`: compute units that
-// the attention's workgroups can count on.
+// the attention's workgroups can count on.  `precise`: sums in 32 bits whatever the slices' length.
 Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int batch,
-                    const int32_t* kv_len, const int32_t* node_offsets, int units = 256, bool empty_wgs = false) {
+                    const int32_t* kv_len, const int32_t* node_offsets, int units = 256, bool empty_wgs = false, bool precise = false) {
   Plan p{};
   int64_t rows = 0;
   for (int b = 0; b < batch; b++) {
@@ -334,7 +335,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
   int chunk = (p.max_len + nsplit - 1) / nsplit;
   chunk = (chunk + 31) / 32 * 32;
   p.chunk = std::max(chunk, 32);
-  p.precise = p.impl == 2 && precise_sums(c, p.chunk);
+  p.precise = p.impl == 2 && (precise || precise_sums(c, p.chunk));
   if (p.precise && c.head_dim == 128 && nsplit > 1 && nsplit > max_splits / 2) {
     // fp32 partial states are twice the size, and the workspace is cut for bf16 ones (longer splits stay precise)
     nsplit = std::max(1, max_splits / 2);
@@ -351,7 +352,7 @@ Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int o
     ap.nsplit = p.nsplit;
     ap.precise = p.precise;
     ap.kv.block_size = c.block_size;
-    if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units, empty_wgs);
+    if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units, empty_wgs, precise);
   }
   return p;
 }
@@ -383,6 +384,36 @@ int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, cons
   return std::min(96, ((int)(lg / (20e3 * 0.7 * us)) / 8 + 1) * 8);
 }
 
+// The plan of a call, a verification or the attention alone.
+// What a call holds in 32 bits is a property of its shape that callers rely on, so it is decided by one measure, whatever the
+// kernels would like to have: the splits planned as if the logits never rode beside wide tiles and a batch's grid held a
+// workgroup for every split of its longest sequence (empty_wgs).  A call is precise where the slices of that plan are long, or its own.
+Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int opt_logits_wgs, int batch,
+               const int32_t* kv_len, const int32_t* node_offsets, bool verification) {
+  auto planned = [&](int units, bool empty_wgs, bool precise) {
+    return plan_attention(c, max_splits, scalar_splits, opt_impl, opt_splits, batch, kv_len, node_offsets, units, empty_wgs, precise);
+  };
+  // A verification in fp32, or with small tiles, or whose logits hide behind the sweep, is one launch: its first workgroups do the logits work, and the
+  // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
+  // option does not change the splits and with them the rounding).
+  int max_nodes = 0, n_logits = 0;
+  for (int b = 0; b < batch; b++) max_nodes = std::max(max_nodes, node_offsets[b + 1] - node_offsets[b]);
+  const bool small_tiles = attn_mfma_tile_rows(max_nodes * (c.num_q_heads / c.num_kv_heads)) == 64;
+  const bool f32_tiles = c.qkv_dtype == CB_F32 && opt_impl != 1;
+  if (!verification) {
+  } else if (small_tiles || f32_tiles) {
+    n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
+  } else if (c.qkv_dtype == CB_BF16) {
+    const Plan alone = planned(248, false, false);
+    if (alone.impl == 2) n_logits = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets);
+  }
+  if (n_logits && opt_logits_wgs > 0) n_logits = opt_logits_wgs;
+  const Plan measure = planned(small_tiles || f32_tiles ? 256 - n_logits : 256, true, false);
+  Plan p = planned(256 - n_logits, false, measure.precise);
+  p.logits_wgs = n_logits;
+  return p;
+}
+
 // The scratch layout of a cb_tree_attention_noalloc call, and the plan it is cut for.  Whether a call fits the fixed array
 // is a property of its shape that callers rely on, so it is decided by one measure per kind of call, whatever the
 // kernels would like to have: bf16 states in 16-row tiles at the planned splits for bf16 with head_dim 128, fp32 rows at the
@@ -398,7 +429,7 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
     return ns <= 1 ? 0 : attn_mfma_partial_bytes(c.head_dim, precise, mrows, total, c.num_q_heads, c.num_kv_heads, batch, ns);
   };
   auto planned = [&](int most) {
-    return plan_attention(c, most, std::min(most, full.scalar_splits), 0, 0, batch, kv_len, node_offsets);
+    return plan_call(c, most, std::min(most, full.scalar_splits), 0, 0, 0, batch, kv_len, node_offsets, false);
   };
   auto cut = [&](size_t partial_bytes) {
     WsLayout L{};
@@ -480,24 +511,11 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     CB_HIP(ctx, launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.amax_best), ctx->lay.max_total_nodes, kAmaxStride, 1));
     ctx->amax_dirty = false;
   }
-  // A verification in fp32, or with small tiles, or whose logits hide behind the sweep, is one launch: its first workgroups do the logits work, and the
-  // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
-  // option does not change the splits and with them the rounding).
-  int max_nodes = 0;
-  for (int b = 0; b < batch; b++) max_nodes = std::max(max_nodes, node_offsets[b + 1] - node_offsets[b]);
-  const bool small_tiles = attn_mfma_tile_rows(max_nodes * (c.num_q_heads / c.num_kv_heads)) == 64;
   const bool f32_tiles = c.qkv_dtype == CB_F32 && ctx->opt_impl != 1;
-  int n_logits = 0;
-  if (!(stage_mask & 8)) {
-  } else if (small_tiles || f32_tiles) {
-    n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
-  } else if (c.qkv_dtype == CB_BF16) {
-    const Plan alone = plan_attention(c, ctx->lay.max_splits, ctx->lay.scalar_splits, ctx->opt_impl, ctx->opt_splits, batch, kv_len, node_offsets, 248);
-    if (alone.impl == 2) n_logits = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets);
-  }
-  if (n_logits && ctx->opt_logits_wgs > 0) n_logits = (int)ctx->opt_logits_wgs;
   const Plan plan = ctx->fixed_plan ? *ctx->fixed_plan
-                                    : plan_attention(c, ctx->lay.max_splits, ctx->lay.scalar_splits, ctx->opt_impl, ctx->opt_splits, batch, kv_len, node_offsets, 256 - n_logits);
+                                    : plan_call(c, ctx->lay.max_splits, ctx->lay.scalar_splits, (int)ctx->opt_impl, (int)ctx->opt_splits, (int)ctx->opt_logits_wgs,
+                                                batch, kv_len, node_offsets, (stage_mask & 8) != 0);
+  const int n_logits = plan.logits_wgs;
 
   AttnParams ap{};
   ap.q = q;
@@ -674,7 +692,7 @@ int cb_plan_attention(const cb_config* cfg, int32_t batch, const int32_t* kv_len
     if (n < 1 || n > cfg->max_nodes || kv_len[b] < 0 || (int64_t)kv_len[b] + n > (1ll << 30)) return CB_EINVAL;
   }
   const WsLayout lay = ws_layout(*cfg);
-  const Plan p = plan_attention(*cfg, lay.max_splits, lay.scalar_splits, 0, forced_splits, batch, kv_len, node_offsets);
+  const Plan p = plan_call(*cfg, lay.max_splits, lay.scalar_splits, 0, forced_splits, 0, batch, kv_len, node_offsets, false);
   const int g = cfg->num_q_heads / cfg->num_kv_heads;
   const int tile = p.impl == 2 ? attn_mfma_tile_rows(p.max_nodes * g) : 1;
   int64_t wgs = 0;
@@ -688,6 +706,21 @@ int cb_plan_attention(const cb_config* cfg, int32_t batch, const int32_t* kv_len
   plan[2] = p.chunk;
   plan[3] = tile;
   plan[4] = (int32_t)std::min<int64_t>(wgs, INT32_MAX);
+  return CB_OK;
+}
+
+// (declared in cb_internal.h: tests of the planning alone)
+int cb_debug_plan(const cb_config* cfg, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets, int32_t verification, int32_t plan[6]) {
+  int32_t base[5];
+  if (const int rc = cb_plan_attention(cfg, batch, kv_len, node_offsets, 0, base)) return rc;
+  const WsLayout lay = ws_layout(*cfg);
+  const Plan p = plan_call(*cfg, lay.max_splits, lay.scalar_splits, 0, 0, 0, batch, kv_len, node_offsets, verification != 0);
+  plan[0] = p.impl;
+  plan[1] = p.nsplit;
+  plan[2] = p.chunk;
+  plan[3] = p.precise;
+  plan[4] = p.logits_wgs;
+  plan[5] = p.impl == 2 || cfg->qkv_dtype == CB_F32 ? p.logits_wgs > 0 : 0;
   return CB_OK;
 }
 

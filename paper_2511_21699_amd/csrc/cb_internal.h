@@ -220,3 +220,9 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
                             int total_nodes, const LogitsWork* logits_work, int* merge_kind);
 
 }  // namespace cb
+
+// For tests, without a device: the plan of a verification or of the attention alone.  plan[0] = attention kernel family (1 fp32 or
+// scalar, 2 bf16 MFMA), [1] = splits, [2] = keys per split, [3] = 1 if probabilities and partial sums are in 32 bits (bf16 MFMA),
+// [4] = workgroups planned for the logits work, [5] = 1 if they are workgroups of the attention's launch
+extern "C" int cb_debug_plan(const cb_config* cfg, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets,
+                             int32_t verification, int32_t plan[6]);

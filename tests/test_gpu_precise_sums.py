@@ -23,6 +23,9 @@ CASES = [  # name, B, Hq, Hkv, D, lengths, trees, paged block (0: contiguous), s
     ("merge by the last workgroup", 24, 32, 32, 64, [500] * 24, [tree(9)] * 24, 0, 2),
     ("head_dim 128, table of 1100 entries, small tiles", 2, 8, 8, 128, [1090, 60], [tree(33), tree(5)], 1, 1),
     ("head_dim 128, two slices of 1100 entries, wide tiles", 1, 8, 2, 128, [2150], [tree(40)], 1, 2),
+    # (the plan's slices are shorter, in 32 bits as the shape decides)
+    ("head_dim 128, batch in slices of under 1022 entries, small tiles", 5, 32, 32, 128, [2500, 3000, 3500, 4000, 4500], [tree(9)] * 5, 1, 0),
+    ("head_dim 128, batch in slices of under 1022 entries, wide tiles", 4, 64, 16, 128, [1600, 2100, 2600, 3100], [tree(70)] * 4, 1, 0),
 ]
 
 

@@ -1,0 +1,41 @@
+"""Launch planning, on the host alone: what a call's shape decides whatever split count the planner finds fastest."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2511_21699_amd import binding as B
+
+
+def plan(hq, hkv, lens, nodes, block=0, vocab=32000, verification=True, d=128, logits="bf16"):
+    """nodes: one size for all sequences, or one each."""
+    n = np.broadcast_to(np.asarray(nodes, dtype=np.int32), len(lens))
+    cfg = B.make_config(hq, hkv, d, "bf16", logits, len(lens), int(n.max()), 8, vocab, block)
+    a = np.asarray(lens, dtype=np.int32)
+    offs = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    out = (C.c_int32 * 6)()
+    ip = lambda x: x.ctypes.data_as(C.POINTER(C.c_int32))  # noqa: E731
+    assert B.load().cb_debug_plan(C.byref(cfg), len(lens), ip(a), ip(offs), int(verification), out) == 0
+    return dict(zip(("impl", "nsplit", "chunk", "precise", "logits_wgs", "fused"), out))
+
+
+def steps(lo, step, batch):
+    return [lo + step * b for b in range(batch)]
+
+
+# Plans of fewer and longer splits put these calls' sums in 32 bits: slices of the block table beyond 1022 entries.
+LONG_SLICES = [  # heads, kv heads, block, lengths, nodes, verification
+    (32, 32, 8, steps(8100, 5700, 10), 64, False), (40, 40, 16, steps(9600, 5000, 11), 16, False), (8, 8, 16, steps(22800, 3000, 11), 4, False),
+    (8, 8, 8, steps(11700, 4000, 13), 128, False), (32, 32, 8, steps(27900, 200, 8), 230, True), (32, 8, 16, steps(27300, 5000, 9), 128, True),
+    (40, 40, 16, steps(10500, 3400, 13), 4, True), (8, 8, 8, steps(11100, 2100, 11), 230, True), (64, 8, 8, [36247], 230, True)]
+
+
+@pytest.mark.parametrize("hq,hkv,block,lens,nodes,verification", LONG_SLICES)
+def test_sums_stay_in_32_bits_whatever_the_splits(hq, hkv, block, lens, nodes, verification):
+    p = plan(hq, hkv, lens, nodes, block, verification=verification)
+    assert p["impl"] == 2 and p["precise"] == 1, p
+
+
+def test_sums_of_short_slices_are_in_16_bits():
+    assert plan(32, 32, [4111], 63, 16)["precise"] == 0
+    assert plan(32, 8, steps(3000, 800, 12), 64, 16)["precise"] == 0
