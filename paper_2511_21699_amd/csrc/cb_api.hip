@@ -387,11 +387,12 @@ int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, cons
 // The plan of a call, a verification or the attention alone.
 // What a call holds in 32 bits is a property of its shape that callers rely on, so it is decided by one measure, whatever the
 // kernels would like to have: the splits planned as if the logits never rode beside wide tiles and a batch's grid held a
-// workgroup for every split of its longest sequence (empty_wgs).  A call is precise where the slices of that plan are long, or its own.
+// workgroup for every split of its longest sequence (empty_wgs).  A call is precise where the slices of that plan are long, or its own;
+// one that the measure does not split, whose sums stay in the accumulators to the end, is not split (partial states are bf16).
 Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int opt_logits_wgs, int batch,
                const int32_t* kv_len, const int32_t* node_offsets, bool verification) {
-  auto planned = [&](int units, bool empty_wgs, bool precise) {
-    return plan_attention(c, max_splits, scalar_splits, opt_impl, opt_splits, batch, kv_len, node_offsets, units, empty_wgs, precise);
+  auto planned = [&](int units, bool empty_wgs, bool precise, int splits) {
+    return plan_attention(c, max_splits, scalar_splits, opt_impl, splits, batch, kv_len, node_offsets, units, empty_wgs, precise);
   };
   // A verification in fp32, or with small tiles, or whose logits hide behind the sweep, is one launch: its first workgroups do the logits work, and the
   // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
@@ -404,12 +405,13 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
   } else if (small_tiles || f32_tiles) {
     n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
   } else if (c.qkv_dtype == CB_BF16) {
-    const Plan alone = planned(248, false, false);
+    const Plan alone = planned(248, false, false, opt_splits);
     if (alone.impl == 2) n_logits = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets);
   }
   if (n_logits && opt_logits_wgs > 0) n_logits = opt_logits_wgs;
-  const Plan measure = planned(small_tiles || f32_tiles ? 256 - n_logits : 256, true, false);
-  Plan p = planned(256 - n_logits, false, measure.precise);
+  const Plan measure = planned(small_tiles || f32_tiles ? 256 - n_logits : 256, true, false, opt_splits);
+  const bool whole = measure.impl == 2 && measure.nsplit == 1 && !measure.precise;
+  Plan p = planned(256 - n_logits, false, measure.precise, whole ? 1 : opt_splits);
   p.logits_wgs = n_logits;
   return p;
 }

@@ -39,3 +39,16 @@ def test_sums_stay_in_32_bits_whatever_the_splits(hq, hkv, block, lens, nodes, v
 def test_sums_of_short_slices_are_in_16_bits():
     assert plan(32, 32, [4111], 63, 16)["precise"] == 0
     assert plan(32, 8, steps(3000, 800, 12), 64, 16)["precise"] == 0
+
+
+# Batches whose sums stay in the accumulators to the end: one split each.  (Partial states would round them to bf16.)
+WHOLE = [  # heads, kv heads, lengths, nodes, verification
+    (32, 32, steps(2700, 200, 12), 4, False), (40, 40, steps(3300, 800, 8), 4, False), (40, 40, steps(4200, 600, 6), 230, True),
+    (40, 40, steps(7200, 400, 6), 128, True), (64, 8, steps(3600, 600, 4), 230, True), (64, 8, steps(7800, 200, 8), 128, True),
+    (64, 8, steps(3000, 500, 8), 128, True)]
+
+
+@pytest.mark.parametrize("block", [0, 16])
+@pytest.mark.parametrize("hq,hkv,lens,nodes,verification", WHOLE)
+def test_sequences_that_fill_the_chip_are_not_split(hq, hkv, lens, nodes, verification, block):
+    assert plan(hq, hkv, lens, nodes, block, verification=verification)["nsplit"] == 1
