@@ -90,7 +90,7 @@ WsLayout ws_layout(const cb_config& c) {
   L.dbg = take(1024 * 8 * 8);
   // The scalar kernel's fp32 partials are twice the size of the MFMA kernel's.  A configuration
   // the MFMA kernel takes (bf16) runs the scalar one only on request (option
-  // "attn_impl" = 1, a test aid) or when its geometry is not the MFMA kernel's (see plan_attention): it gets
+  // "attn_impl" = 1, a test aid) or when its geometry is not the MFMA kernel's (see Planner::cut): it gets
   // room for 8 splits there, not for max_splits.
   const bool mfma_cfg = c.qkv_dtype == CB_BF16;
   L.scalar_splits = mfma_cfg ? std::min(L.max_splits, 8) : L.max_splits;
@@ -224,138 +224,171 @@ int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const
   return std::max(8, std::min(share, most) / 8 * 8);
 }
 
-// Pure host arithmetic: no device call, no context state beyond the numbers passed in.  `units`: compute units that
-// the attention's workgroups can count on.  `precise`: sums in 32 bits whatever the slices' length.
-Plan plan_attention(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int batch,
-                    const int32_t* kv_len, const int32_t* node_offsets, int units = 256, bool empty_wgs = false, bool precise = false) {
-  Plan p{};
-  int64_t rows = 0;
-  for (int b = 0; b < batch; b++) {
-    const int n = node_offsets[b + 1] - node_offsets[b];
-    p.max_nodes = std::max(p.max_nodes, n);
-    p.max_len = std::max(p.max_len, kv_len[b] + n);
-    rows += (int64_t)n * c.num_q_heads;
+// What splitting a call's sequences into chunks of so many keys means.  Its jobs are (sequence, kv head, row tile, chunk with keys);
+// work is counted in stages of 64 keys, with six for what a job costs beside its sweep (start-up and tail).
+struct SplitSums {
+  int chunk;              // (0: not known yet)
+  int grid_x;             // chunks of the longest sequence
+  int64_t jobs, merged;   // merged: tiles that have partial states
+  double work, shortest;
+  double longest_chunk, longest_whole;  // job, of a sequence that is split and of one that is not
+  double longest(double merge) const { return std::max(longest_chunk > 0.0 ? longest_chunk + merge : 0.0, longest_whole); }
+};
+
+// The split plan of one call's attention.  Pure host arithmetic: no device call, no context state beyond the numbers passed in.
+// What a split count means for a batch is worked out once, whatever number of plans is made.
+struct Planner {
+  const cb_config& c;
+  const int max_splits, scalar_splits, opt_splits, batch;
+  const int32_t *const kv_len, *const node_offsets;
+  const bool f32_tiles;
+  const int impl, g;
+  int max_nodes = 0, max_len = 0, tile_rows = 0;
+  int64_t rows = 0, keys = 0;     // query rows of all heads; (row tile, key) pairs
+  int32_t len[CB_MAX_BATCH];
+  int64_t tiles[CB_MAX_BATCH];
+  static constexpr int kKnown = 64;   // (the default for max_splits)
+  SplitSums known[kKnown + 2] = {};   // of the counts up to kKnown, and the last one beyond
+
+  Planner(const cb_config& c_, int max_splits_, int scalar_splits_, int opt_impl, int opt_splits_, int batch_, const int32_t* kv_len_, const int32_t* node_offsets_)
+      : c(c_), max_splits(max_splits_), scalar_splits(scalar_splits_), opt_splits(opt_splits_), batch(batch_), kv_len(kv_len_), node_offsets(node_offsets_),
+        f32_tiles(c_.qkv_dtype == CB_F32 && opt_impl != 1), impl(opt_impl == 1 || c_.qkv_dtype != CB_BF16 ? 1 : 2), g(c_.num_q_heads / c_.num_kv_heads) {
+    for (int b = 0; b < batch; b++) {
+      const int n = node_offsets[b + 1] - node_offsets[b];
+      len[b] = kv_len[b] + n;
+      max_nodes = std::max(max_nodes, n);
+      max_len = std::max(max_len, len[b]);
+      rows += (int64_t)n * c.num_q_heads;
+    }
+    tile_rows = attn_mfma_tile_rows(max_nodes * g);
+    for (int b = 0; b < batch; b++) {
+      tiles[b] = (int64_t)(((node_offsets[b + 1] - node_offsets[b]) * g + tile_rows - 1) / tile_rows) * c.num_kv_heads;
+      keys += tiles[b] * len[b];
+    }
   }
-  const bool mfma_ok = c.qkv_dtype == CB_BF16;
-  p.impl = (opt_impl == 1 || !mfma_ok) ? 1 : 2;
-  if (p.impl == 1) max_splits = scalar_splits;
-  int nsplit;
-  if (opt_splits > 0) {
-    nsplit = (int)std::min<int64_t>(opt_splits, max_splits);
-  } else if (p.impl == 1 && c.qkv_dtype == CB_F32 && opt_impl != 1) {
-    nsplit = attn_f32_splits(c.num_q_heads, c.num_kv_heads, c.head_dim, max_splits, batch, kv_len, node_offsets, p.max_len, units);
-  } else if (p.impl == 1) {
-    // one workgroup per (row, split): aim for a few workgroups per compute unit, but never split
-    // below 1024 keys -- a second (merge) launch costs more than a short row does
-    const int64_t want = 2048;
-    nsplit = (int)std::max<int64_t>(1, std::min<int64_t>((want + rows - 1) / rows, p.max_len / 1024));
-  } else {
+  int cap() const { return (int)std::max<int64_t>(1, std::min<int64_t>(max_splits, (max_len + 127) / 128)); }
+  int chunk_of(int ns) const { return ((max_len + ns - 1) / ns + 31) / 32 * 32; }
+
+  const SplitSums& split_into(int ns) {
+    SplitSums& s = known[std::min(ns, kKnown + 1)];
+    if (s.chunk == chunk_of(ns)) return s;
+    s = SplitSums{};
+    s.chunk = chunk_of(ns);
+    s.grid_x = (max_len + s.chunk - 1) / s.chunk;
+    s.shortest = 1e30;
+    const double job_chunk = 6.0 + (s.chunk + 63) / 64, per_key = 1.0 / s.chunk;
+    for (int b = 0; b < batch; b++) {
+      int full = (int)(len[b] * per_key);  // (a division, off by one at most)
+      full += (int64_t)(full + 1) * s.chunk <= len[b];
+      full -= (int64_t)full * s.chunk > len[b];
+      const int rest = len[b] - full * s.chunk, real = full + (rest > 0 ? 1 : 0);
+      const double job_rest = rest > 0 ? 6.0 + ((rest + 63) >> 6) : 0.0, job = full > 0 ? job_chunk : job_rest;
+      s.work += tiles[b] * (full * job_chunk + job_rest);
+      s.jobs += tiles[b] * real;
+      if (real > 1) s.merged += tiles[b];
+      double& longest = real > 1 ? s.longest_chunk : s.longest_whole;
+      longest = std::max(longest, job);
+      s.shortest = std::min(s.shortest, job);
+    }
+    return s;
+  }
+
+  // The split count on `units` compute units (those that the attention's workgroups can count on).  empty_wgs: as if a batch's grid
+  // held a workgroup for every split of its longest sequence.
+  int splits(int units, bool empty_wgs) {
+    if (opt_splits > 0) return opt_splits;
+    if (impl == 1 && f32_tiles) {
+      return attn_f32_splits(c.num_q_heads, c.num_kv_heads, c.head_dim, scalar_splits, batch, kv_len, node_offsets, max_len, units);
+    }
+    if (impl == 1) {
+      // one workgroup per (row, split): aim for a few workgroups per compute unit, but never split
+      // below 1024 keys -- a second (merge) launch costs more than a short row does
+      const int64_t want = 2048;
+      return (int)std::max<int64_t>(1, std::min<int64_t>((want + rows - 1) / rows, max_len / 1024));
+    }
     // one workgroup per (row tile of 64 or 256 rows, kv head, split)
-    const int g = c.num_q_heads / c.num_kv_heads;
-    const int mrows = p.max_nodes * g;
-    const int rows_per_wg = attn_mfma_tile_rows(mrows);
+    const int last = cap(), tiles_max = (max_nodes * g + tile_rows - 1) / tile_rows;
+    if (batch > 1 && (c.num_kv_heads * tiles_max) % 8 == 0) {
+      // Several sequences, launched longest first within every XCD (see the kernel's workgroup
+      // numbering).  Such a list schedule ends no later than max(longest job, work / units + a job
+      // of the shortest sequence), so: estimate that for every split count, with what a tile's merge costs its last
+      // workgroup (and one stage for every workgroup that finds no keys, where such are launched), and take the cheapest count -- the
+      // fewest splits that still spread the longest sequence wide enough.
+      empty_wgs |= c.num_kv_heads % 8 != 0;
+      double best = 0.0;
+      int nsplit = 1;
+      for (int ns = 1; ns <= last; ns++) {
+        if (ns > 1 && chunk_of(ns) == chunk_of(ns - 1)) continue;  // (keys per split are a multiple of 32: the same plan)
+        const SplitSums& s = split_into(ns);
+        const double merge = s.grid_x > 1 ? 0.7 * s.grid_x * (tile_rows / 128.0) : 0.0;
+        const double empty = empty_wgs ? (double)((int64_t)c.num_kv_heads * tiles_max * s.grid_x * batch - s.jobs) : 0.0;
+        const double cost = s.jobs <= units ? s.longest(merge) : std::max(s.longest(merge), (s.work + s.merged * merge + empty) / units + s.shortest);
+        if (ns == 1 || cost < best - 1e-9) { best = cost; nsplit = ns; }
+      }
+      return nsplit;
+    }
     // Every variant has a ring of more than half of the LDS: one workgroup per compute unit, so the grid
     // should come out just under a whole number of rounds of `units` workgroups.  Take the fewest
     // splits that fill >= 85% of them in whole rounds (fewer splits = fewer partials).
     // efficiency of ns splits: keys swept / (units x whole rounds x keys of a full split)
-    auto workgroups = [&](int ns) {
-      const int chunk = ((p.max_len + ns - 1) / ns + 31) / 32 * 32;
-      int64_t t = 0;
-      for (int b = 0; b < batch; b++) {
-        const int n = node_offsets[b + 1] - node_offsets[b];
-        t += (int64_t)((n * g + rows_per_wg - 1) / rows_per_wg) * c.num_kv_heads * ((kv_len[b] + n + chunk - 1) / chunk);
-      }
-      return t;
-    };
     auto efficiency = [&](int ns) {
-      const int chunk = ((p.max_len + ns - 1) / ns + 31) / 32 * 32;
-      int64_t t = 0, keys = 0;
-      for (int b = 0; b < batch; b++) {
-        const int n = node_offsets[b + 1] - node_offsets[b];
-        const int64_t tl = (int64_t)((n * g + rows_per_wg - 1) / rows_per_wg) * c.num_kv_heads;
-        t += tl * ((kv_len[b] + n + chunk - 1) / chunk);
-        keys += tl * (kv_len[b] + n);
-      }
-      const int64_t rounds = (t + units - 1) / units;
-      return (double)keys / ((double)rounds * units * chunk);
+      const SplitSums& s = split_into(ns);
+      const int64_t rounds = (s.jobs + units - 1) / units;
+      return (double)keys / ((double)rounds * units * s.chunk);
     };
-    const int cap = (int)std::max<int64_t>(1, std::min<int64_t>(max_splits, (p.max_len + 127) / 128));
-    const int tiles_max = (mrows + rows_per_wg - 1) / rows_per_wg;
-    if (batch > 1 && (c.num_kv_heads * tiles_max) % 8 == 0) {
-      // Several sequences, launched longest first within every XCD (see the kernel's workgroup
-      // numbering).  Such a list schedule ends no later than max(longest job, work / units + a job
-      // of the shortest sequence), so: estimate that for every split count, in units of one 64-key
-      // stage, with what a workgroup costs beside its stages (start-up and tail: about six stages;
-      // one that finds no keys, where such are launched: one), and what a tile's merge costs its last
-      // workgroup, and take the cheapest count -- the fewest splits that still spread the longest
-      // sequence wide enough.
-      double best_cost = 0.0;
-      nsplit = 1;
-      for (int ns = 1; ns <= cap; ns++) {
-        const int chunk = ((p.max_len + ns - 1) / ns + 31) / 32 * 32;
-        const int grid_x = (p.max_len + chunk - 1) / chunk;
-        const double merge = grid_x > 1 ? 0.7 * grid_x * (rows_per_wg / 128.0) : 0.0;
-        double work = 0.0, longest = 0.0, shortest = 1e30;
-        int64_t jobs = 0;
-        for (int b = 0; b < batch; b++) {
-          const int n = node_offsets[b + 1] - node_offsets[b];
-          const int len = kv_len[b] + n;
-          const int64_t tl = (int64_t)((n * g + rows_per_wg - 1) / rows_per_wg) * c.num_kv_heads;
-          const int full = len / chunk, rest = len - full * chunk;
-          const double job_full = 6.0 + (chunk + 63) / 64, job_rest = rest > 0 ? 6.0 + (rest + 63) / 64 : 0.0;
-          const int real = full + (rest > 0 ? 1 : 0);
-          work += tl * (full * job_full + job_rest + (real > 1 ? merge : 0.0));
-          if (empty_wgs || c.num_kv_heads % 8 != 0) work += ((int64_t)c.num_kv_heads * tiles_max * grid_x - tl * real) * 1.0;
-          jobs += tl * real;
-          longest = std::max(longest, (full > 0 ? job_full : job_rest) + (real > 1 ? merge : 0.0));
-          shortest = std::min(shortest, full > 0 ? job_full : job_rest);
-        }
-        const double cost = jobs <= units ? longest : std::max(longest, work / units + shortest);
-        if (ns == 1 || cost < best_cost - 1e-9) { best_cost = cost; nsplit = ns; }
-      }
-    } else {
-    nsplit = cap;
+    int nsplit = last;
     double best = -1.0;
-    for (int ns = 1; ns <= cap; ns++) {
+    for (int ns = 1; ns <= last; ns++) {
       const double eff = efficiency(ns);
       if (eff >= 0.85) { nsplit = ns; best = eff; break; }
       if (eff > best) { best = eff; nsplit = ns; }
     }
     // A grid of one round merges cooperatively (no workgroup pulls a whole tile's partials), so
     // there more splits cost next to nothing: take the best-filling count among the one-round ones.
-    if (best >= 0.85 && workgroups(nsplit) <= units) {
-      for (int ns = nsplit + 1; ns <= cap && ns <= 64 && workgroups(ns) <= units; ns++) {
+    if (best >= 0.85 && split_into(nsplit).jobs <= units) {
+      for (int ns = nsplit + 1; ns <= last && ns <= 64 && split_into(ns).jobs <= units; ns++) {
         const double eff = efficiency(ns);
         if (eff > best + 1e-9) { best = eff; nsplit = ns; }
       }
     }
+    return nsplit;
+  }
+
+  // The plan with (about) ns splits.  `precise`: sums in 32 bits whatever the slices' length.
+  Plan cut(int ns, bool precise) const {
+    Plan p{};
+    p.impl = impl;
+    p.max_nodes = max_nodes;
+    p.max_len = max_len;
+    const int most = impl == 1 ? scalar_splits : max_splits;
+    ns = std::max(1, std::min(ns, most));
+    p.chunk = std::max(chunk_of(ns), 32);
+    p.precise = impl == 2 && (precise || precise_sums(c, p.chunk));
+    if (p.precise && c.head_dim == 128 && ns > 1 && ns > most / 2) {
+      // fp32 partial states are twice the size, and the workspace is cut for bf16 ones (longer splits stay precise)
+      ns = std::max(1, most / 2);
+      p.chunk = chunk_of(ns);
     }
+    p.nsplit = (max_len + p.chunk - 1) / p.chunk;
+    if (impl == 2) {
+      // A geometry that the MFMA kernel does not take (blocks that are no power of two, say) goes to the scalar kernel,
+      // whose fp32 partials have room for fewer splits: it is planned as such.
+      AttnParams ap{};
+      ap.Hq = c.num_q_heads;
+      ap.Hkv = c.num_kv_heads;
+      ap.D = c.head_dim;
+      ap.nsplit = p.nsplit;
+      ap.precise = p.precise;
+      ap.kv.block_size = c.block_size;
+      if (!attn_mfma_supports(ap)) {
+        Planner scalar(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets);
+        return scalar.cut(scalar.splits(256, false), false);
+      }
+    }
+    return p;
   }
-  nsplit = std::max(1, std::min(nsplit, max_splits));
-  int chunk = (p.max_len + nsplit - 1) / nsplit;
-  chunk = (chunk + 31) / 32 * 32;
-  p.chunk = std::max(chunk, 32);
-  p.precise = p.impl == 2 && (precise || precise_sums(c, p.chunk));
-  if (p.precise && c.head_dim == 128 && nsplit > 1 && nsplit > max_splits / 2) {
-    // fp32 partial states are twice the size, and the workspace is cut for bf16 ones (longer splits stay precise)
-    nsplit = std::max(1, max_splits / 2);
-    p.chunk = ((p.max_len + nsplit - 1) / nsplit + 31) / 32 * 32;
-  }
-  p.nsplit = (p.max_len + p.chunk - 1) / p.chunk;
-  if (p.impl == 2) {
-    // A geometry that the MFMA kernel does not take (blocks that are no power of two, say) goes to the scalar kernel,
-    // whose fp32 partials have room for fewer splits: it is planned as such.
-    AttnParams ap{};
-    ap.Hq = c.num_q_heads;
-    ap.Hkv = c.num_kv_heads;
-    ap.D = c.head_dim;
-    ap.nsplit = p.nsplit;
-    ap.precise = p.precise;
-    ap.kv.block_size = c.block_size;
-    if (!attn_mfma_supports(ap)) return plan_attention(c, max_splits, scalar_splits, 1, opt_splits, batch, kv_len, node_offsets, units, empty_wgs, precise);
-  }
-  return p;
-}
+  Plan plan(int units, bool empty_wgs) { return cut(splits(units, empty_wgs), false); }
+};
 
 // Workgroups for the logits work of a verification with wide tiles, whose sweep is bound by its arithmetic: the fewest (in XCD
 // rounds, at most 96) that are through with the logits, at about 20 GB/s each, in 0.7 of the time the attention takes: 13 us
@@ -391,27 +424,30 @@ int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, cons
 // one that the measure does not split, whose sums stay in the accumulators to the end, is not split (partial states are bf16).
 Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int opt_logits_wgs, int batch,
                const int32_t* kv_len, const int32_t* node_offsets, bool verification) {
-  auto planned = [&](int units, bool empty_wgs, bool precise, int splits) {
-    return plan_attention(c, max_splits, scalar_splits, opt_impl, splits, batch, kv_len, node_offsets, units, empty_wgs, precise);
-  };
+  Planner planner(c, max_splits, scalar_splits, opt_impl, opt_splits, batch, kv_len, node_offsets);
   // A verification in fp32, or with small tiles, or whose logits hide behind the sweep, is one launch: its first workgroups do the logits work, and the
   // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
   // option does not change the splits and with them the rounding).
-  int max_nodes = 0, n_logits = 0;
-  for (int b = 0; b < batch; b++) max_nodes = std::max(max_nodes, node_offsets[b + 1] - node_offsets[b]);
-  const bool small_tiles = attn_mfma_tile_rows(max_nodes * (c.num_q_heads / c.num_kv_heads)) == 64;
-  const bool f32_tiles = c.qkv_dtype == CB_F32 && opt_impl != 1;
+  int n_logits = 0;
+  const bool wide = planner.tile_rows != kRowTile && !planner.f32_tiles;
   if (!verification) {
-  } else if (small_tiles || f32_tiles) {
+  } else if (!wide) {
     n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
-  } else if (c.qkv_dtype == CB_BF16) {
-    const Plan alone = planned(248, false, false, opt_splits);
+  } else if (planner.impl == 2) {
+    const Plan alone = planner.plan(248, false);
     if (alone.impl == 2) n_logits = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets);
   }
   if (n_logits && opt_logits_wgs > 0) n_logits = opt_logits_wgs;
-  const Plan measure = planned(small_tiles || f32_tiles ? 256 - n_logits : 256, true, false, opt_splits);
-  const bool whole = measure.impl == 2 && measure.nsplit == 1 && !measure.precise;
-  Plan p = planned(256 - n_logits, false, measure.precise, whole ? 1 : opt_splits);
+  Plan p;
+  if (planner.impl == 1) {
+    p = planner.plan(256 - n_logits, false);
+  } else {
+    const int units = wide ? 256 : 256 - n_logits, measured = planner.splits(units, true);
+    const Plan measure = planner.cut(measured, false);
+    const bool whole = measure.impl == 2 && measure.nsplit == 1 && !measure.precise;
+    const bool same = units == 256 - n_logits && (batch == 1 || c.num_kv_heads % 8 != 0);  // (empty_wgs makes no difference)
+    p = planner.cut(whole ? 1 : (same ? measured : planner.splits(256 - n_logits, false)), measure.precise);
+  }
   p.logits_wgs = n_logits;
   return p;
 }
@@ -451,9 +487,9 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
     return L;
   };
   *plan = planned(full.max_splits);
-  const int measured = plan_attention(c, full.max_splits, full.scalar_splits, 0, 0, batch, kv_len, node_offsets, 256, true).nsplit;
+  const int measured = Planner(c, full.max_splits, full.scalar_splits, 0, 0, batch, kv_len, node_offsets).plan(256, true).nsplit;
   const bool by_rows = c.qkv_dtype == CB_F32 || c.head_dim == 64;
-  const size_t measure = by_rows ? fp32_rows(plan_attention(c, full.max_splits, full.max_splits, 1, 0, batch, kv_len, node_offsets).nsplit)
+  const size_t measure = by_rows ? fp32_rows(Planner(c, full.max_splits, full.max_splits, 1, 0, batch, kv_len, node_offsets).plan(256, false).nsplit)
                          : plan->impl == 2 ? tiles(false, 1, measured) : fp32_rows(measured);
   WsLayout L = cut(measure);
   if (L.total > kStaticScratchBytes) return L;
