@@ -417,19 +417,72 @@ int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, cons
   return std::min(96, ((int)(lg / (20e3 * 0.7 * us)) / 8 + 1) * 8);
 }
 
+// What a verification with wide tiles in `ns` splits is expected to take, in us: with `wgs` workgroups of its launch for the logits, or (0)
+// with a launch of their own in front.  A stage of the sweep takes about 1.7 us in tiles of more than 128 rows and 1.0 in smaller ones;
+// a logits workgroup scans about 20 GB/s of bf16 and, bound by its instructions, 40 of fp32.
+double wide_verification_us(Planner& planner, int ns, int wgs) {
+  const cb_config& c = planner.c;
+  const SplitSums& s = planner.split_into(ns);
+  const double stage = std::min(planner.tile_rows, planner.max_nodes * planner.g) > 128 ? 1.7 : 1.0, memory = 5.5e6;  // (bytes a us)
+  const double lb = c.logits_dtype == CB_F32 ? 4 : 2, lg = (double)planner.node_offsets[planner.batch] * c.vocab_size * lb;
+  double kv = 0.0;
+  for (int b = 0; b < planner.batch; b++) kv += (double)planner.len[b] * c.num_kv_heads * c.head_dim * 4;
+  const double merge = planner.batch > 1 && s.grid_x > 1 ? 0.8 * s.grid_x : 0.0, scan = wgs ? lg / (wgs * lb * 10e3) / stage : 0.0;
+  double stages = std::max(s.longest(merge), scan);
+  if (s.jobs + wgs > 256) {
+    // (a batch's longest-first schedule, the logits' workgroups in front, ends between work / units and that plus its shortest job)
+    if (planner.batch == 1) stages = (double)((s.jobs + wgs + 255) / 256) * s.longest(merge);
+    else stages = std::max(stages, (s.work + s.merged * merge + wgs * scan) / 256 + 0.5 * s.shortest);
+  }
+  return std::max(stages * stage, (kv + (wgs ? lg : 0.0)) / memory) + (wgs ? 0.0 : lg / 5e6 + 4.0);
+}
+
+// The split count of a verification with wide tiles and the workgroups of its launch for the logits (0: a launch of their own),
+// chosen among few by what they are expected to take.  `beside` splits are planned for the units that n workgroups leave, `alone` for all
+// of them.
+// One sequence keeps to one round of workgroups, the logits' among them, so that its splits are merged cooperatively: 72 rows of 40
+// heads x 3303 keys, 128256 entries: 360 workgroups beside 64 for the logits 41 us a pass, 160 beside 64 28.8, 240 behind a logits launch 35.8;
+// 880 rows of 32/8 heads x 3183 keys: 352 beside 72 51.8, 160 beside 72 41, 256 behind a launch 43.4.  In a batch of several rounds
+// the logits' workgroups are jobs of the schedule like the others, and units are free again when they are through: 6 sequences of
+// up to 5247 keys, 32/8 heads x 92 nodes: two splits beside 40 90 us, three 72, three behind a launch 80; 8 of up to 1829 keys, 32 heads x
+// 225 nodes: one split each behind a launch 117, beside 96 126.
+int wide_verification_splits(Planner& planner, int alone, int beside, int n, bool whole, int forced_wgs, int* logits_wgs) {
+  const cb_config& c = planner.c;
+  auto share = [&](int ns) {
+    const int wgs = fused_wide_logits_wgs(c, planner.cut(ns, false), planner.batch, planner.kv_len, planner.node_offsets);
+    return wgs && forced_wgs > 0 ? forced_wgs : wgs;
+  };
+  if (planner.batch == 1 && n && planner.split_into(beside).jobs + n > 256 && planner.split_into(1).jobs + n <= 256) {
+    for (beside = 1; beside < planner.cap() && planner.split_into(beside + 1).jobs + n <= 256;) beside++;
+  }
+  struct { int ns, wgs; } const options[] = {{whole ? 1 : (n ? alone : beside), 0}, {whole ? 1 : beside, whole ? share(1) : n}, {alone, planner.batch > 1 && !whole ? share(alone) : 0}};
+  double best = 0.0;
+  int nsplit = 0;
+  for (const auto& o : options) {
+    if (nsplit != 0 && o.wgs == 0) continue;
+    const double us = wide_verification_us(planner, o.ns, o.wgs);
+    if (nsplit != 0 && us >= best) continue;
+    best = us;
+    nsplit = o.ns;
+    *logits_wgs = o.wgs;
+  }
+  return nsplit;
+}
+
 // The plan of a call, a verification or the attention alone.
-// What a call holds in 32 bits is a property of its shape that callers rely on, so it is decided by one measure, whatever the
+// What a call holds in 32 bits is a property of its shape that callers rely on, so it is decided by measures of the shape, whatever the
 // kernels would like to have: the splits planned as if the logits never rode beside wide tiles and a batch's grid held a
-// workgroup for every split of its longest sequence (empty_wgs).  A call is precise where the slices of that plan are long, or its own;
-// one that the measure does not split, whose sums stay in the accumulators to the end, is not split (partial states are bf16).
+// workgroup for every split of its longest sequence (empty_wgs), and those planned without either.  A call is precise where the
+// slices of one of them are long; one that a measure does not split, whose sums stay in the accumulators to the end, is not
+// split (partial states are bf16).
 Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int opt_logits_wgs, int batch,
                const int32_t* kv_len, const int32_t* node_offsets, bool verification) {
   Planner planner(c, max_splits, scalar_splits, opt_impl, opt_splits, batch, kv_len, node_offsets);
   // A verification in fp32, or with small tiles, or whose logits hide behind the sweep, is one launch: its first workgroups do the logits work, and the
   // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
   // option does not change the splits and with them the rounding).
-  int n_logits = 0;
   const bool wide = planner.tile_rows != kRowTile && !planner.f32_tiles;
+  int n_logits = 0;
   if (!verification) {
   } else if (!wide) {
     n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
@@ -443,10 +496,15 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
     p = planner.plan(256 - n_logits, false);
   } else {
     const int units = wide ? 256 : 256 - n_logits, measured = planner.splits(units, true);
-    const Plan measure = planner.cut(measured, false);
-    const bool whole = measure.impl == 2 && measure.nsplit == 1 && !measure.precise;
     const bool same = units == 256 - n_logits && (batch == 1 || c.num_kv_heads % 8 != 0);  // (empty_wgs makes no difference)
-    p = planner.cut(whole ? 1 : (same ? measured : planner.splits(256 - n_logits, false)), measure.precise);
+    int nsplit = same ? measured : planner.splits(256 - n_logits, false);
+    const Plan m0 = planner.cut(measured, false), m1 = same ? m0 : planner.cut(nsplit, false);
+    const bool precise = m0.precise || m1.precise, whole = (m0.impl == 2 && m0.nsplit == 1 && !m0.precise) || m1.nsplit == 1;
+    if (whole) nsplit = 1;
+    if (verification && wide && opt_splits <= 0 && m1.impl == 2) {
+      nsplit = wide_verification_splits(planner, measured, nsplit, n_logits, whole, opt_logits_wgs, &n_logits);
+    }
+    p = planner.cut(nsplit, precise);
   }
   p.logits_wgs = n_logits;
   return p;

@@ -52,3 +52,22 @@ WHOLE = [  # heads, kv heads, lengths, nodes, verification
 @pytest.mark.parametrize("hq,hkv,lens,nodes,verification", WHOLE)
 def test_sequences_that_fill_the_chip_are_not_split(hq, hkv, lens, nodes, verification, block):
     assert plan(hq, hkv, lens, nodes, block, verification=verification)["nsplit"] == 1
+
+
+# One sequence with wide tiles: a launch of one round, the logits' workgroups among them, merges its splits cooperatively.  (In
+# two rounds, or with the chip half empty, these were slower than with a launch for the logits in front.)
+@pytest.mark.parametrize("hq,hkv,length,nodes,vocab,logits", [
+    (40, 40, 3303, 72, 128256, "bf16"), (40, 40, 4539, 116, 33333, "bf16"), (32, 8, 3183, 220, 32000, "f32"), (32, 32, 1759, 170, 32000, "bf16"),
+    (40, 40, 987, 120, 32000, "f32"), (32, 8, 8192, 128, 32000, "bf16"), (40, 40, 65536, 256, 128256, "bf16")])
+def test_one_sequence_stays_in_one_round(hq, hkv, length, nodes, vocab, logits):
+    p = plan(hq, hkv, [length], nodes, vocab=vocab, logits=logits)
+    grid = -(-nodes * (hq // hkv) // 256) * hkv * p["nsplit"] + p["logits_wgs"]
+    assert p["fused"] and 200 <= grid <= 256, p
+
+
+def test_batches_do_not_split_less_for_the_logits():
+    # as many workgroups as compute units: the logits go in front, instead of a second round
+    p = plan(32, 32, steps(1829 - 7 * 60, 60, 8), steps(155, 10, 8))
+    assert (p["nsplit"], p["fused"]) == (1, 0), p
+    # three splits each, in a round that leaves no units for the logits
+    assert plan(32, 8, [5247, 1919, 4943, 2931, 2578, 2294], [92, 92, 92, 92, 92, 92], vocab=33333)["nsplit"] == 3
