@@ -392,7 +392,9 @@ struct Planner {
 
 // Workgroups for the logits work of a verification with wide tiles, whose sweep is bound by its arithmetic: the fewest (in XCD
 // rounds, at most 96) that are through with the logits, at about 20 GB/s each, in 0.7 of the time the attention takes: 13 us
-// beside the sweep and, per 32 keys, 0.95 us with a tile of more than 128 rows and 0.55 with a smaller one.  Fewer keep the
+// beside the sweep and, per 32 keys, 0.95 us with a tile of more than 128 rows and 0.55 with a smaller one.  Where rows are short a
+// wave's round trip for each bounds them, 2.1 us (kLogitsItemUs for its workgroup): 2080 rows of 1000 entries beside 16 sequences of up
+// to 1300 keys, 32 heads: 8 workgroups 139 us, 16 80, 48 78, a launch of their own 85.  Fewer keep the
 // launch (a pass of 8 sequences of 32/8 heads with 250 rows of 33333 entries: 32 workgroups 41.7 us, 48 33.7; 128 rows
 // of 32000 over 8192 keys: 8 44.5, 16 34.0, 24 33.5), more take compute units from the sweep (the batch with 96: 38.4).
 // 0: a launch of their own, where the logits are more than 2.5 times the K/V bytes.  One launch gains 8 us a pass on short
@@ -401,7 +403,8 @@ struct Planner {
 // 0 too for tiles of up to 128 rows in several rounds of workgroups, unless their sums are in 32 bits: those sweeps are bound by
 // memory (5.5 TB/s), and logits beside them only delay the longest sequences (16 paged sequences of up to 16384 keys with 32 to
 // 96 nodes, 32 heads, a step: 443 us in one launch, 433 in two; with 32-bit sums 629 and 641).
-int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, const int32_t* kv_len, const int32_t* node_offsets) {
+constexpr double kLogitsItemUs = 2.1 / 4;
+int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, const int32_t* kv_len, const int32_t* node_offsets, double item_us) {
   const double lb = c.logits_dtype == CB_F32 ? 4 : 2;
   const int g = c.num_q_heads / c.num_kv_heads, rows = std::min(attn_mfma_tile_rows(alone.max_nodes * g), alone.max_nodes * g);
   double slots = 0, jobs = 0;
@@ -414,7 +417,8 @@ int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, cons
   if (lg > 2.5 * kv) return 0;
   if (rows <= 128 && !alone.precise && jobs > 256) return 0;
   const double us = 13.0 + alone.chunk / 32 * (rows > 128 ? 0.95 : 0.55) * std::max(1.0, jobs / 256);
-  return std::min(96, ((int)(lg / (20e3 * 0.7 * us)) / 8 + 1) * 8);
+  const double items = (double)node_offsets[batch] * ((c.vocab_size + kArgmaxChunk - 1) / kArgmaxChunk);
+  return std::min(96, ((int)(std::max(lg / 20e3, items * item_us) / (0.7 * us)) / 8 + 1) * 8);
 }
 
 // What a verification with wide tiles in `ns` splits is expected to take, in us: with `wgs` workgroups of its launch for the logits, or (0)
@@ -427,7 +431,8 @@ double wide_verification_us(Planner& planner, int ns, int wgs) {
   const double lb = c.logits_dtype == CB_F32 ? 4 : 2, lg = (double)planner.node_offsets[planner.batch] * c.vocab_size * lb;
   double kv = 0.0;
   for (int b = 0; b < planner.batch; b++) kv += (double)planner.len[b] * c.num_kv_heads * c.head_dim * 4;
-  const double merge = planner.batch > 1 && s.grid_x > 1 ? 0.8 * s.grid_x : 0.0, scan = wgs ? lg / (wgs * lb * 10e3) / stage : 0.0;
+  const double merge = planner.batch > 1 && s.grid_x > 1 ? 0.8 * s.grid_x : 0.0, items = (double)planner.node_offsets[planner.batch] * ((c.vocab_size + kArgmaxChunk - 1) / kArgmaxChunk);
+  const double scan = wgs ? std::max(lg / (lb * 10e3), items * kLogitsItemUs) / wgs / stage : 0.0;
   double stages = std::max(s.longest(merge), scan);
   if (s.jobs + wgs > 256) {
     // (a batch's longest-first schedule, the logits' workgroups in front, ends between work / units and that plus its shortest job)
@@ -449,7 +454,7 @@ double wide_verification_us(Planner& planner, int ns, int wgs) {
 int wide_verification_splits(Planner& planner, int alone, int beside, int n, bool whole, int forced_wgs, int* logits_wgs) {
   const cb_config& c = planner.c;
   auto share = [&](int ns) {
-    const int wgs = fused_wide_logits_wgs(c, planner.cut(ns, false), planner.batch, planner.kv_len, planner.node_offsets);
+    const int wgs = fused_wide_logits_wgs(c, planner.cut(ns, false), planner.batch, planner.kv_len, planner.node_offsets, kLogitsItemUs);
     return wgs && forced_wgs > 0 ? forced_wgs : wgs;
   };
   if (planner.batch == 1 && n && planner.split_into(beside).jobs + n > 256 && planner.split_into(1).jobs + n <= 256) {
@@ -482,15 +487,18 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
   // attention is planned for the compute units they leave (with option "fuse_logits" = 0 too, so that the
   // option does not change the splits and with them the rounding).
   const bool wide = planner.tile_rows != kRowTile && !planner.f32_tiles;
-  int n_logits = 0;
+  int n_logits = 0, n_launched = 0;
   if (!verification) {
   } else if (!wide) {
     n_logits = fused_logits_wgs(c, batch, kv_len, node_offsets);
   } else if (planner.impl == 2) {
     const Plan alone = planner.plan(248, false);
-    if (alone.impl == 2) n_logits = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets);
+    if (alone.impl == 2) {
+      n_logits = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets, 0.0);  // (as the measure has it: by bytes)
+      n_launched = fused_wide_logits_wgs(c, alone, batch, kv_len, node_offsets, kLogitsItemUs);
+    }
   }
-  if (n_logits && opt_logits_wgs > 0) n_logits = opt_logits_wgs;
+  if (n_logits && opt_logits_wgs > 0) n_logits = n_launched = opt_logits_wgs;
   Plan p;
   if (planner.impl == 1) {
     p = planner.plan(256 - n_logits, false);
@@ -502,7 +510,9 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
     const bool precise = m0.precise || m1.precise, whole = (m0.impl == 2 && m0.nsplit == 1 && !m0.precise) || m1.nsplit == 1;
     if (whole) nsplit = 1;
     if (verification && wide && opt_splits <= 0 && m1.impl == 2) {
-      nsplit = wide_verification_splits(planner, measured, nsplit, n_logits, whole, opt_logits_wgs, &n_logits);
+      nsplit = wide_verification_splits(planner, measured, nsplit, n_launched, whole, opt_logits_wgs, &n_logits);
+    } else if (wide) {
+      n_logits = n_launched;
     }
     p = planner.cut(nsplit, precise);
   }

@@ -71,3 +71,11 @@ def test_batches_do_not_split_less_for_the_logits():
     assert (p["nsplit"], p["fused"]) == (1, 0), p
     # three splits each, in a round that leaves no units for the logits
     assert plan(32, 8, [5247, 1919, 4943, 2931, 2578, 2294], [92, 92, 92, 92, 92, 92], vocab=33333)["nsplit"] == 3
+
+
+def test_short_logits_rows_get_workgroups_by_their_number():
+    """A wave's round trip for each row bounds short rows, whatever few bytes they have."""
+    lens, nodes = steps(40, 84, 16), steps(60, 9, 16)
+    short, long_rows = plan(32, 32, lens, nodes, vocab=1000), plan(32, 32, lens, nodes, vocab=8000)
+    assert short["fused"] and 16 <= short["logits_wgs"] <= 96, short
+    assert long_rows["logits_wgs"] >= short["logits_wgs"]
