@@ -47,45 +47,100 @@ def device_asm(src: str) -> str:
         return f.read()
 
 
-_REG = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")
+_VREG = re.compile(r"\bv(?:\[(\d+):(\d+)\]|(\d+)\b)")
+_SREG = re.compile(r"\bs(?:\[(\d+):(\d+)\]|(\d+)\b)")
+
+
+def _ranges(pattern, code: str) -> list:
+    return [(int(m[1]), int(m[2])) if m[1] else (int(m[3]), int(m[3])) for m in pattern.finditer(code)]
+
+
+class _Listing:
+    """The instructions of an assembly listing and where each can go on: `code` without comments, `jump(i)` the target of a
+    branch (long ones are an s_setpc_b64 behind the address arithmetic that names the label), `falls(i)` whether the next line
+    can follow."""
+
+    def __init__(self, asm: str):
+        self.code = [line.split(";")[0].strip() for line in asm.split("\n")]
+        self.labels = {m[1]: i for i, c in enumerate(self.code) if (m := re.match(r"(\.?\w+):", c))}
+        self.regs, self.sregs = {}, {}
+
+    def jump(self, i: int):
+        c = self.code[i]
+        if m := re.match(r"s_c?branch\w* (\.?\w+)", c):
+            return self.labels[m[1]]
+        if c.startswith("s_setpc_b64"):
+            for j in range(i - 1, max(i - 10, -1), -1):
+                if m := re.search(r"(\.LBB\w+)-", self.code[j]):
+                    return self.labels[m[1]]
+            raise RuntimeError(f"line {i + 1}: jump to an unknown place")
+        return None
+
+    def falls(self, i: int) -> bool:
+        return i + 1 < len(self.code) and not re.match(r"s_(branch|setpc_b64|endpgm)", self.code[i])
+
+    def vregs(self, i: int) -> list:
+        if i not in self.regs:
+            self.regs[i] = _ranges(_VREG, self.code[i])
+        return self.regs[i]
+
+    def flags(self, i: int, known: frozenset) -> frozenset:
+        """What line i makes of the scalar pairs known to hold 0 or -1 (and "vcc", known to be zero or not).  A wait that the
+        source skips on a condition is often guarded by such a pair, set where the condition was evaluated."""
+        c = self.code[i]
+        if m := re.match(r"s_mov_b64 s\[(\d+):\d+\], (0|-1)$", c):
+            lo = int(m[1])
+            return frozenset([(k, v) for k, v in known if k == "vcc" or abs(k - lo) > 1] + [(lo, m[2] == "-1")])
+        if not known or c.startswith("s_cbranch"):
+            return known
+        if m := re.match(r"s_(andn2|and)_b64 vcc, exec, s\[(\d+):\d+\]$", c):
+            pairs = {k: v for k, v in known if k != "vcc"}
+            if int(m[2]) in pairs:  # (some lane is active)
+                pairs["vcc"] = pairs[int(m[2])] != (m[1] == "andn2")
+            return frozenset(pairs.items())
+        if i not in self.sregs:
+            self.sregs[i] = _ranges(_SREG, c), "vcc" in c
+        named, vcc = self.sregs[i]
+        return frozenset((k, v) for k, v in known if (not vcc if k == "vcc" else not any(a <= k + 1 and b >= k for a, b in named)))
 
 
 def untracked_load_violations(asm: str) -> list:
-    """The attention kernel issues some loads as inline assembly the compiler does not know to be
-    loads, and waits for them itself before their first use.  That is only right while the compiler
-    leaves the destination registers alone in between (a copy or a spill would read them before
-    the data is there).  For every such load (a global_load_dwordx4 inside an inline-assembly
-    block) this walks down the listing to the first instruction that names one of its registers
-    and reports the load if no vmcnt wait and no branch (where the walk cannot follow) came
-    before it.  Returns a list of (line number, text) pairs, empty if all is well."""
-    lines = asm.split("\n")
+    """The attention kernels issue some loads as inline assembly the compiler does not know to be
+    loads, and wait for them themselves before their first use.  That is only right while the compiler
+    leaves the destination registers alone in between (a copy or a spill, to memory or to an accumulation register, would
+    read them before the data is there).  For every such load (a global_load_dwordx4 inside an inline-assembly
+    block) this follows the listing along both sides of every branch up to the first vmcnt wait, and reports
+    the load if an instruction on the way names one of its registers.  Returns a list of (line number, text) pairs, empty if
+    all is well."""
+    lst = _Listing(asm)
     bad = []
     in_asm = False
-    for i, line in enumerate(lines):
-        if "ASMSTART" in line:
-            in_asm = True
-            continue
-        if "ASMEND" in line:
-            in_asm = False
+    for i, line in enumerate(asm.split("\n")):
+        if "ASMSTART" in line or "ASMEND" in line:
+            in_asm = "ASMSTART" in line
             continue
         # (every register-returning load spelling: the query rows' and the logits item's 16-byte loads today)
         m = re.search(r"(?:global|buffer|flat)_load_dword(?:x[234])? v\[(\d+):(\d+)\]", line) if in_asm else None
         if not m:
             continue
         lo, hi = int(m.group(1)), int(m.group(2))
-        covered = False
-        for j in range(i + 1, len(lines)):
-            code = lines[j].split(";")[0]
-            if "s_waitcnt vmcnt" in code or re.search(r"\bs_(c?branch|endpgm)", code):
-                covered = True
-                break
-            touched = False
-            for r in _REG.finditer(code):
-                a, b = (int(r.group(1)), int(r.group(2))) if r.group(1) else (int(r.group(3)),) * 2
-                touched |= a <= hi and b >= lo
-            if touched:
-                break
-        if not covered:
+        seen, todo, touched = set(), [(i + 1, frozenset())] if lst.falls(i) else [], False
+        while todo and not touched:
+            j, known = todo.pop()
+            if (j, known) in seen:
+                continue
+            seen.add((j, known))
+            if lst.code[j].startswith("s_waitcnt") and "vmcnt" in lst.code[j]:
+                continue
+            touched = any(a <= hi and b >= lo for a, b in lst.vregs(j))
+            after, target = lst.flags(j, known), lst.jump(j)
+            vcc = dict(known).get("vcc") if re.match(r"s_cbranch_vccn?z", lst.code[j]) else None
+            taken = None if vcc is None else vcc == lst.code[j].startswith("s_cbranch_vccnz")
+            if target is not None and taken is not False:
+                todo.append((target, after))
+            if lst.falls(j) and taken is not True:
+                todo.append((j + 1, after))
+        if touched:
             bad.append((i + 1, line.strip()))
     return bad
 
@@ -131,12 +186,12 @@ def kernel_resources(asm: str) -> dict:
     return out
 
 
-def scratch_violations(asm: str) -> list:
-    """Kernels of the listing that use scratch memory (the listing's spill count is not looked at: it also counts
-    vector registers kept in accumulation registers, which no memory access serves).  In the attention kernel a spill
+def scratch_violations(asm: str, file_name: str = "") -> list:
+    """Kernels of the listing that spill registers or use scratch memory.  In the attention kernel a spill
     reload from memory inside the K/V ring phase would be a compiler-generated load, and with it a wait for every load in
-    flight, in a loop whose waits are counted by hand."""
-    return [(k, v) for k, v in kernel_resources(asm).items() if v[2] != 0]
+    flight, in a loop whose waits are counted by hand.  In files with flags of their own (FILE_FLAGS) the listing's spill count
+    also holds vector registers kept in accumulation registers, which no memory access serves: there it is not looked at."""
+    return [(k, v) for k, v in kernel_resources(asm).items() if v[2] != 0 or (v[1] != 0 and file_name not in FILE_FLAGS)]
 
 
 def build(verbose: bool = False) -> str:
@@ -152,9 +207,9 @@ def build(verbose: bool = False) -> str:
         bad = scalar_base_violations(asm)
         if bad:
             raise RuntimeError(f"{name}: loads too close behind a possible write of their scalar base: {bad[:4]}")
-        bad = scratch_violations(asm)
+        bad = scratch_violations(asm, name)
         if bad:
-            raise RuntimeError(f"{name}: kernels that use scratch memory: {bad[:4]}")
+            raise RuntimeError(f"{name}: kernels that spill or use scratch memory: {bad[:4]}")
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     if verbose:
         print(LIB)

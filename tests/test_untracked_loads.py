@@ -1,6 +1,8 @@
 """Host-side check of the build's guard for loads issued as uninterpreted inline assembly
 (build.untracked_load_violations): it accepts the kernel as compiled and catches a planted early use."""
+import functools
 import os
+import re
 import shutil
 
 import pytest
@@ -37,9 +39,51 @@ def test_checker_ignores_loads_the_compiler_tracks():
     assert build.untracked_load_violations(text) == []
 
 
+BRANCHES = """
+\t;;#ASMSTART
+\tglobal_load_dwordx4 v[6:9], v[2:3], off
+\t;;#ASMEND
+\ts_mov_b64 s[2:3], -1
+\ts_cbranch_scc1 .LBB0_2
+\ts_waitcnt vmcnt(4)
+\ts_mov_b64 s[2:3], 0
+.LBB0_2:
+%s\ts_andn2_b64 vcc, exec, s[2:3]
+\ts_cbranch_vccnz .LBB0_4
+\ts_waitcnt vmcnt(0)
+.LBB0_4:
+\tv_accvgpr_write_b32 a0, v7
+\ts_endpgm
+"""
+
+
+def test_checker_follows_both_sides_of_a_branch():
+    wait, skipped = "\ts_waitcnt vmcnt(0)\n", "\ts_cbranch_execz .LBB0_9\n\ts_waitcnt vmcnt(0)\n.LBB0_9:\n"
+    body = "\t;;#ASMSTART\n\tglobal_load_dwordx4 v[6:9], v[2:3], off\n\t;;#ASMEND\n%s\tv_mov_b32_e32 v40, v7\n\ts_endpgm\n"
+    assert build.untracked_load_violations(body % wait) == []
+    assert len(build.untracked_load_violations(body % skipped)) == 1
+    assert len(build.untracked_load_violations(body % "\ts_branch .LBB0_9\n\ts_waitcnt vmcnt(0)\n.LBB0_9:\n")) == 1
+    loop = ".LBB0_9:\n\tv_add_u32_e32 v10, v11, v12\n\ts_cbranch_scc1 .LBB0_9\n"
+    assert build.untracked_load_violations(body % (loop + wait)) == []
+    assert len(build.untracked_load_violations(body % loop)) == 1
+    far = "\ts_getpc_b64 s[8:9]\n.Lpost_getpc0:\n\ts_add_u32 s8, s8, (.LBB0_9-.Lpost_getpc0)&4294967295\n\ts_setpc_b64 s[8:9]\n" + wait + ".LBB0_9:\n"
+    assert len(build.untracked_load_violations(body % far)) == 1
+
+
+@pytest.mark.parametrize("between,ok", [("", True), ("\ts_mov_b64 s[2:3], 0\n", False), ("\ts_xor_b64 s[2:3], s[2:3], s[4:5]\n", False),
+                                        ("\tv_cmp_lt_i32_e64 s[2:3], -1, v51\n", False), ("\ts_mov_b32 s3, s8\n", False), ("\ts_mov_b64 s[4:5], 0\n", True)])
+def test_checker_knows_a_flag_that_skips_a_wait_already_made(between, ok):
+    assert (build.untracked_load_violations(BRANCHES % between) == []) == ok
+
+
+@functools.lru_cache(maxsize=None)
+def _asm(name):
+    return build.device_asm(os.path.join(build.CSRC, name))
+
+
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 def test_compiled_attention_kernel_passes():
-    asm = build.device_asm(os.path.join(build.CSRC, "cb_attn_mfma.hip"))
+    asm = _asm("cb_attn_mfma.hip")
     assert asm.count("global_load_lds_dwordx4") > 50          # the ring's requests are there, as inline assembly
     assert build.untracked_load_violations(asm) == []
     res = build.kernel_resources(asm)
@@ -47,6 +91,30 @@ def test_compiled_attention_kernel_passes():
     assert len(attn) == 8                                      # four variants, each with and without the timeline stamps
     assert build.scratch_violations(asm) == []
     assert all(v[0] <= 256 for v in attn.values())             # two waves per SIMD
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_compiled_wide_kernel_passes():
+    """Its queries go to accumulation registers: behind the ring's wait, never in front of it."""
+    name = "cb_attn_wide.hip"
+    asm = _asm(name)
+    assert asm.count("global_load_lds_dwordx4") > 50
+    assert build.untracked_load_violations(asm) == [] and build.scalar_base_violations(asm) == []
+    res = build.kernel_resources(asm)
+    assert len(res) == 24                                      # head_dim and sums (3), contiguous or paged, alone or with the logits, timeline
+    assert build.scratch_violations(asm, name) == []
+    assert all(v[0] <= 512 for v in res.values())              # one wave per SIMD
+    # the first kernel's first query register moved to an accumulation register in front of its wait, in the common block
+    # behind a loop or at the load
+    lines = asm.split("\n")
+    load = next(i for i, c in enumerate(lines) if re.search(r"global_load_dwordx4 v\[\d+:\d+\]", c) and "ASMSTART" in lines[i - 1])
+    reg = re.search(r"v\[(\d+):", lines[load])[1]
+    last = next(i for i in range(load, len(lines)) if re.search(rf"v_accvgpr_write_b32 a\d+, v{reg}\b", lines[i]))
+    wait = max(i for i in range(load, last) if re.match(r"\s*s_waitcnt vmcnt", lines[i]))
+    for at in (load + 2, max(i for i in range(load, wait) if re.match(r"\.LBB", lines[i])) + 1):
+        planted = lines[:at] + [f"\tv_accvgpr_write_b32 a200, v{reg}"] + lines[at:]
+        bad = build.untracked_load_violations("\n".join(planted))
+        assert load + 1 in [line for line, _ in bad], at
 
 
 def test_scratch_checker_reports_spills():
@@ -62,6 +130,9 @@ def test_scratch_checker_reports_spills():
 """
     assert build.kernel_resources(meta) == {"k_good": (200, 0, 0), "k_spills": (256, 216, 864)}
     assert [k for k, _ in build.scratch_violations(meta)] == ["k_spills"]
+    kept = meta.replace("864", "0")                            # registers kept in others
+    assert [k for k, _ in build.scratch_violations(kept, "cb_attn_mfma.hip")] == ["k_spills"]
+    assert build.scratch_violations(kept, "cb_attn_wide.hip") == []
 
 
 BASE_LISTING = """
@@ -85,9 +156,9 @@ def test_checker_counts_wait_states_before_a_scalar_base(between, ok):
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
-@pytest.mark.parametrize("name", ["cb_attn_mfma.hip", "cb_attn_wide.hip"])
+@pytest.mark.parametrize("name", ["cb_attn_mfma.hip"])  # (the wide kernel's requests have no scalar base)
 def test_compiled_requests_keep_their_distance_from_the_base(name):
-    asm = build.device_asm(os.path.join(build.CSRC, name))
+    asm = _asm(name)
     assert asm.count(", s[") > 0 and "global_load_lds_dwordx4" in asm
     assert build.scalar_base_violations(asm) == []
 
