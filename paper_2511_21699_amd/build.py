@@ -197,10 +197,12 @@ def scratch_violations(asm: str, file_name: str = "") -> list:
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(_compile, srcs))
-    for name in ("cb_attn_mfma.hip", "cb_attn_wide.hip"):
-        asm = device_asm(os.path.join(CSRC, name))
+    checked = ["cb_attn_mfma.hip", "cb_attn_wide.hip"]
+    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + len(checked))) as ex:
+        listings = [ex.submit(device_asm, os.path.join(CSRC, name)) for name in checked]  # (the longest first, beside the compilation)
+        objs = list(ex.map(_compile, sorted(srcs, key=lambda s: os.path.basename(s) not in checked)))
+    for name, listing in zip(checked, listings):
+        asm = listing.result()
         bad = untracked_load_violations(asm)
         if bad:
             raise RuntimeError(f"{name}: registers of untracked loads are touched before their wait: {bad[:4]}")
