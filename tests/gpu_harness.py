@@ -74,7 +74,7 @@ def run_case(case, rows=None, layout=B.CB_LAYOUT_TOKEN_MAJOR, options=None, max_
         out, acc_len, acc_tok = ver.verify_tree(dc.q, dc.kv, case.kv_len, case.node_offsets, case.parent,
                                                 case.tokens, dc.logits)
         torch.cuda.synchronize()
-        status = ver.device_status()
+        status, info = ver.device_status(), ver.last_launch_info()
         assert status & 3 == 0                   # bits 0-1: tree problems; bits 4 and 5 only report how a merge went
         assert status & expect_status == expect_status, f"{what}: device status {status}, expected bits {expect_status}"
         # ---- argmax / acceptance: bit-exact
@@ -107,6 +107,6 @@ def run_case(case, rows=None, layout=B.CB_LAYOUT_TOKEN_MAJOR, options=None, max_
                 k_gpu, v_gpu = k_gpu.swapaxes(1, 2), v_gpu.swapaxes(1, 2)
             assert np.array_equal(k_gpu.view(np.uint8 if False else k_gpu.dtype), k_ref), f"{what}: compacted K differs"
             assert np.array_equal(v_gpu, v_ref), f"{what}: compacted V differs"
-        return dict(scale_free_err=sf, accepted=[int(x) for x in acc_len])
+        return dict(scale_free_err=sf, accepted=[int(x) for x in acc_len], info=info)
     finally:
         ver.close()

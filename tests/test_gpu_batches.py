@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("hkv,g", [(8, 1), (16, 4), (8, 5), (4, 4), (2, 8), (3, 2)])
 @pytest.mark.parametrize("sizes,lens", [([1, 64, 3, 64], [900, 0, 900, 31]), ([100, 7, 150], [5, 1300, 640]), ([256, 1], [64, 2000]),
-                                        ([20] * 11, [37 * i for i in range(11)])])
+                                        ([20] * 11, [37 * i for i in range(11)]),
+                                        ([1 + 5 * i % 17 for i in range(64)], [29 * i * i % 641 for i in range(64)])])  # as many as a call can have
 @pytest.mark.parametrize("splits", [0, 1, 5])
 def test_every_tile_of_a_batch(hkv, g, sizes, lens, splits):
     rng = np.random.default_rng(len(sizes) + hkv)

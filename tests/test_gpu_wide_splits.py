@@ -30,11 +30,19 @@ def test_blocks_beside_a_request(block, D, n, g, monkeypatch):
     run_case(case, rows=sample_rows(case, 60), options={"splits": 2}, what=f"block {block} D={D} rows {n * g}")
 
 
-# splits of the tile x how they are merged: cooperatively (two pieces each, four, several rounds), by the last to arrive, by a kernel
-@pytest.mark.parametrize("splits", [2, 4, 9, 17, 30])
-@pytest.mark.parametrize("options", [{}, {"coop_merge": 0}, {"external_merge": 1}, {"merge_spin_limit": 0}])
+# (splits, 32-key units that make them real: rounded up to whole units a split's keys give that number of splits) x how they are
+# merged: cooperatively, by the last to arrive, by a kernel, cooperatively but every workgroup gives up.  A bf16 merge has up to 16
+# slots in flight: 9 and 14 leave part of a batch, 17 and 31 take a second one.  The 128 pieces of 244 rows at head_dim 128 are merged
+# four at a time up to 15 splits, two beyond.
+@pytest.mark.parametrize("splits,units", [(2, 62), (4, 62), (9, 63), (14, 56), (17, 51), (31, 62)])
+@pytest.mark.parametrize("options,merge", [({}, "cooperative"), ({"coop_merge": 0}, None), ({"external_merge": 1}, "merge_kernel"),
+                                           ({"merge_spin_limit": 0}, "cooperative")])
 @pytest.mark.parametrize("D,n,g", [(128, 61, 4), (128, 90, 1), (64, 75, 3)])
-def test_merges_of_wide_tiles(splits, options, D, n, g):
+def test_merges_of_wide_tiles(splits, units, options, merge, D, n, g):
     par = W.random_tree(np.random.default_rng(splits), n, 4, 7, False)[0]
-    case = W.custom_case(5900 + splits, "bf16", 1, 2 * g, 2, D, 300, [32 * 31 - n], [par], q_scale=2.0)
-    run_case(case, rows=sample_rows(case, 60), options=dict(options, splits=splits), what=f"{splits} splits {options} D={D} rows {n * g}")
+    case = W.custom_case(5900 + splits, "bf16", 1, 2 * g, 2, D, 300, [32 * units - n], [par], q_scale=2.0)
+    info = run_case(case, rows=sample_rows(case, 60), options=dict(options, splits=splits), what=f"{splits} splits {options} D={D} rows {n * g}")["info"]
+    if merge is None:  # (a tile's partial states beyond 320 KiB go to the kernel: what one workgroup would pull takes longer)
+        tile = 32 * D * (4 if D == 64 else 2) + 32 * 8
+        merge = "merge_kernel" if splits * -(-n * g // 32) * tile > 320 * 1024 else "last_arrival"
+    assert (info["nsplit"], info["merge"]) == (splits, merge), info

@@ -17,11 +17,28 @@ pytestmark = pytest.mark.gpu
     (4, 64, [100], [900], 300, "bf16", True, True), (8, 128, [20, 3, 64], [900, 0, 2100], 777, "bf16", True, True),
     (4, 128, [64], [40], 9001, "bf16", False, False)])
 def test_one_launch_and_two_agree(g, D, sizes, lens, V, dtype, paged, one):
-    import torch
     rng = np.random.default_rng(sum(sizes))
     pars = [W.random_tree(rng, n, 4, 7, False)[0] for n in sizes]
     case = W.custom_case(5600 + V, dtype, len(sizes), 2 * g, 2, D, V, lens, pars, paged=paged, q_scale=2.0, p_match=0.8)
-    run_case(case, rows=sample_rows(case, 60), what=f"one launch {sizes}")
+    one_launch_and_two(case, one)
+
+
+# Tiles of up to 128 rows in several rounds of workgroups (12 sequences x 32 heads on 256 compute units): two launches unless
+# the sums are in 32 bits (head_dim 64; slices of the block table beyond 1022 entries) or a tile is larger.
+@pytest.mark.parametrize("D,lens,block,first,one", [(128, range(400, 520, 10), 0, 70, False), (64, range(400, 520, 10), 0, 70, True),
+                                                    (128, range(1100, 1220, 10), 1, 70, True), (128, range(400, 520, 10), 0, 129, True)])
+def test_several_rounds(D, lens, block, first, one, monkeypatch):
+    monkeypatch.setattr(W, "BLOCK_TOKENS", block)
+    rng = np.random.default_rng(first)
+    pars = [W.random_tree(rng, n, 4, 7, False)[0] for n in [first] + [70] * 11]
+    case = W.custom_case(5700 + D, "bf16", 12, 32, 32, D, 300, list(lens), pars, paged=block > 0, q_scale=2.0, p_match=0.8)
+    case.block_size = block
+    one_launch_and_two(case, one)
+
+
+def one_launch_and_two(case, one):
+    import torch
+    run_case(case, rows=sample_rows(case, 60), what=f"one launch {np.diff(case.node_offsets).tolist()}")
     dc = B.DeviceCase(case)
     got = []
     for fuse in (1, 0):
