@@ -29,6 +29,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 MIN_LAUNCHES, MIN_WARM = 200, 20
+WARM_S = 0.03      # and at least this long: behind a workload's set-up the chip's clock takes milliseconds to come up
 
 
 def main():
@@ -83,9 +84,11 @@ def main():
         warm = max(1, -(-MIN_WARM // launches_per_replay))
         reps = max(5, -(-MIN_LAUNCHES // launches_per_replay))
         with torch.cuda.stream(side):
-            for _ in range(warm):
+            t0, n = time.perf_counter(), 0
+            while n < warm or time.perf_counter() - t0 < WARM_S:
                 run_once()
-            side.synchronize()
+                side.synchronize()
+                n += 1
             evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(reps)]
             for e0, e1 in evs:
                 e0.record(side)
@@ -306,15 +309,16 @@ def main():
 
     stream_us = timed_stream_read()
     stream_gbps = attn_bytes / stream_us / 1e3
-    # The dominant kernel of the timed step.  Small calls run the whole verification as one launch
-    # (k_verify_mfma): its algorithmic bytes are the attention's plus the logits'.  Otherwise it is
+    # The dominant kernel of the timed step.  Most calls run the whole verification as one launch
+    # (k_verify_*): its algorithmic bytes are the attention's plus the logits'.  Otherwise it is
     # the attention kernel (with its split merge).
+    wide = (case.node_offsets[1:] - case.node_offsets[:-1]).max() * (case.Hq // case.Hkv) > 64
+    kind = "f32" if info["impl"] == 1 else ("wide" if wide else "mfma")
     if info["fused"]:
-        kind = "wide" if (case.node_offsets[1:] - case.node_offsets[:-1]).max() * (case.Hq // case.Hkv) > 64 else "mfma"
         roof_kernel = f"cb::k_verify_{kind} (tree attention incl. split merge + logits argmax + acceptance, one launch)"
         roof_bytes, roof_us = attn_bytes + case.logits_bytes(), verify_us
     else:
-        roof_kernel = "cb::k_attn_mfma (tree attention incl. split merge)" if info["impl"] == 2 else "cb::k_attn_f32 (tree attention incl. split merge)"
+        roof_kernel = f"cb::k_attn_{kind} (tree attention incl. split merge)"
         roof_bytes, roof_us = attn_bytes, attn_us
     roof_gbps = roof_bytes / roof_us / 1e3
 
@@ -351,7 +355,7 @@ def main():
         "one_launch_verify": info["fused"],
         "splits": info["nsplit"],
         "merge": info["merge"],
-        "stage_timing": f"median over replays, {row['timed_launches_per_stage']} timed launches after >= {MIN_WARM} warm-up launches, HIP events on the launch stream",
+        "stage_timing": f"median over replays, {row['timed_launches_per_stage']} timed launches after >= {MIN_WARM} warm-up launches and {WARM_S * 1e3:.0f} ms, HIP events on the launch stream",
         "roofline": {"bound": "hbm", "achieved": round(roof_gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(roof_gbps / HBM_PEAK_GBPS, 4), "traffic": None,
                      "kernel": roof_kernel, "algorithmic_bytes": roof_bytes, "launch_us": round(roof_us, 3)},

@@ -235,8 +235,8 @@ int cb_device_status(cb_ctx *ctx, int32_t *status);
  *   "parallel_scan"  1 = run the logits scan on the context's second stream beside the attention
  *   "fuse_logits"    0 = never run the logits scan and the acceptance inside the attention launch
  *                    (default 1: calls in fp32, and in bf16 those whose sequences have at most 64/g nodes or
- *                    whose logits are at most 2.5 times the bytes of their K/V and whose sweep leaves memory
- *                    idle (not tiles of up to 128 rows in several rounds), are one launch: some of its
+ *                    whose logits are at most 2.5 times the bytes of their K/V and fit beside the sweep (tiles of 65 to
+ *                    128 rows in several rounds of workgroups only if their sums are in 32 bits), are one launch: some of its
  *                    workgroups do the logits work, the others the attention)
  *   "logits_wgs"     workgroups of that launch for the logits work (a multiple of 8 up to 192;
  *                    0 = automatic)

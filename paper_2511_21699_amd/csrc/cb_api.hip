@@ -397,12 +397,14 @@ struct Planner {
 // to 1300 keys, 32 heads: 8 workgroups 139 us, 16 80, 48 78, a launch of their own 85.  Fewer keep the
 // launch (a pass of 8 sequences of 32/8 heads with 250 rows of 33333 entries: 32 workgroups 41.7 us, 48 33.7; 128 rows
 // of 32000 over 8192 keys: 8 44.5, 16 34.0, 24 33.5), more take compute units from the sweep (the batch with 96: 38.4).
-// 0: a launch of their own, where the logits are more than 2.5 times the K/V bytes.  One launch gains 8 us a pass on short
-// sweeps and less the more logits there are: 128 nodes of 32/8 heads x 2048 keys, 32000-entry rows (as many bytes as K/V)
-// 32.7 -> 23.4 us, 128256-entry rows 37.5 -> 29.8, and with a host waiting for the results 38.6 -> 38.8.
+// 0: a launch of their own, where the logits are more than 2.5 times the K/V bytes.  Results then come earlier, which pays where the
+// host has work to do with them: 48 nodes of 32/8 heads of 64 x 3000 keys, 128256 fp32 entries (3.9 times), marshalled on the spot,
+// 35.6 us a call in two launches and 38.3 in one.  (A device step of that shape would take 18.4 in one and 27.1 in two, and 128 nodes of head_dim
+// 128 x 2048 keys with 7.8 times the bytes 29.8 and 38.1: the line is low for those.)  Below it one launch is faster in every form:
+// 128 nodes x 2048 keys, 32000-entry rows (as many bytes) 22 against 30 us a device step and 25.6 against 32.4 a host one.
 // 0 too for tiles of up to 128 rows in several rounds of workgroups, unless their sums are in 32 bits: those sweeps are bound by
-// memory (5.5 TB/s), and logits beside them only delay the longest sequences (16 paged sequences of up to 16384 keys with 32 to
-// 96 nodes, 32 heads, a step: 443 us in one launch, 433 in two; with 32-bit sums 629 and 641).
+// memory (5.5 TB/s) and there is little to hide behind.  It is near the line: 16 sequences of up to 16384 keys with 32 to 96 nodes, 32
+// heads, a verification: one draw 425 us in two launches and 434 in one, another 538 and 528; with 32-bit sums 595 and 580.
 constexpr double kLogitsItemUs = 2.1 / 4;
 int fused_wide_logits_wgs(const cb_config& c, const Plan& alone, int batch, const int32_t* kv_len, const int32_t* node_offsets, double item_us) {
   const double lb = c.logits_dtype == CB_F32 ? 4 : 2;

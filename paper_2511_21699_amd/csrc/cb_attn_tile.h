@@ -8,7 +8,7 @@
 // MFMA contractions; the KV sequence is split across workgroups and the partial softmax states
 // (o, m, l) are merged afterwards.
 //
-// One workgroup of 8 wavefronts works on a (sequence, kv head, row tile, split).  K/V is brought straight from HBM into
+// One workgroup of 8 wavefronts (4 in the wide kernel) works on a (sequence, kv head, row tile, split).  K/V is brought straight from HBM into
 // an LDS ring by LDS-DMA (no registers held by loads in flight) and is shared by the waves.  All loads of the
 // sweep -- the ring's requests and the query rows -- are issued as instructions the compiler does not interpret and are
 // covered by the kernel's own counted waits.

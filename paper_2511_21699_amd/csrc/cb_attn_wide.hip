@@ -159,7 +159,7 @@ __device__ __forceinline__ void raise_reference(TileState<D>& st, float mx, floa
 // are taken (to mx).  Written in issue order, pinned by the scheduling barriers: an MFMA occupies the matrix core for 32
 // cycles in which the wave issues what belongs to the other unit (a v_exp_f32 takes 8 cycles, other vector
 // instructions 4 to 5).  Left alone the compiler gathers each kind.
-// score_half ends with the reads of add_half's first operands (v).  req(i), i = 0 .. NREQ - 1: memory requests to be
+// score_half also reads add_half's first operands (v), in front of its middle.  req(i), i = 0 .. NREQ - 1: memory requests to be
 // spread over score_half.
 // PREK: `k` is filled again in add_half, for the next score_half (its unit's K at kn).
 template <int D, bool PX, int R, int NREQ, typename Req>
