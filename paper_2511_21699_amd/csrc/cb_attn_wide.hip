@@ -1,8 +1,8 @@
 // Tree attention for tiles of 65 to 256 rows (bf16, head_dim 64 or 128), gfx950 only.
 //
 // Four waves, one to a SIMD, with 32 or 64 rows each.  A tile's rows decide how they share it: RW row groups times KW = 4 / RW
-// key groups -- up to 64 rows two groups of one 32-row tile, up to 128 two of two tiles, both with two key groups, beyond
-// four of two tiles.  A unit of work is 32 keys; a stage is KW units, one for each key group, whose softmax states are
+// key groups -- up to 64 rows two groups of one 32-row tile with two key groups, up to 128 four of one tile (or, see below, two of
+// two), beyond four of two tiles.  A unit of work is 32 keys; a stage is KW units, one for each key group, whose softmax states are
 // combined through LDS at the end.
 //
 // What bounds it: per unit of a 256-row tile the matrix cores have 1088 cycles of work; a wave issues about 250
@@ -624,8 +624,14 @@ __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const Se
   TileJob jb;
   if (!tile_job(p, ml, wg, 256, jb)) return;
   const int rows = jb.M - jb.row0;
+  // Up to 128 rows: four groups of one row tile, one key group.  Two groups of two tiles with two key groups read every operand for
+  // 64 rows and win in long sweeps, but go through their tiles one behind the other and have states to combine.  A pass of the attention
+  // with those and with these: 68 rows of 8 kv heads x 900 keys 12.2 -> 9.8 us, x 20000 29.0 -> 27.7; 128 rows of 32 x 900 18.5 -> 14.9,
+  // x 20000 73.8 -> 71.4, paged 74.3 -> 75.8.  With 32-bit sums at head_dim 128, whose slices are long, 16 sequences of up to 16384 keys
+  // 586 -> 590: they keep the two tiles.
+  constexpr int R128 = PX && D == 128 ? 2 : 1;
   if (rows <= 64) sweep_tile<D, PX, PG, 1, 2, TS>(p, jb, sh, ring, ts);
-  else if (rows <= 128) sweep_tile<D, PX, PG, 2, 2, TS>(p, jb, sh, ring, ts);
+  else if (rows <= 128) sweep_tile<D, PX, PG, R128, 4 / R128, TS>(p, jb, sh, ring, ts);
   else sweep_tile<D, PX, PG, 2, 4, TS>(p, jb, sh, ring, ts);
   if (jb.nsplit == 1 || p.external_merge) return;  // (a following kernel merges: the kernel boundary orders the stores)
   split_merge<D, 32, PX, kWideWaves, 256, TS>(p, jb, sh, ts);
