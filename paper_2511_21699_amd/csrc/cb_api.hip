@@ -227,7 +227,7 @@ int fused_logits_wgs(const cb_config& c, int batch, const int32_t* kv_len, const
 // What splitting a call's sequences into chunks of so many keys means.  Its jobs are (sequence, kv head, row tile, chunk with keys);
 // work is counted in stages of 64 keys, with six for what a job costs beside its sweep (start-up and tail).
 struct SplitSums {
-  int chunk;              // (0: not known yet)
+  int chunk;
   int grid_x;             // chunks of the longest sequence
   int64_t jobs, merged;   // merged: tiles that have partial states
   double work, shortest;
@@ -248,7 +248,8 @@ struct Planner {
   int32_t len[CB_MAX_BATCH];
   int64_t tiles[CB_MAX_BATCH];
   static constexpr int kKnown = 64;   // (the default for max_splits)
-  SplitSums known[kKnown + 2] = {};   // of the counts up to kKnown, and the last one beyond
+  SplitSums known[kKnown + 2];        // of the counts up to kKnown, and the last one beyond,
+  int32_t known_chunk[kKnown + 2] = {};  // where this is their chunk
 
   Planner(const cb_config& c_, int max_splits_, int scalar_splits_, int opt_impl, int opt_splits_, int batch_, const int32_t* kv_len_, const int32_t* node_offsets_)
       : c(c_), max_splits(max_splits_), scalar_splits(scalar_splits_), opt_splits(opt_splits_), batch(batch_), kv_len(kv_len_), node_offsets(node_offsets_),
@@ -270,10 +271,12 @@ struct Planner {
   int chunk_of(int ns) const { return ((max_len + ns - 1) / ns + 31) / 32 * 32; }
 
   const SplitSums& split_into(int ns) {
-    SplitSums& s = known[std::min(ns, kKnown + 1)];
-    if (s.chunk == chunk_of(ns)) return s;
+    const int at = std::min(ns, kKnown + 1), chunk = chunk_of(ns);
+    SplitSums& s = known[at];
+    if (known_chunk[at] == chunk) return s;
+    known_chunk[at] = chunk;
     s = SplitSums{};
-    s.chunk = chunk_of(ns);
+    s.chunk = chunk;
     s.grid_x = (max_len + s.chunk - 1) / s.chunk;
     s.shortest = 1e30;
     const double job_chunk = 6.0 + (s.chunk + 63) / 64, per_key = 1.0 / s.chunk;

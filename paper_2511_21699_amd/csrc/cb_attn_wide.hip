@@ -5,12 +5,12 @@
 // two), beyond four of two tiles.  A unit of work is 32 keys; a stage is KW units, one for each key group, whose softmax states are
 // combined through LDS at the end.
 //
-// What bounds it: per unit of a 256-row tile the matrix cores have 1088 cycles of work; a wave issues about 250
-// instructions beside it (the exponentials twice as long as the others), and takes about 1750 with barrier, requests and
-// waits.  K and V operands serve two row tiles each: with eight waves of 32 rows (two to a SIMD) the LDS had 128 KiB of
+// What bounds it: per unit of a 256-row tile the matrix cores have 1088 cycles of work; a wave issues 129 vector, 24 LDS and 22 scalar
+// instructions beside it (the exponentials twice as long as the others), and takes 1870 with barrier, requests and
+// waits, launch and tail included.  K and V operands serve two row tiles each: with eight waves of 32 rows (two to a SIMD) the LDS had 128 KiB of
 // operand reads to deliver per unit, 1024 cycles, and the SIMDs twice the scalar and address instructions: 1890 cycles.
-// Long sweeps run into the chip's power limit (1.75 GHz at 40 heads x 65536 keys x 256 nodes), so that work taken out counts
-// there and stalls taken out do not.
+// Under long sweeps the chip's clock comes down (1.75 GHz of 2.4 at 40 heads x 65536 keys x 256 nodes: 641 k cycles a wave in 367
+// us), so that work taken out counts there and stalls taken out do not.
 // A pass with eight waves and with four: 128 nodes x 8192 keys of 32/8 heads 31.8 -> 31.3 us, 8 sequences of up to 2000 keys
 // 42.6 -> 40.2, 16 paged sequences of up to 16384 keys, 32-bit sums, 629 -> 590, 256 nodes x 65536 keys of 40 heads 406 -> 383.
 //
