@@ -379,7 +379,7 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   hipError_t e;
   auto launch = [&](auto* stamped, auto* plain, auto... args) { hipLaunchKernelGGL(ts ? stamped : plain, grid, dim3(512), 0, st, args...); };
   if (rt_rows != kSmallRows) {
-    e = launch_attn_wide(st, q, meta, (int)T, logits_work);
+    e = launch_attn_wide(st, q, meta, M, (int)T, logits_work);
   } else if (logits_work) {
     if (p.D == 64) launch(k_verify_mfma<64, true>, k_verify_mfma<64, false>, q, meta, *logits_work);
     else if (p.precise) launch(k_verify_precise<true>, k_verify_precise<false>, q, meta, *logits_work);

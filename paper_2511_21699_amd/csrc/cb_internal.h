@@ -215,7 +215,9 @@ size_t attn_mfma_partial_bytes(int D, bool precise, int mrows, size_t max_total_
 bool attn_mfma_supports(const AttnParams& p);  // shape/geometry the MFMA kernel takes (bf16 is the caller's check)
 // with logits_work != nullptr the same launch also scans the logits and runs the acceptance
 // merge_kind (may be null): 0 one split, 1 cooperative merge, 2 merge by the last workgroup to arrive, 3 merge kernel
-hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles, const LogitsWork* lw);  // (by launch_attn_mfma)
+// (by launch_attn_mfma; rows: of the largest sequence, per kv head; n_tiles: workgroups that do attention)
+hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int rows, int n_tiles, const LogitsWork* lw);
+hipError_t launch_attn_wide_px(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles, const LogitsWork* lw);
 hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call,
                             int total_nodes, const LogitsWork* logits_work, int* merge_kind);
 

@@ -46,3 +46,14 @@ def test_merges_of_wide_tiles(splits, units, options, merge, D, n, g):
         tile = 32 * D * (4 if D == 64 else 2) + 32 * 8
         merge = "merge_kernel" if splits * -(-n * g // 32) * tile > 320 * 1024 else "last_arrival"
     assert (info["nsplit"], info["merge"]) == (splits, merge), info
+
+
+# tiles of 65 to 128 rows: sweeps on either side of the lengths beyond which a wave takes two row tiles (2048 keys of a paged cache
+# with more than 96 rows, 4096 in a batch), and tiles of one row more than a wave's share
+@pytest.mark.parametrize("rows", [65, 96, 97, 128])
+@pytest.mark.parametrize("batch,keys,paged", [(1, 2048, True), (1, 2049, True), (1, 2100, False), (2, 4096, False), (2, 4097, False), (2, 4128, True)])
+def test_sweeps_of_up_to_128_rows(rows, batch, keys, paged):
+    pars = [W.random_tree(np.random.default_rng(rows + b), rows if b == 0 else 71, 4, 7, False)[0] for b in range(batch)]
+    lens = [keys - rows] + [1300] * (batch - 1)
+    case = W.custom_case(6100 + rows, "bf16", batch, 2, 2, 128, 300, lens, pars, paged=paged, q_scale=2.0)
+    run_case(case, rows=sample_rows(case, 80), options={"splits": 1}, what=f"{rows} rows, {batch} sequences, {keys} keys, paged {paged}")
