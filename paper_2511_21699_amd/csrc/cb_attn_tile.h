@@ -1,5 +1,5 @@
 // Tree-masked flash-decode attention on the matrix cores (bf16), gfx950 only: what the kernels of cb_attn_mfma.hip
-// (tiles of up to 64 rows) and cb_attn_wide.hip (up to 256) share -- the workgroup's job, the K/V ring, the partial
+// (tiles of up to 64 rows) and cb_attn_wide.h (up to 256) share -- the workgroup's job, the K/V ring, the partial
 // states and their merge.
 //
 // Tree attention, Section 3.2 of the paper: node i attends to the KV-cached prefix (slots 0..S-1)
