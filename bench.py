@@ -3,7 +3,7 @@
 
 A step is one pass of the whole hot path over one batch of synthetic input: ancestor sets,
 tree-masked attention (with its split merge), vocabulary argmax, greedy acceptance and KV
-compaction, enqueued through the C ABI (cb_verify_tree_device + cb_compact_kv).  The headline
+compaction, enqueued through the C ABI (cb_verify_and_compact_device).  The headline
 workload is the 7B-shaped configuration (batch 1, 32 heads, head_dim 128, bf16, prefix 2048,
 64-node tree from the LRU drafter, logits [64, 32000]); inputs are resident in HBM before the
 timed region.  Steps rotate over enough independent copies of (q, cache, logits) that every pass

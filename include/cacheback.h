@@ -169,6 +169,20 @@ int cb_verify_tree_device(cb_ctx *ctx, void *hip_stream, int32_t batch, const vo
                           int32_t *d_accepted_len, int32_t *d_accepted_tokens);
 
 /*
+ * cb_verify_tree_device followed by cb_compact_kv of `num_layers` caches (0: none) with new_kv_len = NULL, as one call:
+ * the same results, states and errors.  Where `layers` is the one cache that is verified, and neither its k nor its v overlaps
+ * another operand, it is one kernel for calls whose verification is: a kv head's rows move as soon as all that reads
+ * them has, and the acceptance, are through.  Tree slots of one sequence must not be visible to another sequence of the call
+ * (through a shared block of a paged cache), which would read them before or after the move.
+ */
+int cb_verify_and_compact_device(cb_ctx *ctx, void *hip_stream, int32_t batch, const void *q,
+                                 const cb_kv_layer *kv, const int32_t *kv_len,
+                                 const int32_t *node_offsets, const int32_t *d_tree_parent,
+                                 const int32_t *d_draft_tokens, const void *logits, void *attn_out,
+                                 int32_t *d_accepted_len, int32_t *d_accepted_tokens,
+                                 int32_t num_layers, const cb_kv_layer *layers);
+
+/*
  * Tree attention alone (Section 3.2: every node attends to the cached prefix, its ancestors and
  * itself), for the layers of a model below the last one: the arguments of cb_verify_tree_device
  * without tokens, logits and results.  Launches only; leaves the state of the last verify call

@@ -20,7 +20,7 @@ CB_OK, CB_EINVAL, CB_ETREE, CB_ECAP, CB_ESTATE, CB_EHIP = range(6)
 CB_LAYOUT_TOKEN_MAJOR, CB_LAYOUT_HEAD_MAJOR = 0, 1
 ERROR_NAMES = {0: "CB_OK", 1: "CB_EINVAL", 2: "CB_ETREE", 3: "CB_ECAP", 4: "CB_ESTATE", 5: "CB_EHIP"}
 
-EXPORTS = ["cb_workspace_bytes", "cb_init", "cb_check_verify_args", "cb_plan_attention", "cb_verify_tree", "cb_verify_tree_device", "cb_tree_attention_device", "cb_tree_attention_noalloc",
+EXPORTS = ["cb_workspace_bytes", "cb_init", "cb_check_verify_args", "cb_plan_attention", "cb_verify_tree", "cb_verify_tree_device", "cb_verify_and_compact_device", "cb_tree_attention_device", "cb_tree_attention_noalloc",
            "cb_compact_kv", "cb_get_path", "cb_get_argmax", "cb_device_status", "cb_set_option",
            "cb_last_launch_info", "cb_last_attention_ms", "cb_debug_timestamps", "cb_probe_stream_read", "cb_last_error",
            "cb_destroy"]
@@ -67,6 +67,7 @@ def load():
     L.cb_plan_attention.argtypes = [C.POINTER(CbConfig), C.c_int32, i32p, i32p, C.c_int32, i32p]
     L.cb_verify_tree.argtypes = [vp, vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, i32p, i32p, vp, vp, i32p, i32p]
     L.cb_verify_tree_device.argtypes = [vp, vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, vp, vp, vp, vp, vp, vp]
+    L.cb_verify_and_compact_device.argtypes = L.cb_verify_tree_device.argtypes + [C.c_int32, C.POINTER(CbKvLayer)]
     L.cb_tree_attention_device.argtypes = [vp, vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, vp, vp]
     L.cb_tree_attention_noalloc.argtypes = [C.POINTER(CbConfig), vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, vp, vp]
     L.cb_compact_kv.argtypes = [vp, vp, C.c_int32, C.POINTER(CbKvLayer), i32p]
@@ -275,21 +276,19 @@ class Verifier:
 
     def bind_step(self, q, kv: CbKvLayer, kv_len, node_offsets, d_parent, d_tokens, logits, attn_out, d_acc_len,
                   d_acc_tok, layers: Sequence[CbKvLayer], stream=None):
-        """Pre-marshalled cb_verify_tree_device + cb_compact_kv pair: returns a zero-argument callable that
-        only makes the two C calls (for launch loops where per-call marshalling would dominate)."""
+        """Pre-marshalled cb_verify_and_compact_device: returns a zero-argument callable that
+        only makes the C call (for launch loops where per-call marshalling would dominate)."""
         kv_len, node_offsets = _i32(kv_len), _i32(node_offsets)
         arr = (CbKvLayer * len(layers))(*layers) if layers else None
         st = self._stream(stream)
         a = (self.ctx, st, kv_len.shape[0], q.data_ptr(), C.byref(kv), _ip(kv_len), _ip(node_offsets),
              d_parent.data_ptr(), d_tokens.data_ptr(), logits.data_ptr(), attn_out.data_ptr(), d_acc_len.data_ptr(),
-             d_acc_tok.data_ptr())
+             d_acc_tok.data_ptr(), len(layers), arr)
         keep = (kv_len, node_offsets, arr, kv, q, logits, attn_out)
-        verify, compact, nl = self.L.cb_verify_tree_device, self.L.cb_compact_kv, len(layers)
+        step = self.L.cb_verify_and_compact_device
 
         def call(_keep=keep):
-            rc = verify(*a)
-            if rc == 0 and nl:
-                rc = compact(self.ctx, st, nl, arr, None)
+            rc = step(*a)
             if rc:
                 self._raise(rc)
         return call

@@ -30,7 +30,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct WsLayout {
   size_t anc, parent, tokens, amax_best, amax_out, path, len_ctx, res_len, res_tok, new_len, status,
-      tickets, coop_tickets, amax_tickets, dbg, partial, total;
+      tickets, coop_tickets, amax_tickets, moves, dbg, partial, total;
   int amax_chunks;
   int max_total_nodes;
   int max_splits;
@@ -87,6 +87,7 @@ WsLayout ws_layout(const cb_config& c) {
   L.coop_tickets = take((size_t)kCoopTiles * kCoopTicketStride);
   L.amax_tickets = take((size_t)c.max_batch * kTicketWords * 4);
   L.amax_best = take(mt * kAmaxStride * 8);
+  L.moves = take((size_t)c.max_batch * c.num_kv_heads * 4);
   L.dbg = take(1024 * 8 * 8);
   // The scalar kernel's fp32 partials are twice the size of the MFMA kernel's.  A configuration
   // the MFMA kernel takes (bf16) runs the scalar one only on request (option
@@ -154,6 +155,8 @@ struct cb_ctx {
   hipStream_t aux;  // second stream (default priority) for the logits scan beside the attention
   bool ev_valid;
   const Plan* fixed_plan = nullptr;  // (cb_tree_attention_noalloc: the plan its scratch layout was cut for)
+  bool want_move = false;  // the launch that run_pipeline makes next is to compact its cache too, if it can;
+  bool moved = false;      // whether it does
   bool counters_dirty = false;  // a launch failed: the tickets may be left non-zero
   bool amax_dirty = false;      // a scan ran without its acceptance (option "stages"): row maxima are left behind
   char err[256];
@@ -208,6 +211,26 @@ bool make_kv_addr(const cb_config& c, const cb_kv_layer& l, KvAddr* a) {
     return false;
   }
   return true;
+}
+
+// A stretch of the device's address space.
+struct Span {
+  const void* at;
+  size_t bytes;
+  bool meets(const Span& o) const {
+    const uintptr_t a = (uintptr_t)at, b = (uintptr_t)o.at;
+    return bytes != 0 && o.bytes != 0 && a < b + o.bytes && b < a + bytes;
+  }
+};
+// Bytes of a layer's K (or V) that a call with `batch` sequences can touch.
+size_t cache_bytes(const cb_config& c, const cb_kv_layer& l, int batch) {
+  const size_t row = (size_t)c.num_kv_heads * c.head_dim * (c.qkv_dtype == CB_F32 ? 4 : 2);
+  const size_t units = l.capacity_or_num_blocks > 0 ? l.capacity_or_num_blocks : 0;
+  return c.block_size > 0 ? units * c.block_size * row : units * batch * row;
+}
+bool same_cache(const cb_kv_layer& a, const cb_kv_layer& b) {
+  return a.k == b.k && a.v == b.v && a.capacity_or_num_blocks == b.capacity_or_num_blocks && a.block_table == b.block_table &&
+         a.max_blocks_per_seq == b.max_blocks_per_seq && a.layout == b.layout;
 }
 
 // Workgroups of a one-launch verification that do the logits work: the share of the chip that the logits' bytes
@@ -614,7 +637,8 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     const hipError_t e1 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.tickets), ctx->lay.ticket_count / 2, 1, 1);
     const hipError_t e2 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.coop_tickets), kCoopTiles, kCoopTicketStride / 8, 2);
     const hipError_t e3 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.amax_tickets), c.max_batch * kTicketWords / 2, 1, 1);
-    if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) return set_err(ctx, CB_EHIP, "clearing the tickets after a failed launch failed");
+    const hipError_t e4 = launch_zero_words(st, ctx->dev<unsigned long long>(ctx->lay.moves), (c.max_batch * c.num_kv_heads + 1) / 2, 1, 1);
+    if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess) return set_err(ctx, CB_EHIP, "clearing the tickets after a failed launch failed");
     ctx->counters_dirty = false;
     ctx->amax_dirty = ctx->amax_dirty || (stage_mask & 4) != 0;  // (the row maxima too)
   }
@@ -725,6 +749,11 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   }
   if (fork) CB_HIP(ctx, hipEventRecord(ctx->ev_join, ctx->aux));
   const bool timing = ctx->opt_time != 0;
+  // The compaction in the attention's launch, for the matrix-core kernels as they are by default.
+  ctx->moved = ctx->want_move && stages == 15 && (f32_tiles || (use_mfma && (fused || attn_mfma_tile_rows(plan.max_nodes * (c.num_q_heads / c.num_kv_heads)) != kRowTile))) &&
+               !timing && !fork && !ap.timeline;
+  ctx->want_move = false;
+  if (ctx->moved) ap.move = MoveArgs{ctx->dev<uint32_t>(ctx->lay.moves), acc.path, acc.len_ctx, fused ? 1 : 0};
   if (timing) CB_HIP(ctx, hipEventRecord(ctx->ev0, st));
   if (!(stages & 2)) {
   } else if (use_mfma) {
@@ -955,6 +984,33 @@ int cb_verify_tree_device(cb_ctx* ctx, void* hip_stream, int32_t batch, const vo
   if (rc) return rc;
   return run_pipeline(ctx, static_cast<hipStream_t>(hip_stream), batch, q, kv, kv_len, node_offsets, d_tree_parent,
                       d_draft_tokens, logits, attn_out, d_accepted_len, d_accepted_tokens);
+}
+
+int cb_verify_and_compact_device(cb_ctx* ctx, void* hip_stream, int32_t batch, const void* q, const cb_kv_layer* kv,
+                                 const int32_t* kv_len, const int32_t* node_offsets, const int32_t* d_tree_parent,
+                                 const int32_t* d_draft_tokens, const void* logits, void* attn_out,
+                                 int32_t* d_accepted_len, int32_t* d_accepted_tokens, int32_t num_layers, const cb_kv_layer* layers) {
+  // One launch where the cache that is verified is the one that is compacted and its memory is nobody else's: the launch moves rows
+  // while other workgroups still read their own inputs and write their results.
+  bool apart = false;
+  if (ctx && kv && num_layers == 1 && layers && batch >= 1 && batch <= ctx->cfg.max_batch && node_offsets && same_cache(*kv, layers[0]) && ((((uintptr_t)kv->k | (uintptr_t)kv->v) & 15) == 0)) {
+    const cb_config& c = ctx->cfg;
+    const size_t rows = node_offsets[batch] > 0 ? node_offsets[batch] : 0, qo = rows * c.num_q_heads * c.head_dim * (c.qkv_dtype == CB_F32 ? 4 : 2);
+    const size_t cache = cache_bytes(c, *kv, batch);
+    const Span mine[] = {{kv->k, cache}, {kv->v, cache}};
+    const Span others[] = {{kv->k, cache}, {q, qo}, {attn_out, qo}, {logits, rows * c.vocab_size * (c.logits_dtype == CB_F32 ? 4 : 2)},
+                           {d_tree_parent, rows * 4}, {d_draft_tokens, rows * 4}, {d_accepted_len, (size_t)batch * 4},
+                           {d_accepted_tokens, (size_t)batch * (c.max_depth + 1) * 4}, {kv->block_table, c.block_size > 0 ? (size_t)batch * kv->max_blocks_per_seq * 4 : 0}};
+    apart = !mine[1].meets(others[0]);
+    for (size_t i = 1; apart && i < sizeof others / sizeof *others; i++) apart = !mine[0].meets(others[i]) && !mine[1].meets(others[i]);
+  }
+  if (ctx) ctx->want_move = apart;
+  if (ctx) ctx->moved = false;
+  const int rc = cb_verify_tree_device(ctx, hip_stream, batch, q, kv, kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits, attn_out,
+                                       d_accepted_len, d_accepted_tokens);
+  if (ctx) ctx->want_move = false;
+  if (rc || ctx->moved || num_layers == 0) return rc;
+  return cb_compact_kv(ctx, hip_stream, num_layers, layers, nullptr);
 }
 
 int cb_tree_attention_device(cb_ctx* ctx, void* hip_stream, int32_t batch, const void* q, const cb_kv_layer* kv,

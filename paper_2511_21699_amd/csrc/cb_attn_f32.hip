@@ -216,6 +216,8 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p, const SeqMeta
       *reinterpret_cast<f32x4*>(&sh.o[w][r * LS + 64 * n + 16 * h + 4 * i]) = f32x4{o[n][0][i], o[n][1][i], o[n][2][i], o[n][3][i]};
   if (h == 0) sh.ml[w][r] = float2{m, lsum};
   __syncthreads();
+  HeadMove<row_pieces(D, 4), 2> move;
+  if (p.move.words && k1 > S && w == kF32Waves - 1) move.begin(kF32Rows, b, hk, S, N);  // (nobody reads K or V any more)
   const int orow = tid / (D / 4), c = tid % (D / 4) * 4;
   const bool live = orow < kF32Rows && row0 + orow < M;
   const int onode = (row0 + orow) / g;
@@ -242,7 +244,11 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p, const SeqMeta
       if (c == 0) store_pair(pp + D, mm, ll);
     }
   }
-  if (nsplit == 1 || p.external_merge) return;  // (k_merge follows: the kernel boundary orders the stores)
+  auto finish_move = [&] { move.finish(b, hk, S, N); };
+  if (nsplit == 1 || p.external_merge) {  // (k_merge follows: the kernel boundary orders the stores)
+    finish_move();
+    return;
+  }
   // The stores are acknowledged before the ticket is drawn, so whoever completes the tile finds all of them in memory.
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -253,6 +259,7 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p, const SeqMeta
     if (n == (uint32_t)nsplit) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
   }
   __syncthreads();
+  finish_move();
   if (!sh.last || !live) return;
   constexpr int BS = 8;   // splits whose loads are in flight together
   float mm = -INFINITY, ll = 0.f;
@@ -300,7 +307,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_verify_f32(AttnParams p, Seq
   } sh;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   const int wg = (int)blockIdx.x - lw.n_wgs;
-  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept);
+  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept, MoveAfter<row_pieces(D, 4), 2, kF32Waves>{kF32Rows, p.move.words != nullptr});
   else attn_f32_tile<D>(p, ml, wg, sh.attn);
 }
 

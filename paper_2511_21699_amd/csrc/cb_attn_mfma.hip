@@ -138,8 +138,8 @@ __device__ __forceinline__ void compute_unit(const uint4* __restrict__ ks, const
   }
 }
 
-// One attention workgroup; `wg` is its number among those that do attention.
-template <int D, bool PX, bool TS>
+// One attention workgroup; `wg` is its number among those that do attention.  MOVE: the launch may compact its cache.
+template <int D, bool PX, bool MOVE, bool TS>
 __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, unsigned long long ts0,
                                           TileLds& sh, uint4* ring, unsigned long long* ts_sh) {
   using F = Feed<D, 8, 16>;
@@ -235,9 +235,15 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   for (int i = 0; i < P / 2; i++) f[i] = f[i] * w0 + theirs[i * 64] * w1;
   const float lsum = st.lacc[0] * w0 + ml2.y * w1;
 #undef CB_TS
+  HeadMove<row_pieces(D, 2), 1> move;
+  if (MOVE && (p.coop_merge & 2) && tree_split && w == 0) move.begin(kSmallRows, jb.b, jb.hk, S, jb.N);
   write_rows<D, 16, PX, P / 2>(p, jb, wi, grow, f, gi * (P / 2), m, lsum, c2, gi == 0, l);
-  if (jb.nsplit == 1 || p.external_merge) return;  // (a following kernel merges: the kernel boundary orders the stores)
-  split_merge<D, 16, PX, 8, kSmallRows, TS>(p, jb, sh, ts);
+  auto finish_move = [&] { if (MOVE) move.finish(jb.b, jb.hk, S, jb.N); };
+  if (jb.nsplit == 1 || p.external_merge) {  // (a following kernel merges: the kernel boundary orders the stores)
+    finish_move();
+    return;
+  }
+  split_merge<D, 16, PX, 8, kSmallRows, TS>(p, jb, sh, ts, finish_move);
 }
 
 template <int D, bool PX, bool TS>
@@ -247,7 +253,7 @@ __device__ __forceinline__ void attn_workgroup(const AttnParams& p, const SeqMet
   __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
-  attn_tile<D, PX, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
+  attn_tile<D, PX, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
@@ -264,10 +270,10 @@ __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqM
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) {
-    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
+    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), MoveAfter<row_pieces(D, 2), 1, 8>{kSmallRows, (p.coop_merge & 2) != 0});
     return;
   }
-  attn_tile<D, PX, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
+  attn_tile<D, PX, true, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
   flush_timestamps<TS>(p, wg, ts_sh);
 }
 
@@ -374,7 +380,8 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
                   (int64_t)p.Hkv * tiles * p.batch <= kCoopTiles) ? 1 : 0;
   if (q.coop_merge) q.external_merge = 0;
   if (p.force_external_merge && p.nsplit > 1) { q.external_merge = 1; q.coop_merge = 0; }  // (option "external_merge": a test aid)
-  if (merge_kind) *merge_kind = p.nsplit <= 1 ? 0 : (q.coop_merge ? 1 : (q.external_merge ? 3 : 2));
+  if (p.move.words) q.coop_merge |= 2;
+  if (merge_kind) *merge_kind = p.nsplit <= 1 ? 0 : ((q.coop_merge & 1) ? 1 : (q.external_merge ? 3 : 2));
   const bool ts = p.timeline != 0;  // (the timeline build of the same kernels: a measurement aid)
   hipError_t e;
   auto launch = [&](auto* stamped, auto* plain, auto... args) { hipLaunchKernelGGL(ts ? stamped : plain, grid, dim3(512), 0, st, args...); };

@@ -541,8 +541,10 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
 // of the arrivals' XCC_ID (hardware register 20, bits 3:0): all ids equal mine  <=>
 // sum = n*id and sumsq = n*id*id.  A second word per tile holds one bit per split whose
 // workgroup gave up waiting (cooperative merge only).
-template <int D, int TR, bool PX, int NW, int MAXROWS, bool TS>
-__device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& jb, TileLds& sh, CB_LDS unsigned long long* ts) {
+// aside(): what the first wave has to do beside; it is called behind the barrier of the workgroup's arrival, where that wave waits for the other
+// splits, or behind its share of the merge, if it has one.
+template <int D, int TR, bool PX, int NW, int MAXROWS, bool TS, typename Aside>
+__device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& jb, TileLds& sh, CB_LDS unsigned long long* ts, Aside aside) {
   constexpr int P = PartialLayout<D, TR, PX>::P;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const bool do_ts = TS && tid == 0, do_ts64 = TS && tid == 64;
@@ -556,7 +558,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
   // (cooperative merge: the tiles' words are polled, so each tile has a 4 KiB stretch of its own
   // in a separate area -- neighbours in one line would all be served by one memory channel)
   const int64_t tile_id = ((int64_t)jb.b * p.Hkv + jb.hk) * jb.tiles + jb.rt;
-  CB_GLOBAL unsigned long long* ticket = p.coop_merge ? (CB_GLOBAL unsigned long long*)p.coop_tickets + tile_id * (kCoopTicketStride / 8)
+  CB_GLOBAL unsigned long long* ticket = (p.coop_merge & 1) ? (CB_GLOBAL unsigned long long*)p.coop_tickets + tile_id * (kCoopTicketStride / 8)
                                                       : (CB_GLOBAL unsigned long long*)p.tickets + 2 * tile_id;
   constexpr unsigned long long kArrivals = 0xfffull;
   const unsigned long long xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & 15u;
@@ -574,7 +576,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     return jb.row0 + i * TR < jb.M;
   };
 
-  if (!p.coop_merge) {
+  if (!(p.coop_merge & 1)) {
     // Merge by the last workgroup of the tile to arrive: the others leave at once and free their
     // compute units (grids of several rounds of workgroups).
     if (tid == 0) {
@@ -592,6 +594,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     __syncthreads();
     CB_TS(6);
     const int flag = sh.flag;
+    if (w == 0 && !flag) aside();
     if (!flag) return;
     // Same XCD: the write-through stores left the lines in this L2, plain (cached) loads are coherent
     // with them.  Otherwise read past the L2 with agent-coherent loads.
@@ -606,6 +609,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     CB_TS(7);
+    if (w == 0) aside();
     return;
   }
 
@@ -692,6 +696,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
   int64_t gr_first = -1;
   const bool have_first = u_first < NU && tile_row(u_first / upt, &gr_first);
   const uint32_t byte_first = partial_byte<D, TR, PX>(p, jb, u_first / upt);
+  if (w == 0 && !have_first) aside();
   // the waves wait for thread 64's verdicts in LDS
   int flag;
   while ((flag = __hip_atomic_load(&sh.flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0) __builtin_amdgcn_s_sleep(1);
@@ -718,6 +723,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
 
   while (__hip_atomic_load(&sh.flag2, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) __builtin_amdgcn_s_sleep(1);
   if (sh.todo2 != 0) merge_slices(sh.todo2, false);
+  if (w == 0 && have_first) aside();
   if (do_ts64) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     ts[7] = wall_clock64();

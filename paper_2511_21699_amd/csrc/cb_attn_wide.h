@@ -560,7 +560,6 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
   }
   wait_vmcnt<0>();  // (the requests past the split's end, before the ring serves anything else)
   CB_TS(4);
-
   // With two key groups each finishes one half of the pieces: all park their accumulators and (mref, l) in the
   // ring, then each adds up the groups' for its own pieces.
   constexpr int P = Part::P, PP = P / KW;
@@ -630,8 +629,17 @@ __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const Se
   if (rows <= 64) sweep_tile<D, PX, PG, 1, 2, TS>(p, jb, sh, ring, ts);
   else if (rows <= 128) sweep_tile<D, PX, PG, R128, 4 / R128, TS>(p, jb, sh, ring, ts);
   else sweep_tile<D, PX, PG, 2, 4, TS>(p, jb, sh, ring, ts);
-  if (jb.nsplit == 1 || p.external_merge) return;  // (a following kernel merges: the kernel boundary orders the stores)
-  split_merge<D, 32, PX, kWideWaves, 256, TS>(p, jb, sh, ts);
+  HeadMove<row_pieces(D, 2), 1> move;
+  if ((p.coop_merge & 2) && jb.k1 > jb.S) {  // (uniform)
+    bare_barrier();  // (every wave's requests have landed)
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) move.begin(256, jb.b, jb.hk, jb.S, jb.N);
+  }
+  auto finish_move = [&] { move.finish(jb.b, jb.hk, jb.S, jb.N); };
+  if (jb.nsplit == 1 || p.external_merge) {  // (a following kernel merges: the kernel boundary orders the stores)
+    finish_move();
+    return;
+  }
+  split_merge<D, 32, PX, kWideWaves, 256, TS>(p, jb, sh, ts, finish_move);
 }
 
 template <int D, bool PX, bool PG, int R128, bool TS>
@@ -657,7 +665,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void k_verify_wide(AttnParams p
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) {
-    logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
+    logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), MoveAfter<row_pieces(D, 2), 1, kWideWaves>{256, (p.coop_merge & 2) != 0});
     return;
   }
   attn_wide_tile<D, PX, PG, R128, TS>(p, ml, wg, ts0, sh, ring, ts_sh);

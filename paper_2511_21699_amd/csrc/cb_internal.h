@@ -16,6 +16,15 @@ constexpr int kCoopTicketStride = 4096;       // bytes between their ticket word
 // floats per (row, split) partial softmax state: o[D] unnormalised, m, l, padded to 16 bytes
 constexpr int partial_stride(int D) { return D + 4; }
 
+// Every pointer the kernels are handed is device (global) memory, but it reaches them as a
+// generic pointer inside an argument struct.  Accesses through a generic pointer are flat
+// instructions, which also count as LDS traffic; so each access site casts to the global address space.
+#define CBL_GLOBAL __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ CBL_GLOBAL T* as_global(T* p) {
+  return (CBL_GLOBAL T*)p;
+}
+
 // Per-sequence shapes; passed to kernels by value (kernel arguments), so they need no upload and
 // are captured with the launch.
 struct SeqMeta {
@@ -152,6 +161,14 @@ __device__ __forceinline__ int sanitized_parent(const int32_t* parent, int off, 
   return p;
 }
 
+// Compaction inside the verification's launch (cb_move.h).
+struct MoveArgs {
+  uint32_t* words;         // [batch][Hkv] arrivals, zero between launches; null: this launch moves nothing
+  const int32_t* path;     // [batch][max_depth + 1] and
+  const int32_t* len;      // [batch]: the acceptance's results
+  int32_t own_acceptance;  // 1: the acceptance is part of this launch
+};
+
 struct AttnParams {
   const void* q;     // [sumN][Hq][D]
   void* out;         // [sumN][Hq][D]
@@ -176,12 +193,14 @@ struct AttnParams {
   int32_t grid_x, grid_y, grid_z;  // launch grid, repeated here so the kernel reads one argument block
   int32_t external_merge;  // 1: the kernel only writes partials; launch_attn_mfma runs a merge kernel afterwards
   int32_t coop_merge;      // 1: every workgroup of a tile merges a slice of it after a bounded wait for the others
-                           // (set by the launcher when the grid is resident in one round); -1 on input: never
+                           // (set by the launcher when the grid is resident in one round); -1 on input: never.
+                           // Bit 1, set by the launcher: move.words is not null
   int32_t spin_limit;      // cooperative merge: polls of the tile's ticket before a workgroup gives up
   int32_t max_depth;    // deepest node the configuration allows (bounds the ancestor-set rounds)
   int32_t timeline;     // 1: launch the timeline build of the kernel (stamps per workgroup in dbg_ts; a measurement aid)
   int32_t force_external_merge;  // 1: always merge with the separate kernel (a test aid)
   int32_t* status;      // device status word (bit 4: a merge had to use cross-XCD loads)
+  MoveArgs move;
   unsigned long long* dbg_ts;  // timeline build: 8 timestamps (100 MHz) per workgroup, 1024 rows
 };
 

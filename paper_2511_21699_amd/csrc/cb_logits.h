@@ -3,18 +3,9 @@
 // Shared by the stand-alone logits kernel and by the attention kernels, whose first workgroups can
 // do this work in the same launch.  gfx950 only.
 #pragma once
-#include "cb_internal.h"
+#include "cb_move.h"
 
 namespace cb {
-
-// Every pointer these functions are handed is device (global) memory, but it reaches them as a
-// generic pointer inside an argument struct.  Accesses through a generic pointer are flat
-// instructions, which also count as LDS traffic; so each access site casts to the global address space.
-#define CBL_GLOBAL __attribute__((address_space(1)))
-template <typename T>
-__device__ __forceinline__ CBL_GLOBAL T* as_global(T* p) {
-  return (CBL_GLOBAL T*)p;
-}
 
 // Wave-wide reductions that leave the result in every lane, without LDS traffic: four rotations
 // inside each row of 16 lanes (DPP row_ror:1,2,4,8), then the gfx950 row swaps for the four rows
@@ -69,8 +60,8 @@ struct AcceptArgs {
   unsigned long long* best;  // [sumN] row maxima (amax_word), kAmaxStride words apart; zero between launches
   int32_t max_depth;
   int32_t* argmax_out;     // [sumN]
-  int32_t* path;           // [B][max_depth + 1]
-  int32_t* len_ctx;        // [B] (kept for the compaction call)
+  int32_t* path;           // [B][max_depth + 1] (these two are for the compaction, which may be part of the launch:
+  int32_t* len_ctx;        // [B] written through to memory)
   int32_t* len_user;       // [B]
   int32_t* tok_user;       // [B][max_depth + 1]
   int32_t* done_flag;      // [B] or null: host-visible words that receive done_value once the sequence's
@@ -84,6 +75,10 @@ __device__ __forceinline__ void publish_done(const AcceptArgs& g, int b, bool wr
   if (!g.done_flag) return;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
   if (writer) __hip_atomic_store(as_global(g.done_flag) + b, g.done_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ __forceinline__ void store_through(int32_t* p, int x) {
+  __hip_atomic_store(as_global(p), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Parent of node t as loaded -> as used (-1 at the root; an entry outside [0, t) becomes "child of the
@@ -150,17 +145,17 @@ __device__ __forceinline__ void accept_small(const AcceptArgs& g, int b, int off
   const unsigned long long on_path = shfl_u64(mine, best);
   const int stride = g.max_depth + 1;
   if (live && ((on_path >> t) & 1ull)) {
-    as_global(g.path)[b * stride + depth] = t;
+    store_through(g.path + b * stride + depth, t);
     as_global(g.tok_user)[b * stride + depth] = a;
   }
   for (int d = t; d < stride; d += 64) {
     if (d > L) {
-      as_global(g.path)[b * stride + d] = -1;
+      store_through(g.path + b * stride + d, -1);
       as_global(g.tok_user)[b * stride + d] = -1;
     }
   }
   if (t == 0) {
-    as_global(g.len_ctx)[b] = L;
+    store_through(g.len_ctx + b, L);
     as_global(g.len_user)[b] = L;
   }
   publish_done(g, b, t == 0);
@@ -177,6 +172,7 @@ struct AcceptWaveLds {
   uint32_t state[CB_MAX_NODES];      // bits 0-8 ancestor + 1 (0: none left), bit 9 matched, bits 16.. depth
   int16_t jump[8][CB_MAX_NODES];     // each round's ancestor pointers, -1 none
   uint32_t mark[CB_MAX_NODES];
+  unsigned long long accepted;       // sequences that the workgroup accepted (logits_share)
 };
 __device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
@@ -262,18 +258,18 @@ __device__ __forceinline__ void accept_large(AcceptWaveLds& sh, const AcceptArgs
     const int t = lane + 64 * k;
     if (t < N && sh.mark[t]) {
       const int depth = (int)(st[k] >> 16);
-      as_global(g.path)[b * stride + depth] = t;
+      store_through(g.path + b * stride + depth, t);
       as_global(g.tok_user)[b * stride + depth] = a[k];
     }
   }
   for (int d = lane; d < stride; d += 64) {
     if (d > L) {
-      as_global(g.path)[b * stride + d] = -1;
+      store_through(g.path + b * stride + d, -1);
       as_global(g.tok_user)[b * stride + d] = -1;
     }
   }
   if (lane == 0) {
-    as_global(g.len_ctx)[b] = L;
+    store_through(g.len_ctx + b, L);
     as_global(g.len_user)[b] = L;
   }
   publish_done(g, b, lane == 0);
@@ -406,9 +402,14 @@ constexpr int kTicketWords = (kTicketGroups + 1) * kTicketStride;    // per sequ
 constexpr int kTicketDirect = 48;  // arrivals up to which one word serves a sequence
 
 // LOADS: loads of 16 bytes that a lane has in flight, as the kernel's registers allow.  EB: bytes of a logits element
-// where the kernel is built for one type, else 0.
-template <int NW, int LOADS, bool SHORT = false, int EB = 0>
-__device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMetaLanes& ml, int wg, AcceptWaveLds& sh) {
+// where the kernel is built for one type, else 0.  after(b, S, N): what all wavefronts of the workgroup that accepted sequence b do
+// then, behind a barrier; after.wanted() whether there is anything (both uniform).
+struct NothingAfter {
+  __device__ __forceinline__ bool wanted() const { return false; }
+  __device__ __forceinline__ void operator()(int, int, int) const {}
+};
+template <int NW, int LOADS, bool SHORT = false, int EB = 0, typename After = NothingAfter>
+__device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMetaLanes& ml, int wg, AcceptWaveLds& sh, const After& after = After{}) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t items = (int64_t)lw.rows * lw.chunks;
   const int i0 = (int)(items * wg / lw.n_wgs), i1 = (int)(items * (wg + 1) / lw.n_wgs);
@@ -427,7 +428,8 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
   if (!lw.accept_after) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (w != 0) return;
+  if (w != 0 && !after.wanted()) return;
+  unsigned long long accepted = 0;
   auto count = [&](CBL_GLOBAL uint32_t* word, uint32_t n, uint32_t full) {  // true: this arrival completed it
     uint32_t old = 0;
     if (lane == 0) old = __hip_atomic_fetch_add(word, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -435,7 +437,7 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
     if (done && lane == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
     return done;
   };
-  for (int i = i0; i < i1;) {
+  for (int i = w == 0 ? i0 : i1; i < i1;) {
     const int row = i / lw.chunks;
     // sequence of the row: the number of sequences that end at or before it
     const int b = __popcll(__ballot(lane < lw.batch - 1 && ml.o1 <= row));
@@ -457,8 +459,20 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
         j += n;
       }
     }
-    if (done) accept_wave(sh, lw.accept, b, off, N);
+    if (done) {
+      accept_wave(sh, lw.accept, b, off, N);
+      accepted |= 1ull << b;
+    }
     i = seq_end;
+  }
+  if (!after.wanted()) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the results are in memory before anybody is told)
+  if (threadIdx.x == 0) sh.accepted = accepted;
+  __syncthreads();
+  for (unsigned long long todo = sh.accepted; todo != 0; todo &= todo - 1) {
+    const int b = __builtin_amdgcn_readfirstlane(__builtin_ctzll(todo));
+    const SeqShape s = seq_shape(ml, b);
+    after(b, s.S, s.N);
   }
 }
 

@@ -1,0 +1,161 @@
+// Compaction (slot S+j <- slot S+path[j], j = 1..L) inside the launch that verifies: device code shared by the attention kernels,
+// whose workgroups move the K/V of their kv head, and by the acceptance.  gfx950 only.
+//
+// As a launch of its own behind the verification the compaction cost 2 to 3 us of a step of 12 to 32 us, almost all of it start and
+// drain of a kernel that moves a few rows per head (a step in two launches -> in one: 15 rows of 8 fp32 heads of 64 x 256 keys 12.2
+// -> 10.1 us, 64 of 32 heads x 2048 keys 17.7 -> 14.8, 128 of 32/8 heads x 8192 keys 31.1 -> 29.9).  Here nobody waits either: what has to be over before a head's rows may move
+// arrives at a word of the (layer, sequence, kv head), and whoever completes the word moves them.  Arrivals are the workgroups whose split
+// reaches the tree (their sweep has read the tree's K/V), every row tile's, and the acceptance where it is part of the launch.
+// The workgroups with the tree end early, as the last split is the shortest, and move while they would wait for the other splits.
+#pragma once
+#include "cb_internal.h"
+
+namespace cb {
+
+// Pieces of 16 bytes in a head's row.
+__host__ __device__ constexpr int row_pieces(int D, int elem_bytes) { return D * elem_bytes / 16; }
+
+__device__ __forceinline__ int agent_load(const int32_t* p) {
+  return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The kernel's first argument once more, from its memory: what follows a sweep would otherwise be kept in scalar registers all through
+// it (35 of them spilled, 0.5 us a launch of the 64-row kernel).
+typedef const __attribute__((address_space(4))) AttnParams* ArgsPtr;
+__device__ __forceinline__ ArgsPtr fresh_args() {
+  ArgsPtr a = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+s"(a));
+#endif
+  return a;
+}
+__device__ __forceinline__ KvAddr fresh_kv(ArgsPtr a) {
+  return KvAddr{a->kv.k, a->kv.v, a->kv.block_table, a->kv.seq_stride, a->kv.token_stride, a->kv.head_stride, a->kv.num_blocks, a->kv.max_blocks, a->kv.block_size};
+}
+
+// The accepted path of one sequence as a wavefront holds it: lane i has path[1 + i].
+struct AcceptedPath {
+  const int32_t* row;
+  int max_depth, L, first;
+  __device__ __forceinline__ AcceptedPath(ArgsPtr a, int b) : row(a->move.path + (int64_t)b * (a->max_depth + 1)), max_depth(a->max_depth) {
+    L = agent_load(a->move.len + b);
+    first = from(0);
+    L = __builtin_amdgcn_readfirstlane(L < 0 ? 0 : (L > max_depth ? max_depth : L));
+  }
+  __device__ __forceinline__ int from(int j0) const {  // path[1 + j0 + lane]
+    const int j = 1 + j0 + (threadIdx.x & 63);
+    return agent_load(row + (j <= max_depth ? j : max_depth));
+  }
+  // whether any row has to move (the first of the root's children, and of its children's, are in place)
+  __device__ __forceinline__ bool moves() const {
+    const int lane = threadIdx.x & 63;
+    return L > 64 || __builtin_amdgcn_ballot_w64(lane < L && first != lane + 1) != 0;
+  }
+};
+
+// Moves the rows of HB kv heads of one sequence and layer, K and V, by one wavefront whose lanes each own a 16-byte piece of K's or V's row
+// for every JP-th step of the path.  All of a batch's reads are complete before its first write, and later batches read slots that no
+// earlier one wrote (path[j] >= j, increasing), so the result is that of the steps in order.  (hk: a head may be there twice.)
+template <int PIECES, int SHIFT, int HB>  // (SHIFT: log2 of the element's bytes)
+__device__ __forceinline__ void move_heads(const KvAddr& geo, const AcceptedPath& path, int b, int S, int N, const int (&hk)[HB]) {
+  constexpr int PER = 2 * PIECES, JP = 64 / PER;
+  // (loads in flight: as many as the registers hold, which in fp32 with head_dim 64 are 128)
+  constexpr int STEPS = PIECES == 16 && SHIFT == 2 ? 2 : (8 / JP < 4 ? 8 / JP : 4), kBatch = STEPS * JP;
+  static_assert(64 % PER == 0 && 64 % kBatch == 0, "");
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const int lane = threadIdx.x & 63, grp = lane / PER, vec = lane % PIECES;
+  // (a choice between two members would put the struct into memory)
+  const uintptr_t k = (uintptr_t)geo.k, to_v = (uintptr_t)geo.v - k;
+  CBL_GLOBAL char* const base = (CBL_GLOBAL char*)(k + ((lane / PIECES) & 1) * to_v + vec * 16);
+  int window = path.first;
+  for (int j0 = 0; j0 < path.L; j0 += kBatch) {
+    if (j0 > 0 && j0 % 64 == 0) window = path.from(j0);
+    u32x4 x[HB][STEPS];
+    bool live[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; s++) {
+      const int j = j0 + 1 + s * JP + grp;
+      const int src = __shfl(window, (j - 1) & 63, 64);
+      live[s] = j <= path.L && src > j && src < N;  // (src == j: nothing to move)
+      if (live[s]) {
+#pragma unroll
+        for (int i = 0; i < HB; i++) x[i][s] = *(const CBL_GLOBAL u32x4*)(base + (slot_offset(geo, b, S + src, hk[i]) << SHIFT));
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (lanes read what other lanes write)
+#pragma unroll
+    for (int s = 0; s < STEPS; s++) {
+      if (live[s]) {
+#pragma unroll
+        for (int i = 0; i < HB; i++) *(CBL_GLOBAL u32x4*)(base + (slot_offset(geo, b, S + j0 + 1 + s * JP + grp, hk[i]) << SHIFT)) = x[i][s];
+      }
+    }
+  }
+}
+
+// Arrivals that complete a head's word: the row tiles' workgroups whose split reaches the tree, and the acceptance.
+__device__ __forceinline__ uint32_t move_arrivals(ArgsPtr a, int tile_rows, int S, int N) {
+  const int tiles = (N * (a->Hq / a->Hkv) + tile_rows - 1) / tile_rows, splits = (S + N + a->chunk - 1) / a->chunk - S / a->chunk;
+  return (uint32_t)(tiles * splits + (a->move.own_acceptance ? 1 : 0));
+}
+__device__ __forceinline__ CBL_GLOBAL uint32_t* move_word(ArgsPtr a, int b, int hk) { return as_global(a->move.words) + (int64_t)b * a->Hkv + hk; }
+
+// The arrival of an attention workgroup, by one of its wavefronts, in two halves: begin() once every wavefront's K/V requests have
+// landed and been waited for, finish() where a round trip to memory does not hold up anything.
+template <int PIECES, int SHIFT>
+struct HeadMove {
+  bool mine = false;  // (uniform in the wavefront)
+  uint32_t all, old;
+  __device__ __forceinline__ void begin(int tile_rows, int b, int hk, int S, int N) {
+    const ArgsPtr a = fresh_args();
+    mine = true;
+    all = move_arrivals(a, tile_rows, S, N);
+    old = 0;
+    if (all > 1 && (threadIdx.x & 63) == 0) old = __hip_atomic_fetch_add(move_word(a, b, hk), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void finish(int b, int hk, int S, int N) {
+    if (!mine) return;
+    mine = false;
+    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)old) + 1 != all) return;
+    const ArgsPtr a = fresh_args();
+    const AcceptedPath path(a, b);
+    if (all > 1 && (threadIdx.x & 63) == 0) __hip_atomic_store(move_word(a, b, hk), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
+    if (path.moves()) move_heads<PIECES, SHIFT, 1>(fresh_kv(a), path, b, S, N, {hk});
+  }
+};
+
+// The acceptance's arrival for the heads of a sequence, by all NW wavefronts of its workgroup (logits_share), behind a barrier that
+// follows the acknowledgement of its stores; the heads whose attention is through already are moved here.
+template <int PIECES, int SHIFT, int NW>
+struct MoveAfter {
+  int tile_rows;
+  bool any;
+  __device__ __forceinline__ bool wanted() const { return any; }
+  __device__ __forceinline__ void operator()(int b, int S, int N) const {
+    const ArgsPtr a = fresh_args();
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), Hkv = a->Hkv;
+    const uint32_t all = move_arrivals(a, tile_rows, S, N);
+    const AcceptedPath path(a, b);
+    for (int h0 = w; h0 < Hkv; h0 += 64 * NW) {  // (lane i: head h0 + i NW, so that every wavefront has few to move)
+      const int hk = h0 + lane * NW;
+      uint32_t old = 0;
+      if (hk < Hkv) old = __hip_atomic_fetch_add(move_word(a, b, hk), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool last = hk < Hkv && old + 1 == all;
+      if (last) __hip_atomic_store(move_word(a, b, hk), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
+      unsigned long long todo = __builtin_amdgcn_ballot_w64(last);
+      if (!path.moves()) continue;
+      constexpr int HB = SHIFT == 2 ? 1 : 2;
+      while (todo != 0) {
+        int heads[HB];
+#pragma unroll
+        for (int i = 0; i < HB; i++) {
+          heads[i] = i > 0 && todo == 0 ? heads[0] : __builtin_amdgcn_readfirstlane(h0 + __builtin_ctzll(todo) * NW);
+          todo &= todo - 1;
+        }
+        move_heads<PIECES, SHIFT, HB>(fresh_kv(a), path, b, S, N, heads);
+      }
+    }
+  }
+};
+
+}  // namespace cb

@@ -1,0 +1,82 @@
+"""A verification and its compaction as one call (cb_verify_and_compact_device, what bind_step makes) against the two calls: the same
+attention, acceptance and cache bytes, step after step, whichever of a head's attention and the acceptance is through first."""
+import numpy as np
+import pytest
+
+from paper_2511_21699_amd import binding as B
+from paper_2511_21699_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # dtype, heads, kv heads, head_dim, vocabulary, prefixes, tree sizes, options, paged
+    ("bf16", 8, 8, 128, 1000, [1500], [40], {}, False),
+    ("bf16", 8, 8, 128, 128256, [0], [64], {}, False),                    # the acceptance is last
+    ("bf16", 32, 8, 128, 90000, [5], [16], {}, True),
+    ("bf16", 4, 4, 128, 500, [100], [256], {"splits": 11}, False),        # the tree in 9 splits
+    ("bf16", 4, 4, 128, 500, [95], [64], {"splits": 5}, True),            # and in 3, several at its edge
+    ("bf16", 32, 4, 128, 3000, [700, 64, 31], [130, 256, 1], {}, False),  # several row tiles
+    ("bf16", 32, 8, 128, 60000, [40, 2000], [20, 3], {"fuse_logits": 0}, True),
+    ("bf16", 16, 8, 128, 2000, [900] * 5, [50] * 5, {"external_merge": 1, "splits": 3}, False),
+    ("bf16", 16, 8, 128, 2000, [900] * 5, [50] * 5, {"coop_merge": 0, "splits": 3}, False),
+    ("bf16", 8, 2, 64, 700, [300, 10], [64, 33], {}, True),
+    ("bf16", 32, 8, 64, 33333, [1200], [100], {"splits": 4}, False),
+    ("f32", 8, 8, 64, 1000, [256], [15], {}, False),
+    ("f32", 16, 8, 128, 50000, [33, 700], [40, 17], {}, True),
+    ("f32", 6, 3, 128, 300, [120], [64], {"splits": 5}, False),
+    ("bf16", 8, 8, 128, 1000, [600], [40], {"attn_impl": 1}, False),      # (the scalar kernels: two launches)
+]
+
+
+@pytest.mark.parametrize("i", range(len(CASES)))
+@pytest.mark.parametrize("layout", [B.CB_LAYOUT_TOKEN_MAJOR, B.CB_LAYOUT_HEAD_MAJOR])
+def test_one_call_against_two(i, layout):
+    import torch
+    dtype, hq, hkv, d, vocab, lens, nodes, options, paged = CASES[i]
+    print(f"[case] step {CASES[i]} layout={layout}", flush=True)
+    rng = np.random.default_rng(i)
+    pars = [W.random_tree(rng, n, 2, 13, False)[0] for n in nodes]
+    case = W.custom_case(7000 + i, dtype, len(lens), hq, hkv, d, vocab, lens, pars, paged=paged, p_match=0.95)
+    total, moved = case.total_nodes, 0
+    got = []
+    for fused in (True, False):
+        dc = B.DeviceCase(case, layout=layout)
+        ver = B.Verifier(B.config_for_case(case))
+        for k, v in options.items():
+            ver.set_option(k, v)
+        par, tok = torch.from_numpy(case.parent).cuda(), torch.from_numpy(case.tokens).cuda()
+        out, k0 = torch.zeros_like(dc.q), dc.k.clone()
+        n, t = torch.zeros(len(lens), dtype=torch.int32, device="cuda"), torch.zeros(len(lens), case.max_depth + 1, dtype=torch.int32, device="cuda")
+        step = ver.bind_step(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, out, n, t, [dc.kv])
+        for _ in range(3):
+            if fused:
+                step()
+            else:
+                ver.verify_tree_device(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, out, n, t)
+                ver.compact_kv([dc.kv], len(lens), want_len=False)
+            torch.cuda.synchronize()
+            got.append((out.clone(), dc.k.clone(), dc.v.clone(), n.clone(), t.clone(), ver.get_path(len(lens)), ver.get_argmax(total)))
+        moved += int(not torch.equal(dc.k, k0))
+        ver.close()
+    for rep in range(3):
+        for a, b in zip(got[rep], got[3 + rep]):
+            assert (torch.equal(a, b) if isinstance(a, torch.Tensor) else np.array_equal(a, b)), f"step {rep}"
+    assert moved in (0, 2) and (moved == 2 or max(int(x) for x in got[0][3]) < 3)
+
+
+def test_operands_that_overlap_the_cache_take_two_launches():
+    """Queries that lie in the cache's memory: rows that move must not reach them before they are read."""
+    import torch
+    case = W.custom_case(7100, "bf16", 1, 8, 8, 128, 500, [300], [W.random_tree(np.random.default_rng(1), 40, 2, 9, False)[0]], p_match=0.95)
+    ref = None
+    for inside in (False, True):
+        dc = B.DeviceCase(case)
+        q = dc.k[0, 300:340] if inside else dc.k[0, 300:340].clone()   # ([nodes][heads][D], as the queries are)
+        ver = B.Verifier(B.config_for_case(case))
+        par, tok = torch.from_numpy(case.parent).cuda(), torch.from_numpy(case.tokens).cuda()
+        out = torch.zeros_like(dc.q)
+        n, t = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, case.max_depth + 1, dtype=torch.int32, device="cuda")
+        ver.bind_step(q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, out, n, t, [dc.kv])()
+        torch.cuda.synchronize()
+        ref = ref or (out, dc.k.clone())
+        assert torch.equal(out, ref[0]) and torch.equal(dc.k, ref[1])
+        ver.close()
