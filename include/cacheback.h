@@ -183,6 +183,18 @@ int cb_verify_and_compact_device(cb_ctx *ctx, void *hip_stream, int32_t batch, c
                                  int32_t num_layers, const cb_kv_layer *layers);
 
 /*
+ * One step of a model of `num_layers` layers whose queries are all there: cb_tree_attention_device for every layer below the last,
+ * cb_verify_tree_device for the last one and cb_compact_kv of all of them with new_kv_len = NULL, as one call with the same results, states
+ * and errors.  q, layers and attn_out are host arrays of one entry per layer.  Layers that share one geometry and block
+ * table are attended to together in as few launches as possible; where a layer's attn_out overlaps memory that another layer or the
+ * acceptance reads or writes, they are launched one by one, in order.
+ */
+int cb_model_step_device(cb_ctx *ctx, void *hip_stream, int32_t batch, int32_t num_layers, const void *const *q,
+                         const cb_kv_layer *layers, const int32_t *kv_len, const int32_t *node_offsets,
+                         const int32_t *d_tree_parent, const int32_t *d_draft_tokens, const void *logits,
+                         void *const *attn_out, int32_t *d_accepted_len, int32_t *d_accepted_tokens);
+
+/*
  * Tree attention alone (Section 3.2: every node attends to the cached prefix, its ancestors and
  * itself), for the layers of a model below the last one: the arguments of cb_verify_tree_device
  * without tokens, logits and results.  Launches only; leaves the state of the last verify call

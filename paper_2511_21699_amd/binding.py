@@ -20,7 +20,7 @@ CB_OK, CB_EINVAL, CB_ETREE, CB_ECAP, CB_ESTATE, CB_EHIP = range(6)
 CB_LAYOUT_TOKEN_MAJOR, CB_LAYOUT_HEAD_MAJOR = 0, 1
 ERROR_NAMES = {0: "CB_OK", 1: "CB_EINVAL", 2: "CB_ETREE", 3: "CB_ECAP", 4: "CB_ESTATE", 5: "CB_EHIP"}
 
-EXPORTS = ["cb_workspace_bytes", "cb_init", "cb_check_verify_args", "cb_plan_attention", "cb_verify_tree", "cb_verify_tree_device", "cb_verify_and_compact_device", "cb_tree_attention_device", "cb_tree_attention_noalloc",
+EXPORTS = ["cb_workspace_bytes", "cb_init", "cb_check_verify_args", "cb_plan_attention", "cb_verify_tree", "cb_verify_tree_device", "cb_verify_and_compact_device", "cb_model_step_device", "cb_tree_attention_device", "cb_tree_attention_noalloc",
            "cb_compact_kv", "cb_get_path", "cb_get_argmax", "cb_device_status", "cb_set_option",
            "cb_last_launch_info", "cb_last_attention_ms", "cb_debug_timestamps", "cb_probe_stream_read", "cb_last_error",
            "cb_destroy"]
@@ -68,6 +68,7 @@ def load():
     L.cb_verify_tree.argtypes = [vp, vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, i32p, i32p, vp, vp, i32p, i32p]
     L.cb_verify_tree_device.argtypes = [vp, vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, vp, vp, vp, vp, vp, vp]
     L.cb_verify_and_compact_device.argtypes = L.cb_verify_tree_device.argtypes + [C.c_int32, C.POINTER(CbKvLayer)]
+    L.cb_model_step_device.argtypes = [vp, vp, C.c_int32, C.c_int32, C.POINTER(vp), C.POINTER(CbKvLayer), i32p, i32p, vp, vp, vp, C.POINTER(vp), vp, vp]
     L.cb_tree_attention_device.argtypes = [vp, vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, vp, vp]
     L.cb_tree_attention_noalloc.argtypes = [C.POINTER(CbConfig), vp, C.c_int32, vp, C.POINTER(CbKvLayer), i32p, i32p, vp, vp]
     L.cb_compact_kv.argtypes = [vp, vp, C.c_int32, C.POINTER(CbKvLayer), i32p]
@@ -249,27 +250,20 @@ class Verifier:
     def bind_model_step(self, qs, kvs, kv_len, node_offsets, d_parent, d_tokens, logits, attn_outs, d_acc_len, d_acc_tok,
                         stream=None):
         """Pre-marshalled step of a whole model: tree attention for every layer (the last one inside the
-        verification call, which also scans the logits and accepts), then one compaction of all layers.
-        Returns a zero-argument callable that only makes the C calls."""
+        verification call, which also scans the logits and accepts), then one compaction of all layers
+        (cb_model_step_device).  Returns a zero-argument callable that only makes the C call."""
         kv_len, node_offsets = _i32(kv_len), _i32(node_offsets)
         st = self._stream(stream)
         nl = len(kvs)
         arr = (CbKvLayer * nl)(*kvs)
-        b = kv_len.shape[0]
-        att = [(self.ctx, st, b, qs[i].data_ptr(), C.byref(arr[i]), _ip(kv_len), _ip(node_offsets), d_parent.data_ptr(),
-                attn_outs[i].data_ptr()) for i in range(nl - 1)]
-        last = (self.ctx, st, b, qs[-1].data_ptr(), C.byref(arr[nl - 1]), _ip(kv_len), _ip(node_offsets),
-                d_parent.data_ptr(), d_tokens.data_ptr(), logits.data_ptr(), attn_outs[-1].data_ptr(),
-                d_acc_len.data_ptr(), d_acc_tok.data_ptr())
+        ptrs = lambda ts: (C.c_void_p * nl)(*[ts[i].data_ptr() for i in range(nl - 1)], ts[-1].data_ptr())  # noqa: E731
+        a = (self.ctx, st, kv_len.shape[0], nl, ptrs(qs), arr, _ip(kv_len), _ip(node_offsets), d_parent.data_ptr(),
+             d_tokens.data_ptr(), logits.data_ptr(), ptrs(attn_outs), d_acc_len.data_ptr(), d_acc_tok.data_ptr())
         keep = (kv_len, node_offsets, arr, qs, kvs, logits, attn_outs)
-        attention, verify, compact = self.L.cb_tree_attention_device, self.L.cb_verify_tree_device, self.L.cb_compact_kv
+        step = self.L.cb_model_step_device
 
         def call(_keep=keep):
-            rc = 0
-            for a in att:
-                rc = rc or attention(*a)
-            rc = rc or verify(*last)
-            rc = rc or compact(self.ctx, st, nl, arr, None)
+            rc = step(*a)
             if rc:
                 self._raise(rc)
         return call

@@ -23,7 +23,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 # The wide kernel's wavefronts have a SIMD to themselves and use more than 256 registers.  With matrix instructions in their
 # form for accumulation registers the scores would be copied out of those before every vector instruction; in the other
 # form only what the vector ALU rarely touches ends up there (the queries and what does not fit).
-FILE_FLAGS = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for name in ("cb_attn_wide.hip", "cb_attn_wide_px.hip")}
+FILE_FLAGS = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for name in ("cb_attn_wide.hip", "cb_attn_wide_px.hip", "cb_attn_wide_layers.hip", "cb_attn_wide_step.hip")}
 
 
 def _flags(src: str) -> list:
@@ -197,7 +197,7 @@ def scratch_violations(asm: str, file_name: str = "") -> list:
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
-    checked = ["cb_attn_wide_px.hip", "cb_attn_wide.hip", "cb_attn_mfma.hip"]
+    checked = ["cb_attn_wide_px.hip", "cb_attn_wide.hip", "cb_attn_wide_layers.hip", "cb_attn_wide_step.hip", "cb_attn_mfma.hip"]
     with ThreadPoolExecutor(max_workers=min(8, len(srcs) + len(checked))) as ex:
         listings = [ex.submit(device_asm, os.path.join(CSRC, name)) for name in checked]  # (the longest first, beside the compilation)
         objs = list(ex.map(_compile, sorted(srcs, key=lambda s: os.path.basename(s) not in checked)))

@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <vector>
 #include <mutex>
 #include <new>
 
@@ -69,7 +70,8 @@ WsLayout ws_layout(const cb_config& c) {
   L.max_splits = effective_max_splits(c);
   L.amax_chunks = (int)(((int64_t)c.vocab_size + kArgmaxChunk - 1) / kArgmaxChunk);
   const int g = c.num_q_heads / c.num_kv_heads;
-  L.ticket_count = 4 * c.max_batch * c.num_kv_heads * ((c.max_nodes * g + kRowTile - 1) / kRowTile);  // two 64-bit words per tile
+  // two 64-bit words per tile; at least 1024 of those, for launches that serve several layers
+  L.ticket_count = std::max(4096, 4 * c.max_batch * c.num_kv_heads * ((c.max_nodes * g + kRowTile - 1) / kRowTile));
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
   L.anc = take(mt * kAncWords * 4);
@@ -548,6 +550,12 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
   return p;
 }
 
+// A launch that serves several layers.
+struct ModelLaunch {
+  Plan plan;
+  LayerTable table;
+};
+
 // The scratch layout of a cb_tree_attention_noalloc call, and the plan it is cut for.  Whether a call fits the fixed array
 // is a property of its shape that callers rely on, so it is decided by one measure per kind of call, whatever the
 // kernels would like to have: bf16 states in 16-row tiles at the planned splits for bf16 with head_dim 128, fp32 rows at the
@@ -596,6 +604,80 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
   }
 }
 
+// The attention of several layers as one launch, where all their queries are there.  A layer's launch by itself is a chain of latencies --
+// start, first data, partial states, merge, drain -- that fills the chip with splits of a few hundred keys; together the layers
+// fill it with whole sequences (32 layers of 64 nodes x 32 heads x 2048 keys: 1024 workgroups of one split each, four rounds, and
+// nothing to merge).
+// Splits are for steps whose tiles leave compute units idle (2 layers of 8 kv heads), in the first round of workgroups or in the last.  A call that is not split when its layers are launched one by one, whose sums stay in the accumulators, is not
+// split here.  False: launched one by one, where that is expected to be faster (few long tiles and no room for their partial states).
+bool plan_layers(const cb_config& c, const WsLayout& lay, int layers, int batch, const int32_t* kv_len, const int32_t* node_offsets, ModelLaunch* out) {
+  const Plan last = plan_call(c, lay.max_splits, lay.scalar_splits, 0, 0, 0, batch, kv_len, node_offsets, true);
+  const Plan other = plan_call(c, lay.max_splits, lay.scalar_splits, 0, 0, 0, batch, kv_len, node_offsets, false);
+  if (last.impl != other.impl) return false;
+  Planner planner(c, lay.max_splits, lay.scalar_splits, 0, 0, batch, kv_len, node_offsets);
+  const int total = node_offsets[batch];
+  const size_t room = lay.total - lay.partial;
+  // The logits' workgroups come first.  Where the launch has several rounds their compute units go on with the attention afterwards: as
+  // many as give each wavefront one item, so that no unit starts late.  In one round, the fewest that are through in 0.7 of the time.
+  const double lb = c.logits_dtype == CB_F32 ? 4 : 2, lg = (double)total * c.vocab_size * lb;
+  const int64_t items = total * (((int64_t)c.vocab_size + kArgmaxChunk - 1) / kArgmaxChunk);
+  auto logits_wgs = [&](bool rounds, double us, int waves) {
+    const int64_t most = std::min<int64_t>(192, (items + waves - 1) / waves);
+    const int64_t want = rounds ? most : std::min<int64_t>(96, (int64_t)(std::max(lg / 20e3, items * kLogitsItemUs) / (0.7 * us)));
+    return (int)(std::max<int64_t>(want, 1) + 7) / 8 * 8;
+  };
+  Plan& p = out->plan;
+  if (planner.f32_tiles) {
+    double us = 0.0, one = 0.0;
+    auto splits = [&](int most, int n, double* t) { return attn_f32_splits(c.num_q_heads, c.num_kv_heads, c.head_dim, most, batch, kv_len, node_offsets, planner.max_len, 248, n, t); };
+    splits(lay.scalar_splits, 1, &one);
+    const size_t per_split = (size_t)total * c.num_q_heads * partial_stride(c.head_dim) * 4;
+    const int tiles = batch * c.num_kv_heads * ((planner.max_nodes * planner.g + 15) / 16);
+    const bool tickets = (int64_t)tiles * layers <= lay.ticket_count;
+    const int ns = splits(tickets ? (int)std::max<int64_t>(1, std::min<int64_t>(lay.scalar_splits, room / (per_split * layers))) : 1, layers, &us);
+    if (us > (one + 4.0) * layers) return false;
+    p = planner.cut(ns, false);
+    out->table.partial_bytes = p.nsplit > 1 ? (int64_t)per_split * p.nsplit : 0;
+    p.logits_wgs = logits_wgs((int64_t)tiles * layers * p.nsplit > 248, us, 8);
+    return true;
+  }
+  if (last.impl != 2) return false;
+  const bool precise = last.precise || other.precise, whole = last.nsplit == 1 || other.nsplit == 1, wide = planner.tile_rows != kRowTile;
+  const double stage = (wide && std::min(planner.tile_rows, planner.max_nodes * planner.g) > 128 ? 1.7 : 1.0) * c.head_dim / 128;
+  double kv = 0.0;
+  for (int b = 0; b < batch; b++) kv += (double)planner.len[b] * c.num_kv_heads * c.head_dim * 4;
+  auto us_of = [&](int ns, int n) {  // (of one launch for n layers)
+    const SplitSums& s = planner.split_into(ns);
+    const int64_t jobs = s.jobs * n;
+    const double merge = s.grid_x > 1 ? (jobs > 240 ? 4.0 + 0.7 * s.grid_x * (planner.tile_rows / 128.0) : 2.0) / stage : 0.0;  // (by the last to arrive, or cooperative)
+    const double stages = batch == 1 ? (double)((jobs + 255) / 256) * s.longest(merge)
+                                     : std::max(s.longest(merge), jobs > 256 ? (s.work + s.merged * merge) * n / 256 + 0.5 * s.shortest : 0.0);
+    return 5.0 + std::max(stages * stage, n * kv / 5.5e6);
+  };
+  double us = us_of(1, layers);
+  p = planner.cut(1, precise);
+  out->table.partial_bytes = 0;
+  int64_t tiles = 0;  // of a layer, as the tickets are numbered
+  tiles = (int64_t)batch * c.num_kv_heads * ((planner.max_nodes * planner.g + planner.tile_rows - 1) / planner.tile_rows);
+  const int waves = wide ? 4 : 8;
+  if (!whole && tiles * layers <= std::min(kCoopTiles, lay.ticket_count / 4)) {
+    for (int ns = 2; ns <= std::min(planner.cap(), 64); ns++) {
+      if (planner.chunk_of(ns) == planner.chunk_of(ns - 1)) continue;
+      const double t = us_of(ns, layers);
+      const Plan cut = planner.cut(ns, precise);
+      const size_t bytes = attn_mfma_partial_bytes(c.head_dim, cut.precise, planner.max_nodes * planner.g, total, c.num_q_heads, c.num_kv_heads, batch, cut.nsplit);
+      if (cut.impl != 2 || bytes * layers > room) break;
+      if (t >= us || !attn_mfma_merges_inside(c.head_dim, cut.precise, planner.max_nodes * planner.g, cut.nsplit)) continue;
+      us = t;
+      p = cut;
+      out->table.partial_bytes = (int64_t)bytes;
+    }
+  }
+  if (p.impl != 2 || us > us_of(other.nsplit, 1) * layers) return false;
+  p.logits_wgs = logits_wgs(tiles * layers * p.nsplit + 8 > 256, us, waves);
+  return true;
+}
+
 int check_common(cb_ctx* ctx, int32_t batch, const void* q, const cb_kv_layer* kv, const int32_t* kv_len,
                  const int32_t* node_offsets, const void* logits, void* attn_out) {
   if (!ctx) return set_err(nullptr, CB_EINVAL, "null context");
@@ -617,11 +699,12 @@ int order_behind_host_form(cb_ctx* ctx, hipStream_t st) {
   return CB_OK;
 }
 
-// Enqueues the whole verification on `st`; the tree is already on the device.
+// Enqueues the whole verification on `st`; the tree is already on the device.  model: the attention of all layers of its table (q, kv and
+// attn_out are the first one's).
 int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb_kv_layer* kv,
                  const int32_t* kv_len, const int32_t* node_offsets, const int32_t* d_parent,
                  const int32_t* d_tokens, const void* logits, void* attn_out, int32_t* d_len, int32_t* d_tok,
-                 int64_t stage_mask = 15) {
+                 int64_t stage_mask = 15, const ModelLaunch* model = nullptr) {
   const cb_config& c = ctx->cfg;
   SeqMeta meta{};
   for (int b = 0; b < batch; b++) meta.kv_len[b] = kv_len[b];
@@ -647,7 +730,8 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     ctx->amax_dirty = false;
   }
   const bool f32_tiles = c.qkv_dtype == CB_F32 && ctx->opt_impl != 1;
-  const Plan plan = ctx->fixed_plan ? *ctx->fixed_plan
+  const Plan plan = model             ? model->plan
+                    : ctx->fixed_plan ? *ctx->fixed_plan
                                     : plan_call(c, ctx->lay.max_splits, ctx->lay.scalar_splits, (int)ctx->opt_impl, (int)ctx->opt_splits, (int)ctx->opt_logits_wgs,
                                                 batch, kv_len, node_offsets, (stage_mask & 8) != 0);
   const int n_logits = plan.logits_wgs;
@@ -670,16 +754,17 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   ap.batch = batch;
   if (plan.impl == 2) {
     const int g = c.num_q_heads / c.num_kv_heads, rows = attn_mfma_tile_rows(plan.max_nodes * g);
-    int64_t live = 0;  // per kv head
+    const int64_t layers = model ? model->table.count : 1;
+    int64_t live = 0;  // per kv head and layer
     for (int i = 0; i < CB_MAX_BATCH; i++) {
       meta.start[i] = INT32_MAX;
       if (i >= batch) continue;
       const int b = meta.by_length[i];
       const int64_t n = node_offsets[b + 1] - node_offsets[b];
-      meta.start[i] = (int32_t)(live * (c.num_kv_heads / 8));
+      meta.start[i] = (int32_t)(live * (c.num_kv_heads / 8) * layers);
       live += (n * g + rows - 1) / rows * ((kv_len[b] + n + plan.chunk - 1) / plan.chunk);
     }
-    ap.live_wgs = (int32_t)(live * c.num_kv_heads);
+    ap.live_wgs = (int32_t)(live * c.num_kv_heads * layers);
   }
   ap.scale = c.softmax_scale > 0.f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
   ap.status = ctx->dev<int32_t>(ctx->lay.status);
@@ -757,11 +842,11 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   if (timing) CB_HIP(ctx, hipEventRecord(ctx->ev0, st));
   if (!(stages & 2)) {
   } else if (use_mfma) {
-    CB_LAUNCH(ctx, launch_attn_mfma(st, ap, meta, plan.max_nodes, total, fused ? &lw : nullptr, &merge_kind));  // merges its own splits
+    CB_LAUNCH(ctx, launch_attn_mfma(st, ap, meta, plan.max_nodes, total, fused ? &lw : nullptr, model ? &model->table : nullptr, &merge_kind));  // merges its own splits
     kernels += merge_kind == 3 ? 2 : 1;
   } else if (f32_tiles) {
     const bool external = plan.nsplit > 1 && ap.force_external_merge;
-    CB_LAUNCH(ctx, launch_attn_f32(st, ap, meta, plan.max_nodes, fused ? &lw : nullptr));
+    CB_LAUNCH(ctx, launch_attn_f32(st, ap, meta, plan.max_nodes, fused ? &lw : nullptr, model ? &model->table : nullptr));
     if (external) CB_LAUNCH(ctx, launch_merge(st, ap, meta, c.qkv_dtype, total));
     merge_kind = plan.nsplit > 1 ? (external ? 3 : 2) : 0;
     kernels += external ? 2 : 1;
@@ -810,6 +895,61 @@ int check_device_shapes(cb_ctx* ctx, int32_t batch, const cb_kv_layer* kv, const
     if (kv_len[b] + n > room || kv_len[b] + n > (1ll << 30)) return set_err(ctx, CB_ECAP, "sequence %d does not fit the cache", b);
   }
   return CB_OK;
+}
+
+// Whether the layers of a step can be launched together: everything about them valid (otherwise the calls one by one report what is
+// not), one geometry and block table for all, options as they are by default, and no layer's results in the memory that another one, or
+// the acceptance, reads or writes.
+bool layers_together(cb_ctx* ctx, int batch, int n, const void* const* q, const cb_kv_layer* layers, const int32_t* kv_len, const int32_t* node_offsets,
+                     const int32_t* d_parent, const int32_t* d_tokens, const void* logits, void* const* attn_out, const int32_t* d_len, const int32_t* d_tok) {
+  const cb_config& c = ctx->cfg;
+  if (ctx->opt_splits > 0 || ctx->opt_impl || ctx->opt_time || ctx->opt_stages != 15 || ctx->opt_timeline || ctx->opt_external || ctx->opt_fork ||
+      !ctx->opt_fuse || !ctx->opt_coop || ctx->opt_logits_wgs > 0)
+    return false;
+  if (!kv_len || !node_offsets || !d_parent || !d_tokens || !logits || !d_len || !d_tok || batch < 1 || batch > c.max_batch || ((uintptr_t)logits & 15)) return false;
+  const cb_kv_layer& first = layers[0];
+  for (int i = 0; i < n; i++) {
+    const cb_kv_layer& l = layers[i];
+    if (!q[i] || !attn_out[i] || !l.k || !l.v || (((uintptr_t)q[i] | (uintptr_t)attn_out[i] | (uintptr_t)l.k | (uintptr_t)l.v) & 15)) return false;
+    if (l.capacity_or_num_blocks != first.capacity_or_num_blocks || l.block_table != first.block_table || l.max_blocks_per_seq != first.max_blocks_per_seq || l.layout != first.layout) return false;
+  }
+  const int valid = check_device_shapes(ctx, batch, &first, kv_len, node_offsets);
+  ctx->err[0] = 0;
+  if (valid || (first.layout != CB_LAYOUT_TOKEN_MAJOR && first.layout != CB_LAYOUT_HEAD_MAJOR)) return false;
+  struct Use {
+    Span s;
+    bool written;
+  };
+  std::vector<Use> uses;
+  const size_t rows = node_offsets[batch], qo = rows * c.num_q_heads * c.head_dim * (c.qkv_dtype == CB_F32 ? 4 : 2), cache = cache_bytes(c, first, batch);
+  try {
+    uses.reserve((size_t)n * 4 + 6);
+    for (int i = 0; i < n; i++) {
+      uses.push_back({{q[i], qo}, false});
+      uses.push_back({{layers[i].k, cache}, false});
+      uses.push_back({{layers[i].v, cache}, false});
+      uses.push_back({{attn_out[i], qo}, true});
+    }
+    uses.push_back({{logits, rows * c.vocab_size * (c.logits_dtype == CB_F32 ? 4 : 2)}, false});
+    uses.push_back({{d_parent, rows * 4}, false});
+    uses.push_back({{d_tokens, rows * 4}, false});
+    uses.push_back({{first.block_table, c.block_size > 0 ? (size_t)batch * first.max_blocks_per_seq * 4 : 0}, false});
+    uses.push_back({{d_len, (size_t)batch * 4}, true});
+    uses.push_back({{d_tok, (size_t)batch * (c.max_depth + 1) * 4}, true});
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
+  // In the order of their starts, a stretch that meets an earlier one starts before the furthest end of those.
+  std::sort(uses.begin(), uses.end(), [](const Use& a, const Use& b) { return (uintptr_t)a.s.at < (uintptr_t)b.s.at; });
+  uintptr_t any = 0, written = 0;
+  for (const Use& u : uses) {
+    if (u.s.bytes == 0) continue;
+    const uintptr_t at = (uintptr_t)u.s.at, end = at + u.s.bytes;
+    if (at < (u.written ? any : written)) return false;
+    any = std::max(any, end);
+    if (u.written) written = std::max(written, end);
+  }
+  return true;
 }
 
 }  // namespace
@@ -1010,6 +1150,48 @@ int cb_verify_and_compact_device(cb_ctx* ctx, void* hip_stream, int32_t batch, c
                                        d_accepted_len, d_accepted_tokens);
   if (ctx) ctx->want_move = false;
   if (rc || ctx->moved || num_layers == 0) return rc;
+  return cb_compact_kv(ctx, hip_stream, num_layers, layers, nullptr);
+}
+
+int cb_model_step_device(cb_ctx* ctx, void* hip_stream, int32_t batch, int32_t num_layers, const void* const* q, const cb_kv_layer* layers,
+                         const int32_t* kv_len, const int32_t* node_offsets, const int32_t* d_tree_parent, const int32_t* d_draft_tokens,
+                         const void* logits, void* const* attn_out, int32_t* d_accepted_len, int32_t* d_accepted_tokens) {
+  if (!ctx) return set_err(nullptr, CB_EINVAL, "null context");
+  ctx->err[0] = 0;
+  if (num_layers < 1 || !q || !layers || !attn_out) return set_err(ctx, CB_EINVAL, "null argument");
+  if (num_layers == 1)
+    return cb_verify_and_compact_device(ctx, hip_stream, batch, q[0], layers, kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits, attn_out[0],
+                                        d_accepted_len, d_accepted_tokens, 1, layers);
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  int done = 0;
+  if (layers_together(ctx, batch, num_layers, q, layers, kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits, attn_out, d_accepted_len, d_accepted_tokens)) {
+    // (as few launches as the table allows, of about as many layers each)
+    const int launches = (num_layers + kTableLayers - 1) / kTableLayers;
+    ModelLaunch m;
+    for (int i = 0; i < launches; i++) {
+      const int n = num_layers * (i + 1) / launches - done, mask = i + 1 < launches ? 3 : 15;
+      m.table.count = n;
+      if ((i == 0 || n != num_layers / launches) && !plan_layers(ctx->cfg, ctx->lay, n, batch, kv_len, node_offsets, &m)) break;
+      for (int j = 0; j < n; j++) {
+        const int l = done + j;
+        m.table.at[j].q = q[l];
+        m.table.at[j].out = attn_out[l];
+        m.table.at[j].k = layers[l].k;
+        m.table.at[j].v = layers[l].v;
+      }
+      const int rc = run_pipeline(ctx, st, batch, q[done], &layers[done], kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits, attn_out[done],
+                                  d_accepted_len, d_accepted_tokens, mask, &m);
+      if (rc) return rc;
+      done += n;
+    }
+  }
+  for (; done < num_layers; done++) {
+    const int rc = done + 1 < num_layers
+                       ? cb_tree_attention_device(ctx, hip_stream, batch, q[done], &layers[done], kv_len, node_offsets, d_tree_parent, attn_out[done])
+                       : cb_verify_tree_device(ctx, hip_stream, batch, q[done], &layers[done], kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits,
+                                               attn_out[done], d_accepted_len, d_accepted_tokens);
+    if (rc) return rc;
+  }
   return cb_compact_kv(ctx, hip_stream, num_layers, layers, nullptr);
 }
 

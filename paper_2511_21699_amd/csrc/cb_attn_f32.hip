@@ -57,12 +57,23 @@ __device__ __forceinline__ float rows_max(float x) {  // over the four lanes wit
 }
 __device__ __forceinline__ float weight(float m, float ref) { return m == -INFINITY ? 0.f : expf(m - ref); }
 
-template <int D>
-__device__ __forceinline__ void attn_f32_tile(const AttnParams& p, const SeqMetaLanes& ml, int wg, F32Lds<D>& sh) {
+template <int D, bool MOVE, typename Layers>
+__device__ __forceinline__ void attn_f32_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, F32Lds<D>& sh, const Layers& layers) {
   constexpr int NJ = D / 16, NB = D / 64;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, r = l & 15, h = l >> 4;
   // The kv head runs fastest: with a multiple of 8 heads a head's tiles and splits meet in one XCD's L2.  Then row
   // tiles, splits, and the sequences from the longest to the shortest.
+  AttnParams p = p_arg;
+  if constexpr (Layers::kMany) {
+    const int i = __builtin_amdgcn_readfirstlane(wg / layers.wgs);
+    wg -= i * layers.wgs;
+    p.q = layers.at[i].q;
+    p.out = layers.at[i].out;
+    p.kv.k = layers.at[i].k;
+    p.kv.v = layers.at[i].v;
+    p.partial = reinterpret_cast<float*>(reinterpret_cast<char*>(p.partial) + i * layers.partial_bytes);
+    p.tickets += (int64_t)i * layers.tiles;
+  }
   const int hk = wg % p.Hkv;
   int rest = wg / p.Hkv;
   const int rt = rest % p.grid_y;
@@ -217,7 +228,7 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p, const SeqMeta
   if (h == 0) sh.ml[w][r] = float2{m, lsum};
   __syncthreads();
   HeadMove<row_pieces(D, 4), 2> move;
-  if (p.move.words && k1 > S && w == kF32Waves - 1) move.begin(kF32Rows, b, hk, S, N);  // (nobody reads K or V any more)
+  if (MOVE && k1 > S && w == kF32Waves - 1) move.begin(kF32Rows, b, hk, S, N);  // (nobody reads K or V any more)
   const int orow = tid / (D / 4), c = tid % (D / 4) * 4;
   const bool live = orow < kF32Rows && row0 + orow < M;
   const int onode = (row0 + orow) / g;
@@ -244,7 +255,7 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p, const SeqMeta
       if (c == 0) store_pair(pp + D, mm, ll);
     }
   }
-  auto finish_move = [&] { move.finish(b, hk, S, N); };
+  auto finish_move = [&] { if (MOVE) move.finish(b, hk, S, N); };
   if (nsplit == 1 || p.external_merge) {  // (k_merge follows: the kernel boundary orders the stores)
     finish_move();
     return;
@@ -295,26 +306,45 @@ template <int D>
 __global__ __launch_bounds__(64 * kF32Waves) void k_attn_f32(AttnParams p, SeqMeta meta) {
   __shared__ F32Lds<D> sh;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  attn_f32_tile<D>(p, ml, blockIdx.x, sh);
+  attn_f32_tile<D, false>(p, ml, blockIdx.x, sh, OneLayer{});
 }
 
 // The whole verification in one launch: the first lw.n_wgs workgroups do the logits work, the others the attention.
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void k_verify_f32(AttnParams p, SeqMeta meta, LogitsWork lw) {
+template <int D, bool MOVE>
+__device__ __forceinline__ void verify_f32(const AttnParams& p, const SeqMeta& meta, const LogitsWork& lw) {
   __shared__ union Lds {
     F32Lds<D> attn;
     AcceptWaveLds accept;
   } sh;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   const int wg = (int)blockIdx.x - lw.n_wgs;
-  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept, MoveAfter<row_pieces(D, 4), 2, kF32Waves>{kF32Rows, p.move.words != nullptr});
-  else attn_f32_tile<D>(p, ml, wg, sh.attn);
+  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept, after_acceptance<MOVE, row_pieces(D, 4), 2, kF32Waves>(kF32Rows));
+  else attn_f32_tile<D, MOVE>(p, ml, wg, sh.attn, OneLayer{});
+}
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves) void k_verify_f32(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_f32<D, false>(p, meta, lw); }
+// with the compaction (lw.n_wgs is 0 where the logits work has a launch of its own)
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves) void k_step_f32(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_f32<D, true>(p, meta, lw); }
+
+// The attention of several layers in one launch, with the logits work (of the last one) in its first workgroups where lw.n_wgs is not 0.
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves) void k_model_f32(AttnParams p, SeqMeta meta, LogitsWork lw, LayerTable layers) {
+  __shared__ union Lds {
+    F32Lds<D> attn;
+    AcceptWaveLds accept;
+  } sh;
+  const SeqMetaLanes ml = seq_meta_prefetch(meta);
+  const int wg = (int)blockIdx.x - lw.n_wgs;
+  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept);
+  else attn_f32_tile<D, false>(p, ml, wg, sh.attn, layers);
 }
 
 // Splits of the longest sequence.  A workgroup costs about 3 us beside its sweep (start, combine, tail), every 128 keys
 // it sweeps 1.7 us at head_dim 128 (a unit for each wavefront, two of them to a matrix core), a merge 2.5 us and a
-// little for every split; `units` compute units run one workgroup each.
-int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int32_t* kv_len, const int32_t* node_offsets, int max_len, int units) {
+// little for every split; `units` compute units run one workgroup each.  us: that
+// estimate for the count returned.
+int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int32_t* kv_len, const int32_t* node_offsets, int max_len, int units, int layers, double* us) {
   const int cap = max_splits < (max_len + 127) / 128 ? max_splits : (max_len + 127) / 128;
   int best = 1;
   double best_cost = 0.0;
@@ -326,19 +356,36 @@ int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int
       jobs += (int64_t)((n * (Hq / Hkv) + kF32Rows - 1) / kF32Rows) * Hkv * ((kv_len[b] + n + chunk - 1) / chunk);
     }
     const double sweep = 1.7 * D / 128 * ((chunk + 127) / 128);
-    const double cost = (double)((jobs + units - 1) / units) * (3.0 + sweep) + (ns > 1 ? 2.5 + 0.15 * ns : 0.0);
+    const double cost = (double)((jobs * layers + units - 1) / units) * (3.0 + sweep) + (ns > 1 ? 2.5 + 0.15 * ns : 0.0);
     if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
   }
+  if (us) *us = best_cost;
   return best;
 }
 
-hipError_t launch_attn_f32(hipStream_t st, const AttnParams& params, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw) {
+hipError_t launch_attn_f32(hipStream_t st, const AttnParams& params, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw, const LayerTable* layers) {
   AttnParams p = params;
   p.grid_y = (max_nodes_in_call * (p.Hq / p.Hkv) + kF32Rows - 1) / kF32Rows;
   p.external_merge = p.force_external_merge;
-  const int64_t wgs = (int64_t)p.Hkv * p.grid_y * p.nsplit * p.batch + (lw ? lw->n_wgs : 0);
+  const int64_t per_layer = (int64_t)p.Hkv * p.grid_y * p.nsplit * p.batch, wgs = per_layer * (layers ? layers->count : 1) + (lw ? lw->n_wgs : 0);
   if (wgs > INT32_MAX || (p.D != 64 && p.D != 128)) return hipErrorInvalidValue;
   const dim3 grid((uint32_t)wgs), block(64 * kF32Waves);
+  if (layers) {
+    if (p.external_merge) return hipErrorInvalidValue;  // (the merge kernel knows one layer)
+    LayerTable table = *layers;
+    table.wgs = (int32_t)per_layer;
+    table.tiles = p.batch * p.Hkv * p.grid_y;
+    const LogitsWork work = lw ? *lw : LogitsWork{};
+    if (p.D == 64) hipLaunchKernelGGL(k_model_f32<64>, grid, block, 0, st, p, meta, work, table);
+    else hipLaunchKernelGGL(k_model_f32<128>, grid, block, 0, st, p, meta, work, table);
+    return hipGetLastError();
+  }
+  if (p.move.words) {
+    const LogitsWork work = lw ? *lw : LogitsWork{};
+    if (p.D == 64) hipLaunchKernelGGL(k_step_f32<64>, grid, block, 0, st, p, meta, work);
+    else hipLaunchKernelGGL(k_step_f32<128>, grid, block, 0, st, p, meta, work);
+    return hipGetLastError();
+  }
   if (lw && p.D == 64) hipLaunchKernelGGL(k_verify_f32<64>, grid, block, 0, st, p, meta, *lw);
   else if (lw) hipLaunchKernelGGL(k_verify_f32<128>, grid, block, 0, st, p, meta, *lw);
   else if (p.D == 64) hipLaunchKernelGGL(k_attn_f32<64>, grid, block, 0, st, p, meta);

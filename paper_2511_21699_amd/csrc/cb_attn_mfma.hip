@@ -138,10 +138,10 @@ __device__ __forceinline__ void compute_unit(const uint4* __restrict__ ks, const
   }
 }
 
-// One attention workgroup; `wg` is its number among those that do attention.  MOVE: the launch may compact its cache.
-template <int D, bool PX, bool MOVE, bool TS>
+// One attention workgroup; `wg` is its number among those that do attention.  MOVE: the launch compacts its cache.
+template <int D, bool PX, bool MOVE, bool TS, typename Layers>
 __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, unsigned long long ts0,
-                                          TileLds& sh, uint4* ring, unsigned long long* ts_sh) {
+                                          TileLds& sh, uint4* ring, unsigned long long* ts_sh, const Layers& layers) {
   using F = Feed<D, 8, 16>;
   constexpr int NS = F::kSlots, PRO = F::kPrologue, P = PartialLayout<D, 16, PX>::P;
   AttnParams p = p_arg;
@@ -149,7 +149,8 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   CB_LDS unsigned long long* ts = (CB_LDS unsigned long long*)ts_sh;
   first_stamps<TS>(ts, ts0);
   TileJob jb;
-  if (!tile_job(p, ml, wg, kSmallRows, jb)) return;
+  if (!tile_job(p, ml, wg, kSmallRows, layers, jb)) return;
+  take_layer(p, jb, layers);
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const int gi = w >> 2, wi = w & 3;
   const int c = l & 15, kg = l >> 4;
@@ -236,7 +237,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   const float lsum = st.lacc[0] * w0 + ml2.y * w1;
 #undef CB_TS
   HeadMove<row_pieces(D, 2), 1> move;
-  if (MOVE && (p.coop_merge & 2) && tree_split && w == 0) move.begin(kSmallRows, jb.b, jb.hk, S, jb.N);
+  if (MOVE && tree_split && w == 0) move.begin(kSmallRows, jb.b, jb.hk, S, jb.N);
   write_rows<D, 16, PX, P / 2>(p, jb, wi, grow, f, gi * (P / 2), m, lsum, c2, gi == 0, l);
   auto finish_move = [&] { if (MOVE) move.finish(jb.b, jb.hk, S, jb.N); };
   if (jb.nsplit == 1 || p.external_merge) {  // (a following kernel merges: the kernel boundary orders the stores)
@@ -253,14 +254,14 @@ __device__ __forceinline__ void attn_workgroup(const AttnParams& p, const SeqMet
   __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
-  attn_tile<D, PX, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
+  attn_tile<D, PX, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
 // The whole verification in one launch: the first lw.n_wgs workgroups do the logits work (they are dispatched
 // first, so the acceptance is through long before the attention is, and a waiting host has its results then),
 // the others the attention.  Neither waits for the other.
-template <int D, bool PX, bool TS>
+template <int D, bool PX, bool MOVE, bool TS>
 __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqMeta& meta, const LogitsWork& lw) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
@@ -270,11 +271,22 @@ __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqM
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) {
-    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), MoveAfter<row_pieces(D, 2), 1, 8>{kSmallRows, (p.coop_merge & 2) != 0});
+    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<MOVE, row_pieces(D, 2), 1, 8>(kSmallRows));
     return;
   }
-  attn_tile<D, PX, true, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
+  attn_tile<D, PX, MOVE, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, wg, ts_sh);
+}
+
+// The attention of several layers in one launch, with the logits work (of the last one) in its first workgroups where lw.n_wgs is not 0.
+template <int D, bool PX>
+__global__ __launch_bounds__(512) void k_model_mfma(AttnParams p, SeqMeta meta, LogitsWork lw, LayerTable layers) {
+  const SeqMetaLanes ml = seq_meta_prefetch(meta);
+  __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
+  __shared__ TileLds sh;
+  const int wg = (int)blockIdx.x - lw.n_wgs;
+  if (wg < 0) logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
+  else attn_tile<D, PX, false, false>(p, ml, wg, 0ull, sh, ring, nullptr, layers);
 }
 
 // head_dim 64 always holds probabilities and partial sums in 32 bits, head_dim 128 in the precise builds.
@@ -283,9 +295,12 @@ __global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) {
 template <bool TS>
 __global__ __launch_bounds__(512) void k_attn_precise(AttnParams p, SeqMeta meta) { attn_workgroup<128, true, TS>(p, meta); }
 template <int D, bool TS>
-__global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, TS>(p, meta, lw); }
+__global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, false, TS>(p, meta, lw); }
 template <bool TS>
-__global__ __launch_bounds__(512) void k_verify_precise(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<128, true, TS>(p, meta, lw); }
+__global__ __launch_bounds__(512) void k_verify_precise(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<128, true, false, TS>(p, meta, lw); }
+// with the compaction (builds of their own: what follows the sweep takes scalar registers from it, 2 to 3 % of a long one)
+template <int D, bool PX>
+__global__ __launch_bounds__(512) void k_step_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, PX, true, false>(p, meta, lw); }
 
 // Stand-alone merge of the partials, used when a tile's partials are too many for one
 // workgroup to pull through its compute unit: one workgroup per TR-row tile, its four waves take a quarter of the
@@ -339,8 +354,16 @@ bool attn_mfma_supports(const AttnParams& p) {
 // 58).
 int attn_mfma_tile_rows(int mrows) { return mrows <= kSmallRows ? kSmallRows : 256; }
 
+// One workgroup can pull about 50 GB/s of partials through its compute unit: beyond a few hundred
+// KiB per tile a separate, fully parallel merge kernel is cheaper than the merge by a tile's last workgroup.
+bool attn_mfma_merges_inside(int D, bool precise, int mrows, int nsplit) {
+  const int rt_rows = attn_mfma_tile_rows(mrows), tr = rt_rows == kSmallRows ? 16 : 32;
+  const int in_tile = (std::min(mrows, rt_rows) + tr - 1) / tr;
+  return (int64_t)nsplit * in_tile * block_bytes(D, tr, precise) <= 320 * 1024;
+}
+
 hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call,
-                            int total_nodes, const LogitsWork* logits_work, int* merge_kind) {
+                            int total_nodes, const LogitsWork* logits_work, const LayerTable* layers, int* merge_kind) {
   if (!attn_mfma_supports(p)) return hipErrorInvalidValue;
   const int g = p.Hq / p.Hkv;
   const int M = max_nodes_in_call * g;
@@ -359,14 +382,20 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   } else if (q.grid_y % 8 == 0 && p.batch > 1) {
     q.xcd_remap = 3;
   }
+  LayerTable table;
+  if (layers) {
+    table = *layers;
+    table.wgs = (int32_t)T;
+    table.tiles = p.batch * p.Hkv * tiles;
+    if (q.xcd_remap != 2) T *= table.count;
+    if (T > INT32_MAX) return hipErrorInvalidValue;
+  }
+  const int n_layers = layers ? layers->count : 1;
   // (the logits' workgroups come first; a multiple of 8 of them leaves the others' XCDs as they are)
   const int n_logits = logits_work ? logits_work->n_wgs : 0;
   const dim3 grid((uint32_t)(n_logits + T));
-  // one workgroup can pull about 50 GB/s of partials through its compute unit: beyond a few hundred
-  // KiB per tile a separate, fully parallel merge kernel is cheaper than the in-kernel merge
   const int tr = rt_rows == kSmallRows ? 16 : 32;
-  const int in_tile = ((M < rt_rows ? M : rt_rows) + tr - 1) / tr;
-  q.external_merge = (p.nsplit > 1 && (int64_t)p.nsplit * in_tile * block_bytes(p.D, tr, p.precise) > 320 * 1024) ? 1 : 0;
+  q.external_merge = p.nsplit > 1 && !attn_mfma_merges_inside(p.D, p.precise, M, p.nsplit) ? 1 : 0;
   // A grid that is resident in one round (one workgroup per compute unit) merges cooperatively:
   // every workgroup of a tile takes a slice, so the volume per compute unit does not grow with
   // the split count and no second launch is needed.
@@ -377,15 +406,28 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
     else compute_units = -1;
   }
   q.coop_merge = (p.coop_merge >= 0 && p.coop_tickets && p.nsplit > 1 && p.nsplit <= 64 && compute_units > 0 && T + n_logits <= compute_units &&
-                  (int64_t)p.Hkv * tiles * p.batch <= kCoopTiles) ? 1 : 0;
+                  (int64_t)p.Hkv * tiles * p.batch * n_layers <= kCoopTiles) ? 1 : 0;
   if (q.coop_merge) q.external_merge = 0;
   if (p.force_external_merge && p.nsplit > 1) { q.external_merge = 1; q.coop_merge = 0; }  // (option "external_merge": a test aid)
-  if (p.move.words) q.coop_merge |= 2;
-  if (merge_kind) *merge_kind = p.nsplit <= 1 ? 0 : ((q.coop_merge & 1) ? 1 : (q.external_merge ? 3 : 2));
+  if (merge_kind) *merge_kind = p.nsplit <= 1 ? 0 : (q.coop_merge ? 1 : (q.external_merge ? 3 : 2));
+  if (layers && q.external_merge) return hipErrorInvalidValue;  // (the merge kernel knows one layer)
   const bool ts = p.timeline != 0;  // (the timeline build of the same kernels: a measurement aid)
   hipError_t e;
   auto launch = [&](auto* stamped, auto* plain, auto... args) { hipLaunchKernelGGL(ts ? stamped : plain, grid, dim3(512), 0, st, args...); };
-  if (rt_rows != kSmallRows) {
+  if (p.move.words && rt_rows == kSmallRows) {  // (no timeline build; with the logits work always)
+    if (!logits_work) return hipErrorInvalidValue;
+    if (p.D == 64) hipLaunchKernelGGL((k_step_mfma<64, true>), grid, dim3(512), 0, st, q, meta, *logits_work);
+    else if (p.precise) hipLaunchKernelGGL((k_step_mfma<128, true>), grid, dim3(512), 0, st, q, meta, *logits_work);
+    else hipLaunchKernelGGL((k_step_mfma<128, false>), grid, dim3(512), 0, st, q, meta, *logits_work);
+    e = hipGetLastError();
+  } else if (layers) {
+    const LogitsWork lw = logits_work ? *logits_work : LogitsWork{};
+    if (rt_rows != kSmallRows) return launch_attn_wide_layers(st, q, meta, M, (int)T, lw, table);
+    if (p.D == 64) hipLaunchKernelGGL((k_model_mfma<64, true>), grid, dim3(512), 0, st, q, meta, lw, table);
+    else if (p.precise) hipLaunchKernelGGL((k_model_mfma<128, true>), grid, dim3(512), 0, st, q, meta, lw, table);
+    else hipLaunchKernelGGL((k_model_mfma<128, false>), grid, dim3(512), 0, st, q, meta, lw, table);
+    return hipGetLastError();
+  } else if (rt_rows != kSmallRows) {
     e = launch_attn_wide(st, q, meta, M, (int)T, logits_work);
   } else if (logits_work) {
     if (p.D == 64) launch(k_verify_mfma<64, true>, k_verify_mfma<64, false>, q, meta, *logits_work);

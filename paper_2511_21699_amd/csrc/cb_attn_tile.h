@@ -206,9 +206,11 @@ struct TileJob {
   int row0;            // first row of the tile
   int split, nsplit;   // and the sequence's number of splits
   int k0, k1;          // the split's keys
+  int layer;           // of those that the launch serves
 };
 
-__device__ __forceinline__ bool tile_job(const AttnParams& p, const SeqMetaLanes& ml, int d, int tile_rows, TileJob& j) {
+template <typename Layers>
+__device__ __forceinline__ bool tile_job(const AttnParams& p, const SeqMetaLanes& ml, int d, int tile_rows, const Layers& layers, TileJob& j) {
   // Workgroups are handed to the 8 XCDs round-robin in dispatch order.  With xcd_remap the
   // dispatch index d is renumbered to j = (d % 8) * (T / 8) + d / 8, so that consecutive j --
   // in particular all splits of one (sequence, kv head, row tile) -- sit on the same XCD and
@@ -218,6 +220,13 @@ __device__ __forceinline__ bool tile_job(const AttnParams& p, const SeqMetaLanes
   int by;
   j.tiles = p.grid_y / p.Hkv;
   j.g = p.Hq / p.Hkv;
+  j.layer = 0;
+  if constexpr (Layers::kMany) {  // (one layer behind the other; a layer's workgroups are a multiple of 8 where they are renumbered)
+    if (p.xcd_remap != 2) {
+      j.layer = d / layers.wgs;
+      d -= j.layer * layers.wgs;
+    }
+  }
   if (p.xcd_remap == 2) {
     // XCD x = d % 8 works through position r = d / 8 of its own list: all splits of a tile together,
     // the tiles of one sequence together, the sequences from the longest to the shortest -- so the
@@ -233,7 +242,12 @@ __device__ __forceinline__ bool tile_job(const AttnParams& p, const SeqMetaLanes
     const int splits = (s.S + s.N + p.chunk - 1) / p.chunk, tiles = (s.N * j.g + tile_rows - 1) / tile_rows;
     j.split = at % splits;
     const int tile = at / splits;
-    by = (x * (p.Hkv >> 3) + tile / tiles) * j.tiles + tile % tiles;
+    int head = tile / tiles;
+    if constexpr (Layers::kMany) {  // (a sequence's tiles of all layers: the last workgroups are still the shortest)
+      j.layer = head / (p.Hkv >> 3);
+      head -= j.layer * (p.Hkv >> 3);
+    }
+    by = (x * (p.Hkv >> 3) + head) * j.tiles + tile % tiles;
   } else if (p.xcd_remap == 3) {
     const int x = d & 7, r = d >> 3, ypx = p.grid_y >> 3, tile = r / p.grid_x;
     j.split = r % p.grid_x;
@@ -262,6 +276,22 @@ __device__ __forceinline__ bool tile_job(const AttnParams& p, const SeqMetaLanes
   j.k1 = (j.k0 + p.chunk < len) ? j.k0 + p.chunk : len;
   j.nsplit = (len + p.chunk - 1) / p.chunk;
   return true;
+}
+
+// The layer's pointers, scratch memory and tickets in the place of the launch's.
+template <typename Layers>
+__device__ __forceinline__ void take_layer(AttnParams& p, const TileJob& j, const Layers& layers) {
+  if constexpr (Layers::kMany) {
+    const int i = __builtin_amdgcn_readfirstlane(j.layer);
+    p.q = layers.at[i].q;
+    p.out = layers.at[i].out;
+    p.kv.k = layers.at[i].k;
+    p.kv.v = layers.at[i].v;
+    p.partial = reinterpret_cast<float*>(reinterpret_cast<char*>(p.partial) + i * layers.partial_bytes);
+    p.tickets += (int64_t)i * layers.tiles * 4;
+    p.coop_tickets += (int64_t)i * layers.tiles * (kCoopTicketStride / 4);
+    asm volatile("" : "+s"(p.q), "+s"(p.out), "+s"(p.kv.k), "+s"(p.kv.v), "+s"(p.partial), "+s"(p.tickets), "+s"(p.coop_tickets));
+  }
 }
 
 // Timing aid: the stamps go to LDS and are copied out when the kernel ends -- a store to memory inside, even one that
@@ -541,8 +571,8 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
 // of the arrivals' XCC_ID (hardware register 20, bits 3:0): all ids equal mine  <=>
 // sum = n*id and sumsq = n*id*id.  A second word per tile holds one bit per split whose
 // workgroup gave up waiting (cooperative merge only).
-// aside(): what the first wave has to do beside; it is called behind the barrier of the workgroup's arrival, where that wave waits for the other
-// splits, or behind its share of the merge, if it has one.
+// aside(): what the first wave has to do beside, where it would wait for the other splits, or, in the merge by the last to arrive, behind its
+// share of that.
 template <int D, int TR, bool PX, int NW, int MAXROWS, bool TS, typename Aside>
 __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& jb, TileLds& sh, CB_LDS unsigned long long* ts, Aside aside) {
   constexpr int P = PartialLayout<D, TR, PX>::P;
@@ -558,7 +588,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
   // (cooperative merge: the tiles' words are polled, so each tile has a 4 KiB stretch of its own
   // in a separate area -- neighbours in one line would all be served by one memory channel)
   const int64_t tile_id = ((int64_t)jb.b * p.Hkv + jb.hk) * jb.tiles + jb.rt;
-  CB_GLOBAL unsigned long long* ticket = (p.coop_merge & 1) ? (CB_GLOBAL unsigned long long*)p.coop_tickets + tile_id * (kCoopTicketStride / 8)
+  CB_GLOBAL unsigned long long* ticket = p.coop_merge ? (CB_GLOBAL unsigned long long*)p.coop_tickets + tile_id * (kCoopTicketStride / 8)
                                                       : (CB_GLOBAL unsigned long long*)p.tickets + 2 * tile_id;
   constexpr unsigned long long kArrivals = 0xfffull;
   const unsigned long long xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & 15u;
@@ -576,7 +606,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     return jb.row0 + i * TR < jb.M;
   };
 
-  if (!(p.coop_merge & 1)) {
+  if (!p.coop_merge) {
     // Merge by the last workgroup of the tile to arrive: the others leave at once and free their
     // compute units (grids of several rounds of workgroups).
     if (tid == 0) {
@@ -594,12 +624,10 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     __syncthreads();
     CB_TS(6);
     const int flag = sh.flag;
-    if (w == 0 && !flag) aside();
-    if (!flag) return;
     // Same XCD: the write-through stores left the lines in this L2, plain (cached) loads are coherent
     // with them.  Otherwise read past the L2 with agent-coherent loads.
     constexpr int NP = 4, BS = PX ? 4 : 8;
-    for (int u = w; u < MAXROWS / TR * (P / NP); u += NW) {
+    for (int u = flag ? w : MAXROWS; u < MAXROWS / TR * (P / NP); u += NW) {
       const int i = u / (P / NP);
       int64_t gr;
       if (!tile_row(i, &gr)) break;  // (nothing behind it either)
@@ -607,9 +635,10 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
       if (flag == 1) merge_pieces<D, TR, PX, NP, 0, BS>(prsrc, gr, byte, gout, nsplit, (u % (P / NP)) * NP, l);
       else merge_pieces<D, TR, PX, NP, kAgentCoherent, BS>(prsrc, gr, byte, gout, nsplit, (u % (P / NP)) * NP, l);
     }
+    if (w == 0) aside();
+    if (!flag) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     CB_TS(7);
-    if (w == 0) aside();
     return;
   }
 
@@ -696,7 +725,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
   int64_t gr_first = -1;
   const bool have_first = u_first < NU && tile_row(u_first / upt, &gr_first);
   const uint32_t byte_first = partial_byte<D, TR, PX>(p, jb, u_first / upt);
-  if (w == 0 && !have_first) aside();
+  if (w == 0) aside();  // (the wave with the fewest units: it has one of its own only where they are at least NW)
   // the waves wait for thread 64's verdicts in LDS
   int flag;
   while ((flag = __hip_atomic_load(&sh.flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0) __builtin_amdgcn_s_sleep(1);
@@ -723,7 +752,6 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
 
   while (__hip_atomic_load(&sh.flag2, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) __builtin_amdgcn_s_sleep(1);
   if (sh.todo2 != 0) merge_slices(sh.todo2, false);
-  if (w == 0 && have_first) aside();
   if (do_ts64) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     ts[7] = wall_clock64();

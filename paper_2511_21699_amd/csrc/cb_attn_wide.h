@@ -616,25 +616,26 @@ __device__ __forceinline__ void sweep_tile(const AttnParams& p, const TileJob& j
 
 // One attention workgroup of four waves whose tile has up to 256 rows; `wg` is its number among those that do attention.
 // R128: row tiles of a wave where the tile has 65 to 128 rows, four groups of one with one key group, or two of two with two key groups.
-template <int D, bool PX, bool PG, int R128, bool TS>
+template <int D, bool PX, bool PG, int R128, bool MOVE, bool TS, typename Layers>
 __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, unsigned long long ts0,
-                                               TileLds& sh, uint4* ring, unsigned long long* ts_sh) {
+                                               TileLds& sh, uint4* ring, unsigned long long* ts_sh, const Layers& layers) {
   AttnParams p = p_arg;
   pin_args(p);
   CB_LDS unsigned long long* ts = (CB_LDS unsigned long long*)ts_sh;
   first_stamps<TS>(ts, ts0);
   TileJob jb;
-  if (!tile_job(p, ml, wg, 256, jb)) return;
+  if (!tile_job(p, ml, wg, 256, layers, jb)) return;
+  take_layer(p, jb, layers);
   const int rows = jb.M - jb.row0;
   if (rows <= 64) sweep_tile<D, PX, PG, 1, 2, TS>(p, jb, sh, ring, ts);
   else if (rows <= 128) sweep_tile<D, PX, PG, R128, 4 / R128, TS>(p, jb, sh, ring, ts);
   else sweep_tile<D, PX, PG, 2, 4, TS>(p, jb, sh, ring, ts);
   HeadMove<row_pieces(D, 2), 1> move;
-  if ((p.coop_merge & 2) && jb.k1 > jb.S) {  // (uniform)
+  if (MOVE && jb.k1 > jb.S) {  // (uniform)
     bare_barrier();  // (every wave's requests have landed)
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) move.begin(256, jb.b, jb.hk, jb.S, jb.N);
   }
-  auto finish_move = [&] { move.finish(jb.b, jb.hk, jb.S, jb.N); };
+  auto finish_move = [&] { if (MOVE) move.finish(jb.b, jb.hk, jb.S, jb.N); };
   if (jb.nsplit == 1 || p.external_merge) {  // (a following kernel merges: the kernel boundary orders the stores)
     finish_move();
     return;
@@ -649,7 +650,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void k_attn_wide(AttnParams p, 
   __shared__ __align__(1024) uint4 ring[Feed<D, kWideWaves, 32>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
-  attn_wide_tile<D, PX, PG, R128, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh);
+  attn_wide_tile<D, PX, PG, R128, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
@@ -665,11 +666,33 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void k_verify_wide(AttnParams p
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) {
-    logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), MoveAfter<row_pieces(D, 2), 1, kWideWaves>{256, (p.coop_merge & 2) != 0});
+    logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
     return;
   }
-  attn_wide_tile<D, PX, PG, R128, TS>(p, ml, wg, ts0, sh, ring, ts_sh);
+  attn_wide_tile<D, PX, PG, R128, false, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, wg, ts_sh);
+}
+
+// The attention of several layers in one launch, with the logits work (of the last one) in its first workgroups where lw.n_wgs is not 0.
+template <int D, bool PX, bool PG, int R128>
+__global__ __launch_bounds__(64 * kWideWaves, 1) void k_model_wide(AttnParams p, SeqMeta meta, LogitsWork lw, LayerTable layers) {
+  const SeqMetaLanes ml = seq_meta_prefetch(meta);
+  __shared__ __align__(1024) uint4 ring[Feed<D, kWideWaves, 32>::kRingVecs];
+  __shared__ TileLds sh;
+  const int wg = (int)blockIdx.x - lw.n_wgs;
+  if (wg < 0) logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
+  else attn_wide_tile<D, PX, PG, R128, false, false>(p, ml, wg, 0ull, sh, ring, nullptr, layers);
+}
+
+// A verification with the compaction in its launch; lw.n_wgs is 0 where the logits work has a launch of its own.
+template <int D, bool PX, bool PG, int R128>
+__global__ __launch_bounds__(64 * kWideWaves, 1) void k_step_wide(AttnParams p, SeqMeta meta, LogitsWork lw) {
+  const SeqMetaLanes ml = seq_meta_prefetch(meta);
+  __shared__ __align__(1024) uint4 ring[Feed<D, kWideWaves, 32>::kRingVecs];
+  __shared__ TileLds sh;
+  const int wg = (int)blockIdx.x - lw.n_wgs;
+  if (wg < 0) logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<true, row_pieces(D, 2), 1, kWideWaves>(256));
+  else attn_wide_tile<D, PX, PG, R128, true, false>(p, ml, wg, 0ull, sh, ring, nullptr, OneLayer{});
 }
 
 template <int D, bool PX, bool PG, int R128>

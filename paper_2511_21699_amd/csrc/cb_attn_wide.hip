@@ -10,13 +10,14 @@ namespace cb {
 // rows of 32 x 900 18.5 -> 14.9, x 20000 (2528 keys to a split) 73.8 -> 71.4, but paged 74.3 -> 75.8 and with 100 rows x 60000 187 -> 195;
 // 70 rows x 60000 paged 184 -> 181; 8 sequences of up to 8000 paged keys in two splits 189 -> 186, of up to 16000 304 -> 308; 16 of up to
 // 16384 in one split 401 -> 407.  With 32-bit sums at head_dim 128, whose slices are long, those take 586 -> 590.
-static bool two_tiles(const AttnParams& p, int rows) {
+bool attn_wide_two_tiles(const AttnParams& p, int rows) {
   return p.batch > 1 ? p.chunk > 4096 : p.kv.block_size > 0 && rows > 96 && p.chunk > 2048;
 }
 
 hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int rows, int n_tiles, const LogitsWork* lw) {
+  if (p.move.words) return launch_attn_wide_step(st, p, meta, rows, n_tiles, lw);
   if (p.D == 64 || p.precise) return launch_attn_wide_px(st, p, meta, n_tiles, lw);
-  const bool two = two_tiles(p, rows);
+  const bool two = attn_wide_two_tiles(p, rows);
   if (p.kv.block_size > 0) {
     return two ? launch_wide<128, false, true, 2>(st, p, meta, n_tiles, lw) : launch_wide<128, false, true, 1>(st, p, meta, n_tiles, lw);
   }

@@ -193,8 +193,7 @@ struct AttnParams {
   int32_t grid_x, grid_y, grid_z;  // launch grid, repeated here so the kernel reads one argument block
   int32_t external_merge;  // 1: the kernel only writes partials; launch_attn_mfma runs a merge kernel afterwards
   int32_t coop_merge;      // 1: every workgroup of a tile merges a slice of it after a bounded wait for the others
-                           // (set by the launcher when the grid is resident in one round); -1 on input: never.
-                           // Bit 1, set by the launcher: move.words is not null
+                           // (set by the launcher when the grid is resident in one round); -1 on input: never
   int32_t spin_limit;      // cooperative merge: polls of the tile's ticket before a workgroup gives up
   int32_t max_depth;    // deepest node the configuration allows (bounds the ancestor-set rounds)
   int32_t timeline;     // 1: launch the timeline build of the kernel (stamps per workgroup in dbg_ts; a measurement aid)
@@ -202,6 +201,27 @@ struct AttnParams {
   int32_t* status;      // device status word (bit 4: a merge had to use cross-XCD loads)
   MoveArgs move;
   unsigned long long* dbg_ts;  // timeline build: 8 timestamps (100 MHz) per workgroup, 1024 rows
+};
+
+// The layers that an attention launch serves: one, whose pointers are the kernel's arguments, or those of a table, which share
+// the arguments' geometry (a whole model's attention as one launch; a kernel argument of its own, so that launches for one layer do
+// not carry it).
+struct OneLayer {
+  static constexpr bool kMany = false;
+};
+constexpr int kTableLayers = 32;
+struct LayerTable {
+  static constexpr bool kMany = true;
+  int32_t count;
+  int32_t wgs;            // attention workgroups of a layer (xcd_remap 2, where a sequence's tiles are those of all layers: unused)
+  int32_t tiles;          // tickets of a layer
+  int64_t partial_bytes;  // partial states of a layer
+  struct {
+    const void* q;
+    void* out;
+    const void* k;
+    const void* v;
+  } at[kTableLayers];
 };
 
 // ---- launchers (defined in the .hip files); all enqueue on `st` and return the launch status
@@ -224,21 +244,29 @@ hipError_t launch_attn_simt(hipStream_t st, const AttnParams& p, const SeqMeta& 
 // fp32 attention on the matrix cores, 16-row tiles; with lw != nullptr the same launch also scans the logits and runs the
 // acceptance.  Partials in the scalar kernel's layout (force_external_merge: launch_merge has to follow), tickets: a 32-bit
 // word per (sequence, kv head, 16-row tile), zero between launches.
-int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int32_t* kv_len, const int32_t* node_offsets, int max_len, int units);
-hipError_t launch_attn_f32(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw);
+int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int32_t* kv_len, const int32_t* node_offsets, int max_len, int units,
+                    int layers = 1, double* us = nullptr);
+hipError_t launch_attn_f32(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw, const LayerTable* layers);
 hipError_t launch_merge(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int dtype, int total_nodes);
 int attn_mfma_tile_rows(int mrows);            // rows per workgroup tile chosen for a given g*N
 // bytes the MFMA path's partial states can take in calls whose largest sequence has `mrows` rows per kv head (its own layout,
 // padded to 16-row tiles per kv head where one small tile holds them, else to 32-row ones)
 size_t attn_mfma_partial_bytes(int D, bool precise, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
+bool attn_mfma_merges_inside(int D, bool precise, int mrows, int nsplit);  // whether no merge kernel is needed, for tiles of a sequence with mrows rows per kv head
 bool attn_mfma_supports(const AttnParams& p);  // shape/geometry the MFMA kernel takes (bf16 is the caller's check)
-// with logits_work != nullptr the same launch also scans the logits and runs the acceptance
+// with logits_work != nullptr the same launch also scans the logits and runs the acceptance; with layers != nullptr it serves all of the
+// table's layers, in splits that need no merge kernel (p.live_wgs, meta.start: of all layers)
 // merge_kind (may be null): 0 one split, 1 cooperative merge, 2 merge by the last workgroup to arrive, 3 merge kernel
 // (by launch_attn_mfma; rows: of the largest sequence, per kv head; n_tiles: workgroups that do attention)
 hipError_t launch_attn_wide(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int rows, int n_tiles, const LogitsWork* lw);
+// (the compaction in the launch; lw may be null)
+hipError_t launch_attn_wide_step(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int rows, int n_tiles, const LogitsWork* lw);
+bool attn_wide_two_tiles(const AttnParams& p, int rows);
+// (layers: see launch_attn_mfma)
+hipError_t launch_attn_wide_layers(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int rows, int n_tiles, const LogitsWork& lw, const LayerTable& layers);
 hipError_t launch_attn_wide_px(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int n_tiles, const LogitsWork* lw);
 hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call,
-                            int total_nodes, const LogitsWork* logits_work, int* merge_kind);
+                            int total_nodes, const LogitsWork* logits_work, const LayerTable* layers, int* merge_kind);
 
 }  // namespace cb
 

@@ -60,7 +60,7 @@ struct AcceptArgs {
   unsigned long long* best;  // [sumN] row maxima (amax_word), kAmaxStride words apart; zero between launches
   int32_t max_depth;
   int32_t* argmax_out;     // [sumN]
-  int32_t* path;           // [B][max_depth + 1] (these two are for the compaction, which may be part of the launch:
+  int32_t* path;           // [B][max_depth + 1] (these two are for the compaction; where it is part of the launch they are
   int32_t* len_ctx;        // [B] written through to memory)
   int32_t* len_user;       // [B]
   int32_t* tok_user;       // [B][max_depth + 1]
@@ -77,8 +77,10 @@ __device__ __forceinline__ void publish_done(const AcceptArgs& g, int b, bool wr
   if (writer) __hip_atomic_store(as_global(g.done_flag) + b, g.done_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-__device__ __forceinline__ void store_through(int32_t* p, int x) {
-  __hip_atomic_store(as_global(p), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+template <bool THROUGH>
+__device__ __forceinline__ void store_result(int32_t* p, int x) {
+  if (THROUGH) __hip_atomic_store(as_global(p), x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *as_global(p) = x;
 }
 
 // Parent of node t as loaded -> as used (-1 at the root; an entry outside [0, t) becomes "child of the
@@ -107,6 +109,7 @@ __device__ __forceinline__ unsigned long long shfl_u64(unsigned long long x, int
   const uint32_t lo = __shfl((uint32_t)x, lane, 64), hi = __shfl((uint32_t)(x >> 32), lane, 64);
   return (unsigned long long)lo | ((unsigned long long)hi << 32);
 }
+template <bool THROUGH>
 __device__ __forceinline__ void accept_small(const AcceptArgs& g, int b, int off, int N) {
   const int t = threadIdx.x & 63;
   const bool live = t < N;
@@ -145,17 +148,17 @@ __device__ __forceinline__ void accept_small(const AcceptArgs& g, int b, int off
   const unsigned long long on_path = shfl_u64(mine, best);
   const int stride = g.max_depth + 1;
   if (live && ((on_path >> t) & 1ull)) {
-    store_through(g.path + b * stride + depth, t);
+    store_result<THROUGH>(g.path + b * stride + depth, t);
     as_global(g.tok_user)[b * stride + depth] = a;
   }
   for (int d = t; d < stride; d += 64) {
     if (d > L) {
-      store_through(g.path + b * stride + d, -1);
+      store_result<THROUGH>(g.path + b * stride + d, -1);
       as_global(g.tok_user)[b * stride + d] = -1;
     }
   }
   if (t == 0) {
-    store_through(g.len_ctx + b, L);
+    store_result<THROUGH>(g.len_ctx + b, L);
     as_global(g.len_user)[b] = L;
   }
   publish_done(g, b, t == 0);
@@ -176,6 +179,7 @@ struct AcceptWaveLds {
 };
 __device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+template <bool THROUGH>
 __device__ __forceinline__ void accept_large(AcceptWaveLds& sh, const AcceptArgs& g, int b, int off, int N) {
   constexpr int KN = CB_MAX_NODES / 64;
   const int lane = threadIdx.x & 63;
@@ -258,27 +262,28 @@ __device__ __forceinline__ void accept_large(AcceptWaveLds& sh, const AcceptArgs
     const int t = lane + 64 * k;
     if (t < N && sh.mark[t]) {
       const int depth = (int)(st[k] >> 16);
-      store_through(g.path + b * stride + depth, t);
+      store_result<THROUGH>(g.path + b * stride + depth, t);
       as_global(g.tok_user)[b * stride + depth] = a[k];
     }
   }
   for (int d = lane; d < stride; d += 64) {
     if (d > L) {
-      store_through(g.path + b * stride + d, -1);
+      store_result<THROUGH>(g.path + b * stride + d, -1);
       as_global(g.tok_user)[b * stride + d] = -1;
     }
   }
   if (lane == 0) {
-    store_through(g.len_ctx + b, L);
+    store_result<THROUGH>(g.len_ctx + b, L);
     as_global(g.len_user)[b] = L;
   }
   publish_done(g, b, lane == 0);
   wave_lds_sync();
 }
 
+template <bool THROUGH = false>
 __device__ __forceinline__ void accept_wave(AcceptWaveLds& sh, const AcceptArgs& g, int b, int off, int N) {
-  if (N <= 64) accept_small(g, b, off, N);
-  else accept_large(sh, g, b, off, N > CB_MAX_NODES ? CB_MAX_NODES : N);
+  if (N <= 64) accept_small<THROUGH>(g, b, off, N);
+  else accept_large<THROUGH>(sh, g, b, off, N > CB_MAX_NODES ? CB_MAX_NODES : N);
 }
 
 // The logits work of one verification call: items (row, chunk of kArgmaxChunk or kArgmaxShortChunk elements), item = row *
@@ -403,9 +408,9 @@ constexpr int kTicketDirect = 48;  // arrivals up to which one word serves a seq
 
 // LOADS: loads of 16 bytes that a lane has in flight, as the kernel's registers allow.  EB: bytes of a logits element
 // where the kernel is built for one type, else 0.  after(b, S, N): what all wavefronts of the workgroup that accepted sequence b do
-// then, behind a barrier; after.wanted() whether there is anything (both uniform).
+// then, behind a barrier (uniform).
 struct NothingAfter {
-  __device__ __forceinline__ bool wanted() const { return false; }
+  static constexpr bool kAny = false;
   __device__ __forceinline__ void operator()(int, int, int) const {}
 };
 template <int NW, int LOADS, bool SHORT = false, int EB = 0, typename After = NothingAfter>
@@ -428,7 +433,7 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
   if (!lw.accept_after) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (w != 0 && !after.wanted()) return;
+  if (!After::kAny && w != 0) return;
   unsigned long long accepted = 0;
   auto count = [&](CBL_GLOBAL uint32_t* word, uint32_t n, uint32_t full) {  // true: this arrival completed it
     uint32_t old = 0;
@@ -460,12 +465,12 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
       }
     }
     if (done) {
-      accept_wave(sh, lw.accept, b, off, N);
+      accept_wave<After::kAny>(sh, lw.accept, b, off, N);
       accepted |= 1ull << b;
     }
     i = seq_end;
   }
-  if (!after.wanted()) return;
+  if constexpr (!After::kAny) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the results are in memory before anybody is told)
   if (threadIdx.x == 0) sh.accepted = accepted;
   __syncthreads();
@@ -474,6 +479,13 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
     const SeqShape s = seq_shape(ml, b);
     after(b, s.S, s.N);
   }
+}
+
+// What follows the acceptance in a launch that compacts its cache (MOVE), or in one that does not.
+template <bool MOVE, int PIECES, int SHIFT, int NW>
+__device__ __forceinline__ auto after_acceptance(int tile_rows) {
+  if constexpr (MOVE) return MoveAfter<PIECES, SHIFT, NW>{tile_rows};
+  else return NothingAfter{};
 }
 
 }  // namespace cb

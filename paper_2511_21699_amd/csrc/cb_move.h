@@ -53,9 +53,15 @@ struct AcceptedPath {
   }
 };
 
+__device__ __forceinline__ long long lane_value(long long x, int lane) {
+  return (long long)(uint32_t)__shfl((int)x, lane, 64) | ((long long)__shfl((int)(x >> 32), lane, 64) << 32);
+}
+
 // Moves the rows of HB kv heads of one sequence and layer, K and V, by one wavefront whose lanes each own a 16-byte piece of K's or V's row
 // for every JP-th step of the path.  All of a batch's reads are complete before its first write, and later batches read slots that no
 // earlier one wrote (path[j] >= j, increasing), so the result is that of the steps in order.  (hk: a head may be there twice.)
+// Where a step's rows lie is worked out by one lane for all: the block table's entries come in one round trip, and the code, of which every
+// call has a copy, is a quarter of what a division for each row makes it.
 template <int PIECES, int SHIFT, int HB>  // (SHIFT: log2 of the element's bytes)
 __device__ __forceinline__ void move_heads(const KvAddr& geo, const AcceptedPath& path, int b, int S, int N, const int (&hk)[HB]) {
   constexpr int PER = 2 * PIECES, JP = 64 / PER;
@@ -67,27 +73,41 @@ __device__ __forceinline__ void move_heads(const KvAddr& geo, const AcceptedPath
   // (a choice between two members would put the struct into memory)
   const uintptr_t k = (uintptr_t)geo.k, to_v = (uintptr_t)geo.v - k;
   CBL_GLOBAL char* const base = (CBL_GLOBAL char*)(k + ((lane / PIECES) & 1) * to_v + vec * 16);
-  int window = path.first;
-  for (int j0 = 0; j0 < path.L; j0 += kBatch) {
-    if (j0 > 0 && j0 % 64 == 0) window = path.from(j0);
-    u32x4 x[HB][STEPS];
-    bool live[STEPS];
+  int64_t head[HB];
 #pragma unroll
-    for (int s = 0; s < STEPS; s++) {
-      const int j = j0 + 1 + s * JP + grp;
-      const int src = __shfl(window, (j - 1) & 63, 64);
-      live[s] = j <= path.L && src > j && src < N;  // (src == j: nothing to move)
-      if (live[s]) {
-#pragma unroll
-        for (int i = 0; i < HB; i++) x[i][s] = *(const CBL_GLOBAL u32x4*)(base + (slot_offset(geo, b, S + src, hk[i]) << SHIFT));
-      }
+  for (int i = 0; i < HB; i++) head[i] = (int64_t)hk[i] * geo.head_stride << SHIFT;
+#pragma unroll 1
+  for (int w0 = 0; w0 < path.L; w0 += 64) {
+    const int to = w0 + 1 + lane, src = w0 == 0 ? path.first : path.from(w0);
+    const bool mine = to <= path.L && src > to && src < N;  // (src == to: nothing to move)
+    const unsigned long long any = __builtin_amdgcn_ballot_w64(mine);
+    long long from_off = 0, to_off = 0;
+    if (mine) {
+      from_off = slot_offset(geo, b, S + src, 0) << SHIFT;
+      to_off = slot_offset(geo, b, S + to, 0) << SHIFT;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (lanes read what other lanes write)
+    const int steps = path.L - w0 < 64 ? path.L - w0 : 64;
+#pragma unroll 1
+    for (int j0 = 0; j0 < steps; j0 += kBatch) {
+      u32x4 x[HB][STEPS];
 #pragma unroll
-    for (int s = 0; s < STEPS; s++) {
-      if (live[s]) {
+      for (int s = 0; s < STEPS; s++) {
+        const int j = j0 + s * JP + grp;
+        const long long off = lane_value(from_off, j);
+        if ((any >> j) & 1ull) {
 #pragma unroll
-        for (int i = 0; i < HB; i++) *(CBL_GLOBAL u32x4*)(base + (slot_offset(geo, b, S + j0 + 1 + s * JP + grp, hk[i]) << SHIFT)) = x[i][s];
+          for (int i = 0; i < HB; i++) x[i][s] = *(const CBL_GLOBAL u32x4*)(base + (off + head[i]));
+        }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (lanes read what other lanes write)
+#pragma unroll
+      for (int s = 0; s < STEPS; s++) {
+        const int j = j0 + s * JP + grp;
+        const long long off = lane_value(to_off, j);
+        if ((any >> j) & 1ull) {
+#pragma unroll
+          for (int i = 0; i < HB; i++) *(CBL_GLOBAL u32x4*)(base + (off + head[i])) = x[i][s];
+        }
       }
     }
   }
@@ -129,17 +149,17 @@ struct HeadMove {
 template <int PIECES, int SHIFT, int NW>
 struct MoveAfter {
   int tile_rows;
-  bool any;
-  __device__ __forceinline__ bool wanted() const { return any; }
+  static constexpr bool kAny = true;
   __device__ __forceinline__ void operator()(int b, int S, int N) const {
     const ArgsPtr a = fresh_args();
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), Hkv = a->Hkv;
     const uint32_t all = move_arrivals(a, tile_rows, S, N);
-    const AcceptedPath path(a, b);
+    auto arrive = [&](int hk) { return hk < Hkv ? __hip_atomic_fetch_add(move_word(a, b, hk), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u; };
+    uint32_t old = arrive(w + lane * NW);
+    const AcceptedPath path(a, b);  // (its loads and the first arrivals in one round trip)
     for (int h0 = w; h0 < Hkv; h0 += 64 * NW) {  // (lane i: head h0 + i NW, so that every wavefront has few to move)
       const int hk = h0 + lane * NW;
-      uint32_t old = 0;
-      if (hk < Hkv) old = __hip_atomic_fetch_add(move_word(a, b, hk), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (h0 != w) old = arrive(hk);
       const bool last = hk < Hkv && old + 1 == all;
       if (last) __hip_atomic_store(move_word(a, b, hk), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
       unsigned long long todo = __builtin_amdgcn_ballot_w64(last);
