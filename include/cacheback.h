@@ -111,7 +111,8 @@ int cb_init(const cb_config *cfg, void *workspace, size_t workspace_bytes, cb_ct
  * configuration's max_splits), like the "splits" option.  The plan is that of the attention on its own
  * (cb_tree_attention_device, _noalloc): a verification whose logits work is done by workgroups of the same
  * launch plans its attention for the compute units these leave, often with a split fewer, and
- * cb_last_launch_info reports it.  All arrays are host memory.  CB_EINVAL on a bad configuration or shape. */
+ * cb_last_launch_info reports it.  The tiles are the tallest ones: short calls are launched in shorter tiles and fewer
+ * splits of each.  All arrays are host memory.  CB_EINVAL on a bad configuration or shape. */
 int cb_plan_attention(const cb_config *cfg, int32_t batch, const int32_t *kv_len,
                       const int32_t *node_offsets, int32_t forced_splits, int32_t plan[5]);
 
@@ -266,6 +267,8 @@ int cb_device_status(cb_ctx *ctx, int32_t *status);
  *                    workgroups do the logits work, the others the attention)
  *   "logits_wgs"     workgroups of that launch for the logits work (a multiple of 8 up to 192;
  *                    0 = automatic)
+ *   "tile_rows"      query rows of a workgroup of the bf16 MFMA kernels: 64, 128 or 256 where a kv head has as many, in
+ *                    one round of workgroups (0 = automatic)
  *   "coop_merge"     0 = never merge the splits cooperatively (default 1: a grid that fits the
  *                    machine in one round has every workgroup of a tile merge a slice of it; otherwise,
  *                    and with 0, the last workgroup of a tile to finish merges it, or a merge kernel)

@@ -98,8 +98,8 @@ WsLayout ws_layout(const cb_config& c) {
   const bool mfma_cfg = c.qkv_dtype == CB_BF16;
   L.scalar_splits = mfma_cfg ? std::min(L.max_splits, 8) : L.max_splits;
   const size_t scalar_bytes = mt * c.num_q_heads * (size_t)L.scalar_splits * partial_stride(c.head_dim) * 4;
-  auto mfma_partials = [&](int mrows) { return attn_mfma_partial_bytes(c.head_dim, c.head_dim == 64, mrows, mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits); };
-  const size_t mfma_bytes = mfma_cfg ? std::max(mfma_partials(1), mfma_partials(c.max_nodes * g)) : 0;  // (calls with small tiles, and with the largest)
+  auto mfma_partials = [&](int tile_rows) { return attn_mfma_partial_bytes(c.head_dim, c.head_dim == 64, tile_rows, mt, c.num_q_heads, c.num_kv_heads, c.max_batch, L.max_splits); };
+  const size_t mfma_bytes = mfma_cfg ? std::max(mfma_partials(kRowTile), mfma_partials(attn_mfma_tile_rows(c.max_nodes * g))) : 0;  // (calls with small tiles, and with wide ones)
   L.partial = take(std::max(scalar_bytes, mfma_bytes));
   L.total = o;
   return L;
@@ -115,6 +115,7 @@ bool precise_sums(const cb_config& c, int chunk) {
 struct Plan {
   bool precise;  // (impl 2)
   int logits_wgs;  // of a verification: workgroups of the attention's launch that do the logits work (0: a launch of their own)
+  int tile_rows;  // (impl 2)
   int impl;    // 1 fp32 (or the scalar kernel on request), 2 bf16 MFMA
   int nsplit;  // partial slots per row
   int chunk;   // keys per split
@@ -152,7 +153,7 @@ struct cb_ctx {
   int32_t last_len[CB_MAX_BATCH];
   hipStream_t last_stream;
   // options
-  int64_t opt_splits, opt_impl, opt_time, opt_stages, opt_timeline, opt_external, opt_fork, opt_fuse, opt_coop, opt_spin, opt_full_sync, opt_logits_wgs;
+  int64_t opt_splits, opt_impl, opt_time, opt_stages, opt_timeline, opt_external, opt_fork, opt_fuse, opt_coop, opt_spin, opt_full_sync, opt_logits_wgs, opt_tile_rows;
   hipEvent_t ev0, ev1, ev_fork, ev_join;
   hipStream_t aux;  // second stream (default priority) for the logits scan beside the attention
   bool ev_valid;
@@ -276,7 +277,8 @@ struct Planner {
   SplitSums known[kKnown + 2];        // of the counts up to kKnown, and the last one beyond,
   int32_t known_chunk[kKnown + 2] = {};  // where this is their chunk
 
-  Planner(const cb_config& c_, int max_splits_, int scalar_splits_, int opt_impl, int opt_splits_, int batch_, const int32_t* kv_len_, const int32_t* node_offsets_)
+  Planner(const cb_config& c_, int max_splits_, int scalar_splits_, int opt_impl, int opt_splits_, int batch_, const int32_t* kv_len_, const int32_t* node_offsets_,
+          int tile_rows_ = 0)
       : c(c_), max_splits(max_splits_), scalar_splits(scalar_splits_), opt_splits(opt_splits_), batch(batch_), kv_len(kv_len_), node_offsets(node_offsets_),
         f32_tiles(c_.qkv_dtype == CB_F32 && opt_impl != 1), impl(opt_impl == 1 || c_.qkv_dtype != CB_BF16 ? 1 : 2), g(c_.num_q_heads / c_.num_kv_heads) {
     for (int b = 0; b < batch; b++) {
@@ -286,7 +288,7 @@ struct Planner {
       max_len = std::max(max_len, len[b]);
       rows += (int64_t)n * c.num_q_heads;
     }
-    tile_rows = attn_mfma_tile_rows(max_nodes * g);
+    tile_rows = tile_rows_ ? tile_rows_ : attn_mfma_tile_rows(max_nodes * g);
     for (int b = 0; b < batch; b++) {
       tiles[b] = (int64_t)(((node_offsets[b + 1] - node_offsets[b]) * g + tile_rows - 1) / tile_rows) * c.num_kv_heads;
       keys += tiles[b] * len[b];
@@ -386,6 +388,7 @@ struct Planner {
   Plan cut(int ns, bool precise) const {
     Plan p{};
     p.impl = impl;
+    p.tile_rows = tile_rows;
     p.max_nodes = max_nodes;
     p.max_len = max_len;
     const int most = impl == 1 ? scalar_splits : max_splits;
@@ -504,13 +507,71 @@ int wide_verification_splits(Planner& planner, int alone, int beside, int n, boo
   return nsplit;
 }
 
+constexpr int kTallest = 256;  // option "tile_rows": the smallest tile that holds a kv head's rows, at most this
+
+// What one round of workgroups with tiles of so many rows takes, in us (head_dim 128): start and tail, less of both without partial states,
+// and what 32 keys of the longest split cost, more while the ring fills.  Taller tiles read, park, write and merge more rows beside the sweep;
+// shorter ones read the same keys again, from the L2.
+double round_us(int rows, int chunk, bool split) {
+  const double units = chunk / 32, early = std::min(units, 9.0), late = units - early;
+  if (rows == 256) return split ? 14.5 + 0.85 * units : 5.5 + 1.95 * early + 0.85 * late;
+  if (rows == 128) return split ? 10.5 + 0.5 * units : 5.0 + 1.05 * early + 0.5 * late;
+  return split ? 8.0 + 0.45 * units : 5.0 + 0.8 * early + 0.5 * late;
+}
+
+// The same of a call's round: its longest job.  (A sequence whose rows a shorter tile would hold costs what that does.)
+double round_us(const Planner& pl, const SplitSums& s) {
+  double us = 0.0;
+  for (int b = 0; b < pl.batch; b++) {
+    const int rows = std::min((pl.node_offsets[b + 1] - pl.node_offsets[b]) * pl.g, pl.tile_rows);
+    const int tile = pl.tile_rows == kRowTile ? kRowTile : rows <= 128 ? 128 : 256, keys = std::min(pl.len[b] + 31, s.chunk);
+    // (a batch's tiles are not in step with each other: 8 sequences of up to 2000 keys, 32/8 heads x up to 48 nodes, 1024 keys to a
+    // split 28.9 us)
+    us = std::max(us, round_us(tile, keys, pl.len[b] > s.chunk) + (pl.batch > 1 && tile <= 128 ? 0.05 * keys / 32 : 0.0));
+  }
+  return us;
+}
+
+// Calls whose tiles leave compute units idle, or whose splits are so short that start and tail are most of them, take shorter tiles: those of
+// 128 or 64 rows where the launch is still one round and expected to be faster by more than the estimates are off.  The attention alone, a
+// pass in us with tiles of 256, 128 and 64 rows: 256 rows of 8 kv heads x 500 keys 16.3, 10.9, 9.5, x 4000 17.0, 13.6, 15.7, x 16000
+// 29.3, 26.5, 40.0; 512 rows x 8000 28.5, 26.8, 40.2, x 16000 41.5, 43.3, 73.9; 256 rows of 32 kv heads x 200 keys 20.3, 13.6, 13.6, x
+// 4000 33.5, 29.7, 44.6, x 8000 46.2, 47.5, 78.3; 128 rows of 8 kv heads x 1000 keys in 128 and 64 12.8, 10.3, x 8000 17.5, 16.0, x
+// 16000 21.8, 24.4, of 32 x 500 12.6, 11.1, x 2000 16.2, 16.9.  Steps of batches: 3 sequences of 32/8 heads x 353 keys x 123 nodes, 128256 entries
+// 48.9, 39.9, 38.4, 8 of up to 1246 keys x 42 nodes 27.0, 23.4, 29.7, 3 of 32 heads x 240 keys x 90 nodes 19.3, 18.9, 15.1.
+void shorter_tiles(Planner& tall, int rows, bool verification, int forced, Plan* p, double* us) {
+  if (rows >= p->tile_rows || (forced && forced != rows) || (p->precise && tall.c.head_dim == 128)) return;
+  const cb_config& c = tall.c;
+  Planner planner(c, tall.max_splits, tall.scalar_splits, 0, 0, tall.batch, tall.kv_len, tall.node_offsets, rows);
+  int n = verification ? p->logits_wgs : 0;
+  if (n && rows == kRowTile) n = std::max(n, fused_logits_wgs(c, tall.batch, tall.kv_len, tall.node_offsets));
+  const int cap = p->nsplit == 1 ? 1 : std::min(planner.cap(), 64);  // (what is not split stays so: plan_call)
+  const double limit = *us - std::max(0.3, 0.03 * *us);
+  double best = forced ? 1e30 : limit;
+  int ns = 0;
+  for (int i = 1; i <= cap; i++) {
+    if (i > 1 && planner.chunk_of(i) == planner.chunk_of(i - 1)) continue;
+    const SplitSums& s = planner.split_into(i);
+    if (s.jobs + n > 256 && !(forced && i == 1)) break;
+    const double t = round_us(planner, s);
+    if (t >= best) continue;
+    best = t;
+    ns = i;
+  }
+  if (ns == 0) return;
+  const bool precise = p->precise;
+  *p = planner.cut(ns, precise);
+  p->logits_wgs = n;
+  *us = best;
+}
+
 // The plan of a call, a verification or the attention alone.
 // What a call holds in 32 bits is a property of its shape that callers rely on, so it is decided by measures of the shape, whatever the
 // kernels would like to have: the splits planned as if the logits never rode beside wide tiles and a batch's grid held a
 // workgroup for every split of its longest sequence (empty_wgs), and those planned without either.  A call is precise where the
 // slices of one of them are long; one that a measure does not split, whose sums stay in the accumulators to the end, is not
 // split (partial states are bf16).
-Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int opt_logits_wgs, int batch,
+Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_impl, int opt_splits, int opt_logits_wgs, int opt_tile_rows, int batch,
                const int32_t* kv_len, const int32_t* node_offsets, bool verification) {
   Planner planner(c, max_splits, scalar_splits, opt_impl, opt_splits, batch, kv_len, node_offsets);
   // A verification in fp32, or with small tiles, or whose logits hide behind the sweep, is one launch: its first workgroups do the logits work, and the
@@ -547,6 +608,11 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
     p = planner.cut(nsplit, precise);
   }
   p.logits_wgs = n_logits;
+  if (p.impl == 2 && planner.tile_rows > kRowTile && opt_splits <= 0 && opt_tile_rows != kTallest) {
+    const SplitSums& tall = planner.split_into(p.nsplit);
+    double us = 2.5 + (double)((tall.jobs + p.logits_wgs + 255) / 256) * (round_us(planner, tall) - 2.5);
+    for (const int shorter : {128, 64}) shorter_tiles(planner, shorter, verification, opt_tile_rows, &p, &us);
+  }
   return p;
 }
 
@@ -567,11 +633,11 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
   const size_t total = node_offsets[batch];
   const int g = c.num_q_heads / c.num_kv_heads;
   auto fp32_rows = [&](int ns) { return ns <= 1 ? 0 : total * c.num_q_heads * ns * partial_stride(c.head_dim) * 4; };
-  auto tiles = [&](bool precise, int mrows, int ns) {
-    return ns <= 1 ? 0 : attn_mfma_partial_bytes(c.head_dim, precise, mrows, total, c.num_q_heads, c.num_kv_heads, batch, ns);
+  auto tiles = [&](bool precise, int rows, int ns) {
+    return ns <= 1 ? 0 : attn_mfma_partial_bytes(c.head_dim, precise, rows, total, c.num_q_heads, c.num_kv_heads, batch, ns);
   };
   auto planned = [&](int most) {
-    return plan_call(c, most, std::min(most, full.scalar_splits), 0, 0, 0, batch, kv_len, node_offsets, false);
+    return plan_call(c, most, std::min(most, full.scalar_splits), 0, 0, 0, 0, batch, kv_len, node_offsets, false);
   };
   auto cut = [&](size_t partial_bytes) {
     WsLayout L{};
@@ -594,11 +660,11 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
   const int measured = Planner(c, full.max_splits, full.scalar_splits, 0, 0, batch, kv_len, node_offsets).plan(256, true).nsplit;
   const bool by_rows = c.qkv_dtype == CB_F32 || c.head_dim == 64;
   const size_t measure = by_rows ? fp32_rows(Planner(c, full.max_splits, full.max_splits, 1, 0, batch, kv_len, node_offsets).plan(256, false).nsplit)
-                         : plan->impl == 2 ? tiles(false, 1, measured) : fp32_rows(measured);
+                         : plan->impl == 2 ? tiles(false, kRowTile, measured) : fp32_rows(measured);
   WsLayout L = cut(measure);
   if (L.total > kStaticScratchBytes) return L;
   for (;;) {
-    L = cut(plan->impl == 2 ? tiles(plan->precise, plan->max_nodes * g, plan->nsplit) : fp32_rows(plan->nsplit));
+    L = cut(plan->impl == 2 ? tiles(plan->precise, plan->tile_rows, plan->nsplit) : fp32_rows(plan->nsplit));
     if (L.total <= kStaticScratchBytes || plan->nsplit <= 1) return L;
     *plan = planned(plan->nsplit - 1);
   }
@@ -611,8 +677,8 @@ WsLayout noalloc_layout(const cb_config& c, const WsLayout& full, int batch, con
 // Splits are for steps whose tiles leave compute units idle (2 layers of 8 kv heads), in the first round of workgroups or in the last.  A call that is not split when its layers are launched one by one, whose sums stay in the accumulators, is not
 // split here.  False: launched one by one, where that is expected to be faster (few long tiles and no room for their partial states).
 bool plan_layers(const cb_config& c, const WsLayout& lay, int layers, int batch, const int32_t* kv_len, const int32_t* node_offsets, ModelLaunch* out) {
-  const Plan last = plan_call(c, lay.max_splits, lay.scalar_splits, 0, 0, 0, batch, kv_len, node_offsets, true);
-  const Plan other = plan_call(c, lay.max_splits, lay.scalar_splits, 0, 0, 0, batch, kv_len, node_offsets, false);
+  const Plan last = plan_call(c, lay.max_splits, lay.scalar_splits, 0, 0, 0, kTallest, batch, kv_len, node_offsets, true);
+  const Plan other = plan_call(c, lay.max_splits, lay.scalar_splits, 0, 0, 0, kTallest, batch, kv_len, node_offsets, false);
   if (last.impl != other.impl) return false;
   Planner planner(c, lay.max_splits, lay.scalar_splits, 0, 0, batch, kv_len, node_offsets);
   const int total = node_offsets[batch];
@@ -642,40 +708,45 @@ bool plan_layers(const cb_config& c, const WsLayout& lay, int layers, int batch,
     return true;
   }
   if (last.impl != 2) return false;
-  const bool precise = last.precise || other.precise, whole = last.nsplit == 1 || other.nsplit == 1, wide = planner.tile_rows != kRowTile;
-  const double stage = (wide && std::min(planner.tile_rows, planner.max_nodes * planner.g) > 128 ? 1.7 : 1.0) * c.head_dim / 128;
+  const bool precise = last.precise || other.precise, whole = last.nsplit == 1 || other.nsplit == 1;
   double kv = 0.0;
   for (int b = 0; b < batch; b++) kv += (double)planner.len[b] * c.num_kv_heads * c.head_dim * 4;
-  auto us_of = [&](int ns, int n) {  // (of one launch for n layers)
-    const SplitSums& s = planner.split_into(ns);
+  // Of one launch for n layers: rounds of equal jobs, or the longest-first schedule of a batch's; 6 of SplitSums' stages are a job's start
+  // and tail.  A merge
+  // takes 1 us, by the last workgroup to arrive 1.5 and a little for every split.
+  auto us_of = [&](Planner& pl, int ns, int n) {
+    const SplitSums& s = pl.split_into(ns);
     const int64_t jobs = s.jobs * n;
-    const double merge = s.grid_x > 1 ? (jobs > 240 ? 4.0 + 0.7 * s.grid_x * (planner.tile_rows / 128.0) : 2.0) / stage : 0.0;  // (by the last to arrive, or cooperative)
-    const double stages = batch == 1 ? (double)((jobs + 255) / 256) * s.longest(merge)
-                                     : std::max(s.longest(merge), jobs > 256 ? (s.work + s.merged * merge) * n / 256 + 0.5 * s.shortest : 0.0);
-    return 5.0 + std::max(stages * stage, n * kv / 5.5e6);
+    const bool split = s.grid_x > 1;
+    const double merge = !split ? 0.0 : jobs <= 240 ? 1.0 : 1.5 + 0.4 * s.grid_x * (pl.tile_rows / 128.0);
+    // (with tiles of 64 rows a unit keeps a compute unit's memory pipe busy for 0.53 us: 2 layers of 40 heads x 17085 keys)
+    const double start = (pl.tile_rows == 256 ? 9.5 : 7.0) + (split ? 1.0 : 0.0) - 2.5 + merge, stage = (pl.tile_rows == 256 ? 1.7 : pl.tile_rows == 128 ? 1.0 : 1.06) * c.head_dim / 128;
+    const double longest = start + stage * s.chunk / 64;
+    const double us = batch == 1 ? (double)((jobs + 255) / 256) * longest
+                                 : std::max(longest, jobs > 256 ? ((s.work - 6.0 * s.jobs) * stage + s.jobs * start) * n / 256 + 0.5 * (start + (s.shortest - 6.0) * stage) : 0.0);
+    return 2.5 + std::max(us, n * kv / 5.5e6);
   };
-  double us = us_of(1, layers);
-  p = planner.cut(1, precise);
-  out->table.partial_bytes = 0;
-  int64_t tiles = 0;  // of a layer, as the tickets are numbered
-  tiles = (int64_t)batch * c.num_kv_heads * ((planner.max_nodes * planner.g + planner.tile_rows - 1) / planner.tile_rows);
-  const int waves = wide ? 4 : 8;
-  if (!whole && tiles * layers <= std::min(kCoopTiles, lay.ticket_count / 4)) {
-    for (int ns = 2; ns <= std::min(planner.cap(), 64); ns++) {
-      if (planner.chunk_of(ns) == planner.chunk_of(ns - 1)) continue;
-      const double t = us_of(ns, layers);
-      const Plan cut = planner.cut(ns, precise);
-      const size_t bytes = attn_mfma_partial_bytes(c.head_dim, cut.precise, planner.max_nodes * planner.g, total, c.num_q_heads, c.num_kv_heads, batch, cut.nsplit);
+  const double one = us_of(planner, other.nsplit, 1);
+  double us = 0.0;
+  Plan& best = out->plan;
+  best.impl = 0;
+  for (int rows = planner.tile_rows; rows >= kRowTile && !(precise && c.head_dim == 128 && rows != planner.tile_rows); rows = rows == 256 ? 128 : rows / 2) {
+    Planner pl(c, lay.max_splits, lay.scalar_splits, 0, 0, batch, kv_len, node_offsets, rows);
+    const int64_t tiles = (int64_t)batch * c.num_kv_heads * ((pl.max_nodes * pl.g + rows - 1) / rows) * layers;  // as the tickets are numbered
+    for (int ns = 1; ns <= (whole || tiles > std::min(kCoopTiles, lay.ticket_count / 4) ? 1 : std::min(pl.cap(), 64)); ns++) {
+      if (ns > 1 && pl.chunk_of(ns) == pl.chunk_of(ns - 1)) continue;
+      const Plan cut = pl.cut(ns, precise);
+      const size_t bytes = cut.nsplit > 1 ? attn_mfma_partial_bytes(c.head_dim, cut.precise, rows, total, c.num_q_heads, c.num_kv_heads, batch, cut.nsplit) : 0;
       if (cut.impl != 2 || bytes * layers > room) break;
-      if (t >= us || !attn_mfma_merges_inside(c.head_dim, cut.precise, planner.max_nodes * planner.g, cut.nsplit)) continue;
+      const double t = us_of(pl, ns, layers);
+      if ((best.impl && t >= us) || (cut.nsplit > 1 && !attn_mfma_merges_inside(c.head_dim, cut.precise, pl.max_nodes * pl.g, rows, cut.nsplit))) continue;
       us = t;
-      p = cut;
+      best = cut;
+      best.logits_wgs = logits_wgs(tiles * cut.nsplit + 8 > 256, us, rows != kRowTile ? 4 : 8);
       out->table.partial_bytes = (int64_t)bytes;
     }
   }
-  if (p.impl != 2 || us > us_of(other.nsplit, 1) * layers) return false;
-  p.logits_wgs = logits_wgs(tiles * layers * p.nsplit + 8 > 256, us, waves);
-  return true;
+  return best.impl == 2 && us <= 0.96 * one * layers;  // (2 layers of 8 sequences x 4105 keys, 32/8 heads x 180 nodes: 271 us together, 254 one by one)
 }
 
 int check_common(cb_ctx* ctx, int32_t batch, const void* q, const cb_kv_layer* kv, const int32_t* kv_len,
@@ -732,7 +803,7 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   const bool f32_tiles = c.qkv_dtype == CB_F32 && ctx->opt_impl != 1;
   const Plan plan = model             ? model->plan
                     : ctx->fixed_plan ? *ctx->fixed_plan
-                                    : plan_call(c, ctx->lay.max_splits, ctx->lay.scalar_splits, (int)ctx->opt_impl, (int)ctx->opt_splits, (int)ctx->opt_logits_wgs,
+                                    : plan_call(c, ctx->lay.max_splits, ctx->lay.scalar_splits, (int)ctx->opt_impl, (int)ctx->opt_splits, (int)ctx->opt_logits_wgs, (int)ctx->opt_tile_rows,
                                                 batch, kv_len, node_offsets, (stage_mask & 8) != 0);
   const int n_logits = plan.logits_wgs;
 
@@ -753,7 +824,8 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   ap.precise = plan.precise;
   ap.batch = batch;
   if (plan.impl == 2) {
-    const int g = c.num_q_heads / c.num_kv_heads, rows = attn_mfma_tile_rows(plan.max_nodes * g);
+    const int g = c.num_q_heads / c.num_kv_heads, rows = plan.tile_rows;
+    ap.tile_rows = rows;
     const int64_t layers = model ? model->table.count : 1;
     int64_t live = 0;  // per kv head and layer
     for (int i = 0; i < CB_MAX_BATCH; i++) {
@@ -835,7 +907,9 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   if (fork) CB_HIP(ctx, hipEventRecord(ctx->ev_join, ctx->aux));
   const bool timing = ctx->opt_time != 0;
   // The compaction in the attention's launch, for the matrix-core kernels as they are by default.
-  ctx->moved = ctx->want_move && stages == 15 && (f32_tiles || (use_mfma && (fused || attn_mfma_tile_rows(plan.max_nodes * (c.num_q_heads / c.num_kv_heads)) != kRowTile))) &&
+  // Not in many rounds of workgroups, each of which its arrivals make about a microsecond longer (31 sequences of one node x 55 keys, 32
+  // heads: 22.9 us in two launches, 26.1 in one; 18 of 53 x 36, 40 heads, 41.5 and 40.0).
+  ctx->moved = ctx->want_move && stages == 15 && (f32_tiles || (use_mfma && ap.live_wgs <= 3 * 256)) &&
                !timing && !fork && !ap.timeline;
   ctx->want_move = false;
   if (ctx->moved) ap.move = MoveArgs{ctx->dev<uint32_t>(ctx->lay.moves), acc.path, acc.len_ctx, fused ? 1 : 0};
@@ -972,7 +1046,7 @@ int cb_plan_attention(const cb_config* cfg, int32_t batch, const int32_t* kv_len
     if (n < 1 || n > cfg->max_nodes || kv_len[b] < 0 || (int64_t)kv_len[b] + n > (1ll << 30)) return CB_EINVAL;
   }
   const WsLayout lay = ws_layout(*cfg);
-  const Plan p = plan_call(*cfg, lay.max_splits, lay.scalar_splits, 0, forced_splits, 0, batch, kv_len, node_offsets, false);
+  const Plan p = plan_call(*cfg, lay.max_splits, lay.scalar_splits, 0, forced_splits, 0, kTallest, batch, kv_len, node_offsets, false);
   const int g = cfg->num_q_heads / cfg->num_kv_heads;
   const int tile = p.impl == 2 ? attn_mfma_tile_rows(p.max_nodes * g) : 1;
   int64_t wgs = 0;
@@ -994,13 +1068,25 @@ int cb_debug_plan(const cb_config* cfg, int32_t batch, const int32_t* kv_len, co
   int32_t base[5];
   if (const int rc = cb_plan_attention(cfg, batch, kv_len, node_offsets, 0, base)) return rc;
   const WsLayout lay = ws_layout(*cfg);
-  const Plan p = plan_call(*cfg, lay.max_splits, lay.scalar_splits, 0, 0, 0, batch, kv_len, node_offsets, verification != 0);
+  const Plan p = plan_call(*cfg, lay.max_splits, lay.scalar_splits, 0, 0, 0, kTallest, batch, kv_len, node_offsets, verification != 0);
   plan[0] = p.impl;
   plan[1] = p.nsplit;
   plan[2] = p.chunk;
   plan[3] = p.precise;
   plan[4] = p.logits_wgs;
   plan[5] = p.impl == 2 || cfg->qkv_dtype == CB_F32 ? p.logits_wgs > 0 : 0;
+  return CB_OK;
+}
+
+int cb_debug_tiles(const cb_config* cfg, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets, int32_t verification, int32_t plan[6]) {
+  int32_t base[5];
+  if (const int rc = cb_plan_attention(cfg, batch, kv_len, node_offsets, 0, base)) return rc;
+  const WsLayout lay = ws_layout(*cfg);
+  const Plan p = plan_call(*cfg, lay.max_splits, lay.scalar_splits, 0, 0, 0, 0, batch, kv_len, node_offsets, verification != 0);
+  int64_t jobs = 0;
+  if (p.impl == 2) jobs = Planner(*cfg, lay.max_splits, lay.scalar_splits, 0, 0, batch, kv_len, node_offsets, p.tile_rows).split_into(p.nsplit).jobs;
+  const int32_t out[] = {p.impl == 2 ? p.tile_rows : 0, p.nsplit, p.chunk, p.precise, p.logits_wgs, (int32_t)jobs};
+  memcpy(plan, out, sizeof out);
   return CB_OK;
 }
 
@@ -1144,7 +1230,7 @@ int cb_verify_and_compact_device(cb_ctx* ctx, void* hip_stream, int32_t batch, c
     apart = !mine[1].meets(others[0]);
     for (size_t i = 1; apart && i < sizeof others / sizeof *others; i++) apart = !mine[0].meets(others[i]) && !mine[1].meets(others[i]);
   }
-  if (ctx) ctx->want_move = apart;
+  if (ctx) ctx->want_move = apart && node_offsets[batch] > batch;
   if (ctx) ctx->moved = false;
   const int rc = cb_verify_tree_device(ctx, hip_stream, batch, q, kv, kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits, attn_out,
                                        d_accepted_len, d_accepted_tokens);
@@ -1362,12 +1448,15 @@ int cb_compact_kv(cb_ctx* ctx, void* hip_stream, int32_t num_layers, const cb_kv
   const int ordered = order_behind_host_form(ctx, st);
   if (ordered) return ordered;
   const int eb = c.qkv_dtype == CB_F32 ? 4 : 2;
-  CB_HIP(ctx, launch_compact(st, ctx->batch, ctx->meta, addrs, num_layers, c.num_kv_heads, c.head_dim, eb, c.max_depth,
+  const bool roots = ctx->total_nodes == ctx->batch;  // (then nothing can move)
+  if (!roots)
+    CB_HIP(ctx, launch_compact(st, ctx->batch, ctx->meta, addrs, num_layers, c.num_kv_heads, c.head_dim, eb, c.max_depth,
                              ctx->dev<int32_t>(ctx->lay.path), ctx->dev<int32_t>(ctx->lay.len_ctx),
                              ctx->dev<int32_t>(ctx->lay.new_len)));
   if (new_kv_len) {
-    if (ctx->host_knows_len) {
-      for (int b = 0; b < ctx->batch; b++) new_kv_len[b] = ctx->meta.kv_len[b] + ctx->last_len[b] + 1;
+    if (ctx->host_knows_len || roots) {
+      if (!ctx->host_knows_len) CB_HIP(ctx, hipStreamSynchronize(st));
+      for (int b = 0; b < ctx->batch; b++) new_kv_len[b] = ctx->meta.kv_len[b] + (roots ? 0 : ctx->last_len[b]) + 1;
     } else {
       CB_HIP(ctx, hipMemcpyAsync(ctx->h_misc + 1, ctx->dev<int32_t>(ctx->lay.new_len), (size_t)ctx->batch * 4, hipMemcpyDeviceToHost, st));
       CB_HIP(ctx, hipStreamSynchronize(st));
@@ -1420,6 +1509,7 @@ int cb_set_option(cb_ctx* ctx, const char* name, int64_t value) {
   else if (!strcmp(name, "parallel_scan")) ctx->opt_fork = value;
   else if (!strcmp(name, "fuse_logits")) ctx->opt_fuse = value;
   else if (!strcmp(name, "coop_merge")) ctx->opt_coop = value;
+  else if (!strcmp(name, "tile_rows")) ctx->opt_tile_rows = value == 64 || value == 128 || value == 256 ? value : 0;
   else if (!strcmp(name, "logits_wgs")) ctx->opt_logits_wgs = value < 0 ? 0 : (value > 192 ? 192 : value / 8 * 8);
   else if (!strcmp(name, "merge_spin_limit")) ctx->opt_spin = value < 0 ? 0 : (value > 4096 ? 4096 : value);
   else return set_err(ctx, CB_EINVAL, "unknown option '%s'", name);

@@ -228,7 +228,7 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p_arg, const Seq
   if (h == 0) sh.ml[w][r] = float2{m, lsum};
   __syncthreads();
   HeadMove<row_pieces(D, 4), 2> move;
-  if (MOVE && k1 > S && w == kF32Waves - 1) move.begin(kF32Rows, b, hk, S, N);  // (nobody reads K or V any more)
+  if (MOVE && k1 > S && w == kF32Waves - 1) move.begin(b, hk, S, N);  // (nobody reads K or V any more)
   const int orow = tid / (D / 4), c = tid % (D / 4) * 4;
   const bool live = orow < kF32Rows && row0 + orow < M;
   const int onode = (row0 + orow) / g;
@@ -318,7 +318,7 @@ __device__ __forceinline__ void verify_f32(const AttnParams& p, const SeqMeta& m
   } sh;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   const int wg = (int)blockIdx.x - lw.n_wgs;
-  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept, after_acceptance<MOVE, row_pieces(D, 4), 2, kF32Waves>(kF32Rows));
+  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept, after_acceptance<MOVE, row_pieces(D, 4), 2, kF32Waves>());
   else attn_f32_tile<D, MOVE>(p, ml, wg, sh.attn, OneLayer{});
 }
 template <int D>
@@ -366,6 +366,7 @@ int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int
 hipError_t launch_attn_f32(hipStream_t st, const AttnParams& params, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw, const LayerTable* layers) {
   AttnParams p = params;
   p.grid_y = (max_nodes_in_call * (p.Hq / p.Hkv) + kF32Rows - 1) / kF32Rows;
+  p.tile_rows = kF32Rows;
   p.external_merge = p.force_external_merge;
   const int64_t per_layer = (int64_t)p.Hkv * p.grid_y * p.nsplit * p.batch, wgs = per_layer * (layers ? layers->count : 1) + (lw ? lw->n_wgs : 0);
   if (wgs > INT32_MAX || (p.D != 64 && p.D != 128)) return hipErrorInvalidValue;

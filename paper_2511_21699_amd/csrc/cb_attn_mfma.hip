@@ -237,7 +237,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   const float lsum = st.lacc[0] * w0 + ml2.y * w1;
 #undef CB_TS
   HeadMove<row_pieces(D, 2), 1> move;
-  if (MOVE && tree_split && w == 0) move.begin(kSmallRows, jb.b, jb.hk, S, jb.N);
+  if (MOVE && tree_split && w == 0) move.begin(jb.b, jb.hk, S, jb.N);
   write_rows<D, 16, PX, P / 2>(p, jb, wi, grow, f, gi * (P / 2), m, lsum, c2, gi == 0, l);
   auto finish_move = [&] { if (MOVE) move.finish(jb.b, jb.hk, S, jb.N); };
   if (jb.nsplit == 1 || p.external_merge) {  // (a following kernel merges: the kernel boundary orders the stores)
@@ -271,7 +271,7 @@ __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqM
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) {
-    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<MOVE, row_pieces(D, 2), 1, 8>(kSmallRows));
+    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<MOVE, row_pieces(D, 2), 1, 8>());
     return;
   }
   attn_tile<D, PX, MOVE, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});
@@ -329,9 +329,9 @@ __global__ __launch_bounds__(256) void k_merge_partials(AttnParams p, SeqMeta me
 static int block_bytes(int D, int tr, bool precise) { return tr * D * (precise ? 4 : 2) + tr * 8; }
 static_assert(PartialLayout<128, 16, false>::kBytes == 16 * 128 * 2 + 16 * 8 && PartialLayout<64, 32, true>::kBytes == 32 * 64 * 4 + 32 * 8, "");
 
-size_t attn_mfma_partial_bytes(int D, bool precise, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits) {
+size_t attn_mfma_partial_bytes(int D, bool precise, int tile_rows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits) {
   // the last sequence's blocks end at or before tile max_total_nodes * Hq / TR + (Hkv + 1) * max_batch
-  const int tr = attn_mfma_tile_rows(mrows) == kSmallRows ? 16 : 32;
+  const int tr = tile_rows == kSmallRows ? 16 : 32;
   const size_t tiles = max_total_nodes * Hq / tr + (size_t)(Hkv + 1) * max_batch + 1;
   return tiles * (size_t)max_splits * block_bytes(D, tr, precise);
 }
@@ -356,8 +356,8 @@ int attn_mfma_tile_rows(int mrows) { return mrows <= kSmallRows ? kSmallRows : 2
 
 // One workgroup can pull about 50 GB/s of partials through its compute unit: beyond a few hundred
 // KiB per tile a separate, fully parallel merge kernel is cheaper than the merge by a tile's last workgroup.
-bool attn_mfma_merges_inside(int D, bool precise, int mrows, int nsplit) {
-  const int rt_rows = attn_mfma_tile_rows(mrows), tr = rt_rows == kSmallRows ? 16 : 32;
+bool attn_mfma_merges_inside(int D, bool precise, int mrows, int rt_rows, int nsplit) {
+  const int tr = rt_rows == kSmallRows ? 16 : 32;
   const int in_tile = (std::min(mrows, rt_rows) + tr - 1) / tr;
   return (int64_t)nsplit * in_tile * block_bytes(D, tr, precise) <= 320 * 1024;
 }
@@ -367,7 +367,8 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   if (!attn_mfma_supports(p)) return hipErrorInvalidValue;
   const int g = p.Hq / p.Hkv;
   const int M = max_nodes_in_call * g;
-  const int rt_rows = attn_mfma_tile_rows(M);
+  const int rt_rows = p.tile_rows;
+  if (rt_rows != kSmallRows && rt_rows != 128 && rt_rows != 256) return hipErrorInvalidValue;
   const int tiles = (M + rt_rows - 1) / rt_rows;
   AttnParams q = p;
   q.grid_x = p.nsplit;
@@ -395,7 +396,7 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   const int n_logits = logits_work ? logits_work->n_wgs : 0;
   const dim3 grid((uint32_t)(n_logits + T));
   const int tr = rt_rows == kSmallRows ? 16 : 32;
-  q.external_merge = p.nsplit > 1 && !attn_mfma_merges_inside(p.D, p.precise, M, p.nsplit) ? 1 : 0;
+  q.external_merge = p.nsplit > 1 && !attn_mfma_merges_inside(p.D, p.precise, M, rt_rows, p.nsplit) ? 1 : 0;
   // A grid that is resident in one round (one workgroup per compute unit) merges cooperatively:
   // every workgroup of a tile takes a slice, so the volume per compute unit does not grow with
   // the split count and no second launch is needed.
@@ -414,21 +415,21 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   const bool ts = p.timeline != 0;  // (the timeline build of the same kernels: a measurement aid)
   hipError_t e;
   auto launch = [&](auto* stamped, auto* plain, auto... args) { hipLaunchKernelGGL(ts ? stamped : plain, grid, dim3(512), 0, st, args...); };
-  if (p.move.words && rt_rows == kSmallRows) {  // (no timeline build; with the logits work always)
-    if (!logits_work) return hipErrorInvalidValue;
-    if (p.D == 64) hipLaunchKernelGGL((k_step_mfma<64, true>), grid, dim3(512), 0, st, q, meta, *logits_work);
-    else if (p.precise) hipLaunchKernelGGL((k_step_mfma<128, true>), grid, dim3(512), 0, st, q, meta, *logits_work);
-    else hipLaunchKernelGGL((k_step_mfma<128, false>), grid, dim3(512), 0, st, q, meta, *logits_work);
+  if (p.move.words && rt_rows == kSmallRows) {  // (no timeline build; n_wgs is 0 where the logits work has a launch of its own)
+    const LogitsWork lw = logits_work ? *logits_work : LogitsWork{};
+    if (p.D == 64) hipLaunchKernelGGL((k_step_mfma<64, true>), grid, dim3(512), 0, st, q, meta, lw);
+    else if (p.precise) hipLaunchKernelGGL((k_step_mfma<128, true>), grid, dim3(512), 0, st, q, meta, lw);
+    else hipLaunchKernelGGL((k_step_mfma<128, false>), grid, dim3(512), 0, st, q, meta, lw);
     e = hipGetLastError();
   } else if (layers) {
     const LogitsWork lw = logits_work ? *logits_work : LogitsWork{};
-    if (rt_rows != kSmallRows) return launch_attn_wide_layers(st, q, meta, M, (int)T, lw, table);
+    if (rt_rows != kSmallRows) return launch_attn_wide_layers(st, q, meta, std::min(M, rt_rows), (int)T, lw, table);
     if (p.D == 64) hipLaunchKernelGGL((k_model_mfma<64, true>), grid, dim3(512), 0, st, q, meta, lw, table);
     else if (p.precise) hipLaunchKernelGGL((k_model_mfma<128, true>), grid, dim3(512), 0, st, q, meta, lw, table);
     else hipLaunchKernelGGL((k_model_mfma<128, false>), grid, dim3(512), 0, st, q, meta, lw, table);
     return hipGetLastError();
   } else if (rt_rows != kSmallRows) {
-    e = launch_attn_wide(st, q, meta, M, (int)T, logits_work);
+    e = launch_attn_wide(st, q, meta, std::min(M, rt_rows), (int)T, logits_work);
   } else if (logits_work) {
     if (p.D == 64) launch(k_verify_mfma<64, true>, k_verify_mfma<64, false>, q, meta, *logits_work);
     else if (p.precise) launch(k_verify_precise<true>, k_verify_precise<false>, q, meta, *logits_work);

@@ -624,16 +624,16 @@ __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const Se
   CB_LDS unsigned long long* ts = (CB_LDS unsigned long long*)ts_sh;
   first_stamps<TS>(ts, ts0);
   TileJob jb;
-  if (!tile_job(p, ml, wg, 256, layers, jb)) return;
+  if (!tile_job(p, ml, wg, p.tile_rows, layers, jb)) return;
   take_layer(p, jb, layers);
-  const int rows = jb.M - jb.row0;
+  const int rows = jb.rows;
   if (rows <= 64) sweep_tile<D, PX, PG, 1, 2, TS>(p, jb, sh, ring, ts);
   else if (rows <= 128) sweep_tile<D, PX, PG, R128, 4 / R128, TS>(p, jb, sh, ring, ts);
   else sweep_tile<D, PX, PG, 2, 4, TS>(p, jb, sh, ring, ts);
   HeadMove<row_pieces(D, 2), 1> move;
   if (MOVE && jb.k1 > jb.S) {  // (uniform)
     bare_barrier();  // (every wave's requests have landed)
-    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) move.begin(256, jb.b, jb.hk, jb.S, jb.N);
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) move.begin(jb.b, jb.hk, jb.S, jb.N);
   }
   auto finish_move = [&] { if (MOVE) move.finish(jb.b, jb.hk, jb.S, jb.N); };
   if (jb.nsplit == 1 || p.external_merge) {  // (a following kernel merges: the kernel boundary orders the stores)
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void k_step_wide(AttnParams p, 
   __shared__ __align__(1024) uint4 ring[Feed<D, kWideWaves, 32>::kRingVecs];
   __shared__ TileLds sh;
   const int wg = (int)blockIdx.x - lw.n_wgs;
-  if (wg < 0) logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<true, row_pieces(D, 2), 1, kWideWaves>(256));
+  if (wg < 0) logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<true, row_pieces(D, 2), 1, kWideWaves>());
   else attn_wide_tile<D, PX, PG, R128, true, false>(p, ml, wg, 0ull, sh, ring, nullptr, OneLayer{});
 }
 

@@ -184,6 +184,7 @@ struct AttnParams {
   int32_t chunk;        // keys per split
   int32_t nsplit;       // partial slots per row (>= splits any sequence uses)
   int32_t batch;
+  int32_t tile_rows;    // rows of a tile: 64, 128 or 256 (fp32 MFMA kernel: 16, set by its launcher)
   int32_t live_wgs;     // workgroups of the launch that have keys to sweep (the host reads it; MFMA kernels)
   float scale;
   int32_t precise;      // bf16 MFMA kernels: probabilities and partial sums in 32 bits (the host reads it, to choose the build)
@@ -248,11 +249,11 @@ int attn_f32_splits(int Hq, int Hkv, int D, int max_splits, int batch, const int
                     int layers = 1, double* us = nullptr);
 hipError_t launch_attn_f32(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int max_nodes_in_call, const LogitsWork* lw, const LayerTable* layers);
 hipError_t launch_merge(hipStream_t st, const AttnParams& p, const SeqMeta& meta, int dtype, int total_nodes);
-int attn_mfma_tile_rows(int mrows);            // rows per workgroup tile chosen for a given g*N
-// bytes the MFMA path's partial states can take in calls whose largest sequence has `mrows` rows per kv head (its own layout,
-// padded to 16-row tiles per kv head where one small tile holds them, else to 32-row ones)
-size_t attn_mfma_partial_bytes(int D, bool precise, int mrows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
-bool attn_mfma_merges_inside(int D, bool precise, int mrows, int nsplit);  // whether no merge kernel is needed, for tiles of a sequence with mrows rows per kv head
+int attn_mfma_tile_rows(int mrows);            // rows of the smallest tile that holds a given g*N, at most 256, as long sweeps have them
+// bytes the MFMA path's partial states can take (its own layout, padded to 16-row tiles per kv head with tiles of 64 rows, else to
+// 32-row ones)
+size_t attn_mfma_partial_bytes(int D, bool precise, int tile_rows, size_t max_total_nodes, int Hq, int Hkv, int max_batch, int max_splits);
+bool attn_mfma_merges_inside(int D, bool precise, int mrows, int tile_rows, int nsplit);  // whether no merge kernel is needed, for tiles of a sequence with mrows rows per kv head
 bool attn_mfma_supports(const AttnParams& p);  // shape/geometry the MFMA kernel takes (bf16 is the caller's check)
 // with logits_work != nullptr the same launch also scans the logits and runs the acceptance; with layers != nullptr it serves all of the
 // table's layers, in splits that need no merge kernel (p.live_wgs, meta.start: of all layers)
@@ -270,8 +271,13 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
 
 }  // namespace cb
 
-// For tests, without a device: the plan of a verification or of the attention alone.  plan[0] = attention kernel family (1 fp32 or
+// For tests, without a device: the plan of a verification or of the attention alone with the tallest tiles, which decides what is held in
+// 32 bits and whether partial states are.  plan[0] = attention kernel family (1 fp32 or
 // scalar, 2 bf16 MFMA), [1] = splits, [2] = keys per split, [3] = 1 if probabilities and partial sums are in 32 bits (bf16 MFMA),
 // [4] = workgroups planned for the logits work, [5] = 1 if they are workgroups of the attention's launch
 extern "C" int cb_debug_plan(const cb_config* cfg, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets,
                              int32_t verification, int32_t plan[6]);
+// and the plan that is launched: plan[0] = rows of a tile (0: not the bf16 MFMA kernels), [1] to [4] as [1] to [4] there, [5] = workgroups
+// that have keys to sweep
+extern "C" int cb_debug_tiles(const cb_config* cfg, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets,
+                              int32_t verification, int32_t plan[6]);

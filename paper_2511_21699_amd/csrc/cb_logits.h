@@ -483,8 +483,8 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
 
 // What follows the acceptance in a launch that compacts its cache (MOVE), or in one that does not.
 template <bool MOVE, int PIECES, int SHIFT, int NW>
-__device__ __forceinline__ auto after_acceptance(int tile_rows) {
-  if constexpr (MOVE) return MoveAfter<PIECES, SHIFT, NW>{tile_rows};
+__device__ __forceinline__ auto after_acceptance() {
+  if constexpr (MOVE) return MoveAfter<PIECES, SHIFT, NW>{};
   else return NothingAfter{};
 }
 

@@ -114,8 +114,8 @@ __device__ __forceinline__ void move_heads(const KvAddr& geo, const AcceptedPath
 }
 
 // Arrivals that complete a head's word: the row tiles' workgroups whose split reaches the tree, and the acceptance.
-__device__ __forceinline__ uint32_t move_arrivals(ArgsPtr a, int tile_rows, int S, int N) {
-  const int tiles = (N * (a->Hq / a->Hkv) + tile_rows - 1) / tile_rows, splits = (S + N + a->chunk - 1) / a->chunk - S / a->chunk;
+__device__ __forceinline__ uint32_t move_arrivals(ArgsPtr a, int S, int N) {
+  const int tiles = (N * (a->Hq / a->Hkv) + a->tile_rows - 1) / a->tile_rows, splits = (S + N + a->chunk - 1) / a->chunk - S / a->chunk;
   return (uint32_t)(tiles * splits + (a->move.own_acceptance ? 1 : 0));
 }
 __device__ __forceinline__ CBL_GLOBAL uint32_t* move_word(ArgsPtr a, int b, int hk) { return as_global(a->move.words) + (int64_t)b * a->Hkv + hk; }
@@ -126,10 +126,10 @@ template <int PIECES, int SHIFT>
 struct HeadMove {
   bool mine = false;  // (uniform in the wavefront)
   uint32_t all, old;
-  __device__ __forceinline__ void begin(int tile_rows, int b, int hk, int S, int N) {
+  __device__ __forceinline__ void begin(int b, int hk, int S, int N) {
     const ArgsPtr a = fresh_args();
     mine = true;
-    all = move_arrivals(a, tile_rows, S, N);
+    all = move_arrivals(a, S, N);
     old = 0;
     if (all > 1 && (threadIdx.x & 63) == 0) old = __hip_atomic_fetch_add(move_word(a, b, hk), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -148,12 +148,11 @@ struct HeadMove {
 // follows the acknowledgement of its stores; the heads whose attention is through already are moved here.
 template <int PIECES, int SHIFT, int NW>
 struct MoveAfter {
-  int tile_rows;
   static constexpr bool kAny = true;
   __device__ __forceinline__ void operator()(int b, int S, int N) const {
     const ArgsPtr a = fresh_args();
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), Hkv = a->Hkv;
-    const uint32_t all = move_arrivals(a, tile_rows, S, N);
+    const uint32_t all = move_arrivals(a, S, N);
     auto arrive = [&](int hk) { return hk < Hkv ? __hip_atomic_fetch_add(move_word(a, b, hk), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u; };
     uint32_t old = arrive(w + lane * NW);
     const AcceptedPath path(a, b);  // (its loads and the first arrivals in one round trip)
