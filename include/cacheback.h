@@ -230,6 +230,8 @@ int cb_tree_attention_noalloc(const cb_config *cfg, void *hip_stream, int32_t ba
  * Moves the K/V of the path accepted by the last verify call of this context into place, for
  * `num_layers` caches that share one geometry (capacity, block table, layout) and differ only in
  * their k/v pointers: for j = 1..L_b, slot S_b+j <- slot S_b+path_b[j].  Enqueues on `hip_stream`.
+ * (Nothing where no row has to move and the host knows it: trees of roots alone, and after cb_verify_tree paths that are
+ * the trees' first nodes.)
  *   new_kv_len   host [batch] or NULL: S_b + L_b + 1.  After cb_verify_tree it is filled without
  *                waiting; after cb_verify_tree_device filling it synchronises the stream.
  */

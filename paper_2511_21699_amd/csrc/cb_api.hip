@@ -136,9 +136,11 @@ struct cb_ctx {
   int32_t* h_path;
   int32_t* h_argmax;
   int32_t* h_misc;  // [0] status, [1..] new_len
+  int32_t* h_last;  // [max_batch] last nodes of the host form's accepted paths
   int32_t* h_done;  // [max_batch] arrival flags of the host form's results (the call's sequence number)
   int32_t call_seq = 0;        // sequence number of the last host-form call (never 0 once used)
-  int32_t* want_done = nullptr;  // set by cb_verify_tree for the launch it is about to make
+  int32_t* want_done = nullptr;  // these two are set by cb_verify_tree for the launch it is about to make
+  int32_t* want_last = nullptr;
   hipStream_t unsynced = nullptr;  // stream that may still run the tail of a host-form call that has returned
   bool have_unsynced = false;
   int32_t* d_hblock = nullptr;  // the pinned block's address on the device
@@ -147,6 +149,7 @@ struct cb_ctx {
   bool have_verify;
   int32_t launch_info[6];
   bool host_knows_len;
+  bool nothing_moves;  // of the last verification, where the host knows its lengths
   int batch;
   int total_nodes;
   SeqMeta meta;
@@ -878,6 +881,8 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   acc.len_ctx = ctx->dev<int32_t>(ctx->lay.len_ctx);
   acc.len_user = d_len;
   acc.tok_user = d_tok;
+  acc.last_user = ctx->want_last;
+  ctx->want_last = nullptr;
   acc.done_flag = ctx->want_done;
   acc.done_value = ctx->call_seq;
   ctx->want_done = nullptr;
@@ -1156,7 +1161,7 @@ int cb_init(const cb_config* cfg, void* workspace, size_t workspace_bytes, cb_ct
   const size_t mt = lay.max_total_nodes, stride = (size_t)cfg->max_depth + 1;
   // (two tree areas: a host-form call may return while its kernels still run, and the next call
   // must not overwrite the tree they read)
-  const size_t ints = mt * 5 + cfg->max_batch * (1 + 2 * stride) + 1 + 2 * (size_t)cfg->max_batch;
+  const size_t ints = mt * 5 + cfg->max_batch * (1 + 2 * stride) + 1 + 3 * (size_t)cfg->max_batch;
   hipError_t e = hipHostMalloc(&ctx->h_block, ints * 4, hipHostMallocDefault);
   if (e != hipSuccess) {
     delete ctx;
@@ -1179,6 +1184,7 @@ int cb_init(const cb_config* cfg, void* workspace, size_t workspace_bytes, cb_ct
   ctx->h_tok = h; h += cfg->max_batch * stride;
   ctx->h_path = h; h += cfg->max_batch * stride;
   ctx->h_misc = h; h += 1 + cfg->max_batch;
+  ctx->h_last = h; h += cfg->max_batch;
   ctx->h_done = h;
   memset(ctx->h_done, 0, (size_t)cfg->max_batch * 4);
   e = hipEventCreate(&ctx->ev0);
@@ -1380,9 +1386,10 @@ int cb_verify_tree(cb_ctx* ctx, void* hip_stream, int32_t batch, const void* q, 
   int32_t* h_res = ctx->h_len;
   int32_t* d_len = ctx->d_hblock + (h_res - static_cast<int32_t*>(ctx->h_block));
   int32_t* d_tok = d_len + batch;
+  ctx->want_last = ctx->d_hblock + (ctx->h_last - static_cast<int32_t*>(ctx->h_block));
   if (early) ctx->want_done = ctx->d_hblock + (ctx->h_done - static_cast<int32_t*>(ctx->h_block));
   rc = run_pipeline(ctx, st, batch, q, kv, kv_len, node_offsets, d_parent, d_tokens, logits, attn_out, d_len, d_tok);
-  ctx->want_done = nullptr;
+  ctx->want_done = ctx->want_last = nullptr;
   if (rc) return rc;
   if (early) {
     // The acceptance stores a sequence's results, makes them visible at system scope and then stores
@@ -1419,6 +1426,9 @@ int cb_verify_tree(cb_ctx* ctx, void* hip_stream, int32_t batch, const void* q, 
   memcpy(accepted_tokens, h_res + batch, (size_t)batch * stride * 4);
   memcpy(ctx->last_len, h_res, (size_t)batch * 4);
   ctx->host_knows_len = true;
+  // (the nodes of a path are in increasing order, so one whose last node is its length's has each in its place)
+  ctx->nothing_moves = (ctx->opt_stages & 8) != 0;
+  for (int b = 0; b < batch; b++) ctx->nothing_moves = ctx->nothing_moves && ctx->h_last[b] == ctx->last_len[b];
   return CB_OK;
 }
 
@@ -1448,8 +1458,10 @@ int cb_compact_kv(cb_ctx* ctx, void* hip_stream, int32_t num_layers, const cb_kv
   const int ordered = order_behind_host_form(ctx, st);
   if (ordered) return ordered;
   const int eb = c.qkv_dtype == CB_F32 ? 4 : 2;
-  const bool roots = ctx->total_nodes == ctx->batch;  // (then nothing can move)
-  if (!roots)
+  // No launch where nothing moves: trees of roots alone, and accepted paths that are the tree's first nodes, where the host knows them
+  // (one in two or three steps of a decode loop; the launch costs its pass 4 us).
+  const bool roots = ctx->total_nodes == ctx->batch;
+  if (!roots && !(ctx->host_knows_len && ctx->nothing_moves))
     CB_HIP(ctx, launch_compact(st, ctx->batch, ctx->meta, addrs, num_layers, c.num_kv_heads, c.head_dim, eb, c.max_depth,
                              ctx->dev<int32_t>(ctx->lay.path), ctx->dev<int32_t>(ctx->lay.len_ctx),
                              ctx->dev<int32_t>(ctx->lay.new_len)));

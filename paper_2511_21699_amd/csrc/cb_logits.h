@@ -64,6 +64,7 @@ struct AcceptArgs {
   int32_t* len_ctx;        // [B] written through to memory)
   int32_t* len_user;       // [B]
   int32_t* tok_user;       // [B][max_depth + 1]
+  int32_t* last_user;      // [B] or null: host-visible words for the path's last node (the path's length where nothing has to move)
   int32_t* done_flag;      // [B] or null: host-visible words that receive done_value once the sequence's
   int32_t done_value;      // user results are visible to the host (the host form polls them)
 };
@@ -160,6 +161,7 @@ __device__ __forceinline__ void accept_small(const AcceptArgs& g, int b, int off
   if (t == 0) {
     store_result<THROUGH>(g.len_ctx + b, L);
     as_global(g.len_user)[b] = L;
+    if (g.last_user) as_global(g.last_user)[b] = best;
   }
   publish_done(g, b, t == 0);
 }
@@ -275,6 +277,7 @@ __device__ __forceinline__ void accept_large(AcceptWaveLds& sh, const AcceptArgs
   if (lane == 0) {
     store_result<THROUGH>(g.len_ctx + b, L);
     as_global(g.len_user)[b] = L;
+    if (g.last_user) as_global(g.last_user)[b] = best;
   }
   publish_done(g, b, lane == 0);
   wave_lds_sync();
