@@ -244,7 +244,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
     finish_move();
     return;
   }
-  split_merge<D, 16, PX, 8, kSmallRows, TS>(p, jb, sh, ts, finish_move);
+  split_merge<D, 16, PX, 8, kSmallRows, TS>(p, jb, kSmallRows, sh, ts, finish_move);
 }
 
 template <int D, bool PX, bool TS>

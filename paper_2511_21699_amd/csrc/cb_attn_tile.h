@@ -146,7 +146,7 @@ __device__ __forceinline__ void pin_args(AttnParams& p) {
   CB_PIN(p.kv.seq_stride); CB_PIN(p.kv.token_stride); CB_PIN(p.kv.head_stride); CB_PIN(p.kv.num_blocks);
   CB_PIN(p.kv.max_blocks); CB_PIN(p.kv.block_size); CB_PIN(p.parent); CB_PIN(p.partial); CB_PIN(p.tickets); CB_PIN(p.coop_tickets);
   CB_PIN(p.Hq); CB_PIN(p.Hkv); CB_PIN(p.chunk); CB_PIN(p.nsplit); CB_PIN(p.batch); CB_PIN(p.scale);
-  CB_PIN(p.external_merge); CB_PIN(p.tile_rows); CB_PIN(p.max_depth); CB_PIN(p.xcd_remap); CB_PIN(p.grid_x); CB_PIN(p.grid_y); CB_PIN(p.grid_z); CB_PIN(p.coop_merge); CB_PIN(p.spin_limit);
+  CB_PIN(p.external_merge); CB_PIN(p.max_depth); CB_PIN(p.xcd_remap); CB_PIN(p.grid_x); CB_PIN(p.grid_y); CB_PIN(p.grid_z); CB_PIN(p.coop_merge); CB_PIN(p.spin_limit);
   CB_PIN(p.status); CB_PIN(p.dbg_ts);
 }
 #undef CB_PIN
@@ -203,7 +203,7 @@ struct TileJob {
   int b, hk, g;        // sequence, kv head, query heads per kv head
   int off, N, S, M;    // the sequence's first node, nodes, prefix; its rows per kv head
   int rt, tiles;       // row tile, row tiles per kv head of the launch
-  int row0, rows;      // first row of the tile, and its rows
+  int row0;            // first row of the tile
   int split, nsplit;   // and the sequence's number of splits
   int k0, k1;          // the split's keys
   int layer;           // of those that the launch serves
@@ -273,7 +273,6 @@ __device__ __forceinline__ bool tile_job(const AttnParams& p, const SeqMetaLanes
   const int len = shp.S + shp.N;
   j.k0 = j.split * p.chunk;
   if (j.row0 >= j.M || j.k0 >= len) return false;
-  j.rows = j.M - j.row0 < tile_rows ? j.M - j.row0 : tile_rows;
   j.k1 = (j.k0 + p.chunk < len) ? j.k0 + p.chunk : len;
   j.nsplit = (len + p.chunk - 1) / p.chunk;
   return true;
@@ -575,7 +574,7 @@ __device__ __forceinline__ void merge_pieces(__amdgpu_buffer_rsrc_t prsrc, int64
 // aside(): what the first wave has to do beside, where it would wait for the other splits, or, in the merge by the last to arrive, behind its
 // share of that.
 template <int D, int TR, bool PX, int NW, int MAXROWS, bool TS, typename Aside>
-__device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& jb, TileLds& sh, CB_LDS unsigned long long* ts, Aside aside) {
+__device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& jb, int tile_rows, TileLds& sh, CB_LDS unsigned long long* ts, Aside aside) {
   constexpr int P = PartialLayout<D, TR, PX>::P;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
   const bool do_ts = TS && tid == 0, do_ts64 = TS && tid == 64;
@@ -604,7 +603,7 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
     const int row = jb.row0 + i * TR + l % TR;
     const int node = row / jb.g, hg = row - node * jb.g;
     *gr = row < jb.M ? (int64_t)(jb.off + node) * p.Hq + jb.hk * jb.g + hg : -1;
-    return i * TR < jb.rows;
+    return row - l % TR < jb.M && (MAXROWS <= 64 || i * TR < tile_rows);
   };
 
   if (!p.coop_merge) {
@@ -696,7 +695,8 @@ __device__ __forceinline__ void split_merge(const AttnParams& p, const TileJob& 
   // for its first unit -- the lane's output row, the partials' offsets -- is worked out before it
   // waits, so that the loads go out as soon as the verdict is in.  A unit is a round trip to memory for its wave, so
   // where two pieces each make more units than the workgroups have waves a unit is four (a tile of 256 rows has 128 pieces).
-  const int pieces = (jb.rows + TR - 1) / TR * P;
+  const int rows = jb.M - jb.row0 < tile_rows ? jb.M - jb.row0 : tile_rows;
+  const int pieces = (rows + TR - 1) / TR * P;
   // Tiles of up to 64 rows never do: a unit is what makes one 16-byte load, and 16 slots are in flight where there are more
   // than 8 splits (8 in flight: 4 rows over 3911 paged keys, 31 splits, 14.4 us a pass instead of 13.4).
   constexpr bool SMALL = MAXROWS <= 64;

@@ -626,7 +626,7 @@ __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const Se
   TileJob jb;
   if (!tile_job(p, ml, wg, p.tile_rows, layers, jb)) return;
   take_layer(p, jb, layers);
-  const int rows = jb.rows;
+  const int rows = jb.M - jb.row0 < p.tile_rows ? jb.M - jb.row0 : p.tile_rows;
   if (rows <= 64) sweep_tile<D, PX, PG, 1, 2, TS>(p, jb, sh, ring, ts);
   else if (rows <= 128) sweep_tile<D, PX, PG, R128, 4 / R128, TS>(p, jb, sh, ring, ts);
   else sweep_tile<D, PX, PG, 2, 4, TS>(p, jb, sh, ring, ts);
@@ -640,7 +640,7 @@ __device__ __forceinline__ void attn_wide_tile(const AttnParams& p_arg, const Se
     finish_move();
     return;
   }
-  split_merge<D, 32, PX, kWideWaves, 256, TS>(p, jb, sh, ts, finish_move);
+  split_merge<D, 32, PX, kWideWaves, 256, TS>(p, jb, p.tile_rows, sh, ts, finish_move);
 }
 
 template <int D, bool PX, bool PG, int R128, bool TS>
