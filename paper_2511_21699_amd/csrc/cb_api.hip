@@ -326,6 +326,15 @@ struct Planner {
     return s;
   }
 
+  // What a batch in `ns` splits is expected to take on `units` compute units, in stages.
+  double batch_cost(int ns, int units, bool empty_wgs) {
+    const SplitSums& s = split_into(ns);
+    const int tiles_max = (max_nodes * g + tile_rows - 1) / tile_rows;
+    const double merge = s.grid_x > 1 ? 0.7 * s.grid_x * (tile_rows / 128.0) : 0.0;
+    const double empty = empty_wgs ? (double)((int64_t)c.num_kv_heads * tiles_max * s.grid_x * batch - s.jobs) : 0.0;
+    return s.jobs <= units ? s.longest(merge) : std::max(s.longest(merge), (s.work + s.merged * merge + empty) / units + s.shortest);
+  }
+
   // The split count on `units` compute units (those that the attention's workgroups can count on).  empty_wgs: as if a batch's grid
   // held a workgroup for every split of its longest sequence.
   int splits(int units, bool empty_wgs) {
@@ -352,10 +361,7 @@ struct Planner {
       int nsplit = 1;
       for (int ns = 1; ns <= last; ns++) {
         if (ns > 1 && chunk_of(ns) == chunk_of(ns - 1)) continue;  // (keys per split are a multiple of 32: the same plan)
-        const SplitSums& s = split_into(ns);
-        const double merge = s.grid_x > 1 ? 0.7 * s.grid_x * (tile_rows / 128.0) : 0.0;
-        const double empty = empty_wgs ? (double)((int64_t)c.num_kv_heads * tiles_max * s.grid_x * batch - s.jobs) : 0.0;
-        const double cost = s.jobs <= units ? s.longest(merge) : std::max(s.longest(merge), (s.work + s.merged * merge + empty) / units + s.shortest);
+        const double cost = batch_cost(ns, units, empty_wgs);
         if (ns == 1 || cost < best - 1e-9) { best = cost; nsplit = ns; }
       }
       return nsplit;
@@ -607,6 +613,23 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
       nsplit = wide_verification_splits(planner, measured, nsplit, n_launched, whole, opt_logits_wgs, &n_logits);
     } else if (wide) {
       n_logits = n_launched;
+    } else if (verification && batch > 1 && !whole && opt_splits <= 0) {
+      // The units of the logits' workgroups are free again soon: a batch whose jobs are more than the others, but no more than
+      // all, is through when the last of them are, some 8 stages late, and merged by the last to arrive.  3 sequences of 11316 to 17155
+      // paged keys, 32 heads: 192 workgroups beside 8 for the logits 189 us, 256 behind them 135.6.  (Not where the K/V take as long in any case,
+      // 1.05 us a stage, 1.3 from paged ones: 2 of 15000 contiguous keys 91.1 beside, 98.7 behind, 2 of 19672 and 24432 139 and 146.)
+      double slots = 0;
+      for (int b = 0; b < batch; b++) slots += planner.len[b];
+      const double memory = slots * c.num_kv_heads * c.head_dim * 4 / 5.5e6 / (c.block_size > 0 ? 1.3 : 1.05);
+      double best = 0.9 * std::max(memory, planner.batch_cost(nsplit, 256 - n_logits, false));
+      for (int ns = nsplit + 1; ns <= planner.cap(); ns++) {
+        const SplitSums& s = planner.split_into(ns);
+        if (s.jobs > 256) break;
+        const double cost = std::max(memory, s.longest(0.7 * s.grid_x * (planner.tile_rows / 128.0)) + 8.0);
+        if (s.jobs <= 256 - n_logits || cost >= best) continue;
+        best = cost;
+        nsplit = ns;
+      }
     }
     p = planner.cut(nsplit, precise);
   }

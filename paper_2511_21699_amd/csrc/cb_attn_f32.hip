@@ -90,6 +90,11 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p_arg, const Seq
   const CBL_GLOBAL float* const kb = (const CBL_GLOBAL float*)p.kv.k;
   const CBL_GLOBAL float* const vb = (const CBL_GLOBAL float*)p.kv.v;
 
+  // The tree first: loads return in the order of their requests, and the ancestor sets are the longest chain of the start.
+  const bool tree_split = k1 > S;
+  int raw_parent = -1;
+  if (tree_split && tid < N) raw_parent = as_global(p.parent)[shp.off + tid];
+
   const int row = row0 + r < M ? row0 + r : M - 1;   // (rows past the end repeat the last one and are not written)
   const int node = row / g;
   const CBL_GLOBAL f32x4* const qp = (const CBL_GLOBAL f32x4*)((const CBL_GLOBAL float*)p.q +
@@ -118,9 +123,11 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p_arg, const Seq
   f32x4 k[NJ];
   load_k(w, k);
 
-  if (k1 > S) {  // the tree's ancestor sets, behind the first loads; complete for any depth a tree of N nodes can have
+  if (tree_split) {  // the tree's ancestor sets, behind the first loads; complete for any depth a tree of N nodes can have
     const bool report = hk == 0 && rt == 0;
-    const int par = tid < N ? sanitized_parent(p.parent, shp.off, tid, report ? p.status : nullptr) : -1;
+    const bool odd = tid < N && (tid == 0 ? raw_parent != -1 : raw_parent < 0 || raw_parent >= tid);  // (as sanitized_parent)
+    const int par = tid == 0 || tid >= N ? -1 : odd ? 0 : raw_parent;
+    if (odd && report) atomicOr(p.status, 1);
     build_ancestor_sets(sh.anc, N, par, jump_rounds(N - 1));
     if (report && tid < N) {
       int depth = -1;
