@@ -617,11 +617,11 @@ Plan plan_call(const cb_config& c, int max_splits, int scalar_splits, int opt_im
       // The units of the logits' workgroups are free again soon: a batch whose jobs are more than the others, but no more than
       // all, is through when the last of them are, some 8 stages late, and merged by the last to arrive.  3 sequences of 11316 to 17155
       // paged keys, 32 heads: 192 workgroups beside 8 for the logits 189 us, 256 behind them 135.6.  (Not where the K/V take as long in any case,
-      // 1.05 us a stage, 1.3 from paged ones: 2 of 15000 contiguous keys 91.1 beside, 98.7 behind, 2 of 19672 and 24432 139 and 146.)
+      // 1.05 us a stage: 2 of 15000 keys 91.1 beside, 98.7 behind, 2 of 19672 and 24432 139 and 146.)
       double slots = 0;
       for (int b = 0; b < batch; b++) slots += planner.len[b];
-      const double memory = slots * c.num_kv_heads * c.head_dim * 4 / 5.5e6 / (c.block_size > 0 ? 1.3 : 1.05);
-      double best = 0.9 * std::max(memory, planner.batch_cost(nsplit, 256 - n_logits, false));
+      const double memory = slots * c.num_kv_heads * c.head_dim * 4 / 5.5e6 / 1.05;
+      double best = 0.92 * std::max(memory, planner.batch_cost(nsplit, 256 - n_logits, false));
       for (int ns = nsplit + 1; ns <= planner.cap(); ns++) {
         const SplitSums& s = planner.split_into(ns);
         if (s.jobs > 256) break;

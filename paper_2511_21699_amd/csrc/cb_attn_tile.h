@@ -352,9 +352,14 @@ struct Feed {
   KeyAddr ka;
   int bt_seg = 1;       // furthest segment of the table slice that the requests have entered (the first kBtSegs are loaded at the start)
   bool even;            // see issue()
+  bool long_slice = false;  // paged: more table entries than the LDS ring holds
   int64_t ts2;
   uint32_t lane_k[kParts], lane_v[kParts];
   int requested = 0, slot_next = 0;
+  // Paged and `even`: the block-table entries (uniform) of the next two units' groups.  Read where they are needed, an LDS round trip held
+  // up every request; with it and 64-bit scalars (group_off) 20 nodes of 32 heads x 9000 paged keys took 36.3 us a step, without 33.6, and
+  // contiguous ones 29.9 and 29.0.
+  int ahead[2][kParts];
 
   __device__ __forceinline__ Feed(const AttnParams& p_, const TileJob& jb_, int* bt_, uint4* ring_)
       : p(p_), jb(jb_), bt(bt_), ring(ring_), w(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)), l(threadIdx.x & 63),
@@ -371,6 +376,7 @@ struct Feed {
       for (int i = threadIdx.x; i <= last - first && i < kBtLds; i += 64 * NW)
         bt[i] = gbt[(int64_t)jb.b * p.kv.max_blocks + first + i];
       ka.bt_first = first;
+      long_slice = last - first >= kBtLds;
       __syncthreads();  // the K/V addresses below depend on it
     }
     even = p.kv.block_size == 0 || p.kv.block_size >= RPR;
@@ -382,20 +388,31 @@ struct Feed {
       lane_k[i] = (uint32_t)(lr * (int)ts2) + (uint32_t)(lc ^ swizzle_k<D>(rr)) * 16;
       lane_v[i] = (uint32_t)(lr * (int)ts2) + (uint32_t)(lc ^ swizzle_v<D, TR>(rr)) * 16;
     }
+#pragma unroll
+    for (int i = 0; i < kParts; i++) ahead[0][i] = ahead[1][i] = 0;
+    if (p.kv.block_size > 0 && even) {
+      look_up(0, ahead[0]);
+      look_up(1, ahead[1]);
+    }
   }
   __device__ __forceinline__ const uint4* k_at(int slot) const { return ring + slot * (2 * kVecs); }
   __device__ __forceinline__ const uint4* v_at(int slot) const { return ring + slot * (2 * kVecs) + kVecs; }
   // Every wave brings the same rows of K and of V (of one of the two, where a wave makes a single request per unit).
   __device__ __forceinline__ int part_row(int part) const { return (kReq >= 2 ? w * kParts + part : w % (NW / 2)) * RPR; }
+  __device__ __forceinline__ void look_up(int u, int (&entry)[kParts]) const {
+#pragma unroll
+    for (int i = 0; i < kParts; i++) entry[i] = bt[(((jb.k0 + u * kUnitKeys + part_row(i)) >> ka.bs_shift) - ka.bt_first) & (kBtLds - 1)];
+  }
   __device__ __forceinline__ int64_t group_off(int u, int part) const {  // byte offset of the group's first row (uniform; `even` only)
     const int key = jb.k0 + u * kUnitKeys + part_row(part);
+    // (pool sizes, keys and a row's stride have 32 bits: comparisons and products of 64-bit scalars are several instructions each)
     if (p.kv.block_size > 0) {
-      const int lb = key >> ka.bs_shift;
-      int64_t blk = __builtin_amdgcn_readfirstlane(bt[(lb - ka.bt_first) & (kBtLds - 1)]);
-      blk = blk < 0 ? 0 : (blk >= p.kv.num_blocks ? p.kv.num_blocks - 1 : blk);
-      return blk * p.kv.seq_stride * 2 + (int64_t)(key - (lb << ka.bs_shift)) * ts2 + (int64_t)jb.hk * p.kv.head_stride * 2;
+      int blk = __builtin_amdgcn_readfirstlane(ahead[0][part]);  // (of the unit that is next)
+      blk = blk < 0 ? 0 : (blk >= (int)p.kv.num_blocks ? (int)p.kv.num_blocks - 1 : blk);
+      return (int64_t)((uint64_t)(uint32_t)blk * (uint64_t)(p.kv.seq_stride * 2)) +
+             (int64_t)((uint64_t)(uint32_t)(key & (p.kv.block_size - 1)) * (uint32_t)ts2) + (int64_t)jb.hk * p.kv.head_stride * 2;
     }
-    return ((int64_t)jb.b * p.kv.seq_stride + (int64_t)jb.hk * p.kv.head_stride) * 2 + key * ts2;
+    return ((int64_t)jb.b * p.kv.seq_stride + (int64_t)jb.hk * p.kv.head_stride) * 2 + (int64_t)((uint64_t)(uint32_t)key * (uint32_t)ts2);
   }
   __device__ __forceinline__ void issue_group(int slot, int part, int64_t off, bool lanes) const {
     uint4* const kdst = ring + slot * (2 * kVecs) + part_row(part) * VPR;
@@ -443,7 +460,7 @@ struct Feed {
   }
   __device__ __forceinline__ void request_up_to(int limit) {
     while (requested < limit) {
-      if (p.kv.block_size > 0) bt_ahead(requested);
+      if (long_slice) bt_ahead(requested);
       issue(requested, slot_next);
       counted();
     }
@@ -451,6 +468,11 @@ struct Feed {
   __device__ __forceinline__ void counted() {
     slot_next = slot_next + 1 == kSlots ? 0 : slot_next + 1;
     requested++;
+    if (p.kv.block_size > 0 && even) {
+#pragma unroll
+      for (int i = 0; i < kParts; i++) ahead[0][i] = ahead[1][i];
+      look_up(requested + 1, ahead[1]);
+    }
   }
   // Waits until the first `landed` units are in LDS, in this wave's share and, behind the barrier, in every wave's.
   // Requests complete in order, so "at most n requests outstanding" means that all but the youngest n have landed.

@@ -302,11 +302,11 @@ struct WideFeed {
   __device__ __forceinline__ void next(int64_t (&off)[P], uint32_t& dst) {
     const KvAddr& a = f.p.kv;
     if (PG) {
-      f.bt_ahead(f.requested);
+      if (f.long_slice) f.bt_ahead(f.requested);
 #pragma unroll
       for (int i = 0; i < P; i++) {
         int b = blk[i];
-        b = b < 0 ? 0 : (b >= a.num_blocks ? (int)a.num_blocks - 1 : b);
+        b = b < 0 ? 0 : (b >= (int)a.num_blocks ? (int)a.num_blocks - 1 : b);
         off[i] = (int64_t)(uint64_t)(uint32_t)b * (a.seq_stride * 2) + (int64_t)((uint64_t)(uint32_t)(key[i] & (a.block_size - 1)) * (uint32_t)f.ts2);
       }
     } else {
