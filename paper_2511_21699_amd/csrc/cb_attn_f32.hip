@@ -11,9 +11,10 @@
 // What bounds it: a unit is D/2 MFMAs of 32 cycles, two wavefronts to a SIMD, against D * 128 bytes per wavefront from
 // the L2 (a kv head's tiles share an XCD): 32 of the 64 bytes a clock that a compute unit can take, so the matrix cores
 // for long sweeps, and the chain of a unit's loads and products for short ones.
-// Step times (verification and compaction): 16/8 heads of 128, 40 nodes, 1500 keys 20.4 us, against 257 with the scalar
-// kernel, which reads K and V once for every row; 8/8 heads of 64, 15 nodes, 256 keys 13.0 us against 26.8 (two
-// launches fewer are most of that).
+// Step times (verification and compaction): 16/8 heads of 128, 40 nodes, 1500 keys 17.9 us, against 257 with the scalar
+// kernel, which reads K and V once for every row; 8/8 heads of 64, 15 nodes, 256 keys 9.9 us against 26.8 (three
+// launches fewer are most of that).  The values are requested at the head of their own unit's arithmetic: a unit ahead (32 registers more)
+// the short calls took 11.4 us, the first unit's in front of the ancestor sets 10.4.
 //
 // Register layouts (lane l, r = l % 16, h = l / 16):
 //   scores transposed, S^T = K Q^T: MFMA (j, e) contracts the dims 16j + 4h + e; A = K[key r], B = Q[query r], so both
