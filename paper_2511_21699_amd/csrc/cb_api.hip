@@ -562,6 +562,9 @@ void shorter_tiles(Planner& tall, int rows, bool verification, int forced, Plan*
     if (i > 1 && planner.chunk_of(i) == planner.chunk_of(i - 1)) continue;
     const SplitSums& s = planner.split_into(i);
     if (s.jobs + n > 256 && !(forced && i == 1)) break;
+    // (what is in 16 bits stays so: longer slices of the block table would put the sums in 32, at up to twice the time of the estimate, which
+    // is that of 16-bit ones: 6 sequences of up to 17612 paged keys, 32 heads x up to 82 nodes, 418 us in one split instead of 201 in two)
+    if (precise_sums(c, s.chunk) != p->precise) continue;
     const double t = round_us(planner, s);
     if (t >= best) continue;
     best = t;
@@ -764,6 +767,7 @@ bool plan_layers(const cb_config& c, const WsLayout& lay, int layers, int batch,
       const Plan cut = pl.cut(ns, precise);
       const size_t bytes = cut.nsplit > 1 ? attn_mfma_partial_bytes(c.head_dim, cut.precise, rows, total, c.num_q_heads, c.num_kv_heads, batch, cut.nsplit) : 0;
       if (cut.impl != 2 || bytes * layers > room) break;
+      if (cut.precise != precise) continue;  // (longer slices of the block table than the layers have one by one: plan_call decides what is in 32 bits)
       const double t = us_of(pl, ns, layers);
       if ((best.impl && t >= us) || (cut.nsplit > 1 && !attn_mfma_merges_inside(c.head_dim, cut.precise, pl.max_nodes * pl.g, rows, cut.nsplit))) continue;
       us = t;
@@ -1114,6 +1118,19 @@ int cb_debug_tiles(const cb_config* cfg, int32_t batch, const int32_t* kv_len, c
   int64_t jobs = 0;
   if (p.impl == 2) jobs = Planner(*cfg, lay.max_splits, lay.scalar_splits, 0, 0, batch, kv_len, node_offsets, p.tile_rows).split_into(p.nsplit).jobs;
   const int32_t out[] = {p.impl == 2 ? p.tile_rows : 0, p.nsplit, p.chunk, p.precise, p.logits_wgs, (int32_t)jobs};
+  memcpy(plan, out, sizeof out);
+  return CB_OK;
+}
+
+int cb_debug_layers(const cb_config* cfg, int32_t layers, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets, int32_t plan[6]) {
+  int32_t base[5];
+  if (const int rc = cb_plan_attention(cfg, batch, kv_len, node_offsets, 0, base)) return rc;
+  if (layers < 2 || layers > kTableLayers) return CB_EINVAL;
+  ModelLaunch m;
+  memset(plan, 0, 6 * sizeof *plan);
+  if (!plan_layers(*cfg, ws_layout(*cfg), layers, batch, kv_len, node_offsets, &m)) return CB_OK;
+  const Plan& p = m.plan;
+  const int32_t out[] = {1, p.impl == 2 ? p.tile_rows : 0, p.nsplit, p.chunk, p.precise, p.logits_wgs};
   memcpy(plan, out, sizeof out);
   return CB_OK;
 }

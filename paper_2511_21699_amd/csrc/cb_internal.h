@@ -281,3 +281,6 @@ extern "C" int cb_debug_plan(const cb_config* cfg, int32_t batch, const int32_t*
 // that have keys to sweep
 extern "C" int cb_debug_tiles(const cb_config* cfg, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets,
                               int32_t verification, int32_t plan[6]);
+// and the launch of up to 32 of a model's layers: plan[0] = 1 if they are launched together, [1] = rows of a tile (0: fp32), [2] to [4] as [1] to
+// [3] of the first, [5] = workgroups for the logits work
+extern "C" int cb_debug_layers(const cb_config* cfg, int32_t layers, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets, int32_t plan[6]);

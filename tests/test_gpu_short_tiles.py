@@ -67,3 +67,34 @@ def test_shorter_tiles_keep_one_round_and_the_class_of_the_sums():
         else:
             assert p[1] == tall[1] and p[2] == tall[2] and p[4] == tall[4]
     assert shorter > 100
+
+
+# Slices of the block table that one split fewer would make longer than 16-bit sums go with.
+LONG_TABLES = [  # heads, kv heads, lengths, nodes, block, verification
+    (32, 32, [13169, 11104, 2591, 17612, 3498, 8277], [49, 33, 70, 82, 56, 45], 16, False), (40, 40, [23407] * 4, [119, 164, 179, 64], 16, True),
+    (160, 40, [3980], [73], 2, False), (80, 40, [5580], [133], 2, True)]
+
+
+@pytest.mark.parametrize("hq,hkv,lens,nodes,block,ver", LONG_TABLES)
+def test_shorter_tiles_do_not_put_sums_in_32_bits(hq, hkv, lens, nodes, block, ver):
+    tall, p = plans(hq, hkv, lens, nodes, block, ver)
+    assert tall[3] == 0 and p[3] == 0, (tall, p)
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_sums_of_paged_calls_keep_their_class(seed):
+    rng = np.random.default_rng(seed)
+    for _ in range(250):
+        hkv, g = int(rng.choice([8, 32, 40])), int(rng.choice([1, 2, 4, 8]))
+        lens = rng.integers(1, int(np.exp(rng.uniform(6, 10.5))), int(rng.choice([1, 1, 2, 3, 6])))
+        nodes = rng.integers(1, int(rng.choice([100, 256])) + 1, len(lens))
+        block = int(rng.choice([1, 2, 4, 16]))
+        alone, ver = [plans(hkv * g, hkv, lens, nodes, block, v) for v in (False, True)]
+        for tall, p in (alone, ver):
+            assert p[3] == tall[3]
+        n = np.asarray(nodes, dtype=np.int32)
+        cfg = B.make_config(hkv * g, hkv, 128, "bf16", "bf16", len(lens), int(n.max()), 8, 32000, block)
+        a, offs, out = np.asarray(lens, dtype=np.int32), np.concatenate([[0], np.cumsum(n)]).astype(np.int32), (C.c_int32 * 6)()
+        ip = lambda x: x.ctypes.data_as(C.POINTER(C.c_int32))  # noqa: E731
+        assert B.load().cb_debug_layers(C.byref(cfg), int(rng.choice([2, 8, 32])), len(lens), ip(a), ip(offs), out) == 0
+        assert not out[0] or out[4] == (alone[0][3] | ver[0][3])             # (a model's layers in one launch: as one by one)
