@@ -30,6 +30,10 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 constexpr int kF32Rows = 16;   // rows per tile
 constexpr int kF32Unit = 16;   // keys per unit
 constexpr int kF32Waves = 8;
+// Wavefronts that a SIMD has registers for: two whole workgroups at head_dim 64, and at 128 one and a half, so that a workgroup whose
+// wavefronts end one by one makes room for the next before its last one has.  (Verifications at 128 with 169 registers instead of 168,
+// where a workgroup waits for all of the one before it: 32 sequences of 4 nodes x 60 keys, 16/8 heads, 13.5 us for 11.7, 33 x 300 72.5 for 71.5.)
+constexpr int f32_waves(int D) { return D == 64 ? 4 : 3; }
 
 template <int D>
 struct F32Lds {
@@ -311,7 +315,7 @@ __device__ __forceinline__ void attn_f32_tile(const AttnParams& p_arg, const Seq
 }
 
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void k_attn_f32(AttnParams p, SeqMeta meta) {
+__global__ __launch_bounds__(64 * kF32Waves, f32_waves(D)) void k_attn_f32(AttnParams p, SeqMeta meta) {
   __shared__ F32Lds<D> sh;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   attn_f32_tile<D, false>(p, ml, blockIdx.x, sh, OneLayer{});
@@ -330,14 +334,14 @@ __device__ __forceinline__ void verify_f32(const AttnParams& p, const SeqMeta& m
   else attn_f32_tile<D, MOVE>(p, ml, wg, sh.attn, OneLayer{});
 }
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void k_verify_f32(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_f32<D, false>(p, meta, lw); }
+__global__ __launch_bounds__(64 * kF32Waves, f32_waves(D)) void k_verify_f32(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_f32<D, false>(p, meta, lw); }
 // with the compaction (lw.n_wgs is 0 where the logits work has a launch of its own)
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void k_step_f32(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_f32<D, true>(p, meta, lw); }
+__global__ __launch_bounds__(64 * kF32Waves, f32_waves(D)) void k_step_f32(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_f32<D, true>(p, meta, lw); }
 
 // The attention of several layers in one launch, with the logits work (of the last one) in its first workgroups where lw.n_wgs is not 0.
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void k_model_f32(AttnParams p, SeqMeta meta, LogitsWork lw, LayerTable layers) {
+__global__ __launch_bounds__(64 * kF32Waves, f32_waves(D)) void k_model_f32(AttnParams p, SeqMeta meta, LogitsWork lw, LayerTable layers) {
   __shared__ union Lds {
     F32Lds<D> attn;
     AcceptWaveLds accept;

@@ -171,3 +171,12 @@ def test_registers_leave_room_for_four_waves_per_simd(name, kernel):
     res = build.kernel_resources(build.device_asm(os.path.join(build.CSRC, name)))
     counts = [v[0] for k, v in res.items() if kernel in k]
     assert counts and max(counts) <= 128, res
+
+
+# The fp32 kernels count on two workgroups of 8 waves to a compute unit at head_dim 64, and on half of the next one's waves at 128.
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_registers_of_the_fp32_kernels():
+    res = build.kernel_resources(_asm("cb_attn_f32.hip"))
+    for d, most in ((64, 128), (128, 168)):
+        counts = {k: v[0] for k, v in res.items() if f"f32ILi{d}" in k}
+        assert len(counts) == 4 and max(counts.values()) <= most, counts
