@@ -163,6 +163,7 @@ struct cb_ctx {
   const Plan* fixed_plan = nullptr;  // (cb_tree_attention_noalloc: the plan its scratch layout was cut for)
   bool want_move = false;  // the launch that run_pipeline makes next is to compact its cache too, if it can;
   bool moved = false;      // whether it does
+  int32_t step_info[4] = {};  // (cb_debug_step)
   bool counters_dirty = false;  // a launch failed: the tickets may be left non-zero
   bool amax_dirty = false;      // a scan ran without its acceptance (option "stages"): row maxima are left behind
   char err[256];
@@ -971,6 +972,7 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
     kernels++;
   }
   if (!(stage_mask & 8)) return CB_OK;  // attention alone leaves the state of the last verification as it is
+  ctx->step_info[3] = use_mfma ? plan.tile_rows : 0;
   ctx->launch_info[0] = use_mfma ? 2 : 1;
   ctx->launch_info[1] = plan.nsplit;
   ctx->launch_info[2] = plan.chunk;
@@ -1281,7 +1283,10 @@ int cb_verify_and_compact_device(cb_ctx* ctx, void* hip_stream, int32_t batch, c
   const int rc = cb_verify_tree_device(ctx, hip_stream, batch, q, kv, kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits, attn_out,
                                        d_accepted_len, d_accepted_tokens);
   if (ctx) ctx->want_move = false;
-  if (rc || ctx->moved || num_layers == 0) return rc;
+  if (rc) return rc;
+  ctx->step_info[0] = ctx->moved;
+  ctx->step_info[1] = ctx->step_info[2] = 0;
+  if (ctx->moved || num_layers == 0) return rc;
   return cb_compact_kv(ctx, hip_stream, num_layers, layers, nullptr);
 }
 
@@ -1296,6 +1301,7 @@ int cb_model_step_device(cb_ctx* ctx, void* hip_stream, int32_t batch, int32_t n
                                         d_accepted_len, d_accepted_tokens, 1, layers);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   int done = 0;
+  ctx->step_info[0] = ctx->step_info[1] = ctx->step_info[2] = 0;
   if (layers_together(ctx, batch, num_layers, q, layers, kv_len, node_offsets, d_tree_parent, d_draft_tokens, logits, attn_out, d_accepted_len, d_accepted_tokens)) {
     // (as few launches as the table allows, of about as many layers each)
     const int launches = (num_layers + kTableLayers - 1) / kTableLayers;
@@ -1315,6 +1321,8 @@ int cb_model_step_device(cb_ctx* ctx, void* hip_stream, int32_t batch, int32_t n
                                   d_accepted_len, d_accepted_tokens, mask, &m);
       if (rc) return rc;
       done += n;
+      ctx->step_info[1] = done;
+      ctx->step_info[2]++;
     }
   }
   for (; done < num_layers; done++) {
@@ -1572,6 +1580,12 @@ int cb_last_launch_info(cb_ctx* ctx, int32_t info[6]) {
   if (!ctx || !info) return set_err(ctx, CB_EINVAL, "null argument");
   if (!ctx->have_verify) return set_err(ctx, CB_ESTATE, "no verify call yet");
   for (int i = 0; i < 6; i++) info[i] = ctx->launch_info[i];
+  return CB_OK;
+}
+
+int cb_debug_step(cb_ctx* ctx, int32_t info[4]) {
+  if (!ctx || !info) return set_err(ctx, CB_EINVAL, "null argument");
+  for (int i = 0; i < 4; i++) info[i] = ctx->step_info[i];
   return CB_OK;
 }
 

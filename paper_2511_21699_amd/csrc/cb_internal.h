@@ -284,3 +284,7 @@ extern "C" int cb_debug_tiles(const cb_config* cfg, int32_t batch, const int32_t
 // and the launch of up to 32 of a model's layers: plan[0] = 1 if they are launched together, [1] = rows of a tile (0: fp32), [2] to [4] as [1] to
 // [3] of the first, [5] = workgroups for the logits work
 extern "C" int cb_debug_layers(const cb_config* cfg, int32_t layers, int32_t batch, const int32_t* kv_len, const int32_t* node_offsets, int32_t plan[6]);
+// What the last cb_verify_and_compact_device or cb_model_step_device launched: info[0] = 1 if its compaction was part of the verification's
+// launch, [1] = layers that were attended to together and [2] = the launches that served those; [3] = rows of a tile of the context's last
+// verification (0: not the bf16 MFMA kernels)
+extern "C" int cb_debug_step(cb_ctx* ctx, int32_t info[4]);

@@ -110,3 +110,28 @@ def run_case(case, rows=None, layout=B.CB_LAYOUT_TOKEN_MAJOR, options=None, max_
         return dict(scale_free_err=sf, accepted=[int(x) for x in acc_len], info=info)
     finally:
         ver.close()
+
+
+def step_info(ver) -> dict:
+    """What the last step of the context launched."""
+    import ctypes as C
+    out = (C.c_int32 * 4)()
+    assert ver.L.cb_debug_step(ver.ctx, out) == 0
+    return dict(moved=bool(out[0]), layers=out[1], launches=out[2], tile_rows=out[3])
+
+
+def accept_to_the_last_node(case):
+    """Tokens with which each sequence accepts the path to its last node and no other."""
+    arg = O.argmax(case.logits, case.dtype)
+    tokens = np.where(arg == 0, 1, 0).astype(np.int32)
+    for lo, hi in zip(case.node_offsets, case.node_offsets[1:]):
+        par, x = case.parent[lo:hi], hi - lo - 1
+        for i in range(1, hi - lo):
+            tokens[lo + i] = (arg[lo + par[i]] + 1) % case.V
+        while x > 0:
+            tokens[lo + x] = arg[lo + par[x]]
+            x = par[x]
+    case.tokens = tokens
+    _, res = O.verify(case)
+    assert [int(r[1][r[0]]) for r in res] == [int(n) - 1 for n in np.diff(case.node_offsets)]
+    return res

@@ -7,7 +7,7 @@ import pytest
 
 from paper_2511_21699_amd import binding as B
 from paper_2511_21699_amd import workloads as W
-from .gpu_harness import check_attention, structured_rows
+from .gpu_harness import check_attention, step_info, structured_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -87,6 +87,8 @@ def test_layers_in_one_launch(i):
             assert t[b, :L + 1].cpu().tolist() == toks.tolist()
         check_caches(cases, dcs, res, layout)
     assert ver.device_status() & 3 == 0 and ver.last_launch_info()["kernels"] == kernels
+    info = step_info(ver)
+    assert info["layers"] == layers and info["launches"] == -(-layers // 32), info
     rows = structured_rows(case)
     for c, out in zip(cases, outs):
         got = W.to_f64(B.to_host(out, dtype), dtype)
@@ -120,6 +122,7 @@ def test_layers_that_go_one_by_one(kind):
             ver.verify_tree_device(qs[2], kvs[2], case.kv_len, case.node_offsets, par, tok, dcs[-1].logits, outs[2], n, t)
             ver.compact_kv(kvs, 1, want_len=False)
         torch.cuda.synchronize()
+        assert step_info(ver)["layers"] == 0
         got.append([x.clone() for x in outs] + [dc.k.clone() for dc in dcs] + [n.clone(), t.clone()])
         ver.close()
     assert all(torch.equal(a, b) for a, b in zip(*got))

@@ -5,6 +5,7 @@ import pytest
 
 from paper_2511_21699_amd import binding as B
 from paper_2511_21699_amd import workloads as W
+from .gpu_harness import accept_to_the_last_node, step_info
 
 pytestmark = pytest.mark.gpu
 
@@ -24,7 +25,12 @@ CASES = [  # dtype, heads, kv heads, head_dim, vocabulary, prefixes, tree sizes,
     ("f32", 16, 8, 128, 50000, [33, 700], [40, 17], {}, True),
     ("f32", 6, 3, 128, 300, [120], [64], {"splits": 5}, False),
     ("bf16", 8, 8, 128, 1000, [600], [40], {"attn_impl": 1}, False),      # (the scalar kernels: two launches)
+    ("bf16", 32, 8, 128, 3000, [500], [100], {"tile_rows": 64}, False),   # 7 tiles of 64 rows that a head's move waits for
+    ("bf16", 32, 8, 128, 3000, [500], [100], {"tile_rows": 128}, True),   # 4 of 128
+    ("bf16", 4, 4, 128, 500, [300, 31], [256, 70], {"tile_rows": 64}, True),
+    ("bf16", 8, 2, 64, 700, [900], [90], {"tile_rows": 128}, False),
 ]
+TWO_LAUNCHES = {"attn_impl"}
 
 
 @pytest.mark.parametrize("i", range(len(CASES)))
@@ -50,6 +56,8 @@ def test_one_call_against_two(i, layout):
         for _ in range(3):
             if fused:
                 step()
+                info = step_info(ver)
+                assert info["moved"] == (not TWO_LAUNCHES & set(options)) and info["tile_rows"] == options.get("tile_rows", info["tile_rows"])
             else:
                 ver.verify_tree_device(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, out, n, t)
                 ver.compact_kv([dc.kv], len(lens), want_len=False)
@@ -80,3 +88,34 @@ def test_operands_that_overlap_the_cache_take_two_launches():
         ref = ref or (out, dc.k.clone())
         assert torch.equal(out, ref[0]) and torch.equal(dc.k, ref[1])
         ver.close()
+
+
+def chain(n):
+    """A path of n - 2 nodes below the root, each a slot away from its place: node 1 is a leaf beside it."""
+    return [-1, 0, 0] + list(range(2, n - 1))
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d", [("bf16", 4, 4, 128), ("bf16", 16, 8, 64), ("f32", 4, 2, 128), ("f32", 8, 8, 64)])
+@pytest.mark.parametrize("sizes", [[65], [66], [67], [130], [256], [200, 3, 70]])   # accepted: 63, 64, 65, 128, 254 nodes
+@pytest.mark.parametrize("paged", [False, True])
+def test_paths_longer_than_a_wave(dtype, hq, hkv, d, sizes, paged):
+    """Paths of more nodes than a wavefront has lanes, all of which move, against the oracle's cache."""
+    import torch
+    from oracle import cb_oracle as O
+    print(f"[case] long paths {dtype} {hq}/{hkv} x {d} {sizes} paged={paged}", flush=True)
+    case = W.custom_case(7200 + sum(sizes), dtype, len(sizes), hq, hkv, d, 300, [50 + 9 * b for b in range(len(sizes))], [chain(n) for n in sizes],
+                         paged=paged, p_match=0.0)
+    res = accept_to_the_last_node(case)
+    dc = B.DeviceCase(case)
+    ver = B.Verifier(B.config_for_case(case))
+    par, tok = torch.from_numpy(case.parent).cuda(), torch.from_numpy(case.tokens).cuda()
+    n, t = torch.zeros(case.B, dtype=torch.int32, device="cuda"), torch.zeros(case.B, case.max_depth + 1, dtype=torch.int32, device="cuda")
+    ver.bind_step(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, torch.zeros_like(dc.q), n, t, [dc.kv])()
+    torch.cuda.synchronize()
+    assert step_info(ver)["moved"]
+    k, v = case.k.copy(), case.v.copy()
+    for b, (L, path, _) in enumerate(res):
+        assert int(n[b]) == L == sizes[b] - 2
+        O.compact(case, k, v, b, path)
+    assert np.array_equal(B.to_host(dc.k, dtype), k) and np.array_equal(B.to_host(dc.v, dtype), v)
+    ver.close()

@@ -79,3 +79,18 @@ def test_short_logits_rows_get_workgroups_by_their_number():
     short, long_rows = plan(32, 32, lens, nodes, vocab=1000), plan(32, 32, lens, nodes, vocab=8000)
     assert short["fused"] and 16 <= short["logits_wgs"] <= 96, short
     assert long_rows["logits_wgs"] >= short["logits_wgs"]
+
+
+def layers_plan(layers, hq, hkv, lens, nodes, block=0, vocab=32000, d=128):
+    n = np.broadcast_to(np.asarray(nodes, dtype=np.int32), len(lens)).astype(np.int32)
+    cfg = B.make_config(hq, hkv, d, "bf16", "bf16", len(lens), int(n.max()), 8, vocab, block)
+    a, offs, out = np.asarray(lens, dtype=np.int32), np.concatenate([[0], np.cumsum(n)]).astype(np.int32), (C.c_int32 * 6)()
+    ip = lambda x: x.ctypes.data_as(C.POINTER(C.c_int32))  # noqa: E731
+    assert B.load().cb_debug_layers(C.byref(cfg), layers, len(lens), ip(a), ip(offs), out) == 0
+    return dict(zip(("together", "tile_rows", "nsplit", "chunk", "precise", "logits_wgs"), out))
+
+
+def test_layers_go_together_where_that_is_faster():
+    assert layers_plan(32, 32, 32, [2048], 64)["nsplit"] == 1                          # 1024 whole sequences fill the chip
+    assert layers_plan(2, 8, 8, [3000], 33)["nsplit"] > 1                              # 16 do not
+    assert not layers_plan(2, 32, 8, steps(4105 - 7 * 10, 10, 8), 180)["together"]     # few long tiles: one by one
