@@ -941,8 +941,14 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   const bool timing = ctx->opt_time != 0;
   // The compaction in the attention's launch, for the matrix-core kernels as they are by default.
   // Not in many rounds of workgroups, each of which its arrivals make about a microsecond longer (31 sequences of one node x 55 keys, 32
-  // heads: 22.9 us in two launches, 26.1 in one; 18 of 53 x 36, 40 heads, 41.5 and 40.0).
-  ctx->moved = ctx->want_move && stages == 15 && (f32_tiles || (use_mfma && ap.live_wgs <= 3 * 256)) &&
+  // heads: 22.9 us in two launches, 26.1 in one; 18 of 53 x 36, 40 heads, 41.5 and 40.0).  (In fp32, 2048 workgroups of 20 nodes x 1000 keys, 16/8
+  // heads, 194.2 in one launch and 199.8 in two: no such line.)
+  // Nor where a logits workgroup accepts more than two sequences on average: what follows an acceptance is a chain of round trips, which the
+  // sequences beyond take one after the other.  Steps in one launch and in two, 200 keys x 8 nodes, 8 heads, vocabulary 1000 (8
+  // logits workgroups): 16 sequences 11.6 and 13.3 us, 24 16.7 and 16.6, 48 29.5 and 28.0, 64 36.5 and 34.9; fp32 with head_dim 64: 11.2 and 12.6,
+  // 16.3 and 14.9, 30.9 and 24.4, 36.7 and 30.3.
+  const bool few_to_a_workgroup = !fused || batch <= 2 * n_logits;
+  ctx->moved = ctx->want_move && stages == 15 && (f32_tiles || (use_mfma && ap.live_wgs <= 3 * 256)) && few_to_a_workgroup &&
                !timing && !fork && !ap.timeline;
   ctx->want_move = false;
   if (ctx->moved) ap.move = MoveArgs{ctx->dev<uint32_t>(ctx->lay.moves), acc.path, acc.len_ctx, fused ? 1 : 0};

@@ -410,11 +410,11 @@ constexpr int kTicketWords = (kTicketGroups + 1) * kTicketStride;    // per sequ
 constexpr int kTicketDirect = 48;  // arrivals up to which one word serves a sequence
 
 // LOADS: loads of 16 bytes that a lane has in flight, as the kernel's registers allow.  EB: bytes of a logits element
-// where the kernel is built for one type, else 0.  after(b, S, N): what all wavefronts of the workgroup that accepted sequence b do
-// then, behind a barrier (uniform).
+// where the kernel is built for one type, else 0.  after(b, S, N, i, n): what the wavefronts of the workgroup that accepted sequence b do
+// then, behind a barrier, the i-th of n that the sequence has.
 struct NothingAfter {
   static constexpr bool kAny = false;
-  __device__ __forceinline__ void operator()(int, int, int) const {}
+  __device__ __forceinline__ void operator()(int, int, int, int, int) const {}
 };
 template <int NW, int LOADS, bool SHORT = false, int EB = 0, typename After = NothingAfter>
 __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMetaLanes& ml, int wg, AcceptWaveLds& sh, const After& after = After{}) {
@@ -477,17 +477,24 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the results are in memory before anybody is told)
   if (threadIdx.x == 0) sh.accepted = accepted;
   __syncthreads();
-  for (unsigned long long todo = sh.accepted; todo != 0; todo &= todo - 1) {
+  // Several sequences side by side, each by its share of the wavefronts: what follows one is a chain of round trips to memory, about 2 us.
+  constexpr int LOG = __builtin_ctz(NW);
+  static_assert(NW == 1 << LOG, "");
+  const int seqs = __builtin_amdgcn_readfirstlane(__popcll(sh.accepted)), wave = __builtin_amdgcn_readfirstlane(w);
+  const int groups = seqs <= 1 ? 0 : seqs >= NW ? LOG : 32 - __builtin_clz(seqs - 1), log_n = LOG - groups;  // (logarithms)
+  int i = 0;
+  for (unsigned long long todo = sh.accepted; todo != 0; todo &= todo - 1, i++) {
+    if ((i & ((1 << groups) - 1)) != wave >> log_n) continue;
     const int b = __builtin_amdgcn_readfirstlane(__builtin_ctzll(todo));
     const SeqShape s = seq_shape(ml, b);
-    after(b, s.S, s.N);
+    after(b, s.S, s.N, wave & ((1 << log_n) - 1), 1 << log_n);
   }
 }
 
 // What follows the acceptance in a launch that compacts its cache (MOVE), or in one that does not.
-template <bool MOVE, int PIECES, int SHIFT, int NW>
+template <bool MOVE, int PIECES, int SHIFT>
 __device__ __forceinline__ auto after_acceptance() {
-  if constexpr (MOVE) return MoveAfter<PIECES, SHIFT, NW>{};
+  if constexpr (MOVE) return MoveAfter<PIECES, SHIFT>{};
   else return NothingAfter{};
 }
 

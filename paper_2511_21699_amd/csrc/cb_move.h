@@ -144,20 +144,20 @@ struct HeadMove {
   }
 };
 
-// The acceptance's arrival for the heads of a sequence, by all NW wavefronts of its workgroup (logits_share), behind a barrier that
-// follows the acknowledgement of its stores; the heads whose attention is through already are moved here.
-template <int PIECES, int SHIFT, int NW>
+// The acceptance's arrival for the heads of a sequence, by `nw` wavefronts of its workgroup (logits_share), this one the w-th of them, behind a
+// barrier that follows the acknowledgement of its stores; the heads whose attention is through already are moved here.
+template <int PIECES, int SHIFT>
 struct MoveAfter {
   static constexpr bool kAny = true;
-  __device__ __forceinline__ void operator()(int b, int S, int N) const {
+  __device__ __forceinline__ void operator()(int b, int S, int N, int w, int nw) const {
     const ArgsPtr a = fresh_args();
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), Hkv = a->Hkv;
+    const int lane = threadIdx.x & 63, Hkv = a->Hkv;
     const uint32_t all = move_arrivals(a, S, N);
     auto arrive = [&](int hk) { return hk < Hkv ? __hip_atomic_fetch_add(move_word(a, b, hk), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u; };
-    uint32_t old = arrive(w + lane * NW);
+    uint32_t old = arrive(w + lane * nw);
     const AcceptedPath path(a, b);  // (its loads and the first arrivals in one round trip)
-    for (int h0 = w; h0 < Hkv; h0 += 64 * NW) {  // (lane i: head h0 + i NW, so that every wavefront has few to move)
-      const int hk = h0 + lane * NW;
+    for (int h0 = w; h0 < Hkv; h0 += 64 * nw) {  // (lane i: head h0 + i nw, so that every wavefront has few to move)
+      const int hk = h0 + lane * nw;
       if (h0 != w) old = arrive(hk);
       const bool last = hk < Hkv && old + 1 == all;
       if (last) __hip_atomic_store(move_word(a, b, hk), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
@@ -168,7 +168,7 @@ struct MoveAfter {
         int heads[HB];
 #pragma unroll
         for (int i = 0; i < HB; i++) {
-          heads[i] = i > 0 && todo == 0 ? heads[0] : __builtin_amdgcn_readfirstlane(h0 + __builtin_ctzll(todo) * NW);
+          heads[i] = i > 0 && todo == 0 ? heads[0] : __builtin_amdgcn_readfirstlane(h0 + __builtin_ctzll(todo) * nw);
           todo &= todo - 1;
         }
         move_heads<PIECES, SHIFT, HB>(fresh_kv(a), path, b, S, N, heads);

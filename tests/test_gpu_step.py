@@ -30,7 +30,13 @@ CASES = [  # dtype, heads, kv heads, head_dim, vocabulary, prefixes, tree sizes,
     ("bf16", 4, 4, 128, 500, [300, 31], [256, 70], {"tile_rows": 64}, True),
     ("bf16", 8, 2, 64, 700, [900], [90], {"tile_rows": 128}, False),
 ]
-TWO_LAUNCHES = {"attn_impl"}
+TWO_LAUNCHES = {"attn_impl", "many"}
+for n in (16, 17, 40):  # sequences that 8 logits workgroups accept: two each, and more, whose compaction has a launch of its own
+    many = {"logits_wgs": 8} if n == 16 else {"logits_wgs": 8, "many": 1}
+    CASES += [("bf16", 8, 8, 128, 300, [5 + 7 * i % 90 for i in range(n)], [3 + i % 6 for i in range(n)], many, n == 17),
+              ("f32", 4, 4, 64, 300, [5 + 7 * i % 90 for i in range(n)], [3 + i % 6 for i in range(n)], many, n == 16)]
+CASES += [("bf16", 16, 8, 128, 300, [40 * i for i in range(n)], [9 + i for i in range(n)], {"logits_wgs": 8}, False) for n in (9, 12)]
+CASES += [("bf16", 72, 72, 64, 300, [20 * i for i in range(8)], [9 + i for i in range(8)], {"logits_wgs": 8}, False)]   # more heads than lanes
 
 
 @pytest.mark.parametrize("i", range(len(CASES)))
@@ -48,7 +54,8 @@ def test_one_call_against_two(i, layout):
         dc = B.DeviceCase(case, layout=layout)
         ver = B.Verifier(B.config_for_case(case))
         for k, v in options.items():
-            ver.set_option(k, v)
+            if k != "many":
+                ver.set_option(k, v)
         par, tok = torch.from_numpy(case.parent).cuda(), torch.from_numpy(case.tokens).cuda()
         out, k0 = torch.zeros_like(dc.q), dc.k.clone()
         n, t = torch.zeros(len(lens), dtype=torch.int32, device="cuda"), torch.zeros(len(lens), case.max_depth + 1, dtype=torch.int32, device="cuda")
