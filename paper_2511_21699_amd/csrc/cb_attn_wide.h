@@ -691,7 +691,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void k_step_wide(AttnParams p, 
   __shared__ __align__(1024) uint4 ring[Feed<D, kWideWaves, 32>::kRingVecs];
   __shared__ TileLds sh;
   const int wg = (int)blockIdx.x - lw.n_wgs;
-  if (wg < 0) logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<true, row_pieces(D, 2), 1>());
+  if (wg < 0) logits_share<kWideWaves, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<true, row_pieces(D, 2), 1, 4>());
   else attn_wide_tile<D, PX, PG, R128, true, false>(p, ml, wg, 0ull, sh, ring, nullptr, OneLayer{});
 }
 

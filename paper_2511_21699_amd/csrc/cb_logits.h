@@ -492,9 +492,9 @@ __device__ __forceinline__ void logits_share(const LogitsWork& lw, const SeqMeta
 }
 
 // What follows the acceptance in a launch that compacts its cache (MOVE), or in one that does not.
-template <bool MOVE, int PIECES, int SHIFT>
+template <bool MOVE, int PIECES, int SHIFT, int HB>
 __device__ __forceinline__ auto after_acceptance() {
-  if constexpr (MOVE) return MoveAfter<PIECES, SHIFT>{};
+  if constexpr (MOVE) return MoveAfter<PIECES, SHIFT, HB>{};
   else return NothingAfter{};
 }
 

@@ -145,8 +145,10 @@ struct HeadMove {
 };
 
 // The acceptance's arrival for the heads of a sequence, by `nw` wavefronts of its workgroup (logits_share), this one the w-th of them, behind a
-// barrier that follows the acknowledgement of its stores; the heads whose attention is through already are moved here.
-template <int PIECES, int SHIFT>
+// barrier that follows the acknowledgement of its stores; the heads whose attention is through already are moved here, HB at a time.  (A short
+// sweep is through before the acceptance is, and then all heads are: with four wavefronts and two heads at a time, 97 nodes of 40 heads x
+// 790 keys took 17.2 us a step against 16.4 in two launches.)
+template <int PIECES, int SHIFT, int HB>
 struct MoveAfter {
   static constexpr bool kAny = true;
   __device__ __forceinline__ void operator()(int b, int S, int N, int w, int nw) const {
@@ -163,7 +165,6 @@ struct MoveAfter {
       if (last) __hip_atomic_store(move_word(a, b, hk), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
       unsigned long long todo = __builtin_amdgcn_ballot_w64(last);
       if (!path.moves()) continue;
-      constexpr int HB = SHIFT == 2 ? 1 : 2;
       while (todo != 0) {
         int heads[HB];
 #pragma unroll

@@ -29,6 +29,8 @@ CASES = [  # dtype, heads, kv heads, head_dim, vocabulary, prefixes, tree sizes,
     ("bf16", 32, 8, 128, 3000, [500], [100], {"tile_rows": 128}, True),   # 4 of 128
     ("bf16", 4, 4, 128, 500, [300, 31], [256, 70], {"tile_rows": 64}, True),
     ("bf16", 8, 2, 64, 700, [900], [90], {"tile_rows": 128}, False),
+    ("bf16", 40, 40, 128, 32000, [790], [97], {"tile_rows": 256}, False), # 10 heads to a wave of the acceptance's workgroup, 4 at a time
+    ("bf16", 44, 22, 128, 20000, [300, 20], [70, 40], {"tile_rows": 128}, True),
 ]
 TWO_LAUNCHES = {"attn_impl", "many"}
 for n in (16, 17, 40):  # sequences that 8 logits workgroups accept: two each, and more, whose compaction has a launch of its own
