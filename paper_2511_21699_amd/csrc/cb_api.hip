@@ -519,25 +519,27 @@ int wide_verification_splits(Planner& planner, int alone, int beside, int n, boo
 
 constexpr int kTallest = 256;  // option "tile_rows": the smallest tile that holds a kv head's rows, at most this
 
-// What one round of workgroups with tiles of so many rows takes, in us (head_dim 128): start and tail, less of both without partial states,
-// and what 32 keys of the longest split cost, more while the ring fills.  Taller tiles read, park, write and merge more rows beside the sweep;
-// shorter ones read the same keys again, from the L2.
-double round_us(int rows, int chunk, bool split) {
+// What one round of workgroups with tiles of `rows` of a head's rows takes, in us (head_dim 128): start and tail, less of both without partial
+// states (splits 1), and what 32 keys of the longest split cost, more while the ring fills.  Taller tiles read, park, write and merge more rows beside
+// the sweep; shorter ones read the same keys again, from the L2.  A merge is shared out among a tile's splits: up to three have larger slices, which
+// shows where a head has two tiles.  Verifications, splits x units: two tiles of 64 rows 4 x 4 10.0, 7 x 5 10.1, 15 x 14 14.9, 3 x 5
+// 11.5, 3 x 8 13.0, 3 x 10 14.1; one of 128 with 66 rows 5 x 4 11.2, with 97 12.1, with 128 12.5.
+double round_us(int rows, int head_rows, int chunk, int splits) {
   const double units = chunk / 32, early = std::min(units, 9.0), late = units - early;
-  if (rows == 256) return split ? 14.5 + 0.85 * units : 5.5 + 1.95 * early + 0.85 * late;
-  if (rows == 128) return split ? 10.5 + 0.5 * units : 5.0 + 1.05 * early + 0.5 * late;
-  return split ? 8.0 + 0.45 * units : 5.0 + 0.8 * early + 0.5 * late;
+  if (rows > 128) return splits > 1 ? 14.5 + 0.85 * units : 5.5 + 1.95 * early + 0.85 * late;
+  if (rows > 64) return splits > 1 ? (head_rows > 128 ? 10.5 : 9.4 + 0.022 * (head_rows - 66)) + 0.5 * units : 5.0 + 1.05 * early + 0.5 * late;
+  return splits > 1 ? 8.0 + 0.45 * units + (splits <= 3 && head_rows <= 128 ? 0.9 : 0.0) : 5.0 + 0.8 * early + 0.5 * late;
 }
 
 // The same of a call's round: its longest job.  (A sequence whose rows a shorter tile would hold costs what that does.)
 double round_us(const Planner& pl, const SplitSums& s) {
   double us = 0.0;
   for (int b = 0; b < pl.batch; b++) {
-    const int rows = std::min((pl.node_offsets[b + 1] - pl.node_offsets[b]) * pl.g, pl.tile_rows);
-    const int tile = pl.tile_rows == kRowTile ? kRowTile : rows <= 128 ? 128 : 256, keys = std::min(pl.len[b] + 31, s.chunk);
+    const int head_rows = (pl.node_offsets[b + 1] - pl.node_offsets[b]) * pl.g, keys = std::min(pl.len[b] + 31, s.chunk);
+    const int rows = pl.tile_rows == kRowTile ? kRowTile : std::max(std::min(head_rows, pl.tile_rows), kRowTile + 1);
     // (a batch's tiles are not in step with each other: 8 sequences of up to 2000 keys, 32/8 heads x up to 48 nodes, 1024 keys to a
     // split 28.9 us)
-    us = std::max(us, round_us(tile, keys, pl.len[b] > s.chunk) + (pl.batch > 1 && tile <= 128 ? 0.05 * keys / 32 : 0.0));
+    us = std::max(us, round_us(rows, head_rows, keys, (pl.len[b] + s.chunk - 1) / s.chunk) + (pl.batch > 1 && rows <= 128 ? 0.05 * keys / 32 : 0.0));
   }
   return us;
 }

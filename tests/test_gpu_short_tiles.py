@@ -98,3 +98,11 @@ def test_sums_of_paged_calls_keep_their_class(seed):
         ip = lambda x: x.ctypes.data_as(C.POINTER(C.c_int32))  # noqa: E731
         assert B.load().cb_debug_layers(C.byref(cfg), int(rng.choice([2, 8, 32])), len(lens), ip(a), ip(offs), out) == 0
         assert not out[0] or out[4] == (alone[0][3] | ver[0][3])             # (a model's layers in one launch: as one by one)
+
+
+# Two tiles to a head in three splits, whose merge has large slices, are no faster than one tile in more splits; one split, or more of them, are.
+@pytest.mark.parametrize("hkv,length,nodes,tile", [(32, 790, 70, 256), (40, 790, 70, 256), (32, 800, 97, 256), (32, 800, 128, 256), (40, 800, 128, 256),
+                                                   (40, 400, 70, 256), (32, 650, 96, 256), (32, 120, 66, 64), (8, 800, 97, 64), (16, 1000, 70, 64),
+                                                   (32, 400, 97, 64), (8, 3200, 128, 64)])
+def test_two_tiles_to_a_head(hkv, length, nodes, tile):
+    assert plans(hkv, hkv, [length], [nodes], 0, True, vocab=1000)[1][0] == tile
