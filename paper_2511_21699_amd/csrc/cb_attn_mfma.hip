@@ -139,10 +139,10 @@ __device__ __forceinline__ void compute_unit(const uint4* __restrict__ ks, const
 }
 
 // One attention workgroup; `wg` is its number among those that do attention.  MOVE: the launch compacts its cache.
-template <int D, bool PX, bool MOVE, bool TS, typename Layers>
+template <int D, bool PX, bool PG, bool MOVE, bool TS, typename Layers>
 __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, unsigned long long ts0,
                                           TileLds& sh, uint4* ring, unsigned long long* ts_sh, const Layers& layers) {
-  using F = Feed<D, 8, 16>;
+  using F = Feed<D, 8, 16, !PG>;
   constexpr int NS = F::kSlots, PRO = F::kPrologue, P = PartialLayout<D, 16, PX>::P;
   AttnParams p = p_arg;
   pin_args(p);
@@ -247,25 +247,25 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   split_merge<D, 16, PX, 8, kSmallRows, TS>(p, jb, kSmallRows, sh, ts, finish_move);
 }
 
-template <int D, bool PX, bool TS>
+template <int D, bool PX, bool PG, bool TS>
 __device__ __forceinline__ void attn_workgroup(const AttnParams& p, const SeqMeta& meta) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
+  __shared__ uint4 ring[Feed<D, 8, 16, !PG>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
-  attn_tile<D, PX, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh, OneLayer{});
+  attn_tile<D, PX, PG, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
 // The whole verification in one launch: the first lw.n_wgs workgroups do the logits work (they are dispatched
 // first, so the acceptance is through long before the attention is, and a waiting host has its results then),
 // the others the attention.  Neither waits for the other.
-template <int D, bool PX, bool MOVE, bool TS>
+template <int D, bool PX, bool PG, bool MOVE, bool TS>
 __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqMeta& meta, const LogitsWork& lw) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
+  __shared__ uint4 ring[Feed<D, 8, 16, !PG>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
@@ -274,33 +274,65 @@ __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqM
     logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<MOVE, row_pieces(D, 2), 1, 2>());
     return;
   }
-  attn_tile<D, PX, MOVE, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});
+  attn_tile<D, PX, PG, MOVE, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, wg, ts_sh);
 }
 
 // The attention of several layers in one launch, with the logits work (of the last one) in its first workgroups where lw.n_wgs is not 0.
-template <int D, bool PX>
+template <int D, bool PX, bool PG>
 __global__ __launch_bounds__(512) void k_model_mfma(AttnParams p, SeqMeta meta, LogitsWork lw, LayerTable layers) {
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  __shared__ uint4 ring[Feed<D, 8, 16>::kRingVecs];
+  __shared__ uint4 ring[Feed<D, 8, 16, !PG>::kRingVecs];
   __shared__ TileLds sh;
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
-  else attn_tile<D, PX, false, false>(p, ml, wg, 0ull, sh, ring, nullptr, layers);
+  else attn_tile<D, PX, PG, false, false>(p, ml, wg, 0ull, sh, ring, nullptr, layers);
 }
 
 // head_dim 64 always holds probabilities and partial sums in 32 bits, head_dim 128 in the precise builds.
 template <int D, bool TS>
-__global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) { attn_workgroup<D, D == 64, TS>(p, meta); }
-template <bool TS>
-__global__ __launch_bounds__(512) void k_attn_precise(AttnParams p, SeqMeta meta) { attn_workgroup<128, true, TS>(p, meta); }
+__global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) { attn_workgroup<D, D == 64, false, TS>(p, meta); }
 template <int D, bool TS>
-__global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, false, TS>(p, meta, lw); }
-template <bool TS>
-__global__ __launch_bounds__(512) void k_verify_precise(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<128, true, false, TS>(p, meta, lw); }
-// with the compaction (builds of their own: what follows the sweep takes scalar registers from it, 2 to 3 % of a long one)
-template <int D, bool PX>
-__global__ __launch_bounds__(512) void k_step_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, PX, true, false>(p, meta, lw); }
+__global__ __launch_bounds__(512) void k_attn_paged(AttnParams p, SeqMeta meta) { attn_workgroup<D, D == 64, true, TS>(p, meta); }
+template <bool PG, bool TS>
+__global__ __launch_bounds__(512) void k_attn_precise(AttnParams p, SeqMeta meta) { attn_workgroup<128, true, PG, TS>(p, meta); }
+template <int D, bool TS>
+__global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, false, false, TS>(p, meta, lw); }
+template <int D, bool TS>
+__global__ __launch_bounds__(512) void k_verify_paged(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, true, false, TS>(p, meta, lw); }
+template <bool PG, bool TS>
+__global__ __launch_bounds__(512) void k_verify_precise(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<128, true, PG, false, TS>(p, meta, lw); }
+// with the compaction (builds of their own: what follows the sweep takes scalar registers from it)
+template <int D, bool PX, bool PG>
+__global__ __launch_bounds__(512) void k_step_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, PX, PG, true, false>(p, meta, lw); }
+
+// Launches for tiles of up to 64 rows.  (Steps and launches for several layers have no timeline build; their lw.n_wgs is 0 where the logits
+// work has a launch of its own.)
+template <bool PG>
+static hipError_t launch_small(hipStream_t st, dim3 grid, const AttnParams& p, const SeqMeta& meta, const LogitsWork* logits_work, const LayerTable* layers) {
+  const LogitsWork lw = logits_work ? *logits_work : LogitsWork{};
+  auto launch = [&](auto* kernel, auto... args) { hipLaunchKernelGGL(kernel, grid, dim3(512), 0, st, p, meta, args...); };
+  auto either = [&](auto* stamped, auto* plain, auto... args) { launch(p.timeline != 0 ? stamped : plain, args...); };
+  if (p.move.words) {
+    if (p.D == 64) launch(k_step_mfma<64, true, PG>, lw);
+    else if (p.precise) launch(k_step_mfma<128, true, PG>, lw);
+    else launch(k_step_mfma<128, false, PG>, lw);
+  } else if (layers) {
+    if (p.D == 64) launch(k_model_mfma<64, true, PG>, lw, *layers);
+    else if (p.precise) launch(k_model_mfma<128, true, PG>, lw, *layers);
+    else launch(k_model_mfma<128, false, PG>, lw, *layers);
+  } else if (p.precise && p.D == 128) {
+    if (logits_work) either(k_verify_precise<PG, true>, k_verify_precise<PG, false>, lw);
+    else either(k_attn_precise<PG, true>, k_attn_precise<PG, false>);
+  } else if (logits_work) {
+    if (p.D == 64) PG ? either(k_verify_paged<64, true>, k_verify_paged<64, false>, lw) : either(k_verify_mfma<64, true>, k_verify_mfma<64, false>, lw);
+    else PG ? either(k_verify_paged<128, true>, k_verify_paged<128, false>, lw) : either(k_verify_mfma<128, true>, k_verify_mfma<128, false>, lw);
+  } else {
+    if (p.D == 64) PG ? either(k_attn_paged<64, true>, k_attn_paged<64, false>) : either(k_attn_mfma<64, true>, k_attn_mfma<64, false>);
+    else PG ? either(k_attn_paged<128, true>, k_attn_paged<128, false>) : either(k_attn_mfma<128, true>, k_attn_mfma<128, false>);
+  }
+  return hipGetLastError();
+}
 
 // Stand-alone merge of the partials, used when a tile's partials are too many for one
 // workgroup to pull through its compute unit: one workgroup per TR-row tile, its four waves take a quarter of the
@@ -412,34 +444,14 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   if (p.force_external_merge && p.nsplit > 1) { q.external_merge = 1; q.coop_merge = 0; }  // (option "external_merge": a test aid)
   if (merge_kind) *merge_kind = p.nsplit <= 1 ? 0 : (q.coop_merge ? 1 : (q.external_merge ? 3 : 2));
   if (layers && q.external_merge) return hipErrorInvalidValue;  // (the merge kernel knows one layer)
-  const bool ts = p.timeline != 0;  // (the timeline build of the same kernels: a measurement aid)
   hipError_t e;
-  auto launch = [&](auto* stamped, auto* plain, auto... args) { hipLaunchKernelGGL(ts ? stamped : plain, grid, dim3(512), 0, st, args...); };
-  if (p.move.words && rt_rows == kSmallRows) {  // (no timeline build; n_wgs is 0 where the logits work has a launch of its own)
-    const LogitsWork lw = logits_work ? *logits_work : LogitsWork{};
-    if (p.D == 64) hipLaunchKernelGGL((k_step_mfma<64, true>), grid, dim3(512), 0, st, q, meta, lw);
-    else if (p.precise) hipLaunchKernelGGL((k_step_mfma<128, true>), grid, dim3(512), 0, st, q, meta, lw);
-    else hipLaunchKernelGGL((k_step_mfma<128, false>), grid, dim3(512), 0, st, q, meta, lw);
-    e = hipGetLastError();
+  if (rt_rows == kSmallRows) {
+    e = p.kv.block_size > 0 ? launch_small<true>(st, grid, q, meta, logits_work, layers ? &table : nullptr)
+                            : launch_small<false>(st, grid, q, meta, logits_work, layers ? &table : nullptr);
   } else if (layers) {
-    const LogitsWork lw = logits_work ? *logits_work : LogitsWork{};
-    if (rt_rows != kSmallRows) return launch_attn_wide_layers(st, q, meta, std::min(M, rt_rows), (int)T, lw, table);
-    if (p.D == 64) hipLaunchKernelGGL((k_model_mfma<64, true>), grid, dim3(512), 0, st, q, meta, lw, table);
-    else if (p.precise) hipLaunchKernelGGL((k_model_mfma<128, true>), grid, dim3(512), 0, st, q, meta, lw, table);
-    else hipLaunchKernelGGL((k_model_mfma<128, false>), grid, dim3(512), 0, st, q, meta, lw, table);
-    return hipGetLastError();
-  } else if (rt_rows != kSmallRows) {
-    e = launch_attn_wide(st, q, meta, std::min(M, rt_rows), (int)T, logits_work);
-  } else if (logits_work) {
-    if (p.D == 64) launch(k_verify_mfma<64, true>, k_verify_mfma<64, false>, q, meta, *logits_work);
-    else if (p.precise) launch(k_verify_precise<true>, k_verify_precise<false>, q, meta, *logits_work);
-    else launch(k_verify_mfma<128, true>, k_verify_mfma<128, false>, q, meta, *logits_work);
-    e = hipGetLastError();
+    e = launch_attn_wide_layers(st, q, meta, std::min(M, rt_rows), (int)T, logits_work ? *logits_work : LogitsWork{}, table);
   } else {
-    if (p.D == 64) launch(k_attn_mfma<64, true>, k_attn_mfma<64, false>, q, meta);
-    else if (p.precise) launch(k_attn_precise<true>, k_attn_precise<false>, q, meta);
-    else launch(k_attn_mfma<128, true>, k_attn_mfma<128, false>, q, meta);
-    e = hipGetLastError();
+    e = launch_attn_wide(st, q, meta, std::min(M, rt_rows), (int)T, logits_work);
   }
   if (e != hipSuccess) return e;
   if (q.external_merge) {
