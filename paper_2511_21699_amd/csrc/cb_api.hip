@@ -205,7 +205,9 @@ bool make_kv_addr(const cb_config& c, const cb_kv_layer& l, KvAddr* a) {
   a->block_table = l.block_table;
   a->max_blocks = l.max_blocks_per_seq;
   a->block_size = c.block_size;
-  a->num_blocks = c.block_size > 0 ? l.capacity_or_num_blocks : 0;
+  // (the kernels compare in 32 bits; a pool of more blocks than a table entry can name is one whose descriptor says so only: K and V of
+  // that many of the smallest are 512 GiB)
+  a->num_blocks = c.block_size > 0 ? std::min<int64_t>(l.capacity_or_num_blocks, INT32_MAX) : 0;
   const int64_t tokens_per_unit = c.block_size > 0 ? c.block_size : l.capacity_or_num_blocks;
   a->seq_stride = tokens_per_unit * H * D;
   if (l.layout == CB_LAYOUT_TOKEN_MAJOR) {
@@ -1143,6 +1145,11 @@ int cb_debug_layers(const cb_config* cfg, int32_t layers, int32_t batch, const i
   const int32_t out[] = {1, p.impl == 2 ? p.tile_rows : 0, p.nsplit, p.chunk, p.precise, p.logits_wgs};
   memcpy(plan, out, sizeof out);
   return CB_OK;
+}
+
+int64_t cb_debug_pool_blocks(const cb_config* cfg, const cb_kv_layer* layer) {
+  KvAddr a{};
+  return make_kv_addr(*cfg, *layer, &a) ? a.num_blocks : -1;
 }
 
 int cb_check_verify_args(const cb_config* cfg, int32_t batch, const cb_kv_layer* kv, const int32_t* kv_len,

@@ -70,7 +70,7 @@ struct KvAddr {
   int64_t seq_stride;    // contiguous: per sequence; paged: per physical block
   int64_t token_stride;
   int64_t head_stride;
-  int64_t num_blocks;    // paged: pool size (block ids are clamped into it)
+  int64_t num_blocks;    // paged: pool size (block ids are clamped into it), below 2^31
   int32_t max_blocks;    // paged: row length of the block table
   int32_t block_size;    // 0 = contiguous
 };
@@ -288,3 +288,5 @@ extern "C" int cb_debug_layers(const cb_config* cfg, int32_t layers, int32_t bat
 // launch, [1] = layers that were attended to together and [2] = the launches that served those; [3] = rows of a tile of the context's last
 // verification (0: not the bf16 MFMA kernels)
 extern "C" int cb_debug_step(cb_ctx* ctx, int32_t info[4]);
+// The pool size that the kernels clamp the block table's entries to (0: contiguous, -1: unknown layout).
+extern "C" int64_t cb_debug_pool_blocks(const cb_config* cfg, const cb_kv_layer* layer);

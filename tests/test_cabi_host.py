@@ -220,3 +220,12 @@ def test_no_alloc_entry_point_splits_less_near_the_scratch_limit(hq, hkv, d, dty
     ip = lambda x: x.ctypes.data_as(C.POINTER(C.c_int32))
     rc = L.cb_tree_attention_noalloc(C.byref(cfg), None, len(lens), 0x10000, C.byref(kv), ip(a), ip(b), 0x30000, 0x20000)
     assert rc == B.CB_EHIP, (rc, L.cb_last_error(None).decode())
+
+
+@pytest.mark.parametrize("blocks", [1, 100, 2 ** 31 - 1, 2 ** 31, 2 ** 31 + 7, 2 ** 32, 2 ** 33 + 5, 2 ** 62])
+def test_pool_sizes_fit_the_32_bits_that_entries_are_compared_in(blocks):
+    lib = B.load()
+    lib.cb_debug_pool_blocks.restype = C.c_int64
+    cfg = B.make_config(8, 8, 128, "bf16", "bf16", 1, 8, 4, 100, 16)
+    kv = B.CbKvLayer(4096, 4096, blocks, 4096, 4, B.CB_LAYOUT_TOKEN_MAJOR)
+    assert lib.cb_debug_pool_blocks(C.byref(cfg), C.byref(kv)) == min(blocks, 2 ** 31 - 1)

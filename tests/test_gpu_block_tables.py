@@ -3,6 +3,7 @@ LDS at a time (1024 entries): the ring of table segments is refilled during the 
 import numpy as np
 import pytest
 
+from paper_2511_21699_amd import binding as B
 from paper_2511_21699_amd import workloads as W
 from tests.gpu_harness import run_case, sample_rows
 
@@ -43,3 +44,24 @@ def test_blocks_that_are_no_power_of_two(D, S, splits, monkeypatch):
     case = W.custom_case(4300 + S, "bf16", 1, 4, 1, D, 500, [S], [par], paged=True, q_scale=2.0)
     case.block_size = 24
     run_case(case, rows=sample_rows(case, 60), options={"splits": splits}, what=f"block 24 D={D} S={S}")
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,n", [("bf16", 4, 4, 128, 20), ("bf16", 8, 2, 128, 100), ("bf16", 4, 4, 64, 30), ("f32", 4, 2, 64, 9)])
+@pytest.mark.parametrize("blocks", [2 ** 31 - 1, 2 ** 31, 2 ** 33 + 3])
+def test_pools_that_are_said_to_be_larger_than_an_entry_can_name(dtype, hq, hkv, d, n, blocks):
+    """The size only bounds entries, so with a valid table the results are those of the true one."""
+    import torch
+    print(f"[case] pool of {blocks} blocks {dtype} {hq}/{hkv} x {d}", flush=True)
+    case = W.custom_case(4400 + n, dtype, 2, hq, hkv, d, 300, [300, 40], [W.random_tree(np.random.default_rng(n + b), n, 3, 7, False)[0] for b in range(2)],
+                         paged=True, p_match=0.9)
+    got = []
+    for size in (None, blocks):
+        dc, ver = B.DeviceCase(case), B.Verifier(B.config_for_case(case))
+        if size:
+            dc.kv.capacity_or_num_blocks = size
+        out, acc_len, acc_tok = ver.verify_tree(dc.q, dc.kv, case.kv_len, case.node_offsets, case.parent, case.tokens, dc.logits)
+        ver.compact_kv([dc.kv], 2)
+        torch.cuda.synchronize()
+        got.append((out.clone(), dc.k, dc.v, torch.from_numpy(acc_len), torch.from_numpy(acc_tok)))
+        ver.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
