@@ -228,14 +228,15 @@ struct Span {
   size_t bytes;
   bool meets(const Span& o) const {
     const uintptr_t a = (uintptr_t)at, b = (uintptr_t)o.at;
-    return bytes != 0 && o.bytes != 0 && a < b + o.bytes && b < a + bytes;
+    return a < b ? b - a < bytes && o.bytes != 0 : a - b < o.bytes && bytes != 0;
   }
 };
-// Bytes of a layer's K (or V) that a call with `batch` sequences can touch.
+// Bytes of a layer's K (or V) that a call with `batch` sequences can touch, by the descriptor (whose capacity may be just a large number: at
+// most half of the address space, from where it begins).
 size_t cache_bytes(const cb_config& c, const cb_kv_layer& l, int batch) {
-  const size_t row = (size_t)c.num_kv_heads * c.head_dim * (c.qkv_dtype == CB_F32 ? 4 : 2);
+  const size_t row = (size_t)c.num_kv_heads * c.head_dim * (c.qkv_dtype == CB_F32 ? 4 : 2), per_unit = row * (c.block_size > 0 ? c.block_size : batch);
   const size_t units = l.capacity_or_num_blocks > 0 ? l.capacity_or_num_blocks : 0;
-  return c.block_size > 0 ? units * c.block_size * row : units * batch * row;
+  return std::min(units, (SIZE_MAX / 2) / per_unit) * per_unit;
 }
 bool same_cache(const cb_kv_layer& a, const cb_kv_layer& b) {
   return a.k == b.k && a.v == b.v && a.capacity_or_num_blocks == b.capacity_or_num_blocks && a.block_table == b.block_table &&
@@ -1062,7 +1063,7 @@ bool layers_together(cb_ctx* ctx, int batch, int n, const void* const* q, const 
   uintptr_t any = 0, written = 0;
   for (const Use& u : uses) {
     if (u.s.bytes == 0) continue;
-    const uintptr_t at = (uintptr_t)u.s.at, end = at + u.s.bytes;
+    const uintptr_t at = (uintptr_t)u.s.at, end = at + std::min<uintptr_t>(u.s.bytes, UINTPTR_MAX - at);
     if (at < (u.written ? any : written)) return false;
     any = std::max(any, end);
     if (u.written) written = std::max(written, end);

@@ -99,6 +99,28 @@ def test_operands_that_overlap_the_cache_take_two_launches():
         ver.close()
 
 
+@pytest.mark.parametrize("layers", [1, 2])
+def test_operands_in_a_cache_of_any_size(layers):
+    """A descriptor's capacity may be just a large number (of one sequence only the length is looked at); 2^53 slots of 2 KiB are 2^64 bytes."""
+    import torch
+    case = W.custom_case(7150, "bf16", 1, 8, 8, 128, 500, [300], [W.random_tree(np.random.default_rng(1), 40, 2, 9, False)[0]], p_match=0.95, extra_capacity=100)
+    for capacity in (None, 2 ** 53):
+        dc = B.DeviceCase(case)
+        dc.kv.capacity_or_num_blocks = capacity or dc.kv.capacity_or_num_blocks
+        q, outs = dc.k[0, 300:340], [dc.k[0, 380:420], torch.zeros_like(dc.q)]   # ([nodes][heads][D], as the queries are)
+        ver = B.Verifier(B.config_for_case(case))
+        par, tok = torch.from_numpy(case.parent).cuda(), torch.from_numpy(case.tokens).cuda()
+        n, t = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, case.max_depth + 1, dtype=torch.int32, device="cuda")
+        if layers == 1:
+            ver.bind_step(q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, outs[1], n, t, [dc.kv])()
+        else:
+            ver.bind_model_step([q, q], [dc.kv, dc.kv], case.kv_len, case.node_offsets, par, tok, dc.logits, outs, n, t)()
+        torch.cuda.synchronize()
+        info = step_info(ver)
+        assert not info["moved"] and not info["layers"], (capacity, info)
+        ver.close()
+
+
 def chain(n):
     """A path of n - 2 nodes below the root, each a slot away from its place: node 1 is a leaf beside it."""
     return [-1, 0, 0] + list(range(2, n - 1))
