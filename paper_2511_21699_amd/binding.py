@@ -371,7 +371,8 @@ class HostStep:
         st = ver._stream(stream)
         self._kv = kv
         self._layers = (CbKvLayer * len(layers))(*layers) if layers else None
-        self._keep = (q, logits, attn_out)
+        # (the call holds addresses: what the attributes are set to later makes no difference to it)
+        self._keep = (q, logits, attn_out, self.kv_len, self.node_offsets, self.parent, self.tokens, self.accepted_len, self.accepted_tokens)
         self._verify_args = (ver.ctx, st, batch, q.data_ptr(), C.byref(self._kv), _ip(self.kv_len), _ip(self.node_offsets),
                              _ip(self.parent), _ip(self.tokens), logits.data_ptr(), attn_out.data_ptr(),
                              _ip(self.accepted_len), _ip(self.accepted_tokens))
@@ -466,7 +467,8 @@ class TreeGrower:
         self.parent = np.empty(node_budget, dtype=np.int32)
         self.token = np.empty(node_budget, dtype=np.int32)
         self.depth = np.empty(node_budget, dtype=np.int32)
-        self._out = (_ip(self.parent), _ip(self.token), _ip(self.depth))
+        self._keep = (self.parent, self.token, self.depth)  # (the call holds their addresses)
+        self._out = tuple(_ip(a) for a in self._keep)
         self._n = C.c_int32(0)
         self._nref = C.byref(self._n)
         self._ctx_arr, self._ctx_ptr = None, None

@@ -229,3 +229,23 @@ def test_pool_sizes_fit_the_32_bits_that_entries_are_compared_in(blocks):
     cfg = B.make_config(8, 8, 128, "bf16", "bf16", 1, 8, 4, 100, 16)
     kv = B.CbKvLayer(4096, 4096, blocks, 4096, 4, B.CB_LAYOUT_TOKEN_MAJOR)
     assert lib.cb_debug_pool_blocks(C.byref(cfg), C.byref(kv)) == min(blocks, 2 ** 31 - 1)
+
+
+def test_bound_calls_keep_their_arrays():
+    """A bound call goes to its own arrays for as long as it lives, whatever its attributes are set to."""
+    import gc
+    import types
+    import weakref
+    t = types.SimpleNamespace(data_ptr=lambda: 4096)
+    cfg = B.make_config(8, 8, 128, "bf16", "bf16", 2, 8, 4, 100, 0)
+    ver = types.SimpleNamespace(cfg=cfg, stride=5, ctx=None, L=B.load(), _stream=lambda s: None)
+    step = B.HostStep(ver, t, B.CbKvLayer(), t, t, 2, [], None)
+    table = B.DraftTable(1, 3, 64, 4)
+    grower = B.TreeGrower([table], 8, 4)
+    for obj, names in ((step, ("kv_len", "node_offsets", "parent", "tokens", "accepted_len", "accepted_tokens")), (grower, ("parent", "token", "depth"))):
+        for name in names:
+            held = weakref.ref(getattr(obj, name))
+            setattr(obj, name, np.zeros(8, dtype=np.int32))
+            gc.collect()
+            assert held() is not None, name
+    table.close()
