@@ -48,18 +48,37 @@ class CbError(RuntimeError):
         self.code = code
 
 
-_lib = None
+_lib = _lib_by_address = None
+
+
+class _Int32s:
+    """An argument of int32 values: an address (_ip), or whatever ctypes takes for a pointer to them."""
+    _pointer = C.POINTER(C.c_int32)
+
+    @classmethod
+    def from_param(cls, x):
+        return C.c_void_p(x) if isinstance(x, int) else cls._pointer.from_param(x)
 
 
 def load():
     """dlopen the HIP library; raises if it is missing (no fallback of any kind)."""
     global _lib
-    if _lib is not None:
-        return _lib
+    _lib = _lib or _prototyped(_Int32s)
+    return _lib
+
+
+def _by_address():
+    """The same with plain addresses for int32 arrays, whose element type nobody checks: for this module's own calls."""
+    global _lib_by_address
+    _lib_by_address = _lib_by_address or _prototyped(C.c_void_p)
+    return _lib_by_address
+
+
+def _prototyped(i32p):
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is not built; run `python -m paper_2511_21699_amd.build` (needs hipcc)")
     L = C.CDLL(LIB_PATH)
-    vp = i32p = C.c_void_p  # (int32 arrays go by address: _ip)
+    vp = C.c_void_p
     L.cb_workspace_bytes.argtypes = [C.POINTER(CbConfig), C.POINTER(C.c_size_t)]
     L.cb_init.argtypes = [C.POINTER(CbConfig), vp, C.c_size_t, C.POINTER(vp)]
     L.cb_check_verify_args.argtypes = [C.POINTER(CbConfig), C.c_int32, C.POINTER(CbKvLayer), i32p, i32p, i32p,
@@ -98,7 +117,6 @@ def load():
     for name in EXPORTS:
         if name not in ("cb_last_error", "cb_destroy"):
             getattr(L, name).restype = C.c_int
-    _lib = L
     return L
 
 
@@ -137,7 +155,7 @@ def kv_layer(k, v, block_table=None, layout: int = CB_LAYOUT_TOKEN_MAJOR, paged:
 
 def check_verify_args(cfg: CbConfig, batch: int, kv: CbKvLayer, kv_len, node_offsets, parent) -> Tuple[int, str]:
     """Host-only argument check (no GPU needed)."""
-    L = load()
+    L = _by_address()
     buf = C.create_string_buffer(256)
     a, b, c = _i32(kv_len), _i32(node_offsets), _i32(parent)
     rc = L.cb_check_verify_args(C.byref(cfg), batch, C.byref(kv), _ip(a), _ip(b), _ip(c), buf, 256)
@@ -148,7 +166,7 @@ def plan_attention(cfg: CbConfig, kv_len, node_offsets, forced_splits: int = 0) 
     """Host-only: the attention stage's split plan for these lengths (no GPU needed)."""
     a, b = _i32(kv_len), _i32(node_offsets)
     out = (C.c_int32 * 5)()
-    rc = load().cb_plan_attention(C.byref(cfg), len(a), _ip(a), _ip(b), forced_splits, out)
+    rc = _by_address().cb_plan_attention(C.byref(cfg), len(a), _ip(a), _ip(b), forced_splits, out)
     if rc:
         raise CbError(rc, "cb_plan_attention rejected the shape")
     return dict(impl=out[0], nsplit=out[1], chunk=out[2], tile_rows=out[3], workgroups=out[4])
@@ -169,7 +187,7 @@ def tree_attention_noalloc(cfg: CbConfig, q, kv: CbKvLayer, kv_len, node_offsets
     import torch
     st = stream if stream is not None else torch.cuda.current_stream()
     kv_len, node_offsets = _i32(kv_len), _i32(node_offsets)
-    L = load()
+    L = _by_address()
     rc = L.cb_tree_attention_noalloc(C.byref(cfg), C.c_void_p(st.cuda_stream), kv_len.shape[0], q.data_ptr(), C.byref(kv),
                                      _ip(kv_len), _ip(node_offsets), d_parent.data_ptr(), attn_out.data_ptr())
     if rc:
@@ -190,7 +208,7 @@ class Verifier:
     def __init__(self, cfg: CbConfig, device: str = "cuda:0"):
         import torch
         self._torch = torch
-        self.L = load()
+        self.L, self._F = load(), _by_address()
         self.cfg = cfg
         self.device = torch.device(device)
         torch.cuda.set_device(self.device)
@@ -237,7 +255,7 @@ class Verifier:
             attn_out = self._torch.empty_like(q)
         acc_len = np.zeros(batch, dtype=np.int32)
         acc_tok = np.zeros((batch, self.stride), dtype=np.int32)
-        rc = self.L.cb_verify_tree(self.ctx, self._stream(stream), batch, q.data_ptr(), C.byref(kv), _ip(kv_len),
+        rc = self._F.cb_verify_tree(self.ctx, self._stream(stream), batch, q.data_ptr(), C.byref(kv), _ip(kv_len),
                                    _ip(node_offsets), _ip(parent), _ip(tokens), logits.data_ptr(),
                                    attn_out.data_ptr(), _ip(acc_len), _ip(acc_tok))
         self._raise(rc)
@@ -247,7 +265,7 @@ class Verifier:
                            d_acc_len, d_acc_tok, stream=None):
         """Device-resident form: enqueues launches only."""
         kv_len, node_offsets = _i32(kv_len), _i32(node_offsets)
-        rc = self.L.cb_verify_tree_device(self.ctx, self._stream(stream), kv_len.shape[0], q.data_ptr(), C.byref(kv),
+        rc = self._F.cb_verify_tree_device(self.ctx, self._stream(stream), kv_len.shape[0], q.data_ptr(), C.byref(kv),
                                           _ip(kv_len), _ip(node_offsets), d_parent.data_ptr(), d_tokens.data_ptr(),
                                           logits.data_ptr(), attn_out.data_ptr(), d_acc_len.data_ptr(),
                                           d_acc_tok.data_ptr())
@@ -256,7 +274,7 @@ class Verifier:
     def tree_attention_device(self, q, kv: CbKvLayer, kv_len, node_offsets, d_parent, attn_out, stream=None):
         """Tree attention alone (a model's layers below the last): enqueues launches only."""
         kv_len, node_offsets = _i32(kv_len), _i32(node_offsets)
-        rc = self.L.cb_tree_attention_device(self.ctx, self._stream(stream), kv_len.shape[0], q.data_ptr(), C.byref(kv),
+        rc = self._F.cb_tree_attention_device(self.ctx, self._stream(stream), kv_len.shape[0], q.data_ptr(), C.byref(kv),
                                              _ip(kv_len), _ip(node_offsets), d_parent.data_ptr(), attn_out.data_ptr())
         self._raise(rc)
 
@@ -273,7 +291,7 @@ class Verifier:
         a = (self.ctx, st, kv_len.shape[0], nl, ptrs(qs), arr, _ip(kv_len), _ip(node_offsets), d_parent.data_ptr(),
              d_tokens.data_ptr(), logits.data_ptr(), ptrs(attn_outs), d_acc_len.data_ptr(), d_acc_tok.data_ptr())
         keep = (kv_len, node_offsets, arr, qs, kvs, logits, attn_outs)
-        step = self.L.cb_model_step_device
+        step = self._F.cb_model_step_device
 
         def call(_keep=keep):
             rc = step(*a)
@@ -292,7 +310,7 @@ class Verifier:
              d_parent.data_ptr(), d_tokens.data_ptr(), logits.data_ptr(), attn_out.data_ptr(), d_acc_len.data_ptr(),
              d_acc_tok.data_ptr(), len(layers), arr)
         keep = (kv_len, node_offsets, arr, kv, q, logits, attn_out)
-        step = self.L.cb_verify_and_compact_device
+        step = self._F.cb_verify_and_compact_device
 
         def call(_keep=keep):
             rc = step(*a)
@@ -311,18 +329,18 @@ class Verifier:
     def compact_kv(self, layers: Sequence[CbKvLayer], batch: int, want_len: bool = True, stream=None):
         arr = C.byref(layers[0]) if len(layers) == 1 else (CbKvLayer * len(layers))(*layers)
         new_len = np.zeros(batch, dtype=np.int32)
-        rc = self.L.cb_compact_kv(self.ctx, self._stream(stream), len(layers), arr, _ip(new_len) if want_len else None)
+        rc = self._F.cb_compact_kv(self.ctx, self._stream(stream), len(layers), arr, _ip(new_len) if want_len else None)
         self._raise(rc)
         return new_len if want_len else None
 
     def get_path(self, batch: int) -> np.ndarray:
         out = np.zeros((batch, self.stride), dtype=np.int32)
-        self._raise(self.L.cb_get_path(self.ctx, _ip(out)))
+        self._raise(self._F.cb_get_path(self.ctx, _ip(out)))
         return out
 
     def get_argmax(self, total_nodes: int) -> np.ndarray:
         out = np.zeros(total_nodes, dtype=np.int32)
-        self._raise(self.L.cb_get_argmax(self.ctx, _ip(out)))
+        self._raise(self._F.cb_get_argmax(self.ctx, _ip(out)))
         return out
 
     def device_status(self) -> int:
@@ -377,7 +395,7 @@ class HostStep:
                              _ip(self.parent), _ip(self.tokens), logits.data_ptr(), attn_out.data_ptr(),
                              _ip(self.accepted_len), _ip(self.accepted_tokens))
         self._compact_args = (ver.ctx, st, len(layers), self._layers, None)
-        self._verify_fn, self._compact_fn = ver.L.cb_verify_tree, ver.L.cb_compact_kv
+        self._verify_fn, self._compact_fn = ver._F.cb_verify_tree, ver._F.cb_compact_kv
 
     def verify(self):
         rc = self._verify_fn(*self._verify_args)
@@ -396,14 +414,14 @@ class DraftTable:
 
     def __init__(self, ll: int, fl: int, lc: int, fc: int, frozen_from=None):
         """An empty table, or (``frozen_from`` = token sample) the frozen table built from a corpus sample."""
-        self.L = load()
+        self.L, self._F = load(), _by_address()
         self.ll, self.fl, self.lc, self.fc = ll, fl, lc, fc
         h = C.c_void_p()
         if frozen_from is None:
             rc = self.L.cbd_table_create(ll, fl, lc, fc, C.byref(h))
         else:
             a = _i32(frozen_from)
-            rc = self.L.cbd_table_build_frozen(ll, fl, lc, fc, _ip(a), len(a), C.byref(h))
+            rc = self._F.cbd_table_build_frozen(ll, fl, lc, fc, _ip(a), len(a), C.byref(h))
         if rc:
             raise CbError(rc, "cbd_table_create")
         self.h = h
@@ -424,13 +442,13 @@ class DraftTable:
         a, b = _i32(leader), _i32(follower)
         if len(a) != self.ll or len(b) != self.fl:
             raise ValueError("leader/follower length mismatch")
-        rc = self.L.cbd_table_insert(self.h, _ip(a), _ip(b))
+        rc = self._F.cbd_table_insert(self.h, _ip(a), _ip(b))
         if rc:
             raise CbError(rc, "cbd_table_insert")
 
     def update(self, tokens, start: int = 0):
         a = _i32(tokens)
-        rc = self.L.cbd_table_update(self.h, _ip(a), len(a), start)
+        rc = self._F.cbd_table_update(self.h, _ip(a), len(a), start)
         if rc:
             raise CbError(rc, "cbd_table_update")
 
@@ -439,7 +457,7 @@ class DraftTable:
         if len(a) != self.ll:
             raise ValueError("leader length mismatch")
         n = C.c_int32(0)
-        rc = self.L.cbd_table_query(self.h, _ip(a), 1 if refresh else 0, self._fol, C.byref(n))
+        rc = self._F.cbd_table_query(self.h, _ip(a), 1 if refresh else 0, self._fol, C.byref(n))
         if rc:
             raise CbError(rc, "cbd_table_query")
         return [tuple(self._fol[i * self.fl:(i + 1) * self.fl]) for i in range(n.value)]
@@ -459,7 +477,7 @@ class TreeGrower:
     returns views of its own buffers (valid until the next call)."""
 
     def __init__(self, tables, node_budget: int, depth_cap: int, crt: int = 0):
-        self._fn = load().cbd_grow_tree
+        self._fn = _by_address().cbd_grow_tree
         self._tables = list(tables)
         self._hs = (C.c_void_p * len(tables))(*[t.h for t in tables])
         self._args = (len(tables),)
@@ -488,7 +506,7 @@ class TreeGrower:
 
 def grow_tree(context, tables, node_budget: int, depth_cap: int, crt: int = 0):
     """Native tree growth; returns int32 arrays (parent, token, depth)."""
-    L = load()
+    L = _by_address()
     ctx = _i32(context)
     hs = (C.c_void_p * len(tables))(*[t.h for t in tables])
     par = np.empty(node_budget, dtype=np.int32)

@@ -238,7 +238,7 @@ def test_bound_calls_keep_their_arrays():
     import weakref
     t = types.SimpleNamespace(data_ptr=lambda: 4096)
     cfg = B.make_config(8, 8, 128, "bf16", "bf16", 2, 8, 4, 100, 0)
-    ver = types.SimpleNamespace(cfg=cfg, stride=5, ctx=None, L=B.load(), _stream=lambda s: None)
+    ver = types.SimpleNamespace(cfg=cfg, stride=5, ctx=None, _F=B._by_address(), _stream=lambda s: None)
     step = B.HostStep(ver, t, B.CbKvLayer(), t, t, 2, [], None)
     table = B.DraftTable(1, 3, 64, 4)
     grower = B.TreeGrower([table], 8, 4)
@@ -249,3 +249,15 @@ def test_bound_calls_keep_their_arrays():
             gc.collect()
             assert held() is not None, name
     table.close()
+
+
+def test_callers_of_the_library_have_their_arrays_types_checked():
+    lib = B.load()
+    cfg = B.make_config(8, 8, 128, "bf16", "bf16", 1, 8, 4, 100, 0)
+    ok, lens, offs = (C.c_int32 * 5)(), (C.c_int32 * 1)(100), (C.c_int32 * 2)(0, 4)
+    assert lib.cb_plan_attention(C.byref(cfg), 1, lens, offs, 0, ok) == 0
+    a, b = np.array([100], dtype=np.int32), np.array([0, 4], dtype=np.int32)
+    assert lib.cb_plan_attention(C.byref(cfg), 1, B._ip(a), B._ip(b), 0, ok) == 0
+    for wrong in ((C.c_int64 * 1)(100), (C.c_float * 1)(100), C.c_void_p(4096)):
+        with pytest.raises(C.ArgumentError):
+            lib.cb_plan_attention(C.byref(cfg), 1, wrong, offs, 0, ok)
