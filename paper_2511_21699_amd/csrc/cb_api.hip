@@ -1281,9 +1281,10 @@ int cb_verify_and_compact_device(cb_ctx* ctx, void* hip_stream, int32_t batch, c
                                  const int32_t* d_draft_tokens, const void* logits, void* attn_out,
                                  int32_t* d_accepted_len, int32_t* d_accepted_tokens, int32_t num_layers, const cb_kv_layer* layers) {
   // One launch where the cache that is verified is the one that is compacted and its memory is nobody else's: the launch moves rows
-  // while other workgroups still read their own inputs and write their results.
+  // while other workgroups still read their own inputs and write their results.  (Nor another sequence's: the tables of a paged batch may share
+  // blocks, with one sequence's tree in what another attends to -- a row that is there twice to fill a captured batch up, say.)
   bool apart = false;
-  if (ctx && kv && num_layers == 1 && layers && batch >= 1 && batch <= ctx->cfg.max_batch && node_offsets && same_cache(*kv, layers[0]) && ((((uintptr_t)kv->k | (uintptr_t)kv->v) & 15) == 0)) {
+  if (ctx && kv && num_layers == 1 && (ctx->cfg.block_size == 0 || batch == 1) && layers && batch >= 1 && batch <= ctx->cfg.max_batch && node_offsets && same_cache(*kv, layers[0]) && ((((uintptr_t)kv->k | (uintptr_t)kv->v) & 15) == 0)) {
     const cb_config& c = ctx->cfg;
     const size_t rows = node_offsets[batch] > 0 ? node_offsets[batch] : 0, qo = rows * c.num_q_heads * c.head_dim * (c.qkv_dtype == CB_F32 ? 4 : 2);
     const size_t cache = cache_bytes(c, *kv, batch);

@@ -66,7 +66,7 @@ def test_one_call_against_two(i, layout):
             if fused:
                 step()
                 info = step_info(ver)
-                assert info["moved"] == (not TWO_LAUNCHES & set(options)) and info["tile_rows"] == options.get("tile_rows", info["tile_rows"])
+                assert info["moved"] == (not TWO_LAUNCHES & set(options) and (len(lens) == 1 or not paged)) and info["tile_rows"] == options.get("tile_rows", info["tile_rows"])
             else:
                 ver.verify_tree_device(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, out, n, t)
                 ver.compact_kv([dc.kv], len(lens), want_len=False)
@@ -121,6 +121,35 @@ def test_operands_in_a_cache_of_any_size(layers):
         ver.close()
 
 
+def test_a_sequence_that_is_in_a_paged_batch_twice():
+    """Rows of the block table that share the blocks with the tree: no row moves while the other sequence reads it."""
+    import torch
+    tree, n = [-1, 0, 0] + [1] * 37, 40                                      # accepted: 0, 2
+    case = W.custom_case(7160, "bf16", 2, 8, 8, 128, 500, [300, 300], [tree, tree], paged=True, p_match=0.0)
+    case.block_table[1] = case.block_table[0]
+    for x in (case.q, case.logits):
+        x[n:] = x[:n]
+    arg = np.argmax(W.to_f64(case.logits, case.dtype), axis=1)
+    case.tokens = np.asarray([(arg[p] + 1) % 500 for p in case.parent], dtype=np.int32)
+    case.tokens[2] = case.tokens[n + 2] = arg[0]
+    got = []
+    for fused in (True, False):
+        dc, ver = B.DeviceCase(case), B.Verifier(B.config_for_case(case))
+        par, tok, out = torch.from_numpy(case.parent).cuda(), torch.from_numpy(case.tokens).cuda(), torch.zeros_like(dc.q)
+        m, t = torch.zeros(2, dtype=torch.int32, device="cuda"), torch.zeros(2, case.max_depth + 1, dtype=torch.int32, device="cuda")
+        if fused:
+            ver.bind_step(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, out, m, t, [dc.kv])()
+            assert not step_info(ver)["moved"]
+        else:
+            ver.verify_tree_device(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, out, m, t)
+            ver.compact_kv([dc.kv], 2, want_len=False)
+        torch.cuda.synchronize()
+        assert m.tolist() == [1, 1] and torch.equal(out[:n], out[n:])
+        got.append((out, dc.k, dc.v, t))
+        ver.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 def chain(n):
     """A path of n - 2 nodes below the root, each a slot away from its place: node 1 is a leaf beside it."""
     return [-1, 0, 0] + list(range(2, n - 1))
@@ -143,7 +172,7 @@ def test_paths_longer_than_a_wave(dtype, hq, hkv, d, sizes, paged):
     n, t = torch.zeros(case.B, dtype=torch.int32, device="cuda"), torch.zeros(case.B, case.max_depth + 1, dtype=torch.int32, device="cuda")
     ver.bind_step(dc.q, dc.kv, case.kv_len, case.node_offsets, par, tok, dc.logits, torch.zeros_like(dc.q), n, t, [dc.kv])()
     torch.cuda.synchronize()
-    assert step_info(ver)["moved"]
+    assert step_info(ver)["moved"] == (not paged or case.B == 1)
     k, v = case.k.copy(), case.v.copy()
     for b, (L, path, _) in enumerate(res):
         assert int(n[b]) == L == sizes[b] - 2
