@@ -1023,7 +1023,7 @@ bool layers_together(cb_ctx* ctx, int batch, int n, const void* const* q, const 
                      const int32_t* d_parent, const int32_t* d_tokens, const void* logits, void* const* attn_out, const int32_t* d_len, const int32_t* d_tok) {
   const cb_config& c = ctx->cfg;
   if (ctx->opt_splits > 0 || ctx->opt_impl || ctx->opt_time || ctx->opt_stages != 15 || ctx->opt_timeline || ctx->opt_external || ctx->opt_fork ||
-      !ctx->opt_fuse || !ctx->opt_coop || ctx->opt_logits_wgs > 0)
+      !ctx->opt_fuse || !ctx->opt_coop || ctx->opt_logits_wgs > 0 || ctx->opt_tile_rows)
     return false;
   if (!kv_len || !node_offsets || !d_parent || !d_tokens || !logits || !d_len || !d_tok || batch < 1 || batch > c.max_batch || ((uintptr_t)logits & 15)) return false;
   const cb_kv_layer& first = layers[0];

@@ -96,12 +96,12 @@ def test_layers_in_one_launch(i):
     ver.close()
 
 
-@pytest.mark.parametrize("kind", ["chained", "one output", "splits"])
+@pytest.mark.parametrize("kind", ["chained", "one output", "splits", "tile rows"])
 def test_layers_that_go_one_by_one(kind):
     """A layer's result as the next one's queries, or all in one place: the layers follow each other; options too."""
     import torch
     rng = np.random.default_rng(3)
-    case = W.custom_case(8100, "bf16", 1, 8, 8, 128, 500, [300], [W.random_tree(rng, 40, 2, 9, False)[0]], p_match=0.95)
+    case = W.custom_case(8100, "bf16", 1, 8 if kind != "tile rows" else 32, 8, 128, 500, [300], [W.random_tree(rng, 40, 2, 9, False)[0]], p_match=0.95)
     got = []
     for together in (True, False):
         _, dcs, kvs, par, tok, n, t = step_of(case, 3, 0)
@@ -112,8 +112,10 @@ def test_layers_that_go_one_by_one(kind):
             qs = [qs[0], outs[0], outs[1]]
         elif kind == "one output":
             outs = [outs[0]] * 3
-        else:
+        elif kind == "splits":
             ver.set_option("splits", 3)
+        else:
+            ver.set_option("tile_rows", 128)
         if together:
             ver.bind_model_step(qs, kvs, case.kv_len, case.node_offsets, par, tok, dcs[-1].logits, outs, n, t)()
         else:
@@ -122,7 +124,7 @@ def test_layers_that_go_one_by_one(kind):
             ver.verify_tree_device(qs[2], kvs[2], case.kv_len, case.node_offsets, par, tok, dcs[-1].logits, outs[2], n, t)
             ver.compact_kv(kvs, 1, want_len=False)
         torch.cuda.synchronize()
-        assert step_info(ver)["layers"] == 0
+        assert step_info(ver)["layers"] == 0 and step_info(ver)["tile_rows"] == (64 if kind != "tile rows" else 128)
         got.append([x.clone() for x in outs] + [dc.k.clone() for dc in dcs] + [n.clone(), t.clone()])
         ver.close()
     assert all(torch.equal(a, b) for a, b in zip(*got))
