@@ -111,8 +111,9 @@ int cb_init(const cb_config *cfg, void *workspace, size_t workspace_bytes, cb_ct
  * configuration's max_splits), like the "splits" option.  The plan is that of the attention on its own
  * (cb_tree_attention_device, _noalloc): a verification whose logits work is done by workgroups of the same
  * launch plans its attention for the compute units these leave, often with a split fewer, and
- * cb_last_launch_info reports it.  The tiles are the tallest ones: short calls are launched in shorter tiles and fewer
- * splits of each.  All arrays are host memory.  CB_EINVAL on a bad configuration or shape. */
+ * cb_last_launch_info reports it.  The tiles are the tallest ones that a kv head's rows go into, whose plan decides
+ * what is held in 32 bits: calls whose launch they would leave short are launched in tiles of 128 or 64 rows instead, in
+ * splits of their own, fewer or more.  All arrays are host memory.  CB_EINVAL on a bad configuration or shape. */
 int cb_plan_attention(const cb_config *cfg, int32_t batch, const int32_t *kv_len,
                       const int32_t *node_offsets, int32_t forced_splits, int32_t plan[5]);
 
@@ -184,10 +185,11 @@ int cb_verify_and_compact_device(cb_ctx *ctx, void *hip_stream, int32_t batch, c
 
 /*
  * One step of a model of `num_layers` layers whose queries are all there: cb_tree_attention_device for every layer below the last,
- * cb_verify_tree_device for the last one and cb_compact_kv of all of them with new_kv_len = NULL, as one call with the same results, states
- * and errors.  q, layers and attn_out are host arrays of one entry per layer.  Layers that share one geometry and block
- * table are attended to together in as few launches as possible; where a layer's attn_out overlaps memory that another layer or the
- * acceptance reads or writes, they are launched one by one, in order.
+ * cb_verify_tree_device for the last one and cb_compact_kv of all of them with new_kv_len = NULL, as one call with the same acceptance,
+ * cache contents, states and errors, and the same attention up to the rounding of other tiles and splits.  q, layers and attn_out are host
+ * arrays of one entry per layer.  Layers that share one geometry and block table are attended to together in as few launches as possible;
+ * where a layer's attn_out overlaps memory that another layer or the acceptance reads or writes -- as in a forward pass, whose layers'
+ * queries come from the layers below -- they are launched one by one, in order.
  */
 int cb_model_step_device(cb_ctx *ctx, void *hip_stream, int32_t batch, int32_t num_layers, const void *const *q,
                          const cb_kv_layer *layers, const int32_t *kv_len, const int32_t *node_offsets,
@@ -269,7 +271,8 @@ int cb_device_status(cb_ctx *ctx, int32_t *status);
  *   "logits_wgs"     workgroups of that launch for the logits work (a multiple of 8 up to 192;
  *                    0 = automatic)
  *   "tile_rows"      query rows of a workgroup of the bf16 MFMA kernels: 64, 128 or 256 where a kv head has as many, in
- *                    one round of workgroups (0 = automatic)
+ *                    one round of workgroups and the sums stay in the class that the tallest tiles give them; not with
+ *                    "splits" (0 = automatic)
  *   "coop_merge"     0 = never merge the splits cooperatively (default 1: a grid that fits the
  *                    machine in one round has every workgroup of a tile merge a slice of it; otherwise,
  *                    and with 0, the last workgroup of a tile to finish merges it, or a merge kernel)
