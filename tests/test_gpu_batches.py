@@ -5,6 +5,7 @@ import pytest
 
 from paper_2511_21699_amd import workloads as W
 from tests.gpu_harness import run_case, sample_rows
+from tests.test_gpu_short_tiles import plans
 
 pytestmark = pytest.mark.gpu
 
@@ -19,3 +20,20 @@ def test_every_tile_of_a_batch(hkv, g, sizes, lens, splits):
     pars = [W.random_tree(rng, n, 4, 7, False)[0] for n in sizes]
     case = W.custom_case(6000 + hkv + g, "bf16", len(sizes), hkv * g, hkv, 128, 400, lens, pars, q_scale=2.0)
     run_case(case, rows=sample_rows(case, 150), options={"splits": splits}, what=f"{hkv} x {g} heads {sizes} splits={splits}")
+
+
+# Jobs that fill the chip behind the logits' workgroups instead of beside them (planned so by the host: asserted), some in two splits.
+BEHIND = [(32, 2, [106, 17, 391, 595, 712], [16, 15, 28, 19, 26], 300), (32, 1, [818, 301, 475, 527, 18], [23, 45, 37, 27, 23], 300),
+          (40, 2, [97, 511, 34, 1006], [30, 23, 15, 11], 32000)]
+
+
+@pytest.mark.parametrize("hkv,g,lens,sizes,vocab", BEHIND)
+@pytest.mark.parametrize("paged", [False, True])
+def test_batches_whose_jobs_are_behind_the_logits(hkv, g, lens, sizes, vocab, paged):
+    tall, p = plans(hkv * g, hkv, lens, sizes, 16 if paged else 0, True, vocab=vocab)
+    assert p[4] > 0 and 256 - p[4] < p[5] <= 256 and p[1] > 1, p
+    rng = np.random.default_rng(len(sizes) + hkv)
+    pars = [W.random_tree(rng, n, 4, 7, False)[0] for n in sizes]
+    case = W.custom_case(6100 + hkv + g, "bf16", len(sizes), hkv * g, hkv, 128, vocab, lens, pars, paged=paged, q_scale=2.0, p_match=0.9)
+    got = run_case(case, rows=sample_rows(case, 150), what=f"behind the logits {hkv} x {g} heads {sizes} paged={paged}")
+    assert got["info"]["fused"] and got["info"]["nsplit"] == p[1] and got["info"]["chunk"] == p[2]
