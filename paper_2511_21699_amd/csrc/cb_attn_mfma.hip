@@ -139,10 +139,10 @@ __device__ __forceinline__ void compute_unit(const uint4* __restrict__ ks, const
 }
 
 // One attention workgroup; `wg` is its number among those that do attention.  MOVE: the launch compacts its cache.
-template <int D, bool PX, bool PG, bool MOVE, bool TS, typename Layers>
+template <int D, bool PX, bool LEAN, bool MOVE, bool TS, typename Layers>
 __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMetaLanes& ml, int wg, unsigned long long ts0,
                                           TileLds& sh, uint4* ring, unsigned long long* ts_sh, const Layers& layers) {
-  using F = Feed<D, 8, 16, !PG>;
+  using F = Feed<D, 8, 16, LEAN>;
   constexpr int NS = F::kSlots, PRO = F::kPrologue, P = PartialLayout<D, 16, PX>::P;
   AttnParams p = p_arg;
   pin_args(p);
@@ -247,25 +247,25 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p_arg, const SeqMeta
   split_merge<D, 16, PX, 8, kSmallRows, TS>(p, jb, kSmallRows, sh, ts, finish_move);
 }
 
-template <int D, bool PX, bool PG, bool TS>
+template <int D, bool PX, bool LEAN, bool TS>
 __device__ __forceinline__ void attn_workgroup(const AttnParams& p, const SeqMeta& meta) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  __shared__ uint4 ring[Feed<D, 8, 16, !PG>::kRingVecs];
+  __shared__ uint4 ring[Feed<D, 8, 16, LEAN>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
-  attn_tile<D, PX, PG, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh, OneLayer{});
+  attn_tile<D, PX, LEAN, false, TS>(p, ml, blockIdx.x, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, blockIdx.x, ts_sh);
 }
 
 // The whole verification in one launch: the first lw.n_wgs workgroups do the logits work (they are dispatched
 // first, so the acceptance is through long before the attention is, and a waiting host has its results then),
 // the others the attention.  Neither waits for the other.
-template <int D, bool PX, bool PG, bool MOVE, bool TS>
+template <int D, bool PX, bool LEAN, bool MOVE, bool TS>
 __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqMeta& meta, const LogitsWork& lw) {
   const unsigned long long ts0 = TS ? wall_clock64() : 0ull;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  __shared__ uint4 ring[Feed<D, 8, 16, !PG>::kRingVecs];
+  __shared__ uint4 ring[Feed<D, 8, 16, LEAN>::kRingVecs];
   __shared__ TileLds sh;
   __shared__ unsigned long long ts_sh[TS ? 16 : 1];
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
@@ -274,62 +274,62 @@ __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqM
     logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<MOVE, row_pieces(D, 2), 1, 2>());
     return;
   }
-  attn_tile<D, PX, PG, MOVE, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});
+  attn_tile<D, PX, LEAN, MOVE, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});
   flush_timestamps<TS>(p, wg, ts_sh);
 }
 
 // The attention of several layers in one launch, with the logits work (of the last one) in its first workgroups where lw.n_wgs is not 0.
-template <int D, bool PX, bool PG>
+template <int D, bool PX, bool LEAN>
 __global__ __launch_bounds__(512) void k_model_mfma(AttnParams p, SeqMeta meta, LogitsWork lw, LayerTable layers) {
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
-  __shared__ uint4 ring[Feed<D, 8, 16, !PG>::kRingVecs];
+  __shared__ uint4 ring[Feed<D, 8, 16, LEAN>::kRingVecs];
   __shared__ TileLds sh;
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring));
-  else attn_tile<D, PX, PG, false, false>(p, ml, wg, 0ull, sh, ring, nullptr, layers);
+  else attn_tile<D, PX, LEAN, false, false>(p, ml, wg, 0ull, sh, ring, nullptr, layers);
 }
 
 // head_dim 64 always holds probabilities and partial sums in 32 bits, head_dim 128 in the precise builds.
 template <int D, bool TS>
 __global__ __launch_bounds__(512) void k_attn_mfma(AttnParams p, SeqMeta meta) { attn_workgroup<D, D == 64, false, TS>(p, meta); }
 template <int D, bool TS>
-__global__ __launch_bounds__(512) void k_attn_paged(AttnParams p, SeqMeta meta) { attn_workgroup<D, D == 64, true, TS>(p, meta); }
-template <bool PG, bool TS>
-__global__ __launch_bounds__(512) void k_attn_precise(AttnParams p, SeqMeta meta) { attn_workgroup<128, true, PG, TS>(p, meta); }
+__global__ __launch_bounds__(512) void k_attn_lean(AttnParams p, SeqMeta meta) { attn_workgroup<D, D == 64, true, TS>(p, meta); }
+template <bool LEAN, bool TS>
+__global__ __launch_bounds__(512) void k_attn_precise(AttnParams p, SeqMeta meta) { attn_workgroup<128, true, LEAN, TS>(p, meta); }
 template <int D, bool TS>
 __global__ __launch_bounds__(512) void k_verify_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, false, false, TS>(p, meta, lw); }
 template <int D, bool TS>
-__global__ __launch_bounds__(512) void k_verify_paged(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, true, false, TS>(p, meta, lw); }
-template <bool PG, bool TS>
-__global__ __launch_bounds__(512) void k_verify_precise(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<128, true, PG, false, TS>(p, meta, lw); }
+__global__ __launch_bounds__(512) void k_verify_lean(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, D == 64, true, false, TS>(p, meta, lw); }
+template <bool LEAN, bool TS>
+__global__ __launch_bounds__(512) void k_verify_precise(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<128, true, LEAN, false, TS>(p, meta, lw); }
 // with the compaction (builds of their own: what follows the sweep takes scalar registers from it)
-template <int D, bool PX, bool PG>
-__global__ __launch_bounds__(512) void k_step_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, PX, PG, true, false>(p, meta, lw); }
+template <int D, bool PX, bool LEAN>
+__global__ __launch_bounds__(512) void k_step_mfma(AttnParams p, SeqMeta meta, LogitsWork lw) { verify_workgroup<D, PX, LEAN, true, false>(p, meta, lw); }
 
 // Launches for tiles of up to 64 rows.  (Steps and launches for several layers have no timeline build; their lw.n_wgs is 0 where the logits
 // work has a launch of its own.)
-template <bool PG>
+template <bool LEAN>
 static hipError_t launch_small(hipStream_t st, dim3 grid, const AttnParams& p, const SeqMeta& meta, const LogitsWork* logits_work, const LayerTable* layers) {
   const LogitsWork lw = logits_work ? *logits_work : LogitsWork{};
   auto launch = [&](auto* kernel, auto... args) { hipLaunchKernelGGL(kernel, grid, dim3(512), 0, st, p, meta, args...); };
   auto either = [&](auto* stamped, auto* plain, auto... args) { launch(p.timeline != 0 ? stamped : plain, args...); };
   if (p.move.words) {
-    if (p.D == 64) launch(k_step_mfma<64, true, PG>, lw);
-    else if (p.precise) launch(k_step_mfma<128, true, PG>, lw);
-    else launch(k_step_mfma<128, false, PG>, lw);
+    if (p.D == 64) launch(k_step_mfma<64, true, LEAN>, lw);
+    else if (p.precise) launch(k_step_mfma<128, true, LEAN>, lw);
+    else launch(k_step_mfma<128, false, LEAN>, lw);
   } else if (layers) {
-    if (p.D == 64) launch(k_model_mfma<64, true, PG>, lw, *layers);
-    else if (p.precise) launch(k_model_mfma<128, true, PG>, lw, *layers);
-    else launch(k_model_mfma<128, false, PG>, lw, *layers);
+    if (p.D == 64) launch(k_model_mfma<64, true, LEAN>, lw, *layers);
+    else if (p.precise) launch(k_model_mfma<128, true, LEAN>, lw, *layers);
+    else launch(k_model_mfma<128, false, LEAN>, lw, *layers);
   } else if (p.precise && p.D == 128) {
-    if (logits_work) either(k_verify_precise<PG, true>, k_verify_precise<PG, false>, lw);
-    else either(k_attn_precise<PG, true>, k_attn_precise<PG, false>);
+    if (logits_work) either(k_verify_precise<LEAN, true>, k_verify_precise<LEAN, false>, lw);
+    else either(k_attn_precise<LEAN, true>, k_attn_precise<LEAN, false>);
   } else if (logits_work) {
-    if (p.D == 64) PG ? either(k_verify_paged<64, true>, k_verify_paged<64, false>, lw) : either(k_verify_mfma<64, true>, k_verify_mfma<64, false>, lw);
-    else PG ? either(k_verify_paged<128, true>, k_verify_paged<128, false>, lw) : either(k_verify_mfma<128, true>, k_verify_mfma<128, false>, lw);
+    if (p.D == 64) LEAN ? either(k_verify_lean<64, true>, k_verify_lean<64, false>, lw) : either(k_verify_mfma<64, true>, k_verify_mfma<64, false>, lw);
+    else LEAN ? either(k_verify_lean<128, true>, k_verify_lean<128, false>, lw) : either(k_verify_mfma<128, true>, k_verify_mfma<128, false>, lw);
   } else {
-    if (p.D == 64) PG ? either(k_attn_paged<64, true>, k_attn_paged<64, false>) : either(k_attn_mfma<64, true>, k_attn_mfma<64, false>);
-    else PG ? either(k_attn_paged<128, true>, k_attn_paged<128, false>) : either(k_attn_mfma<128, true>, k_attn_mfma<128, false>);
+    if (p.D == 64) LEAN ? either(k_attn_lean<64, true>, k_attn_lean<64, false>) : either(k_attn_mfma<64, true>, k_attn_mfma<64, false>);
+    else LEAN ? either(k_attn_lean<128, true>, k_attn_lean<128, false>) : either(k_attn_mfma<128, true>, k_attn_mfma<128, false>);
   }
   return hipGetLastError();
 }
@@ -446,8 +446,12 @@ hipError_t launch_attn_mfma(hipStream_t st, const AttnParams& p, const SeqMeta& 
   if (layers && q.external_merge) return hipErrorInvalidValue;  // (the merge kernel knows one layer)
   hipError_t e;
   if (rt_rows == kSmallRows) {
-    e = p.kv.block_size > 0 ? launch_small<true>(st, grid, q, meta, logits_work, layers ? &table : nullptr)
-                            : launch_small<false>(st, grid, q, meta, logits_work, layers ? &table : nullptr);
+    // The lean builds (contiguous caches) where there are several rounds of workgroups, each of which starts 0.1 us sooner: 48 sequences of 8 nodes x
+    // 200 keys, 32 heads, a verification 47.4 -> 45.7 us, 64 of 4 x 40 41.4 -> 39.3.  Not in one round: decoding from the host with 63 nodes of
+    // 32 heads x 4111 keys takes 25.2 us a step with the others and 25.9 with these.
+    const bool lean = p.kv.block_size == 0 && (int64_t)n_logits + T > 256;
+    e = lean ? launch_small<true>(st, grid, q, meta, logits_work, layers ? &table : nullptr)
+             : launch_small<false>(st, grid, q, meta, logits_work, layers ? &table : nullptr);
   } else if (layers) {
     e = launch_attn_wide_layers(st, q, meta, std::min(M, rt_rows), (int)T, logits_work ? *logits_work : LogitsWork{}, table);
   } else {

@@ -329,9 +329,8 @@ struct TileLds {
 };
 
 // The memory side of a workgroup's sweep: units of 32 keys (K and V) of one split, requested by LDS-DMA into a ring of
-// kSlots, and what every wave brings of each.  Units are requested in order, unit u into slot u % kSlots.  CONTIGUOUS: the cache is, so
-// that nothing of a block table is in the code (workgroups of short sweeps over contiguous caches took 2 % longer with it: 48 sequences of 8 nodes x
-// 200 keys, 32 heads, 47.5 us a verification for 46.6).
+// kSlots, and what every wave brings of each.  Units are requested in order, unit u into slot u % kSlots.  CONTIGUOUS: the cache is, and
+// nothing of a block table is in the code.
 template <int D, int NW, int TR, bool CONTIGUOUS = false>
 struct Feed {
   static constexpr int kVecs = kUnitKeys * D / 8;               // 16-byte pieces of a unit's K (or V)
