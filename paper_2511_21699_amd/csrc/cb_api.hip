@@ -948,11 +948,11 @@ int run_pipeline(cb_ctx* ctx, hipStream_t st, int batch, const void* q, const cb
   // Not in many rounds of workgroups, each of which its arrivals make about a microsecond longer (31 sequences of one node x 55 keys, 32
   // heads: 22.9 us in two launches, 26.1 in one; 18 of 53 x 36, 40 heads, 41.5 and 40.0).  (In fp32, 2048 workgroups of 20 nodes x 1000 keys, 16/8
   // heads, 194.2 in one launch and 199.8 in two: no such line.)
-  // Nor where a logits workgroup accepts more than two sequences on average: what follows an acceptance is a chain of round trips, which the
-  // sequences beyond take one after the other.  Steps in one launch and in two, 200 keys x 8 nodes, 8 heads, vocabulary 1000 (8
-  // logits workgroups): 16 sequences 11.6 and 13.3 us, 24 16.7 and 16.6, 48 29.5 and 28.0, 64 36.5 and 34.9; fp32 with head_dim 64: 11.2 and 12.6,
-  // 16.3 and 14.9, 30.9 and 24.4, 36.7 and 30.3.
-  const bool few_to_a_workgroup = !fused || batch <= 2 * n_logits;
+  // Nor, in bf16 with head_dim 64, where a logits workgroup accepts more than two sequences on average: what follows an acceptance is a chain of round
+  // trips, which the sequences beyond take one after the other, and those sweeps are through before.  Steps in one launch and in two, 8
+  // heads, vocabulary 1000 (8 logits workgroups): 16 sequences of 20 nodes x 1000 keys 19.4 and 19.6 us, 32 33.8 and 32.7, 64 66.2 and 61.6; with
+  // head_dim 128 19.1 and 20.2, 34.3 and 35.9, 69.3 and 69.0; fp32 with head_dim 64 23.3 and 27.0, 40.7 and 44.4, 74.4 and 78.7.
+  const bool few_to_a_workgroup = !fused || batch <= 2 * n_logits || !use_mfma || c.head_dim != 64;
   ctx->moved = ctx->want_move && stages == 15 && (f32_tiles || (use_mfma && ap.live_wgs <= 3 * 256)) && few_to_a_workgroup &&
                !timing && !fork && !ap.timeline;
   ctx->want_move = false;

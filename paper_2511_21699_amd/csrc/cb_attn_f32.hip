@@ -330,7 +330,7 @@ __device__ __forceinline__ void verify_f32(const AttnParams& p, const SeqMeta& m
   } sh;
   const SeqMetaLanes ml = seq_meta_prefetch(meta);
   const int wg = (int)blockIdx.x - lw.n_wgs;
-  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept, after_acceptance<MOVE, row_pieces(D, 4), 2, 1>());
+  if (wg < 0) logits_share<kF32Waves, 8>(lw, ml, blockIdx.x, sh.accept, after_acceptance<MOVE, row_pieces(D, 4), 2, 4>());
   else attn_f32_tile<D, MOVE>(p, ml, wg, sh.attn, OneLayer{});
 }
 template <int D>

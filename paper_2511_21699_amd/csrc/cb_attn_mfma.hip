@@ -271,7 +271,7 @@ __device__ __forceinline__ void verify_workgroup(const AttnParams& p, const SeqM
   static_assert(sizeof(ring) >= sizeof(AcceptWaveLds), "the acceptance's LDS is the ring's");
   const int wg = (int)blockIdx.x - lw.n_wgs;
   if (wg < 0) {
-    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<MOVE, row_pieces(D, 2), 1, 2>());
+    logits_share<8, 16>(lw, ml, blockIdx.x, *reinterpret_cast<AcceptWaveLds*>(ring), after_acceptance<MOVE, row_pieces(D, 2), 1, 4>());
     return;
   }
   attn_tile<D, PX, LEAN, MOVE, TS>(p, ml, wg, ts0, sh, ring, ts_sh, OneLayer{});

@@ -146,8 +146,9 @@ struct HeadMove {
 
 // The acceptance's arrival for the heads of a sequence, by `nw` wavefronts of its workgroup (logits_share), this one the w-th of them, behind a
 // barrier that follows the acknowledgement of its stores; the heads whose attention is through already are moved here, HB at a time.  (A short
-// sweep is through before the acceptance is, and then all heads are: with four wavefronts and two heads at a time, 97 nodes of 40 heads x
-// 790 keys took 17.2 us a step against 16.4 in two launches.)
+// sweep is through before the acceptance is, and then all heads are: with wide tiles, whose workgroups have four wavefronts, 97 nodes of 40 heads x
+// 790 keys took 17.2 us a step two heads at a time and 16.5 four, two launches 16.4; 64 fp32 sequences of 8 nodes x 200 keys 36.7 one at a
+// time and 31.1 four, two launches 30.4.)
 template <int PIECES, int SHIFT, int HB>
 struct MoveAfter {
   static constexpr bool kAny = true;

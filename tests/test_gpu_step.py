@@ -33,10 +33,10 @@ CASES = [  # dtype, heads, kv heads, head_dim, vocabulary, prefixes, tree sizes,
     ("bf16", 44, 22, 128, 20000, [300, 20], [70, 40], {"tile_rows": 128}, True),
 ]
 TWO_LAUNCHES = {"attn_impl", "many"}
-for n in (16, 17, 40):  # sequences that 8 logits workgroups accept: two each, and more, whose compaction has a launch of its own
-    many = {"logits_wgs": 8} if n == 16 else {"logits_wgs": 8, "many": 1}
-    CASES += [("bf16", 8, 8, 128, 300, [5 + 7 * i % 90 for i in range(n)], [3 + i % 6 for i in range(n)], many, n == 17),
-              ("f32", 4, 4, 64, 300, [5 + 7 * i % 90 for i in range(n)], [3 + i % 6 for i in range(n)], many, n == 16)]
+for n in (16, 17, 40):  # sequences that 8 logits workgroups accept, two each and more; these with head_dim 64 in bf16 have a launch for their compaction
+    lens, sizes, many = [5 + 7 * i % 90 for i in range(n)], [3 + i % 6 for i in range(n)], {"logits_wgs": 8}
+    CASES += [("bf16", 8, 8, 128, 300, lens, sizes, many, False), ("f32", 4, 4, 64, 300, lens, sizes, many, False),
+              ("f32", 8, 4, 128, 300, lens, sizes, many, n == 16), ("bf16", 8, 4, 64, 300, lens, sizes, dict(many, many=1) if n > 16 else many, False)]
 CASES += [("bf16", 16, 8, 128, 300, [40 * i for i in range(n)], [9 + i for i in range(n)], {"logits_wgs": 8}, False) for n in (9, 12)]
 CASES += [("bf16", 72, 72, 64, 300, [20 * i for i in range(8)], [9 + i for i in range(8)], {"logits_wgs": 8}, False)]   # more heads than lanes
 
