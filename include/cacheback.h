@@ -173,8 +173,8 @@ int cb_verify_tree_device(cb_ctx *ctx, void *hip_stream, int32_t batch, const vo
 /*
  * cb_verify_tree_device followed by cb_compact_kv of `num_layers` caches (0: none) with new_kv_len = NULL, as one call:
  * the same results, states and errors.  Where `layers` is the one cache that is verified, neither its k nor its v overlaps
- * another operand, and no other sequence can see the rows (a contiguous cache, or one sequence), it is one kernel for calls whose verification
- * is: a kv head's rows move as soon as all that reads them has, and the acceptance, are through.
+ * another operand, and no other sequence can see the rows (a contiguous cache, or one sequence), it is mostly one kernel for calls whose
+ * verification is: a kv head's rows move as soon as all that reads them has, and the acceptance, are through.
  */
 int cb_verify_and_compact_device(cb_ctx *ctx, void *hip_stream, int32_t batch, const void *q,
                                  const cb_kv_layer *kv, const int32_t *kv_len,

@@ -3,9 +3,10 @@
 //
 // As a launch of its own behind the verification the compaction cost 2 to 3 us of a step of 12 to 32 us, almost all of it start and
 // drain of a kernel that moves a few rows per head (a step in two launches -> in one: 15 rows of 8 fp32 heads of 64 x 256 keys 12.2
-// -> 10.1 us, 64 of 32 heads x 2048 keys 17.7 -> 14.8, 128 of 32/8 heads x 8192 keys 31.1 -> 29.9).  Here nobody waits either: what has to be over before a head's rows may move
-// arrives at a word of the (layer, sequence, kv head), and whoever completes the word moves them.  Arrivals are the workgroups whose split
-// reaches the tree (their sweep has read the tree's K/V), every row tile's, and the acceptance where it is part of the launch.
+// -> 10.1 us, 64 of 32 heads x 2048 keys 17.7 -> 14.8, 128 of 32/8 heads x 8192 keys 31.1 -> 29.9).  Here nobody waits either: what has to be
+// over before a head's rows may move arrives at a word of the (sequence, kv head), and whoever completes the word moves them.  Arrivals are the
+// workgroups whose split reaches the tree (their sweep has read the tree's K/V), every row tile's, and the acceptance where it is
+// part of the launch.
 // The workgroups with the tree end early, as the last split is the shortest, and move while they would wait for the other splits.
 #pragma once
 #include "cb_internal.h"
@@ -147,7 +148,7 @@ struct HeadMove {
 // The acceptance's arrival for the heads of a sequence, by `nw` wavefronts of its workgroup (logits_share), this one the w-th of them, behind a
 // barrier that follows the acknowledgement of its stores; the heads whose attention is through already are moved here, HB at a time.  (A short
 // sweep is through before the acceptance is, and then all heads are: with wide tiles, whose workgroups have four wavefronts, 97 nodes of 40 heads x
-// 790 keys took 17.2 us a step two heads at a time and 16.5 four, two launches 16.4; 64 fp32 sequences of 8 nodes x 200 keys 36.7 one at a
+// 790 keys took 17.2 us a step two heads at a time and 16.5 four, two launches 16.5; 64 fp32 sequences of 8 nodes x 200 keys 36.7 one at a
 // time and 31.1 four, two launches 30.4.)
 template <int PIECES, int SHIFT, int HB>
 struct MoveAfter {
